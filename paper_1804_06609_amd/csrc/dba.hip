@@ -26,12 +26,12 @@ using namespace dba;
 // so that the first two tiles are requested before any argument has been read from memory.
 template <int U, int FMT, int NW>
 __device__ __forceinline__ void stream_phase(const StepParams &p, const void *logp, int V, int k, int first_step,
-                                             int b, int h, StreamSmem &sm)
+                                             int b, int h, StreamSmem<NW> &sm)
 {
     typedef typename Logp<FMT>::elem_t elem_t;
     const int row = b * k + h;
     const int lane = lane_id();
-    const int wave = (int)(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     constexpr int nwaves = NW;
     const bool gatherer = wave == nwaves - 1;     // this wave also fetches the constraint tokens
 
@@ -76,7 +76,6 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
 
     RowTop st;
     st.list = 0;
-    st.kth = 0;
     st.floor = -INFINITY;
     st.thr = kLowestFinite;
     u64 ckey = 0;
@@ -91,7 +90,7 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
         const float cx = cw >= 0 ? Logp<FMT>::widen_one(logp_row[cw]) : -INFINITY;
         // Sec. 3.3: no end-of-sentence before all constraints are met
         const int eos_block = (fin & kFinEosBlocked) ? p.eos_id : -1;
-        parked = rs.run(prev, eos_block, code_base, k, wave, nwaves, sm, st);
+        parked = rs.run(prev, eos_block, code_base, k, wave, sm, st);
         const float cs = prev + cx;
         if (cw >= 0 && cs > -INFINITY)
             ckey = pack_sel(p.met_bits, cbank, ord_from_float(cs), code_base | (uint32_t)cw);
@@ -103,7 +102,7 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
     if (gatherer) {
         p.conskeys[(size_t)row * kMaxCons + lane] = ckey;
     }
-    const u64 acc = finish_row(sm, st.list, parked, wave, nwaves, fin_wave);
+    const u64 acc = finish_row(sm, st.list, parked, wave, fin_wave);
     if (finisher) {
         // Handed on as selection keys: every listed sum with the bank it would land in - the
         // constraints met once the hypothesis has emitted that token (add(), Sec. 3.1).  Each lane
@@ -136,7 +135,7 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
 template <int U, int FMT, int NW>
 __global__ __launch_bounds__(NW * kWave) void dba_stream_kernel(const void *logp, int V, int k_first, const StepParams p)
 {
-    __shared__ StreamSmem sm;
+    __shared__ StreamSmem<NW> sm;
     stream_phase<U, FMT, NW>(p, logp, V, k_first & 0xFFFF, k_first >> 16, (int)blockIdx.y, (int)blockIdx.x, sm);
 }
 

@@ -26,7 +26,6 @@ constexpr int kMaxBeam = 64;
 constexpr int kMaxCons = 64;          // constraint tokens (and phrases) per sentence
 constexpr int kBlock = 256;           // threads per workgroup of the small helper kernels
 constexpr int kWavesPerBlock = kBlock / kWave;
-constexpr int kStreamWaves = 8;       // most waves a stream-phase workgroup (one beam row) can have: 4 or 8 are used
 constexpr int kTileLoads = 4;         // 16-byte loads per lane and tile in the stream phase
 constexpr int kFmtF32 = 0;            // element type of the log-probs: fp32,
 constexpr int kFmtF16 = 1;            // IEEE binary16,
@@ -140,7 +139,6 @@ struct MergeSmem {
 // ---------------------------------------------------------------------------
 struct RowTop {
     u64 list;      // this lane's entry of the wave's decreasing top-64
-    u64 kth;       // key at place k-1 (0 while fewer than k entries)
     float floor;   // a proven lower bound of the row's k-th best sum (-inf if none)
     float thr;     // sums below this cannot reach the row's top k; never below -FLT_MAX, so
                    // that "s >= thr" also rejects -inf sums
@@ -150,54 +148,30 @@ constexpr float kLowestFinite = -3.402823466e+38f;
 
 __device__ __forceinline__ void refresh_threshold(RowTop &st, int kk)
 {
-    st.kth = read_lane(st.list, kk - 1);
-    const float own = (st.kth == 0) ? kLowestFinite : float_from_ord((uint32_t)(st.kth >> 32));
+    const u64 kth = read_lane(st.list, kk - 1);
+    const float own = (kth == 0) ? kLowestFinite : float_from_ord((uint32_t)(kth >> 32));
     st.thr = fmaxf(fmaxf(st.floor, own), kLowestFinite);
 }
 
-// Key of a wave-uniform element, built from uniform values (scalar unit).
-__device__ __forceinline__ u64 make_key_uniform(uint32_t sbits, uint32_t flat)
+// lanes below the caller's in the mask m
+__device__ __forceinline__ int lanes_before(u64 m)
 {
-    if (sbits == 0x80000000u) sbits = 0;                       // -0.0 -> +0.0
-    const uint32_t mask = (uint32_t)((int32_t)sbits >> 31);    // all ones for negative floats
-    const uint32_t ord = sbits ^ (mask | 0x80000000u);
-    return ((u64)ord << 32) | (u64)(0xFFFFFFFFu - flat);
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-constexpr int kStageCap = 128;        // candidate keys one wave can park in LDS between flushes
+constexpr int kGroupCap = 128;        // 16-byte groups one wave can set aside in LDS,
+constexpr int kKeyCap = 128;          // and keys it can park there
 
-// Candidates of one wave are parked in LDS (stage[0..cnt)) and folded into the wave's sorted
-// list 64 at a time: one 64-lane sort and one merge per chunk instead of one serial insert per
-// candidate.  The threshold tightens at every flush.
-__device__ __attribute__((noinline)) u64 fold_stage(u64 list, const u64 *stage, int cnt)
+// Keys of one wave folded into its sorted list 64 at a time: one 64-lane sort and one merge per
+// chunk instead of one serial insert per key.
+__device__ __forceinline__ u64 fold_keys(u64 list, const u64 *keys, int cnt)
 {
     const int lane = lane_id();
     for (int base = 0; base < cnt; base += kWave) {
-        const u64 key = (base + lane < cnt) ? stage[base + lane] : 0ull;
+        const u64 key = (base + lane < cnt) ? keys[base + lane] : 0ull;
         list = merge_desc<u64>(list, sort64_desc<u64>(key));
     }
     return list;
-}
-
-__device__ __forceinline__ void flush_stage(RowTop &st, u64 *stage, int &cnt, int kk)
-{
-    st.list = fold_stage(st.list, stage, cnt);
-    cnt = 0;
-    refresh_threshold(st, kk);
-}
-
-// Wave-wide: every lane offers one element; m = ballot of the lanes whose sum may belong to
-// the row's top k (m != 0).  Lane l's coordinate is flat0 + l*lane_stride.
-__device__ __forceinline__ void stage_candidates(RowTop &st, u64 *stage, int &cnt, float s, u64 m,
-                                                 uint32_t flat0, uint32_t lane_stride, int kk)
-{
-    const int n = __popcll(m);
-    if (cnt + n > kStageCap) flush_stage(st, stage, cnt, kk);
-    const int lane = lane_id();
-    const int pos = cnt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    if ((m >> lane) & 1ull) stage[pos] = make_key(s, flat0 + (uint32_t)lane * lane_stride);
-    cnt += n;
 }
 
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -216,7 +190,8 @@ __device__ __forceinline__ float max4(const v4f &x)
 // ---- element formats of the log-prob tensor ----------------------------------------------
 // A lane reads 16 bytes at a time: a "group" of G consecutive elements.  Every format answers
 // three questions about a group: may any of its elements reach the threshold (cheap, and
-// allowed to say yes too often, never no wrongly), what are its G elements as fp32 (exact), and
+// allowed to say yes too often, never no wrongly; the threshold comes as a bound on the elements
+// themselves, worked out only when it changes), what are its G elements as fp32 (exact), and
 // which single fp32 value is certainly not above the group's greatest element (for the
 // threshold floor).  The sum itself is always one fp32 addition prev + element.
 template <int FMT>
@@ -227,14 +202,21 @@ struct Logp<kFmtF32> {
     static constexpr int G = 4;
     typedef float elem_t;
     typedef v4f vec_t;
-    struct Quick {};                                  // the quick test uses the fp32 threshold itself
+    struct Quick {
+        float xmin;       // no element below this reaches the threshold; never below -FLT_MAX
+    };
     static __device__ __forceinline__ vec_t neg_inf() { return v4f{-INFINITY, -INFINITY, -INFINITY, -INFINITY}; }
-    static __device__ __forceinline__ Quick quick(float, float) { return Quick{}; }
-    // rounding is monotone, so max(prev + x_i) == prev + max(x_i): one add decides for four
-    static __device__ __forceinline__ bool may_reach(const vec_t &x, float prev, float thr, const Quick &)
+    // fl(prev + x) >= thr needs prev + x >= thr - ulp(thr), and d = fl(thr - prev) is off by at most
+    // ulp(d): both are below 2^-22 of the magnitudes, and three roundings of that size fit what is
+    // left (the last term covers sums in the subnormal range).
+    static __device__ __forceinline__ Quick quick(float prev, float thr)
     {
-        return prev + max4(x) >= thr;
+        const float d = thr - prev;
+        const float x = d - ((fabsf(thr) + fabsf(d)) * 0x1p-22f + 0x1p-126f);
+        return Quick{x >= kLowestFinite ? x : kLowestFinite};
     }
+    static __device__ __forceinline__ bool may_reach(const vec_t &x, const Quick &q) { return max4(x) >= q.xmin; }
+    static __device__ __forceinline__ vec_t lone(elem_t e) { return v4f{e, -INFINITY, -INFINITY, -INFINITY}; }
     static __device__ __forceinline__ void widen(const vec_t &x, float (&f)[G])
     {
         f[0] = x.x;
@@ -320,9 +302,14 @@ struct Logp16 {
         const uint32_t c = pk_min_u16(pk_min_u16(x.x, x.y), pk_min_u16(x.z, x.w));
         return min(c & 0xFFFFu, c >> 16);
     }
-    static __device__ __forceinline__ bool may_reach(const vec_t &x, float, float, const Quick &q)
+    static __device__ __forceinline__ bool may_reach(const vec_t &x, const Quick &q)
     {
         return min_pattern(x) <= q.umax;
+    }
+    static __device__ __forceinline__ vec_t lone(elem_t e)
+    {
+        const uint32_t w = kNegInf | (kNegInf << 16);
+        return v4u{(uint32_t)e | (kNegInf << 16), w, w, w};
     }
     static __device__ __forceinline__ void widen(const vec_t &x, float (&f)[G])
     {
@@ -386,29 +373,68 @@ __device__ __forceinline__ void block_eos(typename Logp<FMT>::vec_t (&x)[U], int
 }
 
 // LDS shared by the waves of one row's workgroup during the stream phase.
+template <int NW>
 struct StreamSmem {
-    u64 wl[kStreamWaves][kWave];        // the waves' lists, for the final merge
-    u64 stage[kStreamWaves][kStageCap]; // candidates parked between flushes
-    uint32_t boot[kStreamWaves][kWave]; // sorted per-lane maxima of every wave's first tile (order images)
-    int parked[kStreamWaves];           // end of the row: keys each wave has left in its stage,
-    int has_list[kStreamWaves];         // and whether it holds a list from earlier folds
+    v4u group[NW][kGroupCap];           // groups set aside: the 16 bytes as they were read,
+    uint32_t coord[NW][kGroupCap];      // and the coordinate of the first element
+    u64 key[NW][kKeyCap];               // keys parked for the end of the row
+    u64 wl[NW][kWave];                  // the waves' lists, for the final merge
+    uint32_t boot[NW][kWave];           // sorted per-lane maxima of every wave's first tiles (order images)
+    int parked[NW];                     // end of the row: keys each wave has parked,
+    int has_list[NW];                   // and whether it holds a list from earlier folds
 };
+
+// The groups a wave has set aside, element by element: sums that reach the threshold are parked as keys,
+// and the keys are folded into the wave's list whenever they would overflow (the threshold then
+// rises).  Reached only where the floor is weak (few elements, many ties): kept small, not fast.
+template <int FMT>
+__device__ __forceinline__ void drain_groups(RowTop &st, int &parked, const v4u *group, const uint32_t *coord, u64 *key,
+                                             int cnt, float prev, int kk)
+{
+    typedef Logp<FMT> F;
+    const int lane = lane_id();
+    const typename F::elem_t *elem = reinterpret_cast<const typename F::elem_t *>(group);
+#pragma unroll 1
+    for (int base = 0; base < cnt; base += kWave) {
+        const int i = base + lane;
+        const uint32_t at = i < cnt ? coord[i] : 0u;
+#pragma unroll 1
+        for (int c = 0; c < F::G; ++c) {
+            const float s = i < cnt ? prev + F::widen_one(elem[i * F::G + c]) : -INFINITY;
+            const u64 m = __ballot(s >= st.thr);
+            const int n = __popcll(m);
+            if (parked + n > kKeyCap) {
+                st.list = fold_keys(st.list, key, parked);
+                parked = 0;
+                refresh_threshold(st, kk);
+            }
+            if ((m >> lane) & 1ull) key[parked + lanes_before(m)] = make_key(s, at + (uint32_t)c);
+            parked += n;
+        }
+    }
+}
 
 // One wave's share of one row: tiles wave, wave+nwaves, ... of 64*U groups of 16 bytes each.
 // Must be called by every thread of the workgroup (it contains one barrier).
 //
-// s = prev + logp is a single fp32 add (a 16-bit log-prob is widened exactly first).  An
-// element is looked at closely only if its sum can still reach the row's k best (>=: a later
+// s = prev + logp is a single fp32 add (a 16-bit log-prob is widened exactly first).  A group is
+// set aside only if the sum of one of its elements can still reach the row's k best (>=: a later
 // element may tie the k-th score and win on the coordinate); Logp<FMT>::may_reach decides that
-// for a whole 16-byte group at once.
+// for a whole 16-byte group at once.  What is set aside is the group as it was read: one vote and two
+// LDS writes, whatever the number of elements in it.  Its elements are looked at one by one only at the
+// end of the row, 64 groups side by side, so that nothing but the quick test stands between a tile's
+// arrival and the request that refills its registers.  What bounds this phase besides memory is the issue
+// slots that about 4k near candidates per row take (against handling them one element at a time as
+// they pass: stream kernel 27.8 -> 27.0 us at 1280 rows of 32000 fp32, k = 20, 18.6 -> 16.7 us with bf16;
+// 261 -> 256 us at 8192 rows of 50000 fp32, k = 64, 149 -> 137 us with fp16).
 //
 // Thresholds.  (1) Every lane takes an element of its share of the wave's first two tiles (the
 // greatest, where the format finds it cheaply); the k-th greatest of all the workgroup's
 // per-lane values is a floor: k different lanes hold an element at least that large, so nothing
-// below it can be among the row's k best.  (2) A wave whose stage fills up folds it into its
-// list; from then on the score of the list's k-th entry bounds its share of the row.  With the
-// floor in place that is rare: a wave parks about k keys per row.  The row's best element is
-// never below any bound, so it always survives.
+// below it can be among the row's k best.  (2) A wave that runs out of room for groups and keys folds
+// its keys into its list; from then on the score of the list's k-th entry bounds its share of the
+// row.  With the floor in place that is rare: a wave sets about k groups aside per row.  The row's
+// best element is never below any bound, so it always survives.
 template <int U, int FMT>
 struct RowStream {
     typedef Logp<FMT> F;
@@ -420,6 +446,7 @@ struct RowStream {
     const vec_t *vec;
     int V, head, nv, tail, ntiles;
     vec_t cur[U], nxt[U];
+    elem_t lone;          // wave 0: this lane's element outside the aligned body, if there is one
 
     // Issues the loads of this wave's first two tiles.  Needs nothing of the hypothesis, so it
     // runs before the beam state has arrived.
@@ -439,17 +466,29 @@ struct RowStream {
         for (int u = 0; u < U; ++u) nxt[u] = F::neg_inf();
         if (wave < ntiles) load_tile<U>(vec, nv, wave, lane, cur, F::neg_inf());
         if (wave + nwaves < ntiles) load_tile<U>(vec, nv, wave + nwaves, lane, nxt, F::neg_inf());
+        lone = 0;
+        if (wave == 0 && lane < head + tail) lone = row[lone_at(lane)];
     }
 
-    // Returns the number of keys left parked in sm.stage[wave] (not yet folded into st.list).
+    // position of the lane's element before the first / after the last 16-byte aligned group (rows whose
+    // length or start is not a multiple of one group): fewer than two groups of them, one per lane
+    __device__ __forceinline__ int lone_at(int lane) const
+    {
+        return lane < head ? lane : head + nv * G + (lane - head);
+    }
+
+    // Returns the number of keys left parked in sm.key[wave] (not yet folded into st.list).
+    template <int NW>
     __device__ __forceinline__ int run(float prev, int eos_block, uint32_t flat_base, int kk, int wave,
-                                       int nwaves, StreamSmem &sm, RowTop &st);
+                                       StreamSmem<NW> &sm, RowTop &st);
 };
 
 template <int U, int FMT>
+template <int NW>
 __device__ __forceinline__ int RowStream<U, FMT>::run(float prev, int eos_block, uint32_t flat_base, int kk,
-                                                      int wave, int nwaves, StreamSmem &sm, RowTop &st)
+                                                      int wave, StreamSmem<NW> &sm, RowTop &st)
 {
+    constexpr int nwaves = NW;
     const int lane = lane_id();
     constexpr int kTileElems = G * kWave * U;
     const int eos_rel0 = eos_block >= 0 ? eos_block - head : -1;   // position in the aligned body
@@ -493,34 +532,63 @@ __device__ __forceinline__ int RowStream<U, FMT>::run(float prev, int eos_block,
     st.floor = float_from_ord((uint32_t)__builtin_amdgcn_readlane((int)boot, kk - 1));
     st.thr = fmaxf(st.floor, kLowestFinite);
     typename F::Quick quick = F::quick(prev, st.thr);
-    u64 *stage = sm.stage[wave];
-    int cnt = 0;
-    // one tile: test its U groups, park what may belong to the top k
+    v4u *group = sm.group[wave];
+    uint32_t *coord = sm.coord[wave];
+    u64 *key = sm.key[wave];
+    int cnt = 0, parked = 0;              // groups set aside, keys parked
+    const uint32_t lane_coord = flat_base + (uint32_t)(head + G * lane);
+    auto drain = [&]() {
+        drain_groups<FMT>(st, parked, group, coord, key, cnt, prev, kk);
+        cnt = 0;
+        quick = F::quick(prev, st.thr);
+    };
+    auto set_aside = [&](const vec_t &x, bool mine, u64 m, uint32_t at) {
+        if (mine) {
+            const int pos = cnt + lanes_before(m);
+            group[pos] = __builtin_bit_cast(v4u, x);
+            coord[pos] = at;
+        }
+        cnt += __popcll(m);
+    };
+    // one tile: test its U groups, set aside what may belong to the top k
     auto examine = [&](const vec_t (&t)[U], int tile) {
+        bool mine[U];
+        u64 m[U], any = 0;
+        int n = 0;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const vec_t x = t[u];
-            if (__any(F::may_reach(x, prev, st.thr, quick))) {
-                const uint32_t flat0 = flat_base + (uint32_t)(head + G * ((tile * U + u) * kWave));
-                float f[G];
-                F::widen(x, f);
+            mine[u] = F::may_reach(t[u], quick);
+            m[u] = __ballot(mine[u]);
+            any |= m[u];
+            n += __popcll(m[u]);
+        }
+        if (any == 0) return;
+        const uint32_t at0 = lane_coord + (uint32_t)(G * U * kWave) * (uint32_t)tile;
+        if (cnt + n <= kGroupCap) {
 #pragma unroll
-                for (int c = 0; c < G; ++c) {
-                    const float sc = prev + f[c];
-                    const u64 mc = __ballot(sc >= st.thr);
-                    if (mc) stage_candidates(st, stage, cnt, sc, mc, flat0 + (uint32_t)c, (uint32_t)G, kk);
-                }
+            for (int u = 0; u < U; ++u)
+                if (m[u]) set_aside(t[u], mine[u], m[u], at0 + (uint32_t)(G * kWave * u));
+        } else {
+#pragma unroll 1
+            for (int u = 0; u < U; ++u) {
+                vec_t x = t[0];
+#pragma unroll
+                for (int i = 1; i < U; ++i)
+                    if (u == i) x = t[i];
+                const bool r = F::may_reach(x, quick);
+                const u64 mr = __ballot(r);
+                if (cnt + __popcll(mr) > kGroupCap) drain();
+                set_aside(x, r, mr, at0 + (uint32_t)(G * kWave) * (uint32_t)u);
             }
         }
     };
     // after a tile: start the load that refills its registers (two tiles ahead) and make the
-    // other buffer ready (end-of-sentence mask, the quick test's form of the threshold)
+    // other buffer ready (end-of-sentence mask)
     auto advance = [&](vec_t (&done)[U], vec_t (&next)[U], int next_tile) {
         if (next_tile + nwaves < ntiles) load_tile<U>(vec, nv, next_tile + nwaves, lane, done, F::neg_inf());
         if (next_tile < ntiles) {
             const int rel = eos_rel0 - next_tile * kTileElems;
             if (eos_rel0 >= 0 && rel >= 0 && rel < kTileElems) block_eos<U, FMT>(next, rel, lane);
-            quick = F::quick(prev, st.thr);
         }
     };
     while (tl < ntiles) {
@@ -532,36 +600,58 @@ __device__ __forceinline__ int RowStream<U, FMT>::run(float prev, int eos_block,
         advance(nxt, cur, tl + nwaves);
         tl += nwaves;
     }
-    // elements before the first / after the last 16-byte aligned group (rows whose length or
-    // start is not a multiple of one group): fewer than two groups, one element per lane
+    // the elements outside the aligned body: groups of one
     if (wave == 0 && head + tail > 0) {
-        const bool mine = lane < head + tail;
-        const int w = lane < head ? lane : head + nv * G + (lane - head);
-        const float s = mine ? prev + F::widen_one(row[w]) : -INFINITY;
-        u64 m = __ballot(mine && (s >= st.thr) && (w != eos_block));
-        while (m) {
-            const int l = __ffsll((long long)m) - 1;
-            m &= m - 1;
-            const int wl = l < head ? l : head + nv * G + (l - head);
-            const uint32_t sbits = (uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(s), l);
-            if (cnt + 1 > kStageCap) flush_stage(st, stage, cnt, kk);
-            if (lane == 0) stage[cnt] = make_key_uniform(sbits, flat_base + (uint32_t)wl);
-            cnt += 1;
-        }
+        const int w = lone_at(lane);
+        const vec_t x = lane < head + tail && w != eos_block ? F::lone(lone) : F::neg_inf();
+        const bool mine = F::may_reach(x, quick);
+        const u64 m = __ballot(mine);
+        if (cnt + __popcll(m) > kGroupCap) drain();
+        set_aside(x, mine, m, flat_base + (uint32_t)w);
     }
-    return cnt;
+    // the elements of the groups set aside, 64 groups side by side: every lane counts its own, a
+    // prefix sum over the wave gives it its places
+    for (int base = 0; base < cnt; base += kWave) {
+        const int i = base + lane;
+        const bool mine = i < cnt;
+        const uint32_t at = mine ? coord[i] : 0u;
+        float f[G];
+        F::widen(mine ? __builtin_bit_cast(vec_t, group[i]) : F::neg_inf(), f);
+        int n = 0;
+#pragma unroll
+        for (int c = 0; c < G; ++c) {
+            f[c] = prev + f[c];
+            n += f[c] >= st.thr ? 1 : 0;
+        }
+        const int incl = wave_inclusive_sum(n);
+        const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
+        if (parked + total > kKeyCap) {
+            group += base;                // from here on one by one, with folds
+            coord += base;
+            cnt -= base;
+            drain();
+            break;
+        }
+        int pos = parked + incl - n;
+#pragma unroll
+        for (int c = 0; c < G; ++c)
+            if (f[c] >= st.thr) key[pos++] = make_key(f[c], at + (uint32_t)c);
+        parked += total;
+    }
+    return parked;
 }
 
 // End of a row.  Each wave arrives with a sorted list from earlier folds (usually none: with
-// the floor in place a wave parks a few dozen keys per row and never fills its stage) and the
-// keys still parked in its stage.  The parked keys of all waves are pooled and sorted in chunks
+// the floor in place a wave parks a few dozen keys per row and never has to fold) and the
+// keys it has parked.  The parked keys of all waves are pooled and sorted in chunks
 // of 64 - one chunk in the common case, sorted by one wave - instead of one sort per wave plus
 // a merge per wave.  The wave that finishes the row (fin_wave) rotates with the row index, so
 // that the rows sharing a compute unit finish on different SIMDs.  Returns the row's list to
 // the lanes of fin_wave.  Called by every thread of the workgroup (one or two barriers).
-__device__ __forceinline__ u64 finish_row(StreamSmem &sm, u64 list, int parked, int wave, int nwaves,
-                                          int fin_wave)
+template <int NW>
+__device__ __forceinline__ u64 finish_row(StreamSmem<NW> &sm, u64 list, int parked, int wave, int fin_wave)
 {
+    constexpr int nwaves = NW;
     const int lane = lane_id();
     const bool mine_has = read_lane(list, 0) != 0;
     if (lane == 0) {
@@ -570,15 +660,15 @@ __device__ __forceinline__ u64 finish_row(StreamSmem &sm, u64 list, int parked, 
     }
     __syncthreads();
     // keys parked by waves 0..w-1 (pre[w]); all of them (n)
-    int pre[kStreamWaves + 1];
+    int pre[NW + 1];
     int any = 0;
     pre[0] = 0;
 #pragma unroll
-    for (int w = 0; w < kStreamWaves; ++w) {
-        pre[w + 1] = pre[w] + (w < nwaves ? sm.parked[w] : 0);
-        any |= w < nwaves ? sm.has_list[w] : 0;
+    for (int w = 0; w < NW; ++w) {
+        pre[w + 1] = pre[w] + sm.parked[w];
+        any |= sm.has_list[w];
     }
-    const int n = pre[kStreamWaves];
+    const int n = pre[NW];
     const int nchunks = (n + kWave - 1) >> 6;
     u64 part = 0;
     bool have = false;
@@ -588,12 +678,12 @@ __device__ __forceinline__ u64 finish_row(StreamSmem &sm, u64 list, int parked, 
         if (i < n) {
             int w = 0, first = 0;
 #pragma unroll
-            for (int j = 1; j < kStreamWaves; ++j)
+            for (int j = 1; j < NW; ++j)
                 if (i >= pre[j]) {
                     w = j;
                     first = pre[j];
                 }
-            key = sm.stage[w][i - first];
+            key = sm.key[w][i - first];
         }
         const u64 sorted = sort64_desc<u64, true>(key);
         part = have ? merge_desc<u64, true>(part, sorted) : sorted;

@@ -273,6 +273,41 @@ def test_restricted_vocabulary(torch_gpu, keep, fmt):
     _harness().run_parity(wl, logp_format=fmt)
 
 
+class _Shaped(si.Workload):
+    """Rows whose order defeats the threshold floor, which rests on the first tiles: rising rows, where
+    every later 16-byte group reaches it, so that the room for groups and keys overflows again and again;
+    falling ones; and log-probs of extreme magnitudes, where the bound on an element (threshold minus
+    score) is at its roughest."""
+
+    shape = "rising"
+
+    def logp(self, t, sentences=None, out=None):
+        lp = super().logp(t, sentences, out)
+        if self.shape in ("rising", "falling"):
+            lp.sort(axis=-1)
+            if self.shape == "falling":
+                lp[...] = lp[..., ::-1].copy()
+        else:
+            lp *= np.float32({"huge": 1e30, "tiny": 1e-39, "wide": 1.0}[self.shape])
+            if self.shape == "wide":                       # magnitudes from 1e-20 to 1e20 side by side
+                lp *= np.float32(10.0) ** (np.arange(lp.shape[-1]) % 41 - 20).astype(np.float32)
+        return lp
+
+
+@pytest.mark.parametrize("shape,fmt", [("rising", None), ("rising", "f16"), ("rising", "bf16"), ("falling", None),
+                                       ("huge", None), ("huge", "bf16"), ("tiny", None), ("tiny", "bf16"),
+                                       ("wide", None), ("wide", "bf16")])
+@pytest.mark.parametrize("k,V", [(5, 1024), (20, 4099), (33, 8191), (64, 9001)])
+def test_rows_that_defeat_the_floor(torch_gpu, k, V, shape, fmt):
+    """One tile per row up to several per wave, rows on and off 16 bytes, floors from one or from two
+    64-lane passes."""
+    base = si.make_small(5300 + k, 2, k, V, 4, max_phrases=3, max_len=2, dup_prob=0.3, boost=False)
+    wl = _Shaped(B=base.B, k=base.k, V=base.V, T=base.T, seed=base.seed, constraints=base.constraints)
+    wl.shape = shape
+    wl.eos_switch = 2
+    _harness().run_parity(wl, logp_format=fmt)
+
+
 def test_many_sentences_long_decode(torch_gpu):
     """300 sentences (more workgroups in the merge phase than compute units), 150 steps of history,
     the set-up of Sec. 4 (per-word scores, pruning at 20), end-of-sentence likely from step 40 on."""
