@@ -367,6 +367,14 @@ VARIANTS = [
 ]
 
 
+@pytest.mark.parametrize("B", [7, 8, 9, 15, 17])
+@pytest.mark.parametrize("k", [1, 3, 7])
+def test_sentences_eight_abreast(torch_gpu, B, k):
+    """The stream phase numbers the first B & ~7 sentences eight abreast and the rest row by row: batch
+    sizes on both sides of a multiple of eight, beam sizes that are no power of two, and beam one."""
+    _harness().run_parity(si.make_small(6400 + 10 * B + k, B, k, 500, 4, max_phrases=3, max_len=2))
+
+
 @pytest.mark.parametrize("vi", range(len(VARIANTS)))
 @pytest.mark.parametrize("seed", range(6))
 def test_variants_small(torch_gpu, seed, vi):
