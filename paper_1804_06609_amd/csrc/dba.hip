@@ -47,8 +47,8 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
     const float prev_ld = p.score_cur[row];
     const int fin_ld = p.fin_cur[row];
     // workgroups are dealt out round-robin over the 256 compute units, so the ones sharing a
-    // compute unit differ in (row / 256): let that pick the wave (hence the SIMD) that finishes the row
-    const int fin_wave = (row >> 8) & (nwaves - 1);
+    // compute unit differ in (number / 256): let that pick the wave (hence the SIMD) that finishes the row
+    const int fin_wave = (int)(blockIdx.x >> 8) & (nwaves - 1);
     const bool finisher = wave == fin_wave;
     u64 g_met = 0, g_inc = 0, g_sfl = 0, t_bucket = 0;
     int g_ipq = -1, g_nxt = -1, g_ftok = -1, g_P = 0, t_btok = -1;
@@ -355,7 +355,7 @@ namespace {
 
 thread_local char g_init_error[256] = "";
 
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 struct Layout {
     size_t score[2], met[2], ipq[2], len[2], fin[2], inc[2], nxt[2];
@@ -402,6 +402,17 @@ Layout make_layout(size_t B, size_t k, size_t N)
     L.best = take(B * sizeof(BestCompleted));
     L.total = off;
     return L;
+}
+
+constexpr size_t kComputeUnits = 256;
+constexpr size_t kLdsPerUnit = 160 * 1024;
+
+// LDS to add to a stream-phase workgroup of NW waves so that no more than n of them fit a compute unit
+template <int NW>
+constexpr size_t spread_lds(size_t n)
+{
+    static_assert(sizeof(StreamSmem<NW>) < kLdsPerUnit / 4, "LDS of the stream phase");
+    return align_up(kLdsPerUnit / (n + 1) + 1 - sizeof(StreamSmem<NW>), 256);
 }
 
 int bits_for(int v)   // bits needed to hold values 0..v
@@ -750,17 +761,29 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         const int stream_waves =
             (((size_t)c->B * c->k <= 512 && row_bytes >= 32768) || row_bytes >= 163840) ? 8 : 4;
         const dim3 sblock((unsigned)(stream_waves * kWave));
+        // Rows side by side on a compute unit.  More than a unit's even share leaves others short, and lets a
+        // second decode's rows in beside the first one's: where the grid fills the chip, no more than that share
+        // (three decodes of 64 x 20 rows of 32000 in flight: 84 against 94 us for three steps, one of them alone
+        // unchanged; 1152 rows of 32003 bf16: 22.8 against 23.1 us per step).  Where rows follow one another, six
+        // waves per SIMD instead of the eight that fit: fewer streams at a time then serve memory better (8192 rows
+        // of 50000, k = 64: 263 against 267 us per step in fp32, 146 against 148.5 with fp16; 2048 rows of 32000, all
+        // resident with eight: 50.9 against 49.6).  Workgroups are kept apart by LDS they do not use; at
+        // least a tenth of a unit's LDS stays free for other work.
+        const size_t rows = (size_t)c->B * c->k, share = (rows + kComputeUnits - 1) / kComputeUnits;
+        const size_t spare = stream_waves == 8 ? (share > 4 ? spread_lds<8>(3) : 0)
+                             : share <= 4 || share == 8 ? 0
+                                                        : spread_lds<4>(share < 8 ? share : 6);
         if (stream_waves == 8) {
             switch (logp_format) {
-                case DBA_LOGP_F16: dba_stream_kernel<kTileLoads, kFmtF16, 8><<<grid, sblock, 0, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
-                case DBA_LOGP_BF16: dba_stream_kernel<kTileLoads, kFmtBF16, 8><<<grid, sblock, 0, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
-                default: dba_stream_kernel<kTileLoads, kFmtF32, 8><<<grid, sblock, 0, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
+                case DBA_LOGP_F16: dba_stream_kernel<kTileLoads, kFmtF16, 8><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
+                case DBA_LOGP_BF16: dba_stream_kernel<kTileLoads, kFmtBF16, 8><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
+                default: dba_stream_kernel<kTileLoads, kFmtF32, 8><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
             }
         } else {
             switch (logp_format) {
-                case DBA_LOGP_F16: dba_stream_kernel<kTileLoads, kFmtF16, 4><<<grid, sblock, 0, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
-                case DBA_LOGP_BF16: dba_stream_kernel<kTileLoads, kFmtBF16, 4><<<grid, sblock, 0, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
-                default: dba_stream_kernel<kTileLoads, kFmtF32, 4><<<grid, sblock, 0, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
+                case DBA_LOGP_F16: dba_stream_kernel<kTileLoads, kFmtF16, 4><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
+                case DBA_LOGP_BF16: dba_stream_kernel<kTileLoads, kFmtBF16, 4><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
+                default: dba_stream_kernel<kTileLoads, kFmtF32, 4><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
             }
         }
         // The merge phase is compiled for (rows per wave, waves): the beam rows of a sentence are dealt out to
