@@ -153,15 +153,17 @@ __global__ __launch_bounds__(NW * kWave) void dba_stream_kernel(const void *logp
 }
 
 // Second launch of a step: the merge phase.  Grid: one workgroup of MW waves per sentence, each wave
-// taking up to ROWS beam rows (k <= ROWS * MW).  The pointers to the row lists and the beam width
-// come first: they are all the first loads need.
-template <int ROWS, int MW>
-__global__ __launch_bounds__(MW * kWave) void dba_merge_kernel(const u64 *rowlists, const u64 *conskeys, int k,
+// taking up to ROWS beam rows (k <= ROWS * MW); J > 0: and holding J entries per lane of all the sentence's lists
+// (k * k <= 64 * J).  The pointers to the row lists and the beam width (k_inv = k | inv_k << 16) come first:
+// they are all the first loads need.
+template <int ROWS, int MW, int J>
+__global__ __launch_bounds__(MW * kWave) void dba_merge_kernel(const u64 *rowlists, const u64 *conskeys, uint32_t k_inv,
                                                                const StepParams p)
 {
     extern __shared__ __align__(16) unsigned char dyn_smem[];
     __shared__ MergeSmem sm;
-    merge_phase<ROWS, MW>(p, rowlists, conskeys, k, (int)blockIdx.x, sm, reinterpret_cast<u64 *>(dyn_smem));
+    merge_phase<ROWS, MW, J>(p, rowlists, conskeys, (int)(k_inv & 0xFFFFu), k_inv >> 16, (int)blockIdx.x, sm,
+                             reinterpret_cast<u64 *>(dyn_smem));
 }
 
 // Reference read: the largest element of each row, one workgroup per row, with the tile order and
@@ -786,23 +788,33 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
                 default: dba_stream_kernel<kTileLoads, kFmtF32, 4><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
             }
         }
-        // The merge phase is compiled for (rows per wave, waves): the beam rows of a sentence are dealt out to
-        // the waves of its workgroup.  Unless the caller fixes the waves: four waves of four rows up to k = 16;
-        // from there on eight waves (of four rows up to k = 32, of eight beyond): fewer lists per wave to merge
-        // and to scan, a wave of its own for every chunk of candidates, at the price of a deeper tree where the
-        // waves' lists are joined (measured on MI355X, one decode: 6.2 / 6.5 us with four / eight waves at
-        // k = 10, 7.7 / 7.0 at k = 20, 19.3 / 14.6 at k = 64).
+        // The merge phase is compiled for (rows per wave, waves, entries per lane).  Unless the caller fixes the
+        // waves: four up to k = 16, eight beyond (fewer lists per wave to merge and to scan, more waves to rank
+        // candidates, at the price of a deeper tree where the waves' lists are joined; one decode, per step: 22.1 / 22.3 us with
+        // four / eight waves at k = 12, 14.7 / 14.7 at k = 16; merge kernel 7.7 / 7.0 us at k = 20, 19.3 / 14.6 at k = 64).
+        // Up to k = 11 every wave holds the k * k entries that matter, one or two a lane, and finds the bar by
+        // itself (16 sentences, k = 10: 14.6 against 14.9 us per step with merged lists); with four and more a
+        // lane the bisection's counts cost more than the merges (k = 16: 15.4 against 15.3, with bf16, where
+        // scores tie, 15.3 against 14.7; k = 20: 35.2 against 33.1; k = 32: 56.1 against 49.5).
         const dim3 mgrid((unsigned)c->B);
         const dim3 mblock8(8 * kWave), mblock4(4 * kWave);
         const int mw = c->merge_waves ? c->merge_waves : (c->k <= 16 ? 4 : 8);
+        const uint32_t k_inv = (uint32_t)c->k | (uint32_t)(c->k == 1 ? 65535 : 65536 / c->k + 1) << 16;
+#define MERGE(ROWS, MW, J) \
+    dba_merge_kernel<ROWS, MW, J><<<mgrid, MW == 4 ? mblock4 : mblock8, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, k_inv, p)
         if (mw == 4) {
-            if (c->k <= 16) dba_merge_kernel<4, 4><<<mgrid, mblock4, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, p.k, p);
-            else if (c->k <= 32) dba_merge_kernel<8, 4><<<mgrid, mblock4, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, p.k, p);
-            else dba_merge_kernel<16, 4><<<mgrid, mblock4, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, p.k, p);
+            if (c->k <= 8) MERGE(2, 4, 1);
+            else if (c->k <= 11) MERGE(4, 4, 2);
+            else if (c->k <= 16) MERGE(4, 4, 0);
+            else if (c->k <= 32) MERGE(8, 4, 0);
+            else MERGE(16, 4, 0);
         } else {
-            if (c->k <= 32) dba_merge_kernel<4, 8><<<mgrid, mblock8, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, p.k, p);
-            else dba_merge_kernel<8, 8><<<mgrid, mblock8, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, p.k, p);
+            if (c->k <= 8) MERGE(2, 8, 1);
+            else if (c->k <= 11) MERGE(2, 8, 2);
+            else if (c->k <= 32) MERGE(4, 8, 0);
+            else MERGE(8, 8, 0);
         }
+#undef MERGE
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(c, DBA_EHIP, "dba_step: launch failed: %s", hipGetErrorString(e));

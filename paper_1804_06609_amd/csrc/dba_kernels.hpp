@@ -126,7 +126,8 @@ struct MergeSmem {
     // per bank (constraints met, 0..64); sized for every value the 7-bit bank field of a key can hold
     int cnt[2 * kMaxCons];
     int alloc[2 * kMaxCons];
-    int start[2 * kMaxCons];
+    int start[2 * kMaxCons];          // candidates in higher banks
+    int first[2 * kMaxCons];          // slots of lower banks: where the bank's selected keys go in `sel`
     uint32_t bar_score;               // with eight waves: the score image of the bar of the k best, from the waves that join the lists,
     int bar_need;                     // and the places left for keys that tie at that score (-1: no tie to settle)
     int ncand;
@@ -713,6 +714,10 @@ __device__ __forceinline__ int expandable_entry(int P, int nmet, u64 inc, int ip
 // pass the rest to banks with spare candidates, nearest first, the higher
 // neighbour before the lower, as much as each can take.
 // adjust = false (Sec. 5): the base split stays; a bank keeps only the slots it can fill.
+// One chain of dependent steps per donor, and early in a decode most banks are empty donors: a
+// donor's hand-outs are one prefix sum and one lane exchange, or, where it has one or two slots or one or two
+// banks can take any, a few bit scans each (16 sentences with 1 to 16 constraints, k = 10: with the counted
+// ranks and the bar of each wave's own, 15.5 -> 14.6 us per step).
 __device__ __forceinline__ int allocate_wave(int k, int C, int c, int c64, int &a64, bool adjust)
 {
     const int lane = lane_id();
@@ -728,6 +733,38 @@ __device__ __forceinline__ int allocate_wave(int k, int C, int c, int c64, int &
     }
 
     u64 donors = __ballot(a > c);                         // fixed before the hand-outs begin:
+    if (C < 64) {
+        int need = max(0, c - a);
+        u64 receivers = __ballot(need > 0);
+        while (donors != 0 && receivers != 0) {
+            const int b = __ffsll((long long)donors) - 1;
+            donors &= donors - 1;
+            int e = __builtin_amdgcn_readlane(a - c, b);
+            if (e > 2 && __popcll(receivers) > 2) {
+                // all receivers at once: what those served before bank x need is a sum over the banks between
+                // x and its mirror image in b, b's side of which counts first
+                const int incl = wave_inclusive_sum(need), y = 2 * b - lane;
+                const int mirror = __shfl(incl, min(max(y, 0), kWave - 1), kWave), q = y < 0 ? 0 : mirror;
+                const int before = lane > b ? incl - need - q : q - incl;
+                need -= min(need, max(0, e - before));
+                receivers = __ballot(need > 0);
+                continue;
+            }
+            // few slots or few receivers: the nearest receiver on either side is a bit scan away
+            while (e > 0 && receivers != 0) {
+                const u64 above = receivers >> b, below = receivers & ((1ull << b) - 1ull);   // b itself is none
+                const int up = above ? __ffsll((long long)above) - 1 : kWave;
+                const int dn = below ? b - (63 - __clzll((long long)below)) : kWave;
+                const int x = up <= dn ? b + up : b - dn;
+                const int n = __builtin_amdgcn_readlane(need, x), g = min(n, e);
+                if (lane == x) need = n - g;
+                e -= g;
+                if (g == n) receivers &= ~(1ull << x);
+            }
+        }
+        a64 = 0;
+        return c - need;                                  // donors keep what they can fill, receivers got the rest
+    }
     bool donor64 = a64 > c64;                             // a receiver never becomes a donor
     for (;;) {
         int b, e;
@@ -892,33 +929,56 @@ __device__ __forceinline__ uint32_t block_best64_sparse(uint32_t (&buf)[kMergeWa
 // MW: waves of the sentence's workgroup; ROWS: beam rows per wave the code is laid out for
 // (k <= MW * ROWS; wave w takes rows w, w + MW, ...): the loops over a wave's rows are unrolled, so a
 // smaller bound keeps the code of small beams short.
-// rowlists, conskeys, k: what the first loads need (p.rowlists, p.conskeys and p.k, handed over apart).
-template <int ROWS, int MW>
+// J: where k * k <= 64 * J, every wave holds the k best of all the sentence's rows, J per lane (the entries that
+// can be among the sentence's k best), and finds the bar by itself; J = 0: a wave holds the lists of its own
+// rows and the waves' lists are merged.
+// rowlists, conskeys, k, inv_k: what the first loads need (p.rowlists, p.conskeys, p.k; floor(2^16 / k) + 1,
+// with which i * inv_k >> 16 is i / k for i < k * k, k <= 32).
+template <int ROWS, int MW, int J>
 __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowlists, const u64 *conskeys, int k,
-                                            int b, MergeSmem &sm, u64 *cand)
+                                            uint32_t inv_k, int b, MergeSmem &sm, u64 *cand)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // in a scalar register: row guards are scalar branches
     // the row lists first: the chain of this phase starts with them, and their addresses need nothing
     // that has to be read from memory first
+    constexpr bool kPacked = J > 0;
     constexpr int kRowsPerWave = ROWS;
-    u64 rl[kRowsPerWave], ck[kRowsPerWave];
+    constexpr int kLists = kPacked ? J : ROWS;
+    u64 rl[kLists], ck[kRowsPerWave];
+    u64 hd[kPacked ? kRowsPerWave : 1];                    // packed: the heads of the lists of the wave's rows
+    uint32_t head_bits = 0;                                // packed: bit j = this lane's entry j is a row's best
+    if constexpr (kPacked) {
 #pragma unroll
-    for (int i = 0; i < kRowsPerWave; ++i) {
-        const int h = wave + i * MW;
-        rl[i] = 0;
-        if (h < k) {
-            const size_t o = ((size_t)b * k + h) * kWave + lane;
-            rl[i] = rowlists[o];
+        for (int j = 0; j < J; ++j) {
+            const uint32_t i = (uint32_t)(j * kWave + lane);
+            rl[j] = 0;
+            if (i < (uint32_t)(k * k)) {
+                const uint32_t h = (i * inv_k) >> 16, at = i - h * (uint32_t)k;
+                head_bits |= (at == 0 ? 1u : 0u) << j;
+                rl[j] = rowlists[((size_t)b * k + h) * kWave + at];
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kRowsPerWave; ++i) {
+            const int h = wave + i * MW;
+            rl[i] = 0;
+            if (h < k) {
+                const size_t o = ((size_t)b * k + h) * kWave + lane;
+                rl[i] = rowlists[o];
+            }
         }
     }
 #pragma unroll
     for (int i = 0; i < kRowsPerWave; ++i) {
         const int h = wave + i * MW;
         ck[i] = 0;
+        if (kPacked) hd[kPacked ? i : 0] = 0;
         if (h < k) {
-            const size_t o = ((size_t)b * k + h) * kWave + lane;
-            ck[i] = conskeys[o];
+            const size_t o = ((size_t)b * k + h) * kWave;
+            ck[i] = conskeys[o + lane];
+            if (kPacked) hd[kPacked ? i : 0] = rowlists[o];
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -947,34 +1007,57 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     const int ld_fin = p.fin_cur[rs];
     // every load above is on its way before anything waits for one of them: the lists are
     // pinned here, or their loads would be moved down to the conditional code that uses them
+    // meanwhile the counters and the candidate buffer are cleared
+    if (tid < 2 * kMaxCons) {
+        sm.cnt[tid] = 0;
+        sm.alloc[tid] = 0;                             // banks beyond the sentence's get no slot
+        sm.start[tid] = 0;
+        sm.first[tid] = 0;
+    }
+    if (tid < kMaxCons) sm.sel[tid] = 0;               // places beyond the last selected key compare as empty
+    if (tid == 0) {
+        sm.ncand = 0;
+        sm.nsel = 0;
+        sm.kept = 0;
+    }
+    for (int i = tid; i < p.cand_cap; i += MW * kWave) cand[i] = 0;
+    if (kPacked) __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kRowsPerWave; ++i) asm volatile("" : "+v"(rl[i]), "+v"(ck[i]));
+    for (int i = 0; i < kLists; ++i) asm volatile("" : "+v"(rl[i]));
+#pragma unroll
+    for (int i = 0; i < kRowsPerWave; ++i) {
+        asm volatile("" : "+v"(ck[i]));
+        if (kPacked) asm volatile("" : "+v"(hd[kPacked ? i : 0]));
+    }
     // ---- source 1: the sentence's k best (Sec. 3.1 item 1) = top k of the union of the row
     // lists.  All that is needed of them is the bar tau a key has to reach to be among them.
     // The k-th best SCORE comes from merging the 32-bit score images alone.  If the keys with
     // that score or a better one are exactly k, that is the bar.  Otherwise several keys tie
     // for the last places: the same merge over the low words (the coordinates, complemented)
     // of the keys with that score finds the last one that gets in. -------------------------
-    uint32_t fell = 0;
-    uint32_t accs = wave_best64<kRowsPerWave, MW, (kRowsPerWave > 4)>(wave, k, k - 1, [&](int i) { return (uint32_t)(rl[i] >> fb); }, fell);
+    uint32_t tau_s = 0;
+    bool settled = true;
+    int need = 0;                                          // places left for keys that tie at the bar's score
+    uint32_t fell = 0, accs = 0;
+    if constexpr (kPacked) {
+        // Every wave for itself: no exchange between waves (one LDS round trip and one barrier cost as much as
+        // three steps of the bisection).
+        uint32_t image[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) image[j] = (uint32_t)(rl[j] >> fb);
+        int reach;
+        tau_s = kth_greatest<J>(image, k, reach);
+        settled = tau_s == 0 || reach == k;
+    } else {
+        accs = wave_best64<kRowsPerWave, MW, (kRowsPerWave > 4)>(wave, k, k - 1, [&](int i) { return (uint32_t)(rl[i] >> fb); }, fell);
+    }
     // the sentence's tables and beam go to LDS only now: their loads were issued after those of the
     // row lists and arrive later, and the merges above needed none of them
     if (tid <= kMaxCons) sm.ct.poff[tid] = ld_poff;
-    if (tid < 2 * kMaxCons) {
-        sm.cnt[tid] = 0;
-        sm.alloc[tid] = 0;                             // banks beyond the sentence's get no slot
-        sm.start[tid] = 0;
-    }
     if (tid < kMaxCons) {
         sm.ct.tok[tid] = ld_tok;
         sm.fbucket[tid] = ld_bucket;
         sm.btok[tid] = ld_btok;
-        sm.sel[tid] = 0;                               // places beyond the last selected key compare as empty
-    }
-    if (tid == 0) {
-        sm.ncand = 0;
-        sm.nsel = 0;
-        sm.kept = 0;
     }
     if (tid < k) {
         HypState hs;
@@ -986,61 +1069,72 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         hs.misc = (ld_fin & kFinFinished) | (__popcll(ld_met) << 8);
         sm.hyp[tid] = hs;
     }
-    sm.wf[wave][lane] = fell;
-    sm.ws[wave][lane] = accs;
-    __syncthreads();                                       // tables and beam are in LDS too
-    const int C = sm.ct.poff[P];
-    // The sentence's best score images, lane i = i-th best, from the waves' lists.  With eight
-    // waves two share a SIMD, and the join is the same work in every wave: the first four (one
-    // per SIMD) do it and hand the outcome to the others.
-    constexpr int kJoiners = MW < 4 ? MW : 4;
-    uint32_t tau_s = 0;
-    bool settled = true;
-    int need = 0;                                          // places left for keys that tie at the bar's score
-    if (wave < kJoiners) {
-        accs = join_best64<MW>(sm.ws, wave, lane, fell);
-        tau_s = (uint32_t)__builtin_amdgcn_readlane((int)accs, k - 1);
-        if (tau_s != 0) {
-            settled = (int)__popcll(__ballot(accs >= tau_s)) == k;  // places k.. hold lower scores
-            if (settled && k == kWave) {
-                // every place is taken: a tie may hide among the keys the merges dropped
-                for (int w = 1; w < MW; ++w) {
-                    const uint32_t f = sm.wf[(wave + w) & (MW - 1)][lane];
-                    fell = fell > f ? fell : f;
+    if constexpr (!kPacked) {
+        sm.wf[wave][lane] = fell;
+        sm.ws[wave][lane] = accs;
+        __syncthreads();
+        // The sentence's best score images, lane i = i-th best, from the waves' lists.  With eight
+        // waves two share a SIMD, and the join is the same work in every wave: the first four (one
+        // per SIMD) do it and hand the outcome to the others.
+        constexpr int kJoiners = MW < 4 ? MW : 4;
+        if (wave < kJoiners) {
+            accs = join_best64<MW>(sm.ws, wave, lane, fell);
+            tau_s = (uint32_t)__builtin_amdgcn_readlane((int)accs, k - 1);
+            if (tau_s != 0) {
+                settled = (int)__popcll(__ballot(accs >= tau_s)) == k;  // places k.. hold lower scores
+                if (settled && k == kWave) {
+                    // every place is taken: a tie may hide among the keys the merges dropped
+                    for (int w = 1; w < MW; ++w) {
+                        const uint32_t f = sm.wf[(wave + w) & (MW - 1)][lane];
+                        fell = fell > f ? fell : f;
+                    }
+                    settled = wave_max_u32(fell) < tau_s;
                 }
-                settled = wave_max_u32(fell) < tau_s;
+            }
+            need = k - __popcll(__ballot(accs > tau_s));
+            if (MW > kJoiners && tid == 0) {
+                sm.bar_score = tau_s;
+                sm.bar_need = settled ? -1 : need;
             }
         }
-        need = k - __popcll(__ballot(accs > tau_s));
-        if (MW > kJoiners && tid == 0) {
-            sm.bar_score = tau_s;
-            sm.bar_need = settled ? -1 : need;
+        if (MW > kJoiners) {
+            __syncthreads();
+            tau_s = sm.bar_score;
+            need = sm.bar_need;
+            settled = need < 0;
         }
-    }
-    if (MW > kJoiners) {
-        __syncthreads();
-        tau_s = sm.bar_score;
-        need = sm.bar_need;
-        settled = need < 0;
     }
     // tau = what a selection-key body has to reach to be among the k best; 0 while fewer than
     // k finite sums exist, in which case every finite sum is among them.
     u64 tau = (u64)tau_s << fb;
     if (!settled) {                                        // the same decision in every wave
-        const uint32_t low_bias = fb < 32 ? 1u : 0u;
-        uint32_t unused = 0;
-        uint32_t accl = wave_best64<kRowsPerWave, MW, true>(wave, k, need - 1, [&](int i) {
-            // the tied keys of a decreasing list are neighbours: move them to the front
-            // (a low word may be 0 where it has fewer than 32 bits: one is added meanwhile)
-            const uint32_t hi = (uint32_t)(rl[i] >> fb);
-            if (__ballot(hi == tau_s) == 0) return 0u;     // most rows hold none
-            const int first = __popcll(__ballot(hi > tau_s));
-            const uint32_t lo = hi == tau_s ? ((uint32_t)rl[i] & flatmask) + low_bias : 0u;
-            const uint32_t moved = (uint32_t)__shfl((int)lo, (lane + first) & (kWave - 1), kWave);
-            return lane + first < kWave ? moved : 0u;
-        }, unused);
-        accl = block_best64_sparse<MW>(sm.ws2, wave, lane, accl, unused);
-        const uint32_t tau_l = (uint32_t)__builtin_amdgcn_readlane((int)accl, need - 1);
+        const uint32_t low_bias = fb < 32 ? 1u : 0u;       // (a low word may be 0 where it has fewer than 32 bits)
+        uint32_t tau_l;
+        if constexpr (kPacked) {
+            uint32_t low[J];
+            int above = 0, reach;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const uint32_t hi = (uint32_t)(rl[j] >> fb);
+                above += (int)__popcll(__ballot(hi > tau_s));
+                low[j] = hi == tau_s ? ((uint32_t)rl[j] & flatmask) + low_bias : 0u;
+            }
+            need = k - above;
+            tau_l = kth_greatest<J>(low, need, reach);
+        } else {
+            uint32_t unused = 0;
+            uint32_t accl = wave_best64<kRowsPerWave, MW, true>(wave, k, need - 1, [&](int i) {
+                // the tied keys of a decreasing list are neighbours: move them to the front
+                const uint32_t hi = (uint32_t)(rl[i] >> fb);
+                if (__ballot(hi == tau_s) == 0) return 0u;     // most rows hold none
+                const int first = __popcll(__ballot(hi > tau_s));
+                const uint32_t lo = hi == tau_s ? ((uint32_t)rl[i] & flatmask) + low_bias : 0u;
+                const uint32_t moved = (uint32_t)__shfl((int)lo, (lane + first) & (kWave - 1), kWave);
+                return lane + first < kWave ? moved : 0u;
+            }, unused);
+            accl = block_best64_sparse<MW>(sm.ws2, wave, lane, accl, unused);
+            tau_l = (uint32_t)__builtin_amdgcn_readlane((int)accl, need - 1);
+        }
         tau = ((u64)tau_s << fb) | (u64)(tau_l - low_bias);
     }
 
@@ -1053,71 +1147,93 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     // Lanes count what they hold themselves; two prefix sums over the wave then give every lane
     // its places (no wave-wide vote per row).
     const bool by_score = settled && tau_s != 0;
-    // a key of a row's list is kept if it reaches tau; lane 0 holds the row's best and keeps any
-    const u64 keep_from = lane == 0 ? 1ull : (tau > 1 ? tau : 1ull);
     // a constraint token is a candidate while below tau.  Where tau stands for a score alone,
     // one with exactly that score is among the k best only if its row's list holds it (every
     // listed key with that score is): those pass for now and are looked up below.
     const u64 below = by_score ? tau + (1ull << fb) : tau;
-    uint32_t gm = 0, cm = 0;                               // bit i: this lane's key of row i is kept
+    const u64 from = tau > 1 ? tau : 1ull;                 // what a listed key has to reach; a row's best need not
+    uint32_t gm = 0, cm = 0;                               // bit i: this lane's key i of the lists / of constraint tokens is kept
     bool some_tied = false;
-    if (tau != 0) {
+#pragma unroll
+    for (int i = 0; i < kLists; ++i) {
+        const bool head = kPacked ? ((head_bits >> i) & 1u) != 0 : lane == 0;
+        gm |= ((rl[i] & body_mask) >= (head ? 1ull : from) ? 1u : 0u) << i;    // (an empty place holds 0)
+    }
+    if (tau != 0) {                                        // (else all finite sums are listed: none is left for source 2)
 #pragma unroll
         for (int i = 0; i < kRowsPerWave; ++i) {
             if (wave + i * MW < k) {
-                const u64 best = read_lane(rl[i], 0) & body_mask;
-                gm |= ((rl[i] & body_mask) >= keep_from ? 1u : 0u) << i;
+                const u64 best = (kPacked ? hd[kPacked ? i : 0] : read_lane(rl[kPacked ? 0 : i], 0)) & body_mask;
                 const u64 body = ck[i] & body_mask;
                 const bool valid = body - 1 < below - 1 && body != best;      // (an empty place holds 0)
                 cm |= (valid ? 1u : 0u) << i;
                 if (by_score) some_tied |= valid && body >= tau;
             }
         }
-    } else {
-        // fewer than k finite sums: all of them are among the k best, none is left for source 2
-#pragma unroll
-        for (int i = 0; i < kRowsPerWave; ++i)
-            if (wave + i * MW < k) gm |= (rl[i] != 0 ? 1u : 0u) << i;
     }
     if (__ballot(some_tied)) {                             // rare
 #pragma unroll
         for (int i = 0; i < kRowsPerWave; ++i) {
-            if (wave + i * MW < k) {
+            const int h = wave + i * MW;
+            if (h < k) {
                 const u64 body = ck[i] & body_mask;
+                // (places from k on cannot be among the k best)
+                const u64 listed = lane >= k ? 0ull : (kPacked ? rowlists[((size_t)b * k + h) * kWave + lane] : rl[kPacked ? 0 : i]);
                 u64 tied = __ballot(((cm >> i) & 1u) != 0 && body >= tau);
                 while (tied) {
                     const int l = __ffsll((long long)tied) - 1;
                     tied &= tied - 1;
                     const u64 one = read_lane(body, l);
-                    if (__ballot((rl[i] & body_mask) == one) != 0 && lane == l) cm &= ~(1u << i);
+                    if (__ballot((listed & body_mask) == one) != 0 && lane == l) cm &= ~(1u << i);
                 }
             }
         }
     }
     // Both kinds of key arrive with their bank (the constraints met once the token is placed, worked
     // out with add() by the row's own workgroup, Sec. 3.1), so a kept key goes straight to its place.
-    const int g = __popc(gm), c = __popc(cm);              // this lane's keys from sources 1 and 3, from source 2
-    const int g_incl = wave_inclusive_sum(g), c_incl = wave_inclusive_sum(c);
-    const int n13_all = __builtin_amdgcn_readlane(g_incl, kWave - 1);
-    const int total = n13_all + __builtin_amdgcn_readlane(c_incl, kWave - 1);
-    int at = 0;
-    if (lane == 0 && total > 0) at = atomicAdd(&sm.ncand, total);
-    at = __builtin_amdgcn_readfirstlane(at);
-    // The count cannot exceed the room (at most k keys reach tau, a row adds one more only if none of
+    // The counts cannot exceed the room (at most k keys reach tau, a row adds one more only if none of
     // its keys does, the host sized `cand` for every source) as long as the row lists are what the
     // stream phase writes: decreasing, distinct keys.  A wave that finds otherwise writes nothing: a
     // damaged list costs a wrong beam, not a stray write.  (The bank tables hold every value the
     // bank field of a key can take.)
-    if (at + total <= p.cand_cap) {
-        int to = at + g_incl - g;
+    const int c = __popc(cm);                              // this lane's keys from source 2
+    const int c_incl = wave_inclusive_sum(c);
+    const int c_all = __builtin_amdgcn_readlane(c_incl, kWave - 1);
+    int listed_all = 0, room = c_all;                      // packed: every wave knows all kept keys of the lists
+    int g = 0, g_incl = 0;
+    if constexpr (kPacked) {
 #pragma unroll
-        for (int i = 0; i < kRowsPerWave; ++i) {
-            if (wave + i * MW < k && ((gm >> i) & 1u)) {
-                cand[to++] = rl[i];
-                atomicAdd(&sm.cnt[mb ? (int)(rl[i] >> sel_shift) : 0], 1);    // bank = constraints met (Sec. 3.1)
+        for (int j = 0; j < J; ++j) {
+            const u64 mask = __ballot(((gm >> j) & 1u) != 0);
+            if (j % MW == wave && ((gm >> j) & 1u) != 0) {
+                const int to = listed_all + lanes_before(mask);
+                if (to < p.cand_cap) {
+                    cand[to] = rl[j];
+                    atomicAdd(&sm.cnt[mb ? (int)(rl[j] >> sel_shift) : 0], 1);    // bank = constraints met (Sec. 3.1)
+                }
+            }
+            listed_all += (int)__popcll(mask);
+        }
+    } else {
+        g = __popc(gm);                                    // this lane's keys from sources 1 and 3
+        g_incl = wave_inclusive_sum(g);
+        room += __builtin_amdgcn_readlane(g_incl, kWave - 1);
+    }
+    int at = 0;
+    if (lane == 0 && room > 0) at = atomicAdd(&sm.ncand, room);
+    at = listed_all + __builtin_amdgcn_readfirstlane(at);
+    if (at + room <= p.cand_cap) {
+        if constexpr (!kPacked) {
+            int to = at + g_incl - g;
+#pragma unroll
+            for (int i = 0; i < kRowsPerWave; ++i) {
+                if (wave + i * MW < k && ((gm >> i) & 1u)) {
+                    cand[to++] = rl[kPacked ? 0 : i];
+                    atomicAdd(&sm.cnt[mb ? (int)(rl[kPacked ? 0 : i] >> sel_shift) : 0], 1);
+                }
             }
         }
-        to = at + n13_all + c_incl - c;
+        int to = at + room - c_all + c_incl - c;
 #pragma unroll
         for (int i = 0; i < kRowsPerWave; ++i) {
             if (wave + i * MW < k && ((cm >> i) & 1u)) {
@@ -1126,8 +1242,9 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
             }
         }
     }
-    __syncthreads();
-    const int ncand = min(sm.ncand, p.cand_cap);
+    __syncthreads();                                       // tables and beam are in LDS too
+    const int C = sm.ct.poff[P];
+    const int ncand = min(listed_all + sm.ncand, p.cand_cap);
     const int nchunks = (ncand + kWave - 1) >> 6;
 
     // ---- slots per bank (Sec. 3.2) --------------------------------------------------------
@@ -1137,61 +1254,95 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         int a64;
         const int a = allocate_wave(k, C, c, c64, a64, p.adjust != 0);
         sm.alloc[lane] = a;
-        if (lane == 0) sm.alloc[kMaxCons] = a64;
         const int cc = lane <= C ? c : 0;
         const int incl = wave_inclusive_sum(cc);          // candidates in banks <= lane
+        const int slots = wave_inclusive_sum(a);
         const int total63 = __builtin_amdgcn_readlane(incl, 63);
+        const int slots63 = __builtin_amdgcn_readlane(slots, 63);
         const int c64v = C == 64 ? c64 : 0;
         sm.start[lane] = (total63 - incl) + c64v;         // candidates in higher banks
-        if (lane == 0) sm.start[kMaxCons] = 0;
+        sm.first[lane] = slots - a;
+        if (lane == 0) {
+            sm.alloc[kMaxCons] = a64;
+            sm.start[kMaxCons] = 0;
+            sm.first[kMaxCons] = slots63;
+            sm.nsel = slots63 + a64;
+        }
     }
-    // ---- every candidate's place in the order (bank desc, score desc, coordinate asc):
-    // chunks of 64 are sorted by one wave each (wave 0, busy with the allocation, last); a
-    // candidate's rank is its place in its own chunk plus, by a search with three probes a round,
-    // the keys greater than it in every other chunk ------------------------------------------------------------
-    const int my_first = MW - 1 - wave;
-    for (int c = my_first; c < nchunks; c += MW) {
-        const int i = c * kWave + lane;
-        cand[i] = sort64_desc<u64, true>(i < ncand ? cand[i] : 0ull);
-    }
-    __syncthreads();
-    for (int c = my_first; c < nchunks; c += MW) {
-        const u64 mine = cand[c * kWave + lane];
-        int rank = lane;
-        // four searches at a time, so that their LDS reads overlap
-        for (int c0 = 0; c0 < nchunks; c0 += 4) {
-            int pos[4];
-            bool full[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int c2 = c0 + q < nchunks ? c0 + q : c;     // out of range: own chunk, ignored below
-                pos[q] = 0;
-                full[q] = cand[c2 * kWave + 63] > mine;
-            }
-            // three probes a round (quarters, then sixteenths, then single places): three
-            // dependent trips to LDS instead of six
-#pragma unroll
-            for (int step = 16; step >= 1; step >>= 2) {
+    // ---- every candidate's place in the order (bank desc, score desc, coordinate asc), then within a
+    // bank the best alloc[bank] are taken (Sec. 3.1/3.2) -------------------------------------
+    auto select = [&](u64 mine, int rank) {
+        const int bank = mb ? (int)(mine >> sel_shift) : 0;
+        const int place = rank - sm.start[bank];
+        if ((uint32_t)place < (uint32_t)sm.alloc[bank]) sm.sel[min(sm.first[bank] + place, kMaxBeam - 1)] = mine & body_mask;
+    };
+    constexpr int kCounters = MW - 1;                      // waves that count while wave 0 allocates
+    // Up to here counting (n / lanes-per-candidate compares, no chain) is shorter than a 64-lane sort and
+    // searches in the other chunks; at twice as many candidates it is longer (64 sentences, k = 32, 100 to 200
+    // candidates: merge kernel 7.7 us with this limit, 8.3 with twice it, 7.6 sorted throughout; k = 20, about 80 of
+    // them in most steps: 6.6 against 7.2 us sorted throughout).
+    constexpr int kCountLimit = MW == 8 ? 112 : 96;
+    if (ncand <= kCountLimit) {
+        // Few candidates (the usual case): the rank is the number of greater keys, counted over all of them.  A wave
+        // takes 16 or 32 candidates, four or two lanes each, the lanes of a candidate each count a share.
+        static_assert(kCountLimit <= 32 * kCounters, "every candidate has its lanes");
+        const int each = ncand <= 16 * kCounters ? 16 : 32;
+        const int share = kWave / each;                    // lanes per candidate
+        const int i = (wave - 1) * each + (lane & (each - 1));
+        u64 mine = 0;
+        int rank = 0;
+        if (wave > 0 && (wave - 1) * each < ncand) {
+            mine = i < ncand ? cand[i] : 0ull;
+            const u64 *key = cand + lane / each;
+            for (int j = 0; j < ncand; j += 4 * share)     // (places from ncand to the next multiple of 16 hold 0)
+                rank += (key[j] > mine ? 1 : 0) + (key[j + share] > mine ? 1 : 0) + (key[j + 2 * share] > mine ? 1 : 0) +
+                        (key[j + 3 * share] > mine ? 1 : 0);
+            rank += (int)xor_lane_u32<32, true>((uint32_t)rank);
+            if (each == 16) rank += (int)xor_lane_u32<16, true>((uint32_t)rank);
+        }
+        __syncthreads();
+        if (mine != 0 && lane < each) select(mine, rank);
+    } else {
+        // chunks of 64 are sorted by one wave each (wave 0, busy with the allocation, last); a
+        // candidate's rank is its place in its own chunk plus, by a search with three probes a round,
+        // the keys greater than it in every other chunk
+        const int my_first = MW - 1 - wave;
+        for (int c = my_first; c < nchunks; c += MW) {
+            const int i = c * kWave + lane;
+            cand[i] = sort64_desc<u64, true>(i < ncand ? cand[i] : 0ull);
+        }
+        __syncthreads();
+        for (int c = my_first; c < nchunks; c += MW) {
+            const u64 mine = cand[c * kWave + lane];
+            int rank = lane;
+            // four searches at a time, so that their LDS reads overlap
+            for (int c0 = 0; c0 < nchunks; c0 += 4) {
+                int pos[4];
+                bool full[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int c2 = c0 + q < nchunks ? c0 + q : c;
-                    const u64 *at0 = cand + c2 * kWave + pos[q] - 1;
-                    const int above = (at0[step] > mine ? 1 : 0) + (at0[2 * step] > mine ? 1 : 0) +
-                                      (at0[3 * step] > mine ? 1 : 0);
-                    pos[q] += step * above;
+                    const int c2 = c0 + q < nchunks ? c0 + q : c;     // out of range: own chunk, ignored below
+                    pos[q] = 0;
+                    full[q] = cand[c2 * kWave + 63] > mine;
                 }
-            }
+                // three probes a round (quarters, then sixteenths, then single places): three
+                // dependent trips to LDS instead of six
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (c0 + q < nchunks && c0 + q != c) rank += full[q] ? 64 : pos[q];
-        }
-        if (mine != 0) {
-            const int bank = mb ? (int)(mine >> sel_shift) : 0;
-            // within a bank the best alloc[bank] are taken (Sec. 3.1/3.2)
-            if (rank - sm.start[bank] < sm.alloc[bank]) {
-                const int place = atomicAdd(&sm.nsel, 1);
-                if (place < kMaxBeam) sm.sel[place] = mine & body_mask;
+                for (int step = 16; step >= 1; step >>= 2) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int c2 = c0 + q < nchunks ? c0 + q : c;
+                        const u64 *at0 = cand + c2 * kWave + pos[q] - 1;
+                        const int above = (at0[step] > mine ? 1 : 0) + (at0[2 * step] > mine ? 1 : 0) +
+                                          (at0[3 * step] > mine ? 1 : 0);
+                        pos[q] += step * above;
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (c0 + q < nchunks && c0 + q != c) rank += full[q] ? 64 : pos[q];
             }
+            if (mine != 0) select(mine, rank);
         }
     }
     __syncthreads();

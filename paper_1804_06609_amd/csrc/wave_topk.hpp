@@ -253,4 +253,58 @@ __device__ __forceinline__ int wave_inclusive_sum(int v)
     return v;
 }
 
+// Greatest value of v over the wave, as a wave-uniform value (the carries of the prefix sum above).
+__device__ __forceinline__ uint32_t wave_max_uniform(uint32_t v)
+{
+    uint32_t o;
+    o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);  v = v > o ? v : o;
+    o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);  v = v > o ? v : o;
+    o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);  v = v > o ? v : o;
+    o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);  v = v > o ? v : o;
+    o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false); v = v > o ? v : o;
+    o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false); v = v > o ? v : o;
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
+// The k-th greatest of the wave's J * 64 keys, exactly (0 = no key; 0 if there are fewer than k), and how many
+// reach it: k unless several equal it.  Bisection between the least and the greatest key; a step is J compares,
+// J bit counts and a few more scalar instructions, and ends as soon as exactly k keys reach the
+// bound, after about nine steps for scores of some hundred near candidates.
+template <int J>
+__device__ __forceinline__ uint32_t kth_greatest(const uint32_t (&r)[J], int k, int &count)
+{
+    auto reached = [&](uint32_t x) {
+        int c = 0;
+#pragma unroll
+        for (int j = 0; j < J; ++j) c += (int)__popcll(__ballot(r[j] >= x));
+        return c;
+    };
+    auto least_from = [&](uint32_t x) {                   // the least key >= x, x > 0 (~0 if there is none)
+        uint32_t v = 0;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const uint32_t inv = r[j] >= x ? ~r[j] : 0u;
+            v = v > inv ? v : inv;
+        }
+        return ~wave_max_uniform(v);
+    };
+    count = reached(1u);
+    if (count < k) return 0;
+    uint32_t mx = r[0];
+#pragma unroll
+    for (int j = 1; j < J; ++j) mx = mx > r[j] ? mx : r[j];
+    uint32_t lo = least_from(1u), hi = wave_max_uniform(mx);
+    while (count != k && lo < hi) {
+        const uint32_t mid = lo + ((hi - lo + 1) >> 1);
+        const int c = reached(mid);
+        if (c >= k) {
+            lo = mid;
+            count = c;
+        } else {
+            hi = mid - 1;
+        }
+    }
+    return least_from(lo);
+}
+
 }  // namespace dba

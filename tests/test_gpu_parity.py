@@ -425,6 +425,23 @@ def test_merge_phase_with_four_and_with_eight_waves(torch_gpu, cfg, T, B, waves)
     _harness().run_parity(wl, options={dba.DBA_OPT_MERGE_WAVES: waves})
 
 
+@pytest.mark.parametrize("waves", [4, 8])
+@pytest.mark.parametrize("phrases", [0, 3, 9, 30])
+@pytest.mark.parametrize("k", [1, 8, 9, 11, 12, 16, 17, 32, 33])
+def test_merge_phase_at_the_edges_of_its_variants(torch_gpu, k, phrases, waves):
+    """Beam sizes on both sides of every variant (entries of all lists in one or two registers a lane, lists
+    merged), with few and with many candidates (ranks counted or chunks sorted: 96 and 112 candidates lie
+    between 9 and 30 phrases for the middle beam sizes), ordinary scores and scores that tie everywhere."""
+    import paper_1804_06609_amd as dba
+    B, V, T = 3, 700, 5
+    cons = [[[w] for w in range(20 + b, 20 + b + 7 * phrases, 7)] for b in range(B)]
+    boost = [[w for p in s for w in p] for s in cons]
+    for cls in (si.Workload, _TieHeavy):
+        wl = cls(B=B, k=k, V=V, T=T, seed=7100 + k, constraints=cons, boost_tokens=boost, boost_prob=0.4, boost_value=4.0)
+        wl.eos_switch = 3
+        _harness().run_parity(wl, options={dba.DBA_OPT_MERGE_WAVES: waves})
+
+
 def test_paper_setup_config2(torch_gpu):
     """Config 2 shapes with the decoding set-up of Sec. 4: score per word for completed
     hypotheses, pruning threshold 20; end-of-sentence becomes likely after a third of the run."""
