@@ -268,69 +268,112 @@ __global__ void dba_init_state_kernel(int B, int k, const int32_t *phr_off, cons
     }
 }
 
-// End of decoding (Sec. 3.3, length normalisation of Sec. 4): one thread per sentence.
+// End of decoding (Sec. 3.3, length normalisation of Sec. 4): one workgroup per sentence.
 // best != null: the record of the best completed hypothesis seen on any beam decides, if there is one.
-__global__ void dba_finalize_kernel(int B, int k, int T, int N, int pad_id, int normalized,
-                                    const int32_t *hist_token, const int32_t *hist_backptr,
-                                    const float *score, const u64 *met, const int32_t *len,
-                                    const uint8_t *fin, const BestCompleted *best_rec, int32_t *out_tokens,
-                                    int32_t *out_len, float *out_score, int32_t *out_status)
+//
+// The back-pointers form one chain over all steps; followed in memory every link costs a trip there (71 us
+// for 64 sentences of 100 steps, one thread each).  Here the eight waves fetch the parents of all slots of
+// kFinSteps steps at once, one row of a beam per load, into LDS; one wave then reads rows that do not depend on the
+// chain, lane = slot, and follows it with lane reads.  The tokens along it are fetched 64 at a time.
+// (The call, copies to the host included: 172 -> 117 us there, 236 -> 126 for 128 sentences of 120 steps, k = 64.)
+constexpr int kFinWaves = 8, kFinRows = 16, kFinSteps = kFinWaves * kFinRows;
+
+__global__ __launch_bounds__(kFinWaves * kWave) void dba_finalize_kernel(
+    int B, int k, int T, int N, int pad_id, int normalized, const int32_t *hist_token, const int32_t *hist_backptr,
+    const float *score, const u64 *met, const int32_t *len, const uint8_t *fin, const BestCompleted *best_rec,
+    int32_t *out_tokens, int32_t *out_len, float *out_score, int32_t *out_status)
 {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
+    __shared__ uint8_t parent[kFinSteps][kWave];
+    const int b = (int)blockIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     int32_t *toks = out_tokens + (size_t)b * N;
-    for (int i = 0; i < N; ++i) toks[i] = pad_id;
-    out_len[b] = 0;
-    out_score[b] = -INFINITY;
-    out_status[b] = 0;
-    if (T < 1) return;
-    if (best_rec && best_rec[b].have) {
-        const BestCompleted r = best_rec[b];
-        out_status[b] = 1;
-        out_len[b] = r.len;
-        out_score[b] = r.score;
-        int slot = r.slot;
-        for (int t = r.step; t >= 0; --t) {
-            const size_t at = ((size_t)t * B + b) * k + slot;
-            if (t < r.len && t < N) toks[t] = hist_token[at];
-            slot = hist_backptr[at];
+    auto at = [&](int t, int slot) { return ((size_t)t * B + b) * k + slot; };
+    // parents of steps hi - kFinSteps + 1 .. hi, row hi - r in parent[r]
+    int row[kFinRows];
+    auto fetch = [&](int hi) {
+#pragma unroll
+        for (int i = 0; i < kFinRows; ++i) {
+            const int t = hi - (i * kFinWaves + wave);
+            row[i] = 0;
+            if (t >= 0 && lane < k) row[i] = hist_backptr[at(t, lane)];
         }
-        return;
-    }
-    const size_t o = (size_t)b * k;
-    int best = -1;
-    float bestq = 0.0f;
-    for (int h = 0; h < k; ++h) {
-        if (!(score[o + h] > -INFINITY) || !(fin[o + h] & kFinFinished)) continue;
-        // per-word score; already held by the beam when completed hypotheses are stored that way
-        const float q = normalized ? score[o + h] : __fdiv_rn(score[o + h], (float)len[o + h]);
-        if (best < 0 || q > bestq) {
-            best = h;
-            bestq = q;
-        }
-    }
-    if (best >= 0) {
-        out_status[b] = 1;
-    } else {
-        int bestn = -1;
-        for (int h = 0; h < k; ++h) {
-            if (!(score[o + h] > -INFINITY)) continue;
-            const int n = __popcll(met[o + h]);
-            if (best < 0 || n > bestn || (n == bestn && score[o + h] > score[o + best])) {
-                best = h;
-                bestn = n;
+    };
+    fetch(T - 1);                                          // (the last steps are needed nearly always)
+
+    // which hypothesis: every wave finds out for itself, lane = slot
+    int status = 0, length = 0, last = -1, slot = 0;
+    float value = -INFINITY;
+    if (T >= 1) {
+        if (best_rec && best_rec[b].have) {
+            const BestCompleted r = best_rec[b];
+            status = 1;
+            length = r.len;
+            value = r.score;
+            last = r.step;
+            slot = r.slot;
+        } else {
+            const size_t o = (size_t)b * k + (lane < k ? lane : 0);
+            const float s = score[o];
+            const int l = len[o];
+            const bool live = lane < k && s > -INFINITY, done = live && (fin[o] & kFinFinished) != 0;
+            const u64 any_done = __ballot(done), any_live = __ballot(live);
+            u64 among = any_live;                          // slots still in question; ties go to the lowest
+            uint32_t image = 0;
+            if (any_done) {
+                // per-word score; already held by the beam when completed hypotheses are stored that way
+                status = 1;
+                if (done) image = ord_from_float(normalized ? s : __fdiv_rn(s, (float)l));
+                among = any_done;
+            } else if (any_live) {
+                const uint32_t n = live ? 1u + (uint32_t)__popcll(met[o]) : 0u;
+                const uint32_t most = wave_max_uniform(n);     // (every lane takes part)
+                among = __ballot(live && n == most);
+                if ((among >> lane) & 1ull) image = ord_from_float(s);
+            }
+            if (among) {
+                const uint32_t top = wave_max_uniform(image);
+                slot = __ffsll((long long)__ballot(((among >> lane) & 1ull) && image == top)) - 1;
+                length = __builtin_amdgcn_readlane(l, slot);
+                value = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(s), slot));
+                last = T - 1;
             }
         }
-        if (best < 0) return;
     }
-    const int L = len[o + best];
-    out_len[b] = L;
-    out_score[b] = score[o + best];
-    int slot = best;
-    for (int t = T - 1; t >= 0; --t) {
-        const size_t r = ((size_t)t * B + b) * k + slot;
-        if (t < L && t < N) toks[t] = hist_token[r];
-        slot = hist_backptr[r];
+    length = __builtin_amdgcn_readfirstlane(length);
+    last = __builtin_amdgcn_readfirstlane(last);
+    slot = __builtin_amdgcn_readfirstlane(slot);
+    if (threadIdx.x == 0) {
+        out_len[b] = length;
+        out_score[b] = value;
+        out_status[b] = status;
+    }
+    const int ntoks = min(min(length, last + 1), N);       // steps 0 .. ntoks-1 give a token each
+    for (int i = max(ntoks, 0) + (int)threadIdx.x; i < N; i += kFinWaves * kWave) toks[i] = pad_id;
+
+    for (int hi = T - 1; hi >= 0 && last >= 0; hi -= kFinSteps) {
+        if (hi != T - 1) fetch(hi);
+#pragma unroll
+        for (int i = 0; i < kFinRows; ++i) parent[i * kFinWaves + wave][lane] = (uint8_t)row[i];
+        __syncthreads();
+        if (wave == 0) {
+            for (int t0 = min(hi, last); t0 > hi - kFinSteps && t0 >= 0; t0 -= kWave) {
+                int mine = 0;                              // lane j: the slot at step t0 - j
+                const int n = min(min(kWave, t0 + 1), t0 - (hi - kFinSteps));
+                for (int j0 = 0; j0 < n; j0 += 8) {
+                    int p[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) p[j] = parent[min(hi - t0 + j0 + j, kFinSteps - 1)][lane];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        if (lane == j0 + j) mine = slot;
+                        if (j0 + j < n) slot = __builtin_amdgcn_readlane(p[j], slot & (kWave - 1));
+                    }
+                }
+                const int t = t0 - lane;
+                if (lane < n && t < ntoks) toks[t] = hist_token[at(t, min(mine, k - 1))];
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -861,7 +904,7 @@ DBA_API int dba_finalize(dba_ctx *c, int32_t *out_tokens_host, int32_t *out_len_
         return fail(c, DBA_EINVAL, "dba_finalize: an output pointer is NULL");
     const Layout &L = c->L;
     const int cur = c->steps & 1;
-    dba_finalize_kernel<<<(c->B + 63) / 64, 64, 0, c->stream>>>(
+    dba_finalize_kernel<<<c->B, kFinWaves * kWave, 0, c->stream>>>(
         c->B, c->k, c->steps, c->N, c->pad_id, c->normalize, at<int32_t>(c, L.hist_token),
         at<int32_t>(c, L.hist_backptr),
         at<float>(c, L.score[cur]), at<u64>(c, L.met[cur]), at<int32_t>(c, L.len[cur]),

@@ -442,6 +442,21 @@ def test_merge_phase_at_the_edges_of_its_variants(torch_gpu, k, phrases, waves):
         _harness().run_parity(wl, options={dba.DBA_OPT_MERGE_WAVES: waves})
 
 
+@pytest.mark.parametrize("track", [False, True])
+@pytest.mark.parametrize("T", [1, 2, 63, 64, 65, 127, 128, 129, 130, 192, 257])
+@pytest.mark.parametrize("k", [1, 5, 64])
+def test_trace_back_lengths(torch_gpu, T, k, track):
+    """dba_finalize follows the back-pointers 64 steps a time out of blocks of 128: decodes of one block, one more
+    and one less, hypotheses that complete early and late (per-word record kept or not) or, with a constraint
+    that cannot be met, not at all."""
+    V = 70
+    cons = [[], [[5, 6]], [[w] for w in range(4, 4 + min(30, 2 * T))] * 2]
+    wl = si.Workload(B=3, k=k, V=V, T=T, seed=9100 + T, constraints=cons)
+    wl.eos_switch = T // 3
+    wl.eos_high = 0.0
+    _harness().run_parity(wl, check_state_every=0, track=track, normalize=track)
+
+
 def test_paper_setup_config2(torch_gpu):
     """Config 2 shapes with the decoding set-up of Sec. 4: score per word for completed
     hypotheses, pruning threshold 20; end-of-sentence becomes likely after a third of the run."""
