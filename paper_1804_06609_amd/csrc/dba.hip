@@ -5,6 +5,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -589,9 +590,18 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     for (int b = 0; b < B; ++b)
         if (sent_offsets[b + 1] < sent_offsets[b])
             return fail(nullptr, DBA_EINVAL, "dba_init: sent_offsets decreases at %d", b);
-    std::vector<int32_t> tok((size_t)B * kMaxCons, 0), off((size_t)B * (kMaxCons + 1), 0), nph(B, 0);
-    std::vector<u64> sfl((size_t)B * kMaxCons, 0), bloom((size_t)B * kMaxCons, 0);
-    std::vector<int32_t> ftok((size_t)B * kMaxCons, -1), btok((size_t)B * kMaxCons, -1);
+    // (an image of the tables' stretch of the workspace, so that one copy takes them all to the device: a copy from
+    // ordinary host memory costs about 8 us whatever its size)
+    const Layout L = make_layout((size_t)B, (size_t)k, (size_t)N);
+    const size_t tables_bytes = L.rowlists - L.cons_tok;
+    std::vector<unsigned char> image(tables_bytes, 0);
+    auto table = [&](size_t off) { return image.data() + (off - L.cons_tok); };
+    int32_t *tok = reinterpret_cast<int32_t *>(table(L.cons_tok)), *off = reinterpret_cast<int32_t *>(table(L.phr_off));
+    int32_t *nph = reinterpret_cast<int32_t *>(table(L.nphr));
+    u64 *sfl = reinterpret_cast<u64 *>(table(L.sfl)), *bloom = reinterpret_cast<u64 *>(table(L.bloom));
+    int32_t *ftok = reinterpret_cast<int32_t *>(table(L.ftok)), *btok = reinterpret_cast<int32_t *>(table(L.btok));
+    std::fill(ftok, ftok + (size_t)B * kMaxCons, -1);
+    std::fill(btok, btok + (size_t)B * kMaxCons, -1);
     int max_tokens = 0, max_phrases = 0;
     for (int b = 0; b < B; ++b) {
         const int p0 = sent_offsets[b], p1 = sent_offsets[b + 1];
@@ -644,7 +654,6 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
                     "dba_init: bits(k-1)=%d + bits(V-1)=%d + bits(max constraint tokens)=%d exceed the 32-bit "
                     "coordinate field of the selection key (or V > 2^24)", slot_bits, tok_bits, met_bits);
 
-    const Layout L = make_layout((size_t)B, (size_t)k, (size_t)N);
     if (workspace_bytes < L.total)
         return fail(nullptr, DBA_ENOMEM, "dba_init: workspace has %zu bytes, %zu needed", workspace_bytes, L.total);
 
@@ -674,20 +683,7 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     const int ncand_max = (k * (max_phrases + 2) + kWave - 1) / kWave * kWave;
     c->dyn_smem = (size_t)ncand_max * sizeof(u64);
 
-    hipError_t e;
-    e = hipMemcpyAsync(at<int32_t>(c, L.cons_tok), tok.data(), tok.size() * 4, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(at<int32_t>(c, L.phr_off), off.data(), off.size() * 4, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(at<int32_t>(c, L.nphr), nph.data(), nph.size() * 4, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(at<int32_t>(c, L.ftok), ftok.data(), ftok.size() * 4, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(at<u64>(c, L.sfl), sfl.data(), sfl.size() * 8, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(at<u64>(c, L.bloom), bloom.data(), bloom.size() * 8, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(at<int32_t>(c, L.btok), btok.data(), btok.size() * 4, hipMemcpyHostToDevice, c->stream);
+    hipError_t e = hipMemcpyAsync(c->ws + L.cons_tok, image.data(), tables_bytes, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) {
         const int n = B * k;
         dba_init_state_kernel<<<(n + 255) / 256, 256, 0, c->stream>>>(
@@ -697,7 +693,7 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
             at<uint8_t>(c, L.all_finished), at<BestCompleted>(c, L.best));
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);   // host tables are freed on return
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);   // the image is freed on return
     if (e != hipSuccess) {
         const int rc = fail(nullptr, DBA_EHIP, "dba_init: HIP error: %s", hipGetErrorString(e));
         delete c;
@@ -912,17 +908,21 @@ DBA_API int dba_finalize(dba_ctx *c, int32_t *out_tokens_host, int32_t *out_len_
         at<int32_t>(c, L.fin_tokens), at<int32_t>(c, L.fin_len),
         at<float>(c, L.fin_score), at<int32_t>(c, L.fin_status));
     hipError_t e = hipGetLastError();
-    const size_t B = (size_t)c->B;
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(out_tokens_host, at<int32_t>(c, L.fin_tokens), B * c->N * 4, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(out_len_host, at<int32_t>(c, L.fin_len), B * 4, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(out_score_host, at<float>(c, L.fin_score), B * 4, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(out_status_host, at<int32_t>(c, L.fin_status), B * 4, hipMemcpyDeviceToHost, c->stream);
+    // the four results lie side by side: one copy (see dba_init), then apart
+    const size_t B = (size_t)c->B, bytes = L.fin_status + B * 4 - L.fin_tokens;
+    unsigned char *tmp = static_cast<unsigned char *>(malloc(bytes));
+    if (!tmp) return fail(c, DBA_ENOMEM, "dba_finalize: out of host memory");
+    struct Free {
+        unsigned char *p;
+        ~Free() { free(p); }
+    } guard{tmp};
+    if (e == hipSuccess) e = hipMemcpyAsync(tmp, c->ws + L.fin_tokens, bytes, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return fail(c, DBA_EHIP, "dba_finalize: HIP error: %s", hipGetErrorString(e));
+    memcpy(out_tokens_host, tmp, B * c->N * 4);
+    memcpy(out_len_host, tmp + (L.fin_len - L.fin_tokens), B * 4);
+    memcpy(out_score_host, tmp + (L.fin_score - L.fin_tokens), B * 4);
+    memcpy(out_status_host, tmp + (L.fin_status - L.fin_tokens), B * 4);
     return DBA_OK;
 }
 
