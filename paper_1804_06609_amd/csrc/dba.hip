@@ -25,7 +25,7 @@ using namespace dba;
 // logp, V, k, first_step are what the first loads need; the kernels take them as leading scalar
 // arguments, which the hardware hands over in registers at wave start (kernel-argument preload),
 // so that the first two tiles are requested before any argument has been read from memory.
-template <int U, int FMT, int NW>
+template <int U, int FMT, int NW, int D>
 __device__ __forceinline__ void stream_phase(const StepParams &p, const void *logp, int V, int k, int first_step,
                                              int b, int h, StreamSmem<NW> &sm)
 {
@@ -40,7 +40,7 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
     // the hypothesis, and the loads of the hypothesis (uniform, hence scalar loads the wave has to
     // wait for one after the other) would otherwise hold them back
     const elem_t *__restrict__ logp_row = static_cast<const elem_t *>(logp) + (size_t)row * (size_t)V;
-    RowStream<U, FMT> rs;
+    RowStream<U, FMT, D> rs;
     const bool known_empty = first_step && h != 0;   // decoder-init leaves slots 1.. empty
     if (!known_empty) rs.begin(logp_row, V, wave, nwaves);
     __builtin_amdgcn_sched_barrier(0);
@@ -140,7 +140,7 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
 // all dies, which keeps the dies evenly loaded.
 // k_first = k | first_step << 16; rows_abreast = (B & ~7) * k; inv_k = ceil(2^32 / k): with fewer than
 // 2^22 rows and k <= 64, the high half of n * inv_k is n / k.
-template <int U, int FMT, int NW>
+template <int U, int FMT, int NW, int D>
 __global__ __launch_bounds__(NW * kWave) void dba_stream_kernel(const void *logp, int V, int k_first, uint32_t rows_abreast,
                                                                uint32_t inv_k, const StepParams p)
 {
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(NW * kWave) void dba_stream_kernel(const void *logp
     const uint32_t m = abreast ? n >> 3 : n;
     const uint32_t q = k == 1 ? m : __umulhi(m, inv_k);
     const int b = (int)(abreast ? q * 8u + (n & 7u) : q), h = (int)(m - q * k);
-    stream_phase<U, FMT, NW>(p, logp, V, (int)k, k_first >> 16, b, h, sm);
+    stream_phase<U, FMT, NW, D>(p, logp, V, (int)k, k_first >> 16, b, h, sm);
 }
 
 // Second launch of a step: the merge phase.  Grid: one workgroup of MW waves per sentence, each wave
@@ -814,19 +814,26 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         const size_t spare = stream_waves == 8 ? (share > 4 ? spread_lds<8>(3) : 0)
                              : share <= 4 || share == 8 ? 0
                                                         : spread_lds<4>(share < 8 ? share : 6);
-        if (stream_waves == 8) {
-            switch (logp_format) {
-                case DBA_LOGP_F16: dba_stream_kernel<kTileLoads, kFmtF16, 8><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
-                case DBA_LOGP_BF16: dba_stream_kernel<kTileLoads, kFmtBF16, 8><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
-                default: dba_stream_kernel<kTileLoads, kFmtF32, 8><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
-            }
+#define STREAM(FMT, NW, D) \
+    dba_stream_kernel<kTileLoads, FMT, NW, D><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p)
+#define STREAM_ANY(NW, D)                                       \
+    switch (logp_format) {                                      \
+        case DBA_LOGP_F16: STREAM(kFmtF16, NW, D); break;       \
+        case DBA_LOGP_BF16: STREAM(kFmtBF16, NW, D); break;     \
+        default: STREAM(kFmtF32, NW, D); break;                 \
+    }
+        // Tiles in flight per wave: four where every row has a compute unit to itself and its latencies show
+        // (per step: 14.7 -> 13.7 us for 160 rows of 32000 fp32, 16.0 -> 15.0 for 168 of 50001, 26.6 -> 25.0 for 240 of
+        // 100000); two beyond (480 rows of 50000: 24.8 against 25.8 with four).
+        if (stream_waves == 8 && rows <= kComputeUnits) {
+            STREAM_ANY(8, 4)
+        } else if (stream_waves == 8) {
+            STREAM_ANY(8, 2)
         } else {
-            switch (logp_format) {
-                case DBA_LOGP_F16: dba_stream_kernel<kTileLoads, kFmtF16, 4><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
-                case DBA_LOGP_BF16: dba_stream_kernel<kTileLoads, kFmtBF16, 4><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
-                default: dba_stream_kernel<kTileLoads, kFmtF32, 4><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p); break;
-            }
+            STREAM_ANY(4, 2)
         }
+#undef STREAM_ANY
+#undef STREAM
         // The merge phase is compiled for (rows per wave, waves, entries per lane).  Unless the caller fixes the
         // waves: four up to k = 16, eight beyond (fewer lists per wave to merge and to scan, more waves to rank
         // candidates, at the price of a deeper tree where the waves' lists are joined; one decode, per step: 22.1 / 22.3 us with

@@ -569,6 +569,17 @@ def test_small_batches_long_rows(torch_gpu, B, k, V, fmt):
     _harness().run_parity(wl, logp_format=fmt)
 
 
+@pytest.mark.parametrize("fmt", [None, "f16"])
+@pytest.mark.parametrize("tiles", [8, 9, 15, 16, 17, 24, 25, 32, 33, 40])
+@pytest.mark.parametrize("extra", [-3, 0, 4])
+def test_few_rows_around_whole_tiles(torch_gpu, tiles, extra, fmt):
+    """A handful of rows, eight waves each with up to four 4 KB tiles in flight: rows of whole tiles, and a few
+    elements more and less, on and off 16 bytes."""
+    V = tiles * (1024 if fmt is None else 2048) + extra
+    wl = si.make_small(8200 + tiles, 2, 6, V, 3, max_phrases=3, max_len=2, dup_prob=0.3)
+    _harness().run_parity(wl, logp_format=fmt)
+
+
 def test_two_contexts_on_their_own_streams(torch_gpu):
     """Two decodes at once, each context on a stream of its own (default priority), steps enqueued in
     turn without waiting: all work of a context goes to its stream and contexts share nothing."""
