@@ -840,8 +840,10 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         // four / eight waves at k = 12, 14.7 / 14.7 at k = 16; merge kernel 7.7 / 7.0 us at k = 20, 19.3 / 14.6 at k = 64).
         // Up to k = 11 every wave holds the k * k entries that matter, one or two a lane, and finds the bar by
         // itself (16 sentences, k = 10: 14.6 against 14.9 us per step with merged lists); with four and more a
-        // lane the bisection's counts cost more than the merges (k = 16: 15.4 against 15.3, with bf16, where
-        // scores tie, 15.3 against 14.7; k = 20: 35.2 against 33.1; k = 32: 56.1 against 49.5).
+        // lane the bisection's counts cost more than merging (k = 16: 15.4 against 15.3, with bf16, where
+        // scores tie, 15.3 against 14.7; k = 20: 35.2 against 33.1; k = 32: 56.1 against 49.5).  From there to
+        // k = 32 two rows share a register (k = 16: 14.9 against 15.4; k = 20: 32.6 against 33.1, with bf16 22.7 against
+        // 23.4; k = 32: 49.1 against 49.6); beyond, a row's list needs all 64 lanes.
         const dim3 mgrid((unsigned)c->B);
         const dim3 mblock8(8 * kWave), mblock4(4 * kWave);
         const int mw = c->merge_waves ? c->merge_waves : (c->k <= 16 ? 4 : 8);
@@ -851,13 +853,13 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         if (mw == 4) {
             if (c->k <= 8) MERGE(2, 4, 1);
             else if (c->k <= 11) MERGE(4, 4, 2);
-            else if (c->k <= 16) MERGE(4, 4, 0);
-            else if (c->k <= 32) MERGE(8, 4, 0);
+            else if (c->k <= 16) MERGE(4, 4, -1);
+            else if (c->k <= 32) MERGE(8, 4, -1);
             else MERGE(16, 4, 0);
         } else {
             if (c->k <= 8) MERGE(2, 8, 1);
             else if (c->k <= 11) MERGE(2, 8, 2);
-            else if (c->k <= 32) MERGE(4, 8, 0);
+            else if (c->k <= 32) MERGE(4, 8, -1);
             else MERGE(8, 8, 0);
         }
 #undef MERGE

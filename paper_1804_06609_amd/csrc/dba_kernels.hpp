@@ -949,12 +949,25 @@ __device__ __forceinline__ uint32_t block_best64_sparse(uint32_t (&buf)[kMergeWa
     return acc;
 }
 
+// The same for lists of at most 32 keys, two side by side in a register: the 32 greatest of the N registers
+// of a wave, in both halves.
+template <int N>
+__device__ __forceinline__ uint32_t best32_of(uint32_t (&o)[N], uint32_t &fell)
+{
+#pragma unroll
+    for (int span = 1; span < N; span *= 2)
+#pragma unroll
+        for (int w = 0; w + span < N; w += 2 * span) o[w] = merge32_halves(o[w], o[w + span], fell);
+    return join32_halves(o[0], fell);
+}
+
 // MW: waves of the sentence's workgroup; ROWS: beam rows per wave the code is laid out for
 // (k <= MW * ROWS; wave w takes rows w, w + MW, ...): the loops over a wave's rows are unrolled, so a
 // smaller bound keeps the code of small beams short.
 // J: where k * k <= 64 * J, every wave holds the k best of all the sentence's rows, J per lane (the entries that
 // can be among the sentence's k best), and finds the bar by itself; J = 0: a wave holds the lists of its own
-// rows and the waves' lists are merged.
+// rows and the waves' lists are merged; J = -1, k <= 32: the same with two rows to a register, which
+// halves the merges, the registers looked through for candidates and the LDS they pass through.
 // rowlists, conskeys, k, inv_k: what the first loads need (p.rowlists, p.conskeys, p.k; floor(2^16 / k) + 1,
 // with which i * inv_k >> 16 is i / k for i < k * k, k <= 32).
 template <int ROWS, int MW, int J>
@@ -966,8 +979,9 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     // the row lists first: the chain of this phase starts with them, and their addresses need nothing
     // that has to be read from memory first
     constexpr bool kPacked = J > 0;
+    constexpr bool kHalves = J < 0;
     constexpr int kRowsPerWave = ROWS;
-    constexpr int kLists = kPacked ? J : ROWS;
+    constexpr int kLists = kPacked ? J : (kHalves ? ROWS / 2 : ROWS);
     u64 rl[kLists], ck[kRowsPerWave];
     u64 hd[kPacked ? kRowsPerWave : 1];                    // packed: the heads of the lists of the wave's rows
     uint32_t head_bits = 0;                                // packed: bit j = this lane's entry j is a row's best
@@ -982,9 +996,17 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
                 rl[j] = rowlists[((size_t)b * k + h) * kWave + at];
             }
         }
+    } else if constexpr (kHalves) {
+        // register i: rows wave + 2 i MW and wave + (2 i + 1) MW
+#pragma unroll
+        for (int i = 0; i < kLists; ++i) {
+            const int h = wave + (2 * i + (lane >> 5)) * MW;
+            rl[i] = 0;
+            if (h < k && (lane & 31) < k) rl[i] = rowlists[((size_t)b * k + h) * kWave + (lane & 31)];
+        }
     } else {
 #pragma unroll
-        for (int i = 0; i < kRowsPerWave; ++i) {
+        for (int i = 0; i < kLists; ++i) {
             const int h = wave + i * MW;
             rl[i] = 0;
             if (h < k) {
@@ -1071,6 +1093,11 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         int reach;
         tau_s = kth_greatest<J>(image, k, reach);
         settled = tau_s == 0 || reach == k;
+    } else if constexpr (kHalves) {
+        uint32_t image[kLists];
+#pragma unroll
+        for (int i = 0; i < kLists; ++i) image[i] = (uint32_t)(rl[i] >> fb);
+        accs = best32_of(image, fell);
     } else {
         accs = wave_best64<kRowsPerWave, MW, (kRowsPerWave > 4)>(wave, k, k - 1, [&](int i) { return (uint32_t)(rl[i] >> fb); }, fell);
     }
@@ -1092,7 +1119,32 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         hs.misc = (ld_fin & kFinFinished) | (__popcll(ld_met) << 8);
         sm.hyp[tid] = hs;
     }
-    if constexpr (!kPacked) {
+    // the waves' lists of 32, two to a register
+    auto joined32 = [&](uint32_t *buf, uint32_t mine) {
+        if (lane < 32) buf[wave * 32 + lane] = mine;
+        __syncthreads();
+        uint32_t o[MW / 2];
+#pragma unroll
+        for (int i = 0; i < MW / 2; ++i) o[i] = buf[i * kWave + lane];
+        return best32_of(o, fell);
+    };
+    if constexpr (kHalves) {
+        if (k == 32) sm.wf[wave][lane] = fell;
+        accs = joined32(&sm.ws[0][0], accs);
+        tau_s = (uint32_t)__builtin_amdgcn_readlane((int)accs, k - 1);
+        if (tau_s != 0) {
+            settled = (int)__popcll(__ballot(accs >= tau_s) & 0xFFFFFFFFull) == k;  // places k.. hold lower scores
+            if (settled && k == 32) {
+                // every place is taken: a tie may hide among the keys the merges dropped
+                for (int w = 0; w < MW; ++w) {
+                    const uint32_t f = sm.wf[w][lane];
+                    fell = fell > f ? fell : f;
+                }
+                settled = wave_max_uniform(fell) < tau_s;
+            }
+        }
+        need = k - __popcll(__ballot(accs > tau_s) & 0xFFFFFFFFull);
+    } else if constexpr (!kPacked) {
         sm.wf[wave][lane] = fell;
         sm.ws[wave][lane] = accs;
         __syncthreads();
@@ -1144,6 +1196,20 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
             }
             need = k - above;
             tau_l = kth_greatest<J>(low, need, reach);
+        } else if constexpr (kHalves) {
+            uint32_t low[kLists];
+#pragma unroll
+            for (int i = 0; i < kLists; ++i) {
+                // the tied keys of a decreasing list are neighbours: move them to the front of their half
+                const uint32_t hi = (uint32_t)(rl[i] >> fb);
+                const uint32_t lo = hi == tau_s ? ((uint32_t)rl[i] & flatmask) + low_bias : 0u;
+                const u64 better = __ballot(hi > tau_s);
+                const int to = (lane & 31) + (int)__popc((uint32_t)(better >> (lane & 32)));
+                const uint32_t moved = (uint32_t)__shfl((int)lo, (lane & 32) | (to & 31), kWave);
+                low[i] = to < 32 ? moved : 0u;
+            }
+            const uint32_t accl = joined32(&sm.ws2[0][0], best32_of(low, fell));
+            tau_l = (uint32_t)__builtin_amdgcn_readlane((int)accl, need - 1);
         } else {
             uint32_t unused = 0;
             uint32_t accl = wave_best64<kRowsPerWave, MW, true>(wave, k, need - 1, [&](int i) {
@@ -1179,14 +1245,15 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     bool some_tied = false;
 #pragma unroll
     for (int i = 0; i < kLists; ++i) {
-        const bool head = kPacked ? ((head_bits >> i) & 1u) != 0 : lane == 0;
+        const bool head = kPacked ? ((head_bits >> i) & 1u) != 0 : (kHalves ? (lane & 31) == 0 : lane == 0);
         gm |= ((rl[i] & body_mask) >= (head ? 1ull : from) ? 1u : 0u) << i;    // (an empty place holds 0)
     }
     if (tau != 0) {                                        // (else all finite sums are listed: none is left for source 2)
 #pragma unroll
         for (int i = 0; i < kRowsPerWave; ++i) {
             if (wave + i * MW < k) {
-                const u64 best = (kPacked ? hd[kPacked ? i : 0] : read_lane(rl[kPacked ? 0 : i], 0)) & body_mask;
+                const u64 best = (kPacked ? hd[kPacked ? i : 0] : kHalves ? read_lane(rl[i / 2], (i & 1) * 32)
+                                                                          : read_lane(rl[kPacked ? 0 : i], 0)) & body_mask;
                 const u64 body = ck[i] & body_mask;
                 const bool valid = body - 1 < below - 1 && body != best;      // (an empty place holds 0)
                 cm |= (valid ? 1u : 0u) << i;
@@ -1201,7 +1268,8 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
             if (h < k) {
                 const u64 body = ck[i] & body_mask;
                 // (places from k on cannot be among the k best)
-                const u64 listed = lane >= k ? 0ull : (kPacked ? rowlists[((size_t)b * k + h) * kWave + lane] : rl[kPacked ? 0 : i]);
+                const u64 listed = lane >= k ? 0ull
+                                   : (kPacked || kHalves) ? rowlists[((size_t)b * k + h) * kWave + lane] : rl[kPacked ? 0 : i];
                 u64 tied = __ballot(((cm >> i) & 1u) != 0 && body >= tau);
                 while (tied) {
                     const int l = __ffsll((long long)tied) - 1;
@@ -1249,10 +1317,10 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         if constexpr (!kPacked) {
             int to = at + g_incl - g;
 #pragma unroll
-            for (int i = 0; i < kRowsPerWave; ++i) {
-                if (wave + i * MW < k && ((gm >> i) & 1u)) {
-                    cand[to++] = rl[kPacked ? 0 : i];
-                    atomicAdd(&sm.cnt[mb ? (int)(rl[kPacked ? 0 : i] >> sel_shift) : 0], 1);
+            for (int i = 0; i < kLists; ++i) {
+                if ((gm >> i) & 1u) {
+                    cand[to++] = rl[i];
+                    atomicAdd(&sm.cnt[mb ? (int)(rl[i] >> sel_shift) : 0], 1);
                 }
             }
         }

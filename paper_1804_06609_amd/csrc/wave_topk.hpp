@@ -216,6 +216,37 @@ __device__ __forceinline__ uint32_t merge32_desc(uint32_t a, uint32_t b, uint32_
     return v;
 }
 
+// Two decreasing lists of 32 keys side by side, one in each half of the wave.
+// a, b: such pairs.  Returns, in each half, the 32 greatest of the two lists there, decreasing.
+__device__ __forceinline__ uint32_t merge32_halves(uint32_t a, uint32_t b, uint32_t &fell)
+{
+    const uint32_t b_rev = flip_lane_u32<32, true>(b);
+    const uint32_t lo = a > b_rev ? b_rev : a;
+    uint32_t v = a > b_rev ? a : b_rev;
+    fell = fell > lo ? fell : lo;
+    v = clean32_desc<16>(v);
+    v = clean32_desc<8>(v);
+    v = clean32_desc<4>(v);
+    v = clean32_desc<2>(v);
+    v = clean32_desc<1>(v);
+    return v;
+}
+
+// The 32 greatest of the pair's two lists, decreasing, in both halves.
+__device__ __forceinline__ uint32_t join32_halves(uint32_t a, uint32_t &fell)
+{
+    const uint32_t b_rev = flip_lane_u32<64, true>(a);
+    const uint32_t lo = a > b_rev ? b_rev : a;
+    uint32_t v = a > b_rev ? a : b_rev;
+    fell = fell > lo ? fell : lo;
+    v = clean32_desc<16>(v);
+    v = clean32_desc<8>(v);
+    v = clean32_desc<4>(v);
+    v = clean32_desc<2>(v);
+    v = clean32_desc<1>(v);
+    return v;
+}
+
 // greatest value of v over the wave, in every lane
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
 {
