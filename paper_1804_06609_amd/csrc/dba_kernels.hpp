@@ -880,8 +880,8 @@ __device__ __forceinline__ int nmet_after(int nmet, int ip, int iq, bool is_next
 // decreasing list; rows are dealt out to the waves in turn, those from k on are empty).  Two
 // chains of merges run side by side, so that their instructions interleave, and are joined at
 // the end.  A list whose head is below place `kth` of the chain it would join cannot change
-// places 0..kth of the result and may be skipped (LOOK); apart from that the result is exact.
-template <int R, int MW, bool LOOK, typename List>
+// places 0..kth of the result and is skipped; apart from that the result is exact.
+template <int R, int MW, typename List>
 __device__ __forceinline__ uint32_t wave_best64(int wave, int k, int kth, List list, uint32_t &fell)
 {
     uint32_t a0 = wave < k ? list(0) : 0u;
@@ -892,16 +892,10 @@ __device__ __forceinline__ uint32_t wave_best64(int wave, int k, int kth, List l
             const bool pair = i + 1 < R && wave + (i + 1) * MW < k;
             const uint32_t s0 = list(i);
             const uint32_t s1 = pair ? list(i + 1 < R ? i + 1 : i) : 0u;
-            // LOOK: lists are looked at before they are merged (worth it where many are empty or
-            // weak, or a wave has many rows); otherwise every row that exists is merged, and no
-            // value decides a branch
-            bool n0 = true, n1 = pair;
-            if (LOOK) {
-                const uint32_t h0 = (uint32_t)__builtin_amdgcn_readlane((int)s0, 0);
-                const uint32_t h1 = (uint32_t)__builtin_amdgcn_readlane((int)s1, 0);
-                n0 = h0 != 0 && h0 >= (uint32_t)__builtin_amdgcn_readlane((int)a0, kth);
-                n1 = h1 != 0 && h1 >= (uint32_t)__builtin_amdgcn_readlane((int)a1, kth);
-            }
+            const uint32_t h0 = (uint32_t)__builtin_amdgcn_readlane((int)s0, 0);
+            const uint32_t h1 = (uint32_t)__builtin_amdgcn_readlane((int)s1, 0);
+            const bool n0 = h0 != 0 && h0 >= (uint32_t)__builtin_amdgcn_readlane((int)a0, kth);
+            const bool n1 = h1 != 0 && h1 >= (uint32_t)__builtin_amdgcn_readlane((int)a1, kth);
             if (n0 && n1) {
                 a0 = merge32_desc(a0, s0, fell);
                 a1 = merge32_desc(a1, s1, fell);
@@ -912,8 +906,7 @@ __device__ __forceinline__ uint32_t wave_best64(int wave, int k, int kth, List l
             }
         }
     }
-    if (LOOK) return __builtin_amdgcn_readlane((int)a1, 0) != 0 ? merge32_desc(a0, a1, fell) : a0;
-    return (R > 1 && wave + MW < k) ? merge32_desc(a0, a1, fell) : a0;
+    return __builtin_amdgcn_readlane((int)a1, 0) != 0 ? merge32_desc(a0, a1, fell) : a0;
 }
 
 // The 64 greatest keys of the lists the MW waves have left in buf (after a barrier), for the
@@ -1099,7 +1092,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         for (int i = 0; i < kLists; ++i) image[i] = (uint32_t)(rl[i] >> fb);
         accs = best32_of(image, fell);
     } else {
-        accs = wave_best64<kRowsPerWave, MW, (kRowsPerWave > 4)>(wave, k, k - 1, [&](int i) { return (uint32_t)(rl[i] >> fb); }, fell);
+        accs = wave_best64<kRowsPerWave, MW>(wave, k, k - 1, [&](int i) { return (uint32_t)(rl[i] >> fb); }, fell);
     }
     // the sentence's tables and beam go to LDS only now: their loads were issued after those of the
     // row lists and arrive later, and the merges above needed none of them
@@ -1212,7 +1205,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
             tau_l = (uint32_t)__builtin_amdgcn_readlane((int)accl, need - 1);
         } else {
             uint32_t unused = 0;
-            uint32_t accl = wave_best64<kRowsPerWave, MW, true>(wave, k, need - 1, [&](int i) {
+            uint32_t accl = wave_best64<kRowsPerWave, MW>(wave, k, need - 1, [&](int i) {
                 // the tied keys of a decreasing list are neighbours: move them to the front
                 const uint32_t hi = (uint32_t)(rl[i] >> fb);
                 if (__ballot(hi == tau_s) == 0) return 0u;     // most rows hold none
