@@ -208,9 +208,8 @@ DBA_API int dba_get_state(dba_ctx *ctx, float *score_host, uint64_t *met_mask_ho
  *                               workgroup that handles one sentence in the second launch of a step.
  *                               The results are the same for every setting; only the time differs.
  *                               0 lets the library choose for the shortest step of a single decode
- *                               (four up to k = 16, eight beyond).  Four-wave workgroups are placed more
- *                               easily on a GPU that is busy with other work: the better setting where
- *                               several decodes are in flight on the same GPU.
+ *                               (four up to k = 16, eight beyond).  Four-wave workgroups need less room
+ *                               at once on a GPU that is busy with other work.
  */
 #define DBA_OPT_ADJUSTMENT 2
 #define DBA_OPT_NORMALIZE_FINISHED 3
