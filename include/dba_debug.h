@@ -39,6 +39,14 @@ DBA_API int dba_debug_wave_select(int n_cases, const uint64_t *keys_host, const 
                                   size_t scratch_bytes, void *hip_stream);
 
 /*
+ * Diagnostic: how the first launch of a step is laid out for a shape (host only, no GPU needed), so that
+ * tests can tell which kernel a shape reaches.  plan_host [4]: wavefronts per beam row, 4 KB tiles each
+ * wavefront keeps in flight, bytes of LDS a workgroup asks for (its own and what it leaves unused to
+ * keep other workgroups off its compute unit), beam rows numbered eight sentences abreast.
+ */
+DBA_API int dba_debug_stream_plan(int B, int k, int V, int logp_format, int32_t *plan_host);
+
+/*
  * Diagnostic: the reference read.  out_max_dev[r] = largest of the V floats of row r of
  * src_dev [rows, V] (device, 16-byte aligned, V a multiple of 4), one workgroup per row,
  * with the loads and the tile order of the step's streaming phase and no other work.  The

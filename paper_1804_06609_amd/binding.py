@@ -43,6 +43,7 @@ _SIGNATURES = {
     "dba_last_error": (ctypes.c_char_p, [_P]),
     "dba_debug_allocate": (_I, [_I, _I] + [_P] * 5 + [ctypes.c_size_t, _P]),
     "dba_debug_wave_select": (_I, [_I] + [_P] * 5 + [ctypes.c_size_t, _P]),
+    "dba_debug_stream_plan": (_I, [_I] * 4 + [_P]),
     "dba_debug_row_max": (_I, [_P, _I, _I, _P, _P]),
 }
 
@@ -176,3 +177,10 @@ def dba_debug_wave_select(keys: np.ndarray, vals: np.ndarray, out: np.ndarray, f
 
 def dba_debug_row_max(src_dev: int, rows: int, V: int, out_max_dev: int, hip_stream: int = 0) -> int:
     return _check(load().dba_debug_row_max(src_dev, rows, V, out_max_dev, hip_stream or None))
+
+
+def dba_debug_stream_plan(B: int, k: int, V: int, logp_format: int = DBA_LOGP_F32):
+    """(waves, tiles in flight per wave, LDS bytes per workgroup, rows numbered eight sentences abreast)"""
+    plan = np.zeros(4, np.int32)
+    _check(load().dba_debug_stream_plan(B, k, V, logp_format, _host(plan, np.int32)))
+    return tuple(int(x) for x in plan)

@@ -453,12 +453,50 @@ Layout make_layout(size_t B, size_t k, size_t N)
 constexpr size_t kComputeUnits = 256;
 constexpr size_t kLdsPerUnit = 160 * 1024;
 
-// LDS to add to a stream-phase workgroup of NW waves so that no more than n of them fit a compute unit
-template <int NW>
+// LDS to add to a stream-phase workgroup of NW waves so that no more than n <= MOST of them fit a compute unit
+template <int NW, int MOST>
 constexpr size_t spread_lds(size_t n)
 {
-    static_assert(sizeof(StreamSmem<NW>) < kLdsPerUnit / 4, "LDS of the stream phase");
+    static_assert(sizeof(StreamSmem<NW>) <= kLdsPerUnit / (MOST + 1), "a workgroup's own LDS leaves room for MOST + 1 of them");
     return align_up(kLdsPerUnit / (n + 1) + 1 - sizeof(StreamSmem<NW>), 256);
+}
+
+// How the stream phase of a step is launched: one workgroup per beam row, and
+struct StreamPlan {
+    int waves;              // of a workgroup: 4 or 8
+    int tiles;              // of 4 KB that each wave keeps in flight
+    size_t spare_lds;       // LDS a workgroup asks for and does not use, which keeps others off its compute unit
+    uint32_t rows_abreast;  // rows of the sentences that are numbered eight abreast
+};
+
+StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem)
+{
+    StreamPlan plan;
+    const size_t rows = B * k, row_bytes = V * elem;
+    plan.rows_abreast = (uint32_t)((B & ~(size_t)7) * k);
+    // Waves per beam row (measured on MI355X, fp32 and 16-bit inputs, 10 to 8192 rows): eight where the
+    // grid cannot fill the chip by itself (at most two rows per compute unit) and a row has work for
+    // them, and where rows are long (from 160 KB on: the floor then rests on a larger share of the
+    // row and fewer sums are looked at closely); four otherwise - with rows of 64-128 KB and
+    // thousands of them, twice the workgroups per compute unit stream faster than twice the waves.
+    plan.waves = ((rows <= 512 && row_bytes >= 32768) || row_bytes >= 163840) ? 8 : 4;
+    // Rows side by side on a compute unit.  More than a unit's even share leaves others short, and lets a
+    // second decode's rows in beside the first one's: where the grid fills the chip, no more than that share
+    // (three decodes of 64 x 20 rows of 32000 in flight: 84 against 94 us for three steps, one of them alone
+    // unchanged; 1152 rows of 32003 bf16: 22.8 against 23.1 us per step).  Where rows follow one another, six
+    // waves per SIMD instead of the eight that fit: fewer streams at a time then serve memory better (8192 rows
+    // of 50000, k = 64: 263 against 267 us per step in fp32, 146 against 148.5 with fp16; 2048 rows of 32000, all
+    // resident with eight: 50.9 against 49.6).  Workgroups are kept apart by LDS they do not use; at
+    // least a tenth of a unit's LDS stays free for other work.
+    const size_t share = (rows + kComputeUnits - 1) / kComputeUnits;
+    plan.spare_lds = plan.waves == 8 ? (share > 4 ? spread_lds<8, 3>(3) : 0)
+                     : share <= 4 || share == 8 ? 0
+                                                : spread_lds<4, 7>(share < 8 ? share : 6);
+    // Tiles in flight per wave: four where every row has a compute unit to itself and its latencies show
+    // (per step: 14.7 -> 13.7 us for 160 rows of 32000 fp32, 16.0 -> 15.0 for 168 of 50001, 26.6 -> 25.0 for 240 of
+    // 100000); two beyond (480 rows of 50000: 24.8 against 25.8 with four).
+    plan.tiles = plan.waves == 8 && rows <= kComputeUnits ? 4 : 2;
+    return plan;
 }
 
 int bits_for(int v)   // bits needed to hold values 0..v
@@ -786,48 +824,25 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     p.all_finished = at<uint8_t>(c, L.all_finished);
     p.best = at<BestCompleted>(c, L.best);
 
-    // one workgroup per beam row, 4 loads of 16 bytes per lane and tile, two 4 KB tiles in flight per wave: at
-    // 1280 rows of four waves the 1024 SIMDs are filled five deep (measured best on MI355X at V = 32000)
+    // one workgroup per beam row, 4 loads of 16 bytes per lane and tile, two or four 4 KB tiles in flight per wave
+    const StreamPlan plan = stream_plan((size_t)c->B, (size_t)c->k, (size_t)c->V, elem);
     const dim3 grid((unsigned)c->B * (unsigned)c->k);
-    const uint32_t abreast = (uint32_t)(c->B & ~7) * (uint32_t)c->k;
     const uint32_t inv_k = (uint32_t)(((1ull << 32) + (unsigned)c->k - 1) / (unsigned)c->k);
     const int kf = p.k | (p.first_step << 16);
     {
-        // Waves per beam row (measured on MI355X, fp32 and 16-bit inputs, 10 to 8192 rows): eight where the
-        // grid cannot fill the chip by itself (at most two rows per compute unit) and a row has work for
-        // them, and where rows are long (from 160 KB on: the floor then rests on a larger share of the
-        // row and fewer sums are looked at closely); four otherwise - with rows of 64-128 KB and
-        // thousands of them, twice the workgroups per compute unit stream faster than twice the waves.
-        const size_t row_bytes = (size_t)c->V * elem;
-        const int stream_waves =
-            (((size_t)c->B * c->k <= 512 && row_bytes >= 32768) || row_bytes >= 163840) ? 8 : 4;
-        const dim3 sblock((unsigned)(stream_waves * kWave));
-        // Rows side by side on a compute unit.  More than a unit's even share leaves others short, and lets a
-        // second decode's rows in beside the first one's: where the grid fills the chip, no more than that share
-        // (three decodes of 64 x 20 rows of 32000 in flight: 84 against 94 us for three steps, one of them alone
-        // unchanged; 1152 rows of 32003 bf16: 22.8 against 23.1 us per step).  Where rows follow one another, six
-        // waves per SIMD instead of the eight that fit: fewer streams at a time then serve memory better (8192 rows
-        // of 50000, k = 64: 263 against 267 us per step in fp32, 146 against 148.5 with fp16; 2048 rows of 32000, all
-        // resident with eight: 50.9 against 49.6).  Workgroups are kept apart by LDS they do not use; at
-        // least a tenth of a unit's LDS stays free for other work.
-        const size_t rows = (size_t)c->B * c->k, share = (rows + kComputeUnits - 1) / kComputeUnits;
-        const size_t spare = stream_waves == 8 ? (share > 4 ? spread_lds<8>(3) : 0)
-                             : share <= 4 || share == 8 ? 0
-                                                        : spread_lds<4>(share < 8 ? share : 6);
-#define STREAM(FMT, NW, D) \
-    dba_stream_kernel<kTileLoads, FMT, NW, D><<<grid, sblock, spare, c->stream>>>(p.logp, p.V, kf, abreast, inv_k, p)
+        const dim3 sblock((unsigned)(plan.waves * kWave));
+#define STREAM(FMT, NW, D)                                                                                              \
+    dba_stream_kernel<kTileLoads, FMT, NW, D><<<grid, sblock, plan.spare_lds, c->stream>>>(p.logp, p.V, kf, plan.rows_abreast, \
+                                                                                           inv_k, p)
 #define STREAM_ANY(NW, D)                                       \
     switch (logp_format) {                                      \
         case DBA_LOGP_F16: STREAM(kFmtF16, NW, D); break;       \
         case DBA_LOGP_BF16: STREAM(kFmtBF16, NW, D); break;     \
         default: STREAM(kFmtF32, NW, D); break;                 \
     }
-        // Tiles in flight per wave: four where every row has a compute unit to itself and its latencies show
-        // (per step: 14.7 -> 13.7 us for 160 rows of 32000 fp32, 16.0 -> 15.0 for 168 of 50001, 26.6 -> 25.0 for 240 of
-        // 100000); two beyond (480 rows of 50000: 24.8 against 25.8 with four).
-        if (stream_waves == 8 && rows <= kComputeUnits) {
+        if (plan.waves == 8 && plan.tiles == 4) {
             STREAM_ANY(8, 4)
-        } else if (stream_waves == 8) {
+        } else if (plan.waves == 8) {
             STREAM_ANY(8, 2)
         } else {
             STREAM_ANY(4, 2)
@@ -1061,6 +1076,18 @@ DBA_API int dba_debug_wave_select(int n_cases, const uint64_t *keys_host, const 
     if (e == hipSuccess) e = hipMemcpyAsync(fout_host, d_fout, n * 64 * 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail(nullptr, DBA_EHIP, "dba_debug_wave_select: HIP error: %s", hipGetErrorString(e));
+    return DBA_OK;
+}
+
+DBA_API int dba_debug_stream_plan(int B, int k, int V, int logp_format, int32_t *plan_host)
+{
+    if (!shape_ok(B, k, V, 1, 0) || !plan_host || logp_format < DBA_LOGP_F32 || logp_format > DBA_LOGP_BF16)
+        return fail(nullptr, DBA_EINVAL, "dba_debug_stream_plan: bad argument");
+    const StreamPlan plan = stream_plan((size_t)B, (size_t)k, (size_t)V, logp_format == DBA_LOGP_F32 ? 4u : 2u);
+    plan_host[0] = plan.waves;
+    plan_host[1] = plan.tiles;
+    plan_host[2] = (int32_t)((plan.waves == 8 ? sizeof(StreamSmem<8>) : sizeof(StreamSmem<4>)) + plan.spare_lds);
+    plan_host[3] = (int32_t)plan.rows_abreast;
     return DBA_OK;
 }
 

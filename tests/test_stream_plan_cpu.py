@@ -1,0 +1,39 @@
+"""How the first launch of a step is laid out for a shape (worked out on the host, no GPU)."""
+import paper_1804_06609_amd as dba
+
+UNITS, UNIT_LDS, LAUNCH_LDS = 256, 160 * 1024, 64 * 1024
+
+
+def shapes():
+    """Every number of rows per compute unit up to 40 and some beyond, short rows to long ones."""
+    for share in list(range(1, 41)) + [100, 1000, 10000]:
+        for V in (64, 1000, 8191, 16384, 32003, 50000, 131072, 524288):
+            for rows in {256 * share, 256 * share - 129}:
+                for k in (1, 7, 64):
+                    if rows // k <= 65535:
+                        yield max(1, rows // k), k, V
+
+
+def test_unused_lds_lets_no_more_rows_on_a_compute_unit_than_meant():
+    """A workgroup's LDS is within what a launch may ask for, leaves a tenth of the unit free where rows are
+    held back, and never holds them below the unit's even share where all of them would fit at once."""
+    for B, k, V in shapes():
+        for fmt in (dba.DBA_LOGP_F32, dba.DBA_LOGP_F16, dba.DBA_LOGP_BF16):
+            waves, tiles, lds, _ = dba.dba_debug_stream_plan(B, k, V, fmt)
+            own = {4: 17440, 8: 34880}[waves]
+            share, fit = -(-B * k // UNITS), UNIT_LDS // lds
+            assert (waves, tiles) in ((4, 2), (8, 2), (8, 4)) and own <= lds <= LAUNCH_LDS, (B, k, V, waves, tiles, lds)
+            if share <= 32 // waves:
+                assert fit >= share, (B, k, V, fit)
+            if lds > own:
+                assert share > 32 // waves or fit == share, (B, k, V, fit)
+                assert UNIT_LDS - fit * lds >= UNIT_LDS // 10, (B, k, V, fit, lds)
+
+
+def test_bad_arguments_are_refused():
+    for bad in ((0, 1, 100, 0), (1, 65, 100, 0), (1, 5, 4, 0), (1, 5, 100, 3), (1, 5, 100, -1)):
+        try:
+            dba.dba_debug_stream_plan(*bad)
+        except dba.DbaError:
+            continue
+        raise AssertionError(bad)
