@@ -410,14 +410,21 @@ __device__ __forceinline__ void drain_groups(RowTop &st, int &parked, const v4u 
 // Thresholds.  (1) Every lane takes an element of its share of the wave's first two tiles (the
 // greatest, where the format finds it cheaply); the k-th greatest of all the workgroup's
 // per-lane values is a floor: k different lanes hold an element at least that large, so nothing
-// below it can be among the row's k best.  (2) A wave that runs out of room for groups or keys goes on
-// without the fast loop: it folds its keys into its list, whose k-th entry bounds its share of the row from then
-// on, and takes the rest of its tiles 64 groups at a time.  With the floor in place that is rare: a
-// wave sets about k groups aside per row.  The row's best element is never below any bound, so it
-// always survives.
+// below it can be among the row's k best.  About k * V / (elements of those first tiles) elements of the row reach
+// it, so a wide beam over a long row (k = 64: from about 256000 fp32 elements on) or over a row of a single tile, whose
+// floor is near the least of 64 values, fills a wave's room.  (2) Such a wave makes room: of the groups it
+// has set aside the k-th greatest stands for k elements of the row and is a floor as well; groups below it go, and the
+// fast loop goes on behind the tile that found no room (per step, against leaving the fast loop for good and
+// reading the rest 64 groups at a time: 64 rows of 524288 fp32, k = 64: 129 -> 64 us; 1024 rows of 2000 bf16, k = 64:
+// 29.0 -> 24.6; 320 rows of 1000 fp32, k = 20: 18.7 -> 13.3).  (3) Where that gives no room either - most
+// sums tie - the wave folds its keys into its list, whose k-th entry bounds its share of the row from then on, and
+// takes the rest of its tiles 64 groups at a time.  The row's best element is never below any bound, so
+// it always survives.
 //
-// Whatever is rare is kept out of the fast loop and short: one place that looks into groups one element at
-// a time, no end-of-sentence test per tile.  54-56 registers instead of 72 let eight waves share a SIMD
+// Whatever is rare is kept out of the fast loop: one place that looks into groups one element at
+// a time, no end-of-sentence test per tile, and a copy of the loop for the tiles behind one that found no room
+// (a single loop that returns to its start keeps its tiles' registers through all that is rare, and costs rows that
+// never come there 0.2 to 0.4 us).  At most 64 vector registers and 80 scalar ones let eight waves share a SIMD
 // (2048 rows of 32000, k = 32: 50.6 -> 49.5 us per step; 168 rows of 50001: 17.6 -> 17.2).
 // D = tiles in flight per wave.  The first two are requested before anything else; the others once both have
 // arrived, while the floor is worked out - asked for at the start they would only queue in front of other
@@ -531,6 +538,9 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
             group[pos] = __builtin_bit_cast(v4u, x);
             coord[pos] = at;
         }
+        // (no instruction: keeps this join of lanes apart from the uniform branches behind it, which would
+        // otherwise be taken for branches of single lanes and kept in ten more scalar registers: seven waves a SIMD)
+        __builtin_amdgcn_wave_barrier();
         cnt += __popcll(m);
     };
     // the elements outside the aligned body: groups of one
@@ -558,26 +568,116 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
         for (int u = 0; u < U; ++u) set_aside(t[u], mine[u], m[u], at0 + (uint32_t)(G * kWave * u));
         return true;
     };
-    // a tile's registers are refilled as soon as it has been looked at, D tiles ahead
-    int tl = wave;
-    bool room = true;
+    // Makes room: the k-th greatest of the groups' greatest sums is a floor, and groups below it go.  (Groups are
+    // moved within one wave, whose LDS operations keep their order: all are read before any is written.)
+    auto make_room = [&]() {
+        uint32_t image[2], at[2];
+        v4u bytes[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int i = j * kWave + lane;
+            image[j] = 0;
+            at[j] = 0;
+            bytes[j] = v4u{0, 0, 0, 0};
+            if (i < cnt) {
+                bytes[j] = group[i];
+                at[j] = coord[i];
+                float f[G], best = -INFINITY;
+                F::widen(__builtin_bit_cast(vec_t, bytes[j]), f);
+#pragma unroll
+                for (int c = 0; c < G; ++c)
+                    if (at[j] + (uint32_t)c != no_coord) best = fmaxf(best, prev + f[c]);
+                image[j] = ord_from_float(best);
+            }
+        }
+        int reach;
+        const uint32_t tau = kth_greatest<2>(image, kk, reach);
+        if (tau == 0) return;                              // fewer than k groups
+        st.floor = fmaxf(st.floor, float_from_ord(tau));
+        st.thr = fmaxf(st.floor, kLowestFinite);
+        quick = F::quick(prev, st.thr);
+        cnt = 0;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const bool keep = image[j] >= tau;
+            const u64 m = __ballot(keep);
+            set_aside(__builtin_bit_cast(vec_t, bytes[j]), keep, m, at[j]);
+        }
+    };
+    // The partial tile, if it is one of the first D.  All registers are filled before the first load: filled one by
+    // one between the loads, some shared registers with a load on its way and waited for it (160 rows of
+    // 17300 fp32, k = 10: 13.9 -> 13.4 us per step).
+    int tl = wave, u0 = 0;                // tile to look at next; its 64-group columns taken already
 #pragma unroll
     for (int d = 2; d < D; ++d)
-        if (wave + d * nwaves >= nfull && wave + d * nwaves < ntiles)
-            load_tile<U>(vec, nv, wave + d * nwaves, lane, tile_[d], F::neg_inf());
-    while (room && tl < ntiles) {
+        if (wave + d * nwaves >= nfull && wave + d * nwaves < ntiles) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            if (tl >= ntiles) break;
-            room = examine(tile_[d], tl);
-            if (!room) break;
-            if (tl + D * nwaves < ntiles) load_tile<U>(vec, nv, tl + D * nwaves, lane, tile_[d], F::neg_inf());
-            tl += nwaves;
+            for (int u = 0; u < U; ++u) {
+                tile_[d][u] = F::neg_inf();
+                asm volatile("" : "+v"(tile_[d][u]));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = ((wave + d * nwaves) * U + u) * kWave + lane;
+                if (i < nv) tile_[d][u] = __builtin_nontemporal_load(vec + i);
+            }
         }
+    // a tile's registers are refilled as soon as it has been looked at, N tiles ahead
+    auto stream = [&](auto &t) {
+        constexpr int N = sizeof(t) / sizeof(t[0]);
+        bool room = true;
+        while (room && tl < ntiles) {
+#pragma unroll
+            for (int d = 0; d < N; ++d) {
+                if (tl >= ntiles) break;
+                room = examine(t[d], tl);
+                if (!room) break;
+                if (tl + N * nwaves < ntiles) load_tile<U>(vec, nv, tl + N * nwaves, lane, t[d], F::neg_inf());
+                tl += nwaves;
+            }
+        }
+    };
+    stream(tile_);
+    if (__builtin_expect(tl < ntiles, 0)) {
+        vec_t next[2][U];
+        bool again;
+        do {
+            // no room for this tile's groups: they are read again and taken in columns of 64, with room made in between
+            vec_t x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int g = (tl * U + u) * kWave + lane;
+                x[u] = g < nv ? vec[g] : F::neg_inf();
+            }
+            const uint32_t at0 = lane_coord + (uint32_t)(G * U * kWave) * (uint32_t)tl;
+            u0 = 0;
+            for (bool made = false;; made = true) {
+                const int was = u0;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool mine = F::may_reach(x[u], quick);
+                    const u64 m = __ballot(mine);
+                    if (u == u0 && cnt + (int)__popcll(m) <= kGroupCap) {
+                        set_aside(x[u], mine, m, at0 + (uint32_t)(G * kWave * u));
+                        u0 = u + 1;
+                    }
+                }
+                if (u0 == U || (made && u0 == was)) break;
+                make_room();
+            }
+            again = u0 == U;
+            if (again) {
+                tl += nwaves;
+#pragma unroll
+                for (int d = 0; d < 2; ++d) load_tile<U>(vec, nv, tl + d * nwaves, lane, next[d], F::neg_inf());
+                stream(next);
+                again = tl < ntiles;
+            }
+        } while (again);
     }
     // the elements of the groups set aside, 64 groups side by side: every lane counts its own, a
     // prefix sum over the wave gives it its places
-    bool weak = tl < ntiles;
+    bool weak = tl < ntiles, tightened = false;
     int base = 0;
     for (; base < cnt && !weak; base += kWave) {
         const int i = base + lane;
@@ -593,9 +693,16 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
         }
         const int incl = wave_inclusive_sum(n);
         const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
-        if (parked + total > kKeyCap) {
-            weak = true;
-            break;
+        if (__builtin_expect(parked + total > kKeyCap, 0)) {
+            if (tightened || cnt <= kk) {
+                weak = true;
+                break;
+            }
+            tightened = true;                              // once more from the first group, with the floor the groups give
+            make_room();
+            parked = 0;
+            base = -kWave;
+            continue;
         }
         int pos = parked + incl - n;
 #pragma unroll
@@ -607,7 +714,7 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
         // the floor let too much through: one by one, with folds, first what has been set aside, then
         // (if there was no room for a tile's groups) the rest of the share, read again from that tile on
         cnt -= base;
-        for (int i = tl * U;;) {
+        for (int i = tl * U + u0;;) {
             drain_groups<FMT>(st, parked, group + base, coord + base, key, cnt, prev, no_coord, kk);
             base = 0;
             cnt = 0;

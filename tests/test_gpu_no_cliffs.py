@@ -1,0 +1,45 @@
+"""-m gpu: the time of a step at shapes where a rule of the kernels once made it jump.  Times are compared with
+each other on the same GPU, best of several decodes, and the bounds lie between what was measured
+with the fault and without it."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def step_us(B, k, V, dtype="float32", steps=24, skip=4, repeats=7):
+    """Least time of a step (stream and merge kernel), in us, over a few decodes of random log-probs."""
+    import torch
+    from paper_1804_06609_amd.session import Session
+    gen = torch.Generator(device="cuda").manual_seed(V + k)
+    bias = -1.1 * torch.arange(1, V + 1, device="cuda").log()[torch.randperm(V, generator=gen, device="cuda")]
+    logp = [torch.log_softmax(torch.randn((B, k, V), generator=gen, device="cuda") + bias, -1).to(getattr(torch, dtype))
+            for _ in range(3)]
+    best = np.inf
+    for _ in range(repeats):
+        ses = Session(B, k, V, steps, 2, 0, np.zeros(0, np.int32), np.zeros(1, np.int32), np.zeros(B + 1, np.int32))
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        for t in range(steps):
+            if t == skip:
+                start.record()
+            ses.step(logp[t % 3])
+        end.record()
+        torch.cuda.synchronize()
+        best = min(best, start.elapsed_time(end) * 1e3 / (steps - skip))
+        ses.close()
+    return best
+
+
+def test_twice_the_vocabulary_takes_about_twice_the_time():
+    """A wide beam over rows in which every wave runs out of room: 106 us against 44 for half the length when a
+    wave left the fast loop for good, 63 against 41 since room is made."""
+    half, full = step_us(1, 64, 262144), step_us(1, 64, 524288)
+    assert full < 2.0 * half, (half, full)
+
+
+@pytest.mark.parametrize("k,V,dtype", [(20, 1000, "float32"), (32, 1000, "float32"), (32, 2000, "bfloat16")])
+def test_rows_of_one_tile_take_little_longer_than_rows_of_four(k, V, dtype):
+    """One tile gives a floor that much of it passes: 1.5 to 1.8 times the time of four tiles when that sent the
+    wave off the fast loop, 1.1 to 1.25 times since room is made (k = 20: 18.4 and 13.0 against 11.7 us)."""
+    one, four = step_us(16, k, V, dtype), step_us(16, k, 4 * V, dtype)
+    assert one < 1.4 * four, (one, four)

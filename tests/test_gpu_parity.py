@@ -308,6 +308,54 @@ def test_rows_that_defeat_the_floor(torch_gpu, k, V, shape, fmt):
     _harness().run_parity(wl, logp_format=fmt)
 
 
+class _Late(si.Workload):
+    """Rows whose first tiles - the two of every wave the floor rests on - promise little, so that what comes
+    behind them passes and a wave runs out of room there: "rise", every later element is better than all of
+    them, "ties", nine tenths of the later ones are equal as well."""
+
+    shape, first = "rise", 0
+
+    def logp(self, t, sentences=None, out=None):
+        lp = super().logp(t, sentences, out)
+        lp[..., :self.first] -= np.float32(30.0)
+        if self.shape == "ties":
+            late = lp[..., self.first:]
+            late[np.abs(late) % np.float32(0.5) < np.float32(0.45)] = np.float32(-3.0)
+        return lp
+
+
+@pytest.mark.parametrize("shape", ["rise", "ties", "rising"])
+@pytest.mark.parametrize("B,k,V,fmt,plan", [
+    (2, 64, 40003, None, (8, 4)), (3, 20, 40003, None, (8, 4)), (2, 5, 70001, "f16", (8, 4)), (2, 33, 70001, "f16", (8, 4)),
+    (9, 30, 40003, None, (8, 2)), (11, 24, 70001, "bf16", (8, 2)), (9, 29, 40003, "f16", (8, 2)),
+    (26, 20, 20011, None, (4, 2)), (9, 64, 20011, None, (4, 2)), (26, 20, 20011, "bf16", (4, 2)), (58, 9, 32771, "f16", (4, 2))])
+def test_room_runs_out_behind_the_floor(torch_gpu, B, k, V, fmt, plan, shape):
+    """Every kernel of the stream phase on rows of odd length with a third tile per wave and more: room for groups
+    runs out at the third or a later tile, behind tile registers that have been refilled; made by a higher floor
+    ("rise"), not to be made (ties), and running out again at every tile (rising rows)."""
+    import paper_1804_06609_amd as dba
+    code = {None: dba.DBA_LOGP_F32, "f16": dba.DBA_LOGP_F16, "bf16": dba.DBA_LOGP_BF16}[fmt]
+    waves, tiles = dba.dba_debug_stream_plan(B, k, V, code)[:2]
+    tile = 1024 if fmt is None else 2048
+    assert (waves, tiles) == plan and V > 2 * waves * tile + tile
+    base = si.make_small(5500 + k, B, k, V, 3, max_phrases=3, max_len=2, dup_prob=0.3, boost=False)
+    wl = (_Shaped if shape == "rising" else _Late)(B=B, k=k, V=V, T=3, seed=base.seed, constraints=base.constraints)
+    wl.shape, wl.first = shape, 2 * waves * tile
+    wl.eos_switch = 1
+    _harness().run_parity(wl, logp_format=fmt)
+
+
+@pytest.mark.parametrize("k,V,fmt", [(20, 1000, None), (33, 700, None), (48, 1031, None), (64, 256, None), (64, 500, None),
+                                     (64, 1000, None), (64, 1024, None), (64, 3000, None), (40, 900, "bf16"), (64, 300, "bf16"),
+                                     (64, 1000, "f16"), (64, 2000, "bf16"), (64, 2048, "f16"), (32, 400, "bf16")])
+def test_wide_beams_on_rows_of_one_tile(torch_gpu, k, V, fmt):
+    """Rows of one tile or a few: the floor is near the least of 64 values, most groups pass, and room for
+    groups or for keys runs out."""
+    wl = si.make_small(5600 + k, 3, k, V, 5, max_phrases=3, max_len=3, dup_prob=0.3)
+    wl.eos_switch = 3
+    _harness().run_parity(wl, logp_format=fmt)
+
+
 def test_many_sentences_long_decode(torch_gpu):
     """300 sentences (more workgroups in the merge phase than compute units), 150 steps of history,
     the set-up of Sec. 4 (per-word scores, pruning at 20), end-of-sentence likely from step 40 on."""
