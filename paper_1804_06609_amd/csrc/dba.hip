@@ -490,12 +490,15 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem)
     // (three decodes of 64 x 20 rows of 32000 in flight: 84 against 94 us for three steps, one of them alone
     // unchanged; 1152 rows of 32003 bf16: 22.8 against 23.1 us per step).  Where rows follow one another, six
     // waves per SIMD instead of the eight that fit: fewer streams at a time then serve memory better (8192 rows
-    // of 50000, k = 64: 263 against 267 us per step in fp32, 146 against 148.5 with fp16; 2048 rows of 32000, all
-    // resident with eight: 50.9 against 49.6).  Workgroups are kept apart by LDS they do not use; at
+    // of 50000, k = 64: 263 against 267 us per step in fp32, 146 against 148.5 with fp16; 8000 rows of 32000 bf16: 92.2
+    // against 93.3; 2048 rows of 32000, all resident with eight: 50.9 against 49.6) - but only from 48 KB on: shorter rows
+    // are latency more than traffic, and take all eight (2200 rows of 8000 fp32: 24.7 against 26.2 us per step with six, 8000
+    // rows 54.1 against 58.5, 8192 of 2000 41.8 against 48.7, 8000 of 16000 bf16 60.1 against 65.8; at 48000 bytes 0 to 4 %
+    // less up to 4000 rows, 0 to 1.4 % more at 8000 and above).  Workgroups are kept apart by LDS they do not use; at
     // least a tenth of a unit's LDS stays free for other work.
     const size_t share = (rows + kComputeUnits - 1) / kComputeUnits;
     plan.spare_lds = plan.waves == 8 ? (share > 4 ? spread_lds<8, 3>(3) : 0)
-                     : share <= 4 || share == 8 ? 0
+                     : share <= 4 || share == 8 || (share > 8 && row_bytes < 49152) ? 0
                                                 : spread_lds<4, 7>(share < 8 ? share : 6);
     // Tiles in flight per wave: four where every row has a compute unit to itself and its latencies show
     // (per step: 14.7 -> 13.7 us for 160 rows of 32000 fp32, 16.0 -> 15.0 for 168 of 50001, 26.6 -> 25.0 for 240 of

@@ -46,3 +46,13 @@ def test_sentences_are_numbered_eight_abreast_only_where_rows_are_short():
                                   (128, 64, 65536, dba.DBA_LOGP_F32, 0), (128, 64, 65536, dba.DBA_LOGP_F16, 8192),
                                   (16, 64, 131072, dba.DBA_LOGP_BF16, 0), (16, 64, 262144, dba.DBA_LOGP_F32, 0)):
         assert dba.dba_debug_stream_plan(B, k, V, fmt)[3] == abreast, (B, k, V, fmt)
+
+
+def test_only_long_rows_that_follow_one_another_are_held_to_six_waves_a_simd():
+    """Short rows are latency, and more of them at a time hide more of it."""
+    for B, k, V, fmt, held in ((110, 20, 8000, dba.DBA_LOGP_F32, False), (400, 20, 1000, dba.DBA_LOGP_F32, False),
+                               (128, 64, 16000, dba.DBA_LOGP_BF16, False), (128, 64, 12287, dba.DBA_LOGP_F32, False),
+                               (128, 64, 12288, dba.DBA_LOGP_F32, True), (128, 64, 32000, dba.DBA_LOGP_BF16, True),
+                               (110, 20, 32000, dba.DBA_LOGP_F32, True), (64, 32, 32000, dba.DBA_LOGP_F32, False)):
+        waves, _, lds, _ = dba.dba_debug_stream_plan(B, k, V, fmt)
+        assert waves == 4 and UNIT_LDS // lds == (6 if held else 9), (B, k, V, fmt, lds)
