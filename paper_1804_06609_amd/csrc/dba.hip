@@ -133,7 +133,7 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
 
 // First launch of a step.  Grid: B * k workgroups of NW waves, one per beam row.  Workgroups are dealt
 // out to the chip's eight dies (XCDs, each with an L2 of its own) in turn, so consecutive numbers
-// mean consecutive dies: where rows_abreast says so (rows below 256 KB), the first B & ~7 sentences are
+// mean consecutive dies: where rows_abreast says so (rows below 512000 bytes), the first B & ~7 sentences are
 // numbered eight abreast, slot by slot, and a die streams all rows of every eighth sentence - one stretch of
 // memory after the other - instead of every eighth row (8192 rows of 50000, k = 64: 269.7 -> 262.7 us per step in fp32, 151.5 -> 146.5 with
 // fp16; 0.1-0.3 us at 1152 to 2048 rows of 32000).  The other sentences, the last B & 7 or all of them, are
@@ -473,12 +473,12 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem)
 {
     StreamPlan plan;
     const size_t rows = B * k, row_bytes = V * elem;
-    // Sentences eight abreast (see the kernel) where rows are shorter than 256 KB: the rows a die streams at a time
-    // lie one after the other.  Longer rows a power of two apart then keep asking the same part of that die's
-    // L2 (per step, k = 64, fp32, eight abreast / row by row: 32 sentences and 131072 tokens 188.6 / 172.7 us, 16 and 262144
-    // 210.4 / 176.5, 64 and 65536 175.6 / 173.0; other lengths differ by 1 % either way, 64 and 65000 177.6 / 180.3,
-    // 64 and 98304 253.1 / 256.4, 32 and 200000 259.4 / 256.5).
-    plan.rows_abreast = row_bytes < 262144 ? (uint32_t)((B & ~(size_t)7) * k) : 0;
+    // Sentences eight abreast (see the kernel) where rows are shorter than 512000 bytes: the rows a die streams at a
+    // time lie one after the other (per step, k = 64, fp32, eight abreast / row by row: 64 sentences of 70000 tokens
+    // 183.1 / 189.2 us, 98304 252.9 / 256.4, 110000 283.6 / 292.4, 125000 322.6 / 328.0; 64 of 65536 the other way, 174.9 / 172.9).
+    // Beyond, they gain nothing (128000 334.2 / 330.0, 131000 343.2 / 340.2), and rows a large power of two apart
+    // keep asking the same part of the die's L2 (64 of 131072 376.6 / 331.6, 16 of 262144 217.2 / 183.6).
+    plan.rows_abreast = row_bytes < 512000 ? (uint32_t)((B & ~(size_t)7) * k) : 0;
     // Waves per beam row (measured on MI355X, fp32 and 16-bit inputs, 10 to 8192 rows): eight where the
     // grid cannot fill the chip by itself (at most two rows per compute unit) and a row has work for
     // them, and where rows are long (from 160 KB on: the floor then rests on a larger share of the

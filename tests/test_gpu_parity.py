@@ -423,7 +423,7 @@ def test_sentences_eight_abreast(torch_gpu, B, k):
     _harness().run_parity(si.make_small(6400 + 10 * B + k, B, k, 500, 4, max_phrases=3, max_len=2))
 
 
-@pytest.mark.parametrize("V,fmt", [(65535, None), (65536, None), (131071, "bf16"), (131072, "bf16")])
+@pytest.mark.parametrize("V,fmt", [(127999, None), (128000, None), (255999, "bf16"), (256000, "bf16")])
 def test_long_rows_are_numbered_row_by_row(torch_gpu, V, fmt):
     """Nine sentences of three rows on both sides of the row length from which none are numbered eight abreast."""
     _harness().run_parity(si.make_small(6500 + V, 9, 3, V, 3, max_phrases=3, max_len=2), logp_format=fmt)
