@@ -138,6 +138,40 @@ def guarded_decode(case):
             assert [a.tobytes() for a in fin] == want[-4:]
 
 
+@pytest.mark.parametrize("N", [40, 1000, 1092, 1093, 1400])
+def test_the_end_of_a_decode_is_the_same_however_long_its_token_rows_are(N):
+    """dba_finalize brings small results over in one copy and long token rows on their own (from 512 KB on: 120
+    sentences of 1093 tokens): the same decode with room for 9 tokens and for N, into ordinary and into pinned
+    memory, with nothing written beside the four arrays."""
+    import torch
+    import paper_1804_06609_amd as dba
+    B, k, V, T = 120, 4, 60, 9
+    wl = si.make_small(8800, B, k, V, T, max_phrases=2, max_len=2)
+    wl.eos_switch = 4
+    toks, poff, soff = wl.csr()
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def decode(n, pinned):
+        ws = torch.empty(dba.dba_workspace_bytes(B, k, V, n, 64) + 256, dtype=torch.uint8, device="cuda")
+        base = (ws.data_ptr() + 255) // 256 * 256
+        ctx = dba.dba_init(B, k, V, n, wl.eos_id, wl.pad_id, toks, poff, soff, base, ws.numel() - 256, stream)
+        keep = []
+        for t in range(T):
+            keep.append(torch.from_numpy(wl.logp(t)).cuda())
+            dba.dba_step(ctx, keep[-1].data_ptr())
+        whole = [torch.full((64 + m + 64,), -77, dtype=torch.int32, pin_memory=pinned).numpy() for m in (B * n, B, B, B)]
+        tokens, length, score, status = (w[64:-64] for w in whole)
+        dba.dba_finalize(ctx, tokens, length, score.view(np.float32), status)
+        dba.dba_destroy(ctx)
+        assert all((w[:64] == -77).all() and (w[-64:] == -77).all() for w in whole), (n, pinned)
+        return tokens.reshape(B, n), length.tobytes() + score.tobytes() + status.tobytes()
+
+    want = decode(T, False)
+    for pinned in (False, True):
+        got = decode(N, pinned)
+        assert (got[0][:, :T] == want[0]).all() and (got[0][:, T:] == wl.pad_id).all() and got[1] == want[1], (N, pinned)
+
+
 def test_a_decode_replayed_from_a_hip_graph_matches_eager_launches():
     """A step enqueues two kernels and nothing else (no allocation, no memset, no copy), so a decode can
     be recorded into a HIP graph by a caller who wants to.  Steps 1..T-1 of a decode are recorded once and replayed three times, each
