@@ -862,75 +862,43 @@ __device__ __forceinline__ int allocate_wave(int k, int C, int c, int c64, int &
         return min(a, c);
     }
 
-    u64 donors = __ballot(a > c);                         // fixed before the hand-outs begin:
-    if (C < 64) {
-        int need = max(0, c - a);
-        u64 receivers = __ballot(need > 0);
-        while (donors != 0 && receivers != 0) {
-            const int b = __ffsll((long long)donors) - 1;
-            donors &= donors - 1;
-            int e = __builtin_amdgcn_readlane(a - c, b);
-            if (e > 2 && __popcll(receivers) > 2) {
-                // all receivers at once: what those served before bank x need is a sum over the banks between
-                // x and its mirror image in b, b's side of which counts first
-                const int incl = wave_inclusive_sum(need), y = 2 * b - lane;
-                const int mirror = __shfl(incl, min(max(y, 0), kWave - 1), kWave), q = y < 0 ? 0 : mirror;
-                const int before = lane > b ? incl - need - q : q - incl;
-                need -= min(need, max(0, e - before));
-                receivers = __ballot(need > 0);
-                continue;
-            }
-            // few slots or few receivers: the nearest receiver on either side is a bit scan away
-            while (e > 0 && receivers != 0) {
-                const u64 above = receivers >> b, below = receivers & ((1ull << b) - 1ull);   // b itself is none
-                const int up = above ? __ffsll((long long)above) - 1 : kWave;
-                const int dn = below ? b - (63 - __clzll((long long)below)) : kWave;
-                const int x = up <= dn ? b + up : b - dn;
-                const int n = __builtin_amdgcn_readlane(need, x), g = min(n, e);
-                if (lane == x) need = n - g;
-                e -= g;
-                if (g == n) receivers &= ~(1ull << x);
-            }
-        }
-        a64 = 0;
-        return c - need;                                  // donors keep what they can fill, receivers got the rest
+    if (C == 64) {
+        // 65 banks share k <= 64 slots: the base split gives all of them to bank 64, the only donor, and what it
+        // cannot fill goes to the nearest banks below, each taking what those above it have left
+        const int left = max(0, k - c64), incl = wave_inclusive_sum(c);
+        a64 = min(k, c64);
+        return min(c, max(0, left - (__builtin_amdgcn_readlane(incl, kWave - 1) - incl)));
     }
-    bool donor64 = a64 > c64;                             // a receiver never becomes a donor
-    for (;;) {
-        int b, e;
-        if (donors != 0) {
-            b = __ffsll((long long)donors) - 1;
-            donors &= donors - 1;
-            e = __builtin_amdgcn_readlane(a - c, b);
-            if (lane == b) a = c;
-        } else if (donor64) {
-            donor64 = false;
-            b = 64;
-            e = a64 - c64;
-            a64 = c64;
-        } else {
-            break;
+    u64 donors = __ballot(a > c);                         // fixed before the hand-outs begin: a receiver never becomes one
+    int need = max(0, c - a);
+    u64 receivers = __ballot(need > 0);
+    while (donors != 0 && receivers != 0) {
+        const int b = __ffsll((long long)donors) - 1;
+        donors &= donors - 1;
+        int e = __builtin_amdgcn_readlane(a - c, b);
+        if (e > 2 && __popcll(receivers) > 2) {
+            // all receivers at once: what those served before bank x need is a sum over the banks between
+            // x and its mirror image in b, b's side of which counts first
+            const int incl = wave_inclusive_sum(need), y = 2 * b - lane;
+            const int mirror = __shfl(incl, min(max(y, 0), kWave - 1), kWave), q = y < 0 ? 0 : mirror;
+            const int before = lane > b ? incl - need - q : q - incl;
+            need -= min(need, max(0, e - before));
+            receivers = __ballot(need > 0);
+            continue;
         }
-        const int need = max(0, c - a);
-        const int need64 = max(0, c64 - a64);
-        if (__ballot(need > 0) == 0 && need64 == 0) continue;   // nobody can take a slot
-        // lane l looks at distance d = l+1: bank b+d first, then bank b-d
-        const int d = lane + 1;
-        const int xu = b + d, xd = b - d;
-        const int nu = __shfl(need, xu & 63, kWave);
-        const int nd = __shfl(need, xd & 63, kWave);
-        const int up = (xu <= C) ? (xu < 64 ? nu : need64) : 0;
-        const int dn = (xd >= 0) ? nd : 0;
-        const int before = wave_inclusive_sum(up + dn) - (up + dn);
-        const int gu = min(up, max(0, e - before));
-        const int gd = min(dn, max(0, e - before - up));
-        const int from_up = __shfl(gu, (lane - b - 1) & 63, kWave);
-        const int from_dn = __shfl(gd, (b - lane - 1) & 63, kWave);
-        if (lane > b) a += from_up;
-        if (lane < b) a += from_dn;
-        if (b < 64) a64 += __builtin_amdgcn_readlane(gu, 63 - b);   // 0 unless C == 64
+        // few slots or few receivers: the nearest receiver on either side is a bit scan away
+        while (e > 0 && receivers != 0) {
+            const u64 above = receivers >> b, below = receivers & ((1ull << b) - 1ull);   // b itself is none
+            const int up = above ? __ffsll((long long)above) - 1 : kWave;
+            const int dn = below ? b - (63 - __clzll((long long)below)) : kWave;
+            const int x = up <= dn ? b + up : b - dn;
+            const int n = __builtin_amdgcn_readlane(need, x), g = min(n, e);
+            if (lane == x) need = n - g;
+            e -= g;
+            if (g == n) receivers &= ~(1ull << x);
+        }
     }
-    return a;
+    return c - need;                                      // donors keep what they can fill, receivers got the rest
 }
 
 // ---------------------------------------------------------------------------

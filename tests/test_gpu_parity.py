@@ -65,6 +65,27 @@ def test_allocation_device_matches_oracle(torch_gpu):
             assert (alloc[i, C + 1:] == 0).all()
 
 
+def test_allocation_with_64_constraint_tokens(torch_gpu):
+    """65 banks: the base split gives the topmost every slot, and what it cannot fill goes downwards - none, one,
+    exactly as many and more candidates than slots in it and below it, gaps between the banks."""
+    import paper_1804_06609_amd as dba
+    cases = []
+    for k in (1, 2, 5, 31, 63, 64):
+        for top in (0, 1, k - 1, k, k + 1, 200):
+            for low in ([0] * 64, [1] * 64, [0, 3] * 32, [0] * 63 + [1], [1] + [0] * 63, [100] + [0] * 62 + [100], [k] * 64,
+                        [0] * 20 + [7] * 3 + [0] * 41):
+                cases.append((k, low + [max(0, top)]))
+    n = len(cases)
+    cnt = np.array([c for _, c in cases], np.int32)
+    alloc = np.full((n, 65), -7, np.int32)
+    scratch = torch_gpu.empty(n * 132 * 4, dtype=torch_gpu.uint8, device="cuda")
+    for adjust in (True, False):
+        dba.dba_debug_allocate(np.array([k for k, _ in cases], np.int32), np.full(n, 64, np.int32), cnt, alloc,
+                               scratch.data_ptr(), scratch.numel(), torch_gpu.cuda.current_stream().cuda_stream, adjust=adjust)
+        for i, (k, c) in enumerate(cases):
+            assert list(alloc[i]) == list(oracle.allocate(k, c, adjust=adjust)), (adjust, k, c)
+
+
 def test_wave_selection_primitives(torch_gpu):
     """The 64-lane sort / merge / insert networks (DPP and permlane exchanges) against a host
     sort, on random distinct keys, keys differing only in the low word, and sentinels; the 32-bit
