@@ -421,8 +421,8 @@ def main():
         cd["four_wave_merge"] = {str(n): leg(n, {DBA_OPT_MERGE_WAVES: 4}) for n in (2, 3)}
         cd["what"] = ("aggregate over 2 / 3 independent config-4 decodes, each context on a stream of its own (wall "
                       "clock); `value` and `roofline` above are ONE decode, whose every step waits for the one before. "
-                      "four_wave_merge: the same with DBA_OPT_MERGE_WAVES = 4 (smaller workgroups in the second "
-                      "launch, placed more easily on a busy GPU; the default is chosen for one decode)")
+                      "four_wave_merge: the same with DBA_OPT_MERGE_WAVES = 4 (workgroups half the size in the second "
+                      "launch; the default is chosen for one decode)")
         out["concurrent_decodes"] = cd
 
     if args.copy_probe:

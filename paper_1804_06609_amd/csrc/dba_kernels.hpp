@@ -1118,9 +1118,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     const int ld_nxt = p.nxt_cur[rs];
     const int ld_len = p.len_cur[rs];
     const int ld_fin = p.fin_cur[rs];
-    // every load above is on its way before anything waits for one of them: the lists are
-    // pinned here, or their loads would be moved down to the conditional code that uses them
-    // meanwhile the counters and the candidate buffer are cleared
+    // while the loads above are on their way, the counters and the candidate buffer are cleared
     if (tid < 2 * kMaxCons) {
         sm.cnt[tid] = 0;
         sm.alloc[tid] = 0;                             // banks beyond the sentence's get no slot
@@ -1135,6 +1133,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     }
     for (int i = tid; i < p.cand_cap; i += MW * kWave) cand[i] = 0;
     if (kPacked) __syncthreads();
+    // the lists are pinned here, or their loads would be moved down to the conditional code that uses them
 #pragma unroll
     for (int i = 0; i < kLists; ++i) asm volatile("" : "+v"(rl[i]));
 #pragma unroll

@@ -295,10 +295,10 @@ def test_restricted_vocabulary(torch_gpu, keep, fmt):
 
 
 class _Shaped(si.Workload):
-    """Rows whose order defeats the threshold floor, which rests on the first tiles: rising rows, where
-    every later 16-byte group reaches it, so that the room for groups and keys overflows again and again;
-    falling ones; and log-probs of extreme magnitudes, where the bound on an element (threshold minus
-    score) is at its roughest."""
+    """Rows in an order that is bad for the threshold floor, which rests on the first two tiles of every wave:
+    rising rows, where every later 16-byte group reaches it, so that room for groups and keys runs out again and
+    again if there are later tiles; falling ones; and log-probs of extreme magnitudes, where the bound on an
+    element (threshold minus score) is at its roughest."""
 
     shape = "rising"
 
@@ -320,8 +320,9 @@ class _Shaped(si.Workload):
                                        ("wide", None), ("wide", "bf16")])
 @pytest.mark.parametrize("k,V", [(5, 1024), (20, 4099), (33, 8191), (64, 9001)])
 def test_rows_that_defeat_the_floor(torch_gpu, k, V, shape, fmt):
-    """One tile per row up to several per wave, rows on and off 16 bytes, floors from one or from two
-    64-lane passes."""
+    """One tile per row up to two per wave - all of them under the floor, so that what overflows here are the keys
+    and the groups of those tiles; longer rows follow below - on and off 16 bytes, floors from one or from two 64-lane
+    passes."""
     base = si.make_small(5300 + k, 2, k, V, 4, max_phrases=3, max_len=2, dup_prob=0.3, boost=False)
     wl = _Shaped(B=base.B, k=base.k, V=base.V, T=base.T, seed=base.seed, constraints=base.constraints)
     wl.shape = shape
@@ -648,8 +649,8 @@ def test_small_batches_long_rows(torch_gpu, B, k, V, fmt):
 @pytest.mark.parametrize("tiles", [8, 9, 15, 16, 17, 24, 25, 32, 33, 40])
 @pytest.mark.parametrize("extra", [-3, 0, 4])
 def test_few_rows_around_whole_tiles(torch_gpu, tiles, extra, fmt):
-    """A handful of rows, eight waves each with up to four 4 KB tiles in flight: rows of whole tiles, and a few
-    elements more and less, on and off 16 bytes."""
+    """A handful of rows, eight waves each with up to four 4 KB tiles in flight (four waves just below eight tiles): rows
+    of whole tiles, and a few elements more and less, on and off 16 bytes."""
     V = tiles * (1024 if fmt is None else 2048) + extra
     wl = si.make_small(8200 + tiles, 2, 6, V, 3, max_phrases=3, max_len=2, dup_prob=0.3)
     _harness().run_parity(wl, logp_format=fmt)
