@@ -77,7 +77,6 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
 
     RowTop st;
     st.list = 0;
-    st.floor = -INFINITY;
     st.thr = kLowestFinite;
     u64 ckey = 0;
     int parked = 0;

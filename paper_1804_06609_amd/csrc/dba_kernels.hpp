@@ -140,9 +140,8 @@ struct MergeSmem {
 // ---------------------------------------------------------------------------
 struct RowTop {
     u64 list;      // this lane's entry of the wave's decreasing top-64
-    float floor;   // a proven lower bound of the row's k-th best sum (-inf if none)
-    float thr;     // sums below this cannot reach the row's top k; never below -FLT_MAX, so
-                   // that "s >= thr" also rejects -inf sums
+    float thr;     // sums below this cannot reach the row's top k; only ever raised, and never below
+                   // -FLT_MAX, so that "s >= thr" also rejects -inf sums
 };
 
 constexpr float kLowestFinite = -3.402823466e+38f;
@@ -150,8 +149,7 @@ constexpr float kLowestFinite = -3.402823466e+38f;
 __device__ __forceinline__ void refresh_threshold(RowTop &st, int kk)
 {
     const u64 kth = read_lane(st.list, kk - 1);
-    const float own = (kth == 0) ? kLowestFinite : float_from_ord((uint32_t)(kth >> 32));
-    st.thr = fmaxf(fmaxf(st.floor, own), kLowestFinite);
+    if (kth != 0) st.thr = fmaxf(st.thr, float_from_ord((uint32_t)(kth >> 32)));
 }
 
 // lanes below the caller's in the mask m
@@ -424,7 +422,7 @@ __device__ __forceinline__ void drain_groups(RowTop &st, int &parked, const v4u 
 // Whatever is rare is kept out of the fast loop: one place that looks into groups one element at
 // a time, no end-of-sentence test per tile, and a copy of the loop for the tiles behind one that found no room
 // (a single loop that returns to its start keeps its tiles' registers through all that is rare, and costs rows that
-// never come there 0.2 to 0.4 us).  At most 64 vector registers and 80 scalar ones let eight waves share a SIMD
+// never come there 0.2 to 0.4 us).  55-56 vector registers and at most 80 scalar ones let eight waves share a SIMD
 // (2048 rows of 32000, k = 32: 50.6 -> 49.5 us per step; 168 rows of 50001: 17.6 -> 17.2).
 // D = tiles in flight per wave.  The first two are requested before anything else; the others once both have
 // arrived, while the floor is worked out - asked for at the start they would only queue in front of other
@@ -525,8 +523,7 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
                 if (w != wave) boot = merge_desc<uint32_t, LL>(boot, sm.boot[w][lane]);
         }
     }
-    st.floor = float_from_ord((uint32_t)__builtin_amdgcn_readlane((int)boot, kk - 1));
-    st.thr = fmaxf(st.floor, kLowestFinite);
+    st.thr = fmaxf(float_from_ord((uint32_t)__builtin_amdgcn_readlane((int)boot, kk - 1)), kLowestFinite);
     typename F::Quick quick = F::quick(prev, st.thr);
     v4u *group = sm.group[wave];
     uint32_t *coord = sm.coord[wave];
@@ -568,40 +565,37 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
         for (int u = 0; u < U; ++u) set_aside(t[u], mine[u], m[u], at0 + (uint32_t)(G * kWave * u));
         return true;
     };
-    // Makes room: the k-th greatest of the groups' greatest sums is a floor, and groups below it go.  (Groups are
-    // moved within one wave, whose LDS operations keep their order: all are read before any is written.)
+    // Makes room: the k-th greatest of the groups' greatest sums is a floor, and groups below it go.  (Groups move
+    // down within one wave, whose LDS operations keep their order: 64 at a time, all of them read before any is written.)
     auto make_room = [&]() {
-        uint32_t image[2], at[2];
-        v4u bytes[2];
+        uint32_t image[2];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int i = j * kWave + lane;
             image[j] = 0;
-            at[j] = 0;
-            bytes[j] = v4u{0, 0, 0, 0};
             if (i < cnt) {
-                bytes[j] = group[i];
-                at[j] = coord[i];
+                const uint32_t at = coord[i];
                 float f[G], best = -INFINITY;
-                F::widen(__builtin_bit_cast(vec_t, bytes[j]), f);
+                F::widen(__builtin_bit_cast(vec_t, group[i]), f);
 #pragma unroll
                 for (int c = 0; c < G; ++c)
-                    if (at[j] + (uint32_t)c != no_coord) best = fmaxf(best, prev + f[c]);
+                    if (at + (uint32_t)c != no_coord) best = fmaxf(best, prev + f[c]);
                 image[j] = ord_from_float(best);
             }
         }
         int reach;
         const uint32_t tau = kth_greatest<2>(image, kk, reach);
         if (tau == 0) return;                              // fewer than k groups
-        st.floor = fmaxf(st.floor, float_from_ord(tau));
-        st.thr = fmaxf(st.floor, kLowestFinite);
+        st.thr = fmaxf(st.thr, float_from_ord(tau));
         quick = F::quick(prev, st.thr);
         cnt = 0;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const bool keep = image[j] >= tau;
-            const u64 m = __ballot(keep);
-            set_aside(__builtin_bit_cast(vec_t, bytes[j]), keep, m, at[j]);
+            const int i = j * kWave + lane;
+            const v4u bytes = group[i];
+            const uint32_t at = coord[i];
+            set_aside(__builtin_bit_cast(vec_t, bytes), keep, __ballot(keep), at);
         }
     };
     // The partial tile, if it is one of the first D.  All registers are filled before the first load: filled one by
