@@ -132,7 +132,7 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
 
 // First launch of a step.  Grid: B * k workgroups of NW waves, one per beam row.  Workgroups are dealt
 // out to the chip's eight dies (XCDs, each with an L2 of its own) in turn, so consecutive numbers
-// mean consecutive dies: where rows_abreast says so (rows below 512000 bytes), the first B & ~7 sentences are
+// mean consecutive dies: where rows_abreast says so (rows below 512000 bytes, or few of them), the first B & ~7 sentences are
 // numbered eight abreast, slot by slot, and a die streams all rows of every eighth sentence - one stretch of
 // memory after the other - instead of every eighth row (8192 rows of 50000, k = 64: 269.7 -> 262.7 us per step in fp32, 151.5 -> 146.5 with
 // fp16; 0.1-0.3 us at 1152 to 2048 rows of 32000).  The other sentences, the last B & 7 or all of them, are
@@ -476,8 +476,11 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem)
     // time lie one after the other (per step, k = 64, fp32, eight abreast / row by row: 64 sentences of 70000 tokens
     // 183.1 / 189.2 us, 98304 252.9 / 256.4, 110000 283.6 / 292.4, 125000 322.6 / 328.0; 64 of 65536 the other way, 174.9 / 172.9).
     // Beyond, they gain nothing (128000 334.2 / 330.0, 131000 343.2 / 340.2), and rows a large power of two apart
-    // keep asking the same part of the die's L2 (64 of 131072 376.6 / 331.6, 16 of 262144 217.2 / 183.6).
-    plan.rows_abreast = row_bytes < 512000 ? (uint32_t)((B & ~(size_t)7) * k) : 0;
+    // keep asking the same part of the die's L2 (64 of 131072 376.6 / 331.6, 16 of 262144 217.2 / 183.6) - but only
+    // where a die has many of them at a time: below two rows per compute unit eight abreast stays ahead (32 sentences,
+    // k = 8, 131072 tokens 28.3 / 29.5 us, 34 and 159134 45.5 / 46.3, 16, k = 20, 131072 41.5 / 41.8; 8, k = 64, 131072 the other
+    // way, 59.3 / 57.9).
+    plan.rows_abreast = row_bytes < 512000 || rows < 2 * kComputeUnits ? (uint32_t)((B & ~(size_t)7) * k) : 0;
     // Waves per beam row (measured on MI355X, fp32 and 16-bit inputs, 10 to 8192 rows): eight where the
     // grid cannot fill the chip by itself (at most two rows per compute unit) and a row has work for
     // them, and where rows are long (from 160 KB on: the floor then rests on a larger share of the

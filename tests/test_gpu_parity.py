@@ -445,10 +445,11 @@ def test_sentences_eight_abreast(torch_gpu, B, k):
     _harness().run_parity(si.make_small(6400 + 10 * B + k, B, k, 500, 4, max_phrases=3, max_len=2))
 
 
-@pytest.mark.parametrize("V,fmt", [(127999, None), (128000, None), (255999, "bf16"), (256000, "bf16")])
-def test_long_rows_are_numbered_row_by_row(torch_gpu, V, fmt):
-    """Nine sentences of three rows on both sides of the row length from which none are numbered eight abreast."""
-    _harness().run_parity(si.make_small(6500 + V, 9, 3, V, 3, max_phrases=3, max_len=2), logp_format=fmt)
+@pytest.mark.parametrize("B,k,V,fmt", [(9, 57, 127999, None), (9, 57, 128000, None), (9, 56, 128000, None),
+                                       (257, 2, 256000, "bf16"), (9, 3, 255999, "bf16")])
+def test_long_rows_are_numbered_row_by_row(torch_gpu, B, k, V, fmt):
+    """Both sides of the row length, and of the number of rows, from which no sentences are numbered eight abreast."""
+    _harness().run_parity(si.make_small(6500 + V, B, k, V, 2, max_phrases=3, max_len=2), logp_format=fmt)
 
 
 @pytest.mark.parametrize("vi", range(len(VARIANTS)))

@@ -40,11 +40,13 @@ def test_bad_arguments_are_refused():
 
 
 def test_sentences_are_numbered_eight_abreast_only_where_rows_are_short():
-    """Long rows a power of two apart share a part of a die's L2 if the die streams neighbouring rows."""
+    """Many long rows a power of two apart share a part of a die's L2 if the die streams neighbouring rows."""
     for B, k, V, fmt, abreast in ((64, 20, 32000, dba.DBA_LOGP_F32, 1280), (67, 20, 32000, dba.DBA_LOGP_F32, 1280),
                                   (7, 20, 32000, dba.DBA_LOGP_F32, 0), (128, 64, 127999, dba.DBA_LOGP_F32, 8192),
                                   (128, 64, 128000, dba.DBA_LOGP_F32, 0), (128, 64, 128000, dba.DBA_LOGP_F16, 8192),
-                                  (16, 64, 262144, dba.DBA_LOGP_BF16, 0), (16, 64, 262144, dba.DBA_LOGP_F32, 0)):
+                                  (16, 64, 262144, dba.DBA_LOGP_BF16, 0), (16, 64, 262144, dba.DBA_LOGP_F32, 0),
+                                  (8, 64, 131072, dba.DBA_LOGP_F32, 0), (8, 63, 131072, dba.DBA_LOGP_F32, 504),
+                                  (34, 8, 159134, dba.DBA_LOGP_F32, 256)):
         assert dba.dba_debug_stream_plan(B, k, V, fmt)[3] == abreast, (B, k, V, fmt)
 
 
