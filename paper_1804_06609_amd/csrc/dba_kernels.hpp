@@ -213,8 +213,20 @@ struct Logp<kFmtF32> {
         const float x = d - ((fabsf(thr) + fabsf(d)) * 0x1p-22f + 0x1p-126f);
         return Quick{x >= kLowestFinite ? x : kLowestFinite};
     }
+    // the least x with fl(prev + x) >= thr exactly, by bisection between the bound above and one as far on the other side
+    static __device__ __forceinline__ Quick quick_exact(float prev, float thr)
+    {
+        const float d = thr - prev;
+        uint32_t lo = ord_from_float(quick(prev, thr).xmin);
+        uint32_t hi = ord_from_float(d + ((fabsf(thr) + fabsf(d)) * 0x1p-22f + 0x1p-126f));
+        while (lo < hi) {
+            const uint32_t mid = lo + ((hi - lo) >> 1);
+            if (prev + float_from_ord(mid) >= thr) hi = mid;
+            else lo = mid + 1;
+        }
+        return Quick{float_from_ord(lo)};
+    }
     static __device__ __forceinline__ bool may_reach(const vec_t &x, const Quick &q) { return max4(x) >= q.xmin; }
-    static __device__ __forceinline__ vec_t lone(elem_t e) { return v4f{e, -INFINITY, -INFINITY, -INFINITY}; }
     static __device__ __forceinline__ void widen(const vec_t &x, float (&f)[G])
     {
         f[0] = x.x;
@@ -281,6 +293,7 @@ struct Logp16 {
             if (u >= 0x8000u && !(prev + widen_bits(u) >= thr)) --u;
         return Quick{u | (u << 16)};
     }
+    static __device__ __forceinline__ Quick quick_exact(float prev, float thr) { return quick(prev, thr); }
     // unsigned minimum of the eight patterns, in both halves of the result
     static __device__ __forceinline__ uint32_t min_pattern_twice(const vec_t &x)
     {
@@ -295,11 +308,6 @@ struct Logp16 {
     static __device__ __forceinline__ bool may_reach(const vec_t &x, const Quick &q)
     {
         return min_pattern_twice(x) <= q.umax2;
-    }
-    static __device__ __forceinline__ vec_t lone(elem_t e)
-    {
-        const uint32_t w = kNegInf | (kNegInf << 16);
-        return v4u{(uint32_t)e | (kNegInf << 16), w, w, w};
     }
     static __device__ __forceinline__ void widen(const vec_t &x, float (&f)[G])
     {
@@ -385,7 +393,8 @@ struct StreamSmem {
 
 // The groups a wave has set aside, element by element: sums that reach the threshold are parked as keys,
 // and the keys are folded into the wave's list whenever they would overflow (the threshold then
-// rises).  Reached only where the floor is weak (few elements, many ties): kept small, not fast.
+// rises).  Reached only where the k best groups hold more keys than there is room for (few elements, many ties): kept
+// small, not fast.
 template <int FMT>
 __device__ __forceinline__ void drain_groups(RowTop &st, int &parked, const v4u *group, const uint32_t *coord, u64 *key,
                                              int cnt, float prev, uint32_t no_coord, int kk)
@@ -433,14 +442,14 @@ __device__ __forceinline__ void drain_groups(RowTop &st, int &parked, const v4u 
 // per-lane values is a floor: k different lanes hold an element at least that large, so nothing
 // below it can be among the row's k best.  About k * V / (elements of those first tiles) elements of the row reach
 // it, so a wide beam over a long row (k = 64: from about 256000 fp32 elements on) or over a row of a single tile, whose
-// floor is near the least of 64 values, fills a wave's room.  (2) Such a wave makes room: of the groups it
-// has set aside the k-th greatest stands for k elements of the row and is a floor as well; groups below it go, and the
-// fast loop goes on behind the tile that found no room (per step, against leaving the fast loop for good and
-// reading the rest 64 groups at a time: 64 rows of 524288 fp32, k = 64: 129 -> 64 us; 1024 rows of 2000 bf16, k = 64:
-// 29.0 -> 24.6; 320 rows of 1000 fp32, k = 20: 18.7 -> 13.3).  (3) Where that gives no room either - most
-// sums tie - the wave folds its keys into its list, whose k-th entry bounds its share of the row from then on, and
-// takes the rest of its tiles 64 groups at a time.  The row's best element is never below any bound, so
-// it always survives.
+// floor is near the least of 64 values, fills a wave's room, and so does a row whose best sums tie in great number.
+// (2) Such a wave makes room: of the groups it has set aside the k-th greatest stands for k elements of the row and is
+// a floor as well; the k best groups stay, and the fast loop goes on behind the tile that found no room (per step, against
+// leaving the fast loop for good and reading the rest 64 groups at a time: 64 rows of 524288 fp32, k = 64: 129 -> 65
+// us; 1024 rows of 2000 bf16, k = 64: 29.0 -> 24.6; 320 rows of 1000 fp32, k = 20: 18.7 -> 13.4; 1280 rows of 32000 equal
+// elements 245 -> 42, a quarter of them equal and best 93 -> 43).  (3) Keys that find no room at the end of the row, several
+// elements to a group, are folded into the wave's sorted list, whose k-th entry bounds its share of the row.  The row's
+// best element is never below any bound, so it always survives.
 //
 // Whatever is rare is kept out of the fast loop: one place that looks into groups one element at
 // a time, no end-of-sentence test per tile, and a copy of the loop for the tiles behind one that found no room
@@ -563,12 +572,15 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
         __builtin_amdgcn_wave_barrier();
         cnt += __popcll(m);
     };
-    // the elements outside the aligned body: groups of one
+    // the elements outside the aligned body (fewer than two groups of them) are parked as keys at once
     if (wave == 0 && head + tail > 0) {
-        const vec_t x = lane < head + tail ? F::lone(lone) : F::neg_inf();
-        const bool mine = F::may_reach(x, quick);
-        set_aside(x, mine, __ballot(mine), flat_base + (uint32_t)lone_at(lane));
+        const uint32_t at = flat_base + (uint32_t)lone_at(lane);
+        const float s = lane < head + tail && at != no_coord ? prev + F::widen_one(lone) : -INFINITY;
+        const u64 m = __ballot(s >= st.thr);
+        if ((m >> lane) & 1ull) key[lanes_before(m)] = make_key(s, at);
+        parked = __popcll(m);
     }
+    const int parked_alone = parked;
     // one tile: test its U groups, set aside what may belong to the top k.  False: no room for them.
     auto examine = [&](const vec_t (&t)[U], int tile) {
         bool mine[U];
@@ -588,8 +600,11 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
         for (int u = 0; u < U; ++u) set_aside(t[u], mine[u], m[u], at0 + (uint32_t)(G * kWave * u));
         return true;
     };
-    // Makes room: the k-th greatest of the groups' greatest sums is a floor, and groups below it go.  (Groups move
-    // down within one wave, whose LDS operations keep their order: 64 at a time, all of them read before any is written.)
+    // Makes room: leaves the k best groups, k <= 64 of at most 128.  The k-th greatest of the groups' greatest sums is a floor
+    // (the bar); groups below it go.  A wave comes by its groups in the order of their coordinates, so of the groups
+    // that only tie at the bar the first few, up to k in all, are enough, and once there are k, a later element has to be
+    // better than the bar: a sum that only ties would lose to all of them.  (Groups move down within one wave, whose
+    // LDS operations keep their order: 64 at a time, all of them read before any is written.)
     auto make_room = [&]() {
         uint32_t image[2];
 #pragma unroll
@@ -607,21 +622,26 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
             }
         }
         int reach;
-        const uint32_t tau = kth_greatest<2>(image, kk, reach);
-        if (tau == 0) return;                              // fewer than k groups
-        st.thr = fmaxf(st.thr, float_from_ord(tau));
-        quick = F::quick(prev, st.thr);
+        const uint32_t tau = kth_greatest<2>(image, kk, reach), old = ord_from_float(st.thr), bar = tau > old ? tau : old;
+        const u64 better0 = __ballot(image[0] > bar), better1 = __ballot(image[1] > bar);
+        const u64 tied0 = __ballot(image[0] == bar), tied1 = __ballot(image[1] == bar);
+        const int left = kk - __popcll(better0) - __popcll(better1), ties0 = __popcll(tied0);
+        st.thr = float_from_ord(bar);
+        const int ties = ties0 + (int)__popcll(tied1);
         cnt = 0;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const bool keep = image[j] >= tau;
             const int i = j * kWave + lane;
             const v4u bytes = group[i];
             const uint32_t at = coord[i];
+            const bool keep = image[j] > bar || (image[j] == bar && (j ? ties0 : 0) + lanes_before(j ? tied1 : tied0) < left);
             set_aside(__builtin_bit_cast(vec_t, bytes), keep, __ballot(keep), at);
         }
+        // (where many tie the bound has to be exact: the rounded one lets through what ties)
+        quick = ties > left ? F::quick_exact(prev, float_from_ord(bar + 1))
+                            : F::quick(prev, float_from_ord(bar + (ties == left ? 1u : 0u)));
     };
-    int tl = wave, u0 = 0;                // tile to look at next; its 64-group columns taken already
+    int tl = wave;                        // tile to look at next
 #pragma unroll
     for (int d = 2; d < D; ++d)           // the partial tile, if it is one of the first D
         if (wave + d * nwaves >= nfull && wave + d * nwaves < ntiles)
@@ -644,7 +664,6 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
     stream(tile_);
     if (__builtin_expect(tl < ntiles, 0)) {
         vec_t next[2][U];
-        bool again;
         do {
             // no room for this tile's groups: they are read again and taken in columns of 64, with room made in between
             vec_t x[U];
@@ -654,9 +673,7 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
                 x[u] = g < nv ? vec[g] : F::neg_inf();
             }
             const uint32_t at0 = lane_coord + (uint32_t)(G * U * kWave) * (uint32_t)tl;
-            u0 = 0;
-            for (bool made = false;; made = true) {
-                const int was = u0;
+            for (int u0 = 0;;) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const bool mine = F::may_reach(x[u], quick);
@@ -666,24 +683,19 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
                         u0 = u + 1;
                     }
                 }
-                if (u0 == U || (made && u0 == was)) break;
+                if (u0 == U) break;
                 make_room();
             }
-            again = u0 == U;
-            if (again) {
-                tl += nwaves;
+            tl += nwaves;
 #pragma unroll
-                for (int d = 0; d < 2; ++d) load_tile<U, false>(vec, nv, tl + d * nwaves, lane, next[d], F::neg_inf());
-                stream(next);
-                again = tl < ntiles;
-            }
-        } while (again);
+            for (int d = 0; d < 2; ++d) load_tile<U, false>(vec, nv, tl + d * nwaves, lane, next[d], F::neg_inf());
+            stream(next);
+        } while (tl < ntiles);
     }
     // the elements of the groups set aside, 64 groups side by side: every lane counts its own, a
     // prefix sum over the wave gives it its places
-    bool weak = tl < ntiles, tightened = false;
-    int base = 0;
-    for (; base < cnt && !weak; base += kWave) {
+    bool tightened = false;
+    for (int base = 0; base < cnt; base += kWave) {
         const int i = base + lane;
         const bool mine = i < cnt;
         const uint32_t at = mine ? coord[i] : 0u;
@@ -699,12 +711,13 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
         const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
         if (__builtin_expect(parked + total > kKeyCap, 0)) {
             if (tightened || cnt <= kk) {
-                weak = true;
+                // many elements to a group: the rest one by one, with folds
+                drain_groups<FMT>(st, parked, group + base, coord + base, key, cnt - base, prev, no_coord, kk);
                 break;
             }
             tightened = true;                              // once more from the first group, with the floor the groups give
             make_room();
-            parked = 0;
+            parked = parked_alone;
             base = -kWave;
             continue;
         }
@@ -713,25 +726,6 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
         for (int c = 0; c < G; ++c)
             if (f[c] >= st.thr) key[pos++] = make_key(f[c], at + (uint32_t)c);
         parked += total;
-    }
-    if (__builtin_expect(weak, 0)) {
-        // the floor let too much through: one by one, with folds, first what has been set aside, then
-        // (if there was no room for a tile's groups) the rest of the share, read again from that tile on
-        cnt -= base;
-        for (int i = tl * U + u0;;) {
-            drain_groups<FMT>(st, parked, group + base, coord + base, key, cnt, prev, no_coord, kk);
-            base = 0;
-            cnt = 0;
-            if (i >= ntiles * U) break;
-            quick = F::quick(prev, st.thr);
-            while (i < ntiles * U && cnt <= kGroupCap - kWave) {
-                const int g = i * kWave + lane;
-                const vec_t x = g < nv ? vec[g] : F::neg_inf();
-                const bool mine = F::may_reach(x, quick);
-                set_aside(x, mine, __ballot(mine), lane_coord + (uint32_t)(G * kWave) * (uint32_t)i);
-                i += i % U == U - 1 ? U * (nwaves - 1) + 1 : 1;
-            }
-        }
     }
     return parked;
 }

@@ -333,7 +333,9 @@ def test_rows_that_defeat_the_floor(torch_gpu, k, V, shape, fmt):
 class _Late(si.Workload):
     """Rows whose first tiles - the two of every wave the floor rests on - promise little, so that what comes
     behind them passes and a wave runs out of room there: "rise", every later element is better than all of
-    them, "ties", nine tenths of the later ones are equal as well."""
+    them, "ties", nine tenths of the later ones are equal as well, "stairs", three later thirds each equal and
+    better than the one before.  Or all elements are equal ("equal"), or those of a stretch from the first tiles on are
+    equal and the best ("plateau")."""
 
     shape, first = "rise", 0
 
@@ -343,18 +345,27 @@ class _Late(si.Workload):
         if self.shape == "ties":
             late = lp[..., self.first:]
             late[np.abs(late) % np.float32(0.5) < np.float32(0.45)] = np.float32(-3.0)
+        elif self.shape == "stairs":
+            n = (lp.shape[-1] - self.first) // 3
+            for i in range(3):
+                lp[..., self.first + i * n:self.first + (i + 1) * n] = np.float32(-3.0 + 0.5 * i)
+        elif self.shape == "equal":
+            lp[...] = np.float32(-3.0)
+        elif self.shape == "plateau":
+            lp[..., self.first // 4:self.first + 2000] = np.float32(-1.0)
         return lp
 
 
-@pytest.mark.parametrize("shape", ["rise", "ties", "rising"])
+@pytest.mark.parametrize("shape", ["rise", "ties", "rising", "stairs", "equal", "plateau"])
 @pytest.mark.parametrize("B,k,V,fmt,plan", [
     (2, 64, 40003, None, (8, 4)), (3, 20, 40003, None, (8, 4)), (2, 5, 70001, "f16", (8, 4)), (2, 33, 70001, "f16", (8, 4)),
     (9, 30, 40003, None, (8, 2)), (11, 24, 70001, "bf16", (8, 2)), (9, 29, 40003, "f16", (8, 2)),
     (26, 20, 20011, None, (4, 2)), (9, 64, 20011, None, (4, 2)), (26, 20, 20011, "bf16", (4, 2)), (58, 9, 32771, "f16", (4, 2))])
 def test_room_runs_out_behind_the_floor(torch_gpu, B, k, V, fmt, plan, shape):
     """Every kernel of the stream phase on rows of odd length with a third tile per wave and more: room for groups
-    runs out at the third or a later tile, behind tile registers that have been refilled; made by a higher floor
-    ("rise"), not to be made (ties), and running out again at every tile (rising rows)."""
+    runs out at the third or a later tile, behind tile registers that have been refilled, once or again at every tile
+    (rising rows); and sums that tie in great number, where the lowest coordinates win, those outside the aligned
+    part of the row among them."""
     import paper_1804_06609_amd as dba
     code = {None: dba.DBA_LOGP_F32, "f16": dba.DBA_LOGP_F16, "bf16": dba.DBA_LOGP_BF16}[fmt]
     waves, tiles = dba.dba_debug_stream_plan(B, k, V, code)[:2]
