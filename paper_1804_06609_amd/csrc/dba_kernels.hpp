@@ -369,7 +369,10 @@ __device__ __forceinline__ void load_tile(const VEC *__restrict__ vec, int nv, i
 #pragma unroll
         for (int u = 0; u < U; ++u) x[u] = __builtin_nontemporal_load(vec + base + u * kWave + lane);
     } else if (!START) {
+        // (waited for here, by the one wave whose last tile it is: left open, these loads, which lanes may skip, make every
+        // tile of the loop wait for all loads on their way before its first group: 160 rows of 65536 17.55 -> 17.4 us)
         load_partial<U>(vec, nv, tile, lane, x, fill);
+        __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
     } else {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
