@@ -360,7 +360,7 @@ __device__ __forceinline__ void load_partial(const VEC *__restrict__ vec, int nv
 
 // (At the start of a row the compiler's own order of fills and loads is the better one: 160 rows of 32000 13.9 us per step
 // against 14.5 with the fills first.)
-template <int U, bool START, typename VEC>
+template <int U, bool START, bool WAIT, typename VEC>
 __device__ __forceinline__ void load_tile(const VEC *__restrict__ vec, int nv, int tile, int lane, VEC (&x)[U],
                                           const VEC fill)
 {
@@ -369,10 +369,11 @@ __device__ __forceinline__ void load_tile(const VEC *__restrict__ vec, int nv, i
 #pragma unroll
         for (int u = 0; u < U; ++u) x[u] = __builtin_nontemporal_load(vec + base + u * kWave + lane);
     } else if (!START) {
-        // (waited for here, by the one wave whose last tile it is: left open, these loads, which lanes may skip, make every
-        // tile of the loop wait for all loads on their way before its first group: 160 rows of 65536 17.55 -> 17.4 us)
+        // (Waited for here, by the one wave whose last tile it is: left open, these loads, which lanes may skip, make every
+        // tile of the loop wait for all loads on their way before its first group: 160 rows of 65536, four tiles in flight,
+        // 17.5 -> 17.35 us.  With two in flight the wait itself costs more: 1280 rows of 32000 33.45 -> 33.7.)
         load_partial<U>(vec, nv, tile, lane, x, fill);
-        __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
+        if (WAIT) __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
     } else {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -457,7 +458,7 @@ __device__ __forceinline__ void drain_groups(RowTop &st, int &parked, const v4u 
 // Whatever is rare is kept out of the fast loop: one place that looks into groups one element at
 // a time, no end-of-sentence test per tile, and a copy of the loop for the tiles behind one that found no room
 // (a single loop that returns to its start keeps its tiles' registers through all that is rare, and costs rows that
-// never come there 0.2 to 0.4 us).  55-56 vector registers and at most 80 scalar ones let eight waves share a SIMD
+// never come there 0.2 to 0.4 us).  53-55 vector registers and at most 80 scalar ones let eight waves share a SIMD
 // (2048 rows of 32000, k = 32: 50.6 -> 49.5 us per step; 168 rows of 50001: 17.6 -> 17.2).
 // D = tiles in flight per wave.  The first two are requested before anything else; the others once both have
 // arrived, while the floor is worked out - asked for at the start they would only queue in front of other
@@ -493,7 +494,7 @@ struct RowStream {
         for (int u = 0; u < U; ++u) tile_[1][u] = F::neg_inf();
 #pragma unroll
         for (int d = 0; d < 2; ++d)
-            if (wave + d * nwaves < ntiles) load_tile<U, true>(vec, nv, wave + d * nwaves, lane, tile_[d], F::neg_inf());
+            if (wave + d * nwaves < ntiles) load_tile<U, true, false>(vec, nv, wave + d * nwaves, lane, tile_[d], F::neg_inf());
         lone = 0;
         if (wave == 0 && lane < head + tail) lone = row[lone_at(lane)];
     }
@@ -610,9 +611,11 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
     // LDS operations keep their order: 64 at a time, all of them read before any is written.)
     auto make_room = [&]() {
         uint32_t image[2];
+        int l = lane;                                      // (taken anew: what follows from it would otherwise be kept in
+        asm volatile("" : "+v"(l));                        // registers through the loops around this, 58 instead of 55)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const int i = j * kWave + lane;
+            const int i = j * kWave + l;
             image[j] = 0;
             if (i < cnt) {
                 const uint32_t at = coord[i];
@@ -634,7 +637,7 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
         cnt = 0;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const int i = j * kWave + lane;
+            const int i = j * kWave + l;
             const v4u bytes = group[i];
             const uint32_t at = coord[i];
             const bool keep = image[j] > bar || (image[j] == bar && (j ? ties0 : 0) + lanes_before(j ? tied1 : tied0) < left);
@@ -659,7 +662,7 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
                 if (tl >= ntiles) break;
                 room = examine(t[d], tl);
                 if (!room) break;
-                if (tl + N * nwaves < ntiles) load_tile<U, false>(vec, nv, tl + N * nwaves, lane, t[d], F::neg_inf());
+                if (tl + N * nwaves < ntiles) load_tile<U, false, (N > 2)>(vec, nv, tl + N * nwaves, lane, t[d], F::neg_inf());
                 tl += nwaves;
             }
         }
@@ -691,7 +694,7 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
             }
             tl += nwaves;
 #pragma unroll
-            for (int d = 0; d < 2; ++d) load_tile<U, false>(vec, nv, tl + d * nwaves, lane, next[d], F::neg_inf());
+            for (int d = 0; d < 2; ++d) load_tile<U, false, false>(vec, nv, tl + d * nwaves, lane, next[d], F::neg_inf());
             stream(next);
         } while (tl < ntiles);
     }
