@@ -161,6 +161,20 @@ __device__ __forceinline__ int lanes_before(u64 m)
 constexpr int kGroupCap = 128;        // 16-byte groups one wave can set aside in LDS,
 constexpr int kKeyCap = 128;          // and keys it can park there
 
+// Where the floor of a row (below) is taken from cells: the greatest elements of as many neighbouring lanes as the workgroup
+// has waves, 64 cells if every wave has a tile, fewer in shorter rows.  One sort of the cells does for the row, instead of
+// one of every wave's 64 lane maxima and another, or merges with every other wave's list.  The k-th greatest of 64
+// cells lets 64 ln(64 / (64 - k)) of the sampled elements through instead of little more than k: 18 at k = 16, 24 at 20, 44 at 32, 63
+// at 40, 89 at 48.  So: not for more than five eighths of the cells (1280 rows of 10000, k = 64: 28.6 us per step with cells,
+// 23.8 without), and with four waves, where the other way is one more sort, wide beams only if the floor
+// rests on the whole row (2400 rows of 9000 fp16, k = 20: 22.5 / 23.5; 2048 of 8000 fp32, k = 32: 22.8 / 23.4; but 1280 of 32000 bf16, k =
+// 20: 23.5 / 23.2; 2048 of 32000 fp32, k = 32: 49.3 / 49.0).  160 rows of 32000 fp32, k = 10: 13.4 / 13.9; with eight waves 192, k = 32,
+// 15.8 / 17.2, 1024 of 100000 bf16, k = 32, 42.2 / 44.4.
+__device__ __forceinline__ bool floor_from_cells(int k, int ntiles, int nwaves)
+{
+    return 8 * k <= 5 * (kWave / nwaves) * min(nwaves, ntiles) && (nwaves == 8 || k <= 16 || ntiles <= 2 * nwaves);
+}
+
 // Keys of one wave folded into its sorted list 64 at a time: one 64-lane sort and one merge per
 // chunk instead of one serial insert per key.
 __device__ __forceinline__ u64 fold_keys(u64 list, const u64 *keys, int cnt)
@@ -390,7 +404,7 @@ struct StreamSmem {
     uint32_t coord[NW][kGroupCap];      // and the coordinate of the first element
     u64 key[NW][kKeyCap];               // keys parked for the end of the row
     u64 wl[NW][kWave];                  // the waves' lists, for the final merge
-    uint32_t boot[NW][kWave];           // sorted per-lane maxima of every wave's first tiles (order images)
+    uint32_t boot[NW][kWave];           // maxima of every wave's first tiles (order images), of its lanes, sorted, or of its cells
     int parked[NW];                     // end of the row: keys each wave has parked,
     int has_list[NW];                   // and whether it holds a list from earlier folds
 };
@@ -442,9 +456,9 @@ __device__ __forceinline__ void drain_groups(RowTop &st, int &parked, const v4u 
 // 261 -> 256 us at 8192 rows of 50000 fp32, k = 64, 149 -> 137 us with fp16).
 //
 // Thresholds.  (1) Every lane takes an element of its share of the wave's first two tiles (the
-// greatest, where the format finds it cheaply); the k-th greatest of all the workgroup's
-// per-lane values is a floor: k different lanes hold an element at least that large, so nothing
-// below it can be among the row's k best.  About k * V / (elements of those first tiles) elements of the row reach
+// greatest, where the format finds it cheaply); the k-th greatest of the workgroup's
+// values, of single lanes or of cells of a few, is a floor: k different lanes hold an element at
+// least that large, so nothing below it can be among the row's k best.  About k * V / (elements of those first tiles) elements of the row reach
 // it, so a wide beam over a long row (k = 64: from about 256000 fp32 elements on) or over a row of a single tile, whose
 // floor is near the least of 64 values, fills a wave's room, and so does a row whose best sums tie in great number.
 // (2) Such a wave makes room: of the groups it has set aside the k-th greatest stands for k elements of the row and is
@@ -543,16 +557,23 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
 #pragma unroll
         for (int d = 2; d < D; ++d)
             if (wave + d * nwaves < nfull) load_full<U>(vec, wave + d * nwaves, lane, tile_[d]);
-        boot = sort64_desc<uint32_t, LL>(ord_from_float(prev + lane_max));
+        boot = ord_from_float(prev + lane_max);
     }
-    if (nwaves > 1) {
+    // Any k values that different lanes hold give a valid floor
+    constexpr int share = kWave / nwaves;              // entries of every wave that fit one 64-lane sort
+    if (floor_from_cells(kk, ntiles, nwaves)) {
+        boot = max_of_lanes<nwaves>(boot);
+        if (lane % nwaves == 0) sm.boot[wave][lane / nwaves] = boot;
+        __syncthreads();
+        boot = sm.boot[lane / share][lane % share];
+        boot = LL ? sort64_minmax_desc(boot) : sort64_desc<uint32_t, false>(boot);
+    } else {
+        boot = sort64_desc<uint32_t, LL>(boot);
         sm.boot[wave][lane] = boot;
         __syncthreads();
-        const int share = kWave / nwaves;              // entries of every wave's list that fit one 64-lane sort
         if (kk <= 3 * share) {
-            // Any k values that different lanes hold give a valid floor, so the best `share` of every
-            // wave's list, sorted once, do: the k-th of them is the k-th of all unless one wave
-            // holds more than `share` of the k greatest (then it is a little lower, never wrong).
+            // the best `share` of every wave's list, sorted once: the k-th of them is the k-th of all unless one
+            // wave holds more than `share` of the k greatest (then it is a little lower)
             boot = sort64_desc<uint32_t, LL>(sm.boot[lane / share][lane % share]);
         } else {
             for (int w = 0; w < nwaves; ++w)

@@ -199,6 +199,44 @@ __device__ __forceinline__ uint32_t clean32_desc(uint32_t v)
     return (lane_id() & J) ? mn : mx;
 }
 
+// merge_halves_desc of the networks above, for 32-bit keys
+template <int S>
+__device__ __forceinline__ uint32_t merge_halves_minmax_desc(uint32_t v)
+{
+    const uint32_t o = flip_lane_u32<S, true>(v);
+    const uint32_t mx = v > o ? v : o, mn = v > o ? o : v;
+    v = (lane_id() & (S >> 1)) ? mn : mx;
+    if constexpr (S >= 64) v = clean32_desc<16>(v);
+    if constexpr (S >= 32) v = clean32_desc<8>(v);
+    if constexpr (S >= 16) v = clean32_desc<4>(v);
+    if constexpr (S >= 8) v = clean32_desc<2>(v);
+    if constexpr (S >= 4) v = clean32_desc<1>(v);
+    return v;
+}
+
+// Full sort of one 32-bit key per lane, decreasing by lane, where waves run alone and wait on every step.
+__device__ __forceinline__ uint32_t sort64_minmax_desc(uint32_t v)
+{
+    v = merge_halves_minmax_desc<2>(v);
+    v = merge_halves_minmax_desc<4>(v);
+    v = merge_halves_minmax_desc<8>(v);
+    v = merge_halves_minmax_desc<16>(v);
+    v = merge_halves_minmax_desc<32>(v);
+    return merge_halves_minmax_desc<64>(v);
+}
+
+// greatest value of each block of S lanes (S = 4 or 8), in all its lanes
+template <int S>
+__device__ __forceinline__ uint32_t max_of_lanes(uint32_t v)
+{
+    static_assert(S == 4 || S == 8);
+    uint32_t o;
+    o = dpp_mov<kDppXor1>(v); v = v > o ? v : o;
+    o = dpp_mov<kDppXor2>(v); v = v > o ? v : o;
+    if constexpr (S == 8) { o = dpp_mov<kDppHalfMirror>(v); v = v > o ? v : o; }
+    return v;
+}
+
 // a, b: decreasing lists of 32-bit keys.  Returns the 64 greatest of their union, decreasing;
 // `fell` collects, lane by lane, the greatest key that did not make it.
 __device__ __forceinline__ uint32_t merge32_desc(uint32_t a, uint32_t b, uint32_t &fell)

@@ -389,6 +389,18 @@ def test_wide_beams_on_rows_of_one_tile(torch_gpu, k, V, fmt):
     _harness().run_parity(wl, logp_format=fmt)
 
 
+@pytest.mark.parametrize("V,fmt,ks", [(1021, None, (10, 11)), (2045, None, (20, 21)), (3070, None, (30, 31)), (4096, None, (40, 41)),
+                                      (8191, None, (16, 40, 41)), (8190, "bf16", (40, 41)), (16385, "bf16", (16, 17, 41)),
+                                      (8193, None, (40, 41)), (40001, None, (9, 40, 41)), (40001, "f16", (40, 41))])
+def test_floors_from_cells_and_from_sorted_lists(torch_gpu, V, fmt, ks):
+    """Beams on either side of the line between the two, for rows of one tile (16 cells) up to more than two per wave, with
+    four and with eight waves a row."""
+    for k in ks:
+        wl = si.make_small(5700 + k, 2, k, V, 3, max_phrases=2, max_len=2, dup_prob=0.3)
+        wl.eos_switch = 2
+        _harness().run_parity(wl, logp_format=fmt)
+
+
 def test_many_sentences_long_decode(torch_gpu):
     """300 sentences (more workgroups in the merge phase than compute units), 150 steps of history,
     the set-up of Sec. 4 (per-word scores, pruning at 20), end-of-sentence likely from step 40 on."""
