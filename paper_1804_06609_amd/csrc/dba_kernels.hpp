@@ -345,57 +345,9 @@ template <>
 struct Logp<kFmtBF16> : Logp16<kFmtBF16> {};
 
 // The log-probs are read exactly once: non-temporal loads keep them from displacing
-// anything useful in the caches.  nv = groups in the row's aligned body.
-template <int U, typename VEC>
-__device__ __forceinline__ void load_full(const VEC *__restrict__ vec, int tile, int lane, VEC (&x)[U])
-{
-#pragma unroll
-    for (int u = 0; u < U; ++u) x[u] = __builtin_nontemporal_load(vec + tile * (kWave * U) + u * kWave + lane);
-}
-
-// The last, partial tile of a row.  All registers are filled before the first load: filled one by one between the
-// loads, some share registers with a load on its way and wait for it (160 rows, k = 10, per step: 17300 fp32 13.9 -> 13.4
-// us, 45000 15.55 -> 15.2; 1152 rows of 32003 bf16 22.2 -> 22.0).
-template <int U, typename VEC>
-__device__ __forceinline__ void load_partial(const VEC *__restrict__ vec, int nv, int tile, int lane, VEC (&x)[U],
-                                             const VEC fill)
-{
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        x[u] = fill;
-        asm volatile("" : "+v"(x[u]));
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int i = tile * (kWave * U) + u * kWave + lane;
-        if (i < nv) x[u] = __builtin_nontemporal_load(vec + i);
-    }
-}
-
-// (At the start of a row the compiler's own order of fills and loads is the better one: 160 rows of 32000 13.9 us per step
-// against 14.5 with the fills first.)
-template <int U, bool START, bool WAIT, typename VEC>
-__device__ __forceinline__ void load_tile(const VEC *__restrict__ vec, int nv, int tile, int lane, VEC (&x)[U],
-                                          const VEC fill)
-{
-    const int base = tile * (kWave * U);
-    if (base + kWave * U <= nv) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = __builtin_nontemporal_load(vec + base + u * kWave + lane);
-    } else if (!START) {
-        // (Waited for here, by the one wave whose last tile it is: left open, these loads, which lanes may skip, make every
-        // tile of the loop wait for all loads on their way before its first group: 160 rows of 65536, four tiles in flight,
-        // 17.5 -> 17.35 us.  With two in flight the wait itself costs more: 1280 rows of 32000 33.45 -> 33.7.)
-        load_partial<U>(vec, nv, tile, lane, x, fill);
-        if (WAIT) __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
-    } else {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = base + u * kWave + lane;
-            x[u] = (i < nv) ? __builtin_nontemporal_load(vec + i) : fill;
-        }
-    }
-}
+// anything useful in the caches.
+constexpr int kNonTemporal = 2;       // cache-policy bit of a buffer load on gfx950
+constexpr int kRawBuffer = 0x00027000;// last word of a buffer descriptor: 32-bit data, no swizzle
 
 // LDS shared by the waves of one row's workgroup during the stream phase.
 template <int NW>
@@ -486,9 +438,31 @@ struct RowStream {
 
     const elem_t *row;
     const vec_t *vec;
-    int V, head, nv, tail, ntiles;
+    int V, head, nv, tail, ntiles;        // nv: groups in the row's aligned body
+    __amdgpu_buffer_rsrc_t body;
     vec_t tile_[D][U];
     elem_t lone;          // wave 0: this lane's element outside the aligned body, if there is one
+
+    // Requests a tile.  The descriptor ends with the row's aligned body, so lanes beyond it read nothing and get 0:
+    // a partial tile needs neither a branch nor switched-off lanes when it is requested, only to be blanked when it is looked at,
+    // and the waits of the loop count the same loads on every way through it.  (Requested under a lane mask instead, into
+    // registers that were filled first, it came after the floor and waited: per step, 160 rows of 32000 fp32 13.4 -> 13.2 us, 240
+    // of 9000 11.65 -> 11.2, 1280 of 32000 bf16 23.4 -> 23.2, 1152 of 32003 bf16 21.75 -> 21.55; the partial tile at the
+    // front of the row instead: 13.1, 11.2, 23.2, 22.7, as the floor then rests on less.)
+    __device__ __forceinline__ void load(int tile, vec_t (&x)[U]) const
+    {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            x[u] = __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b128(
+                body, (int)sizeof(vec_t) * (tile * (kWave * U) + u * kWave + lane_id()), 0, kNonTemporal));
+    }
+    // The groups that a partial tile does not have read as if no element could reach the threshold.
+    __device__ __forceinline__ void blank(int tile, vec_t (&x)[U]) const
+    {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (tile * (kWave * U) + u * kWave + lane_id() >= nv) x[u] = F::neg_inf();
+    }
 
     // Issues the loads of this wave's first two tiles.  Needs nothing of the hypothesis, so it
     // runs before the beam state has arrived.
@@ -504,11 +478,9 @@ struct RowStream {
         tail = V - head - nv * G;
         vec = reinterpret_cast<const vec_t *>(row + head);
         ntiles = (nv + kWave * U - 1) / (kWave * U);
+        body = __builtin_amdgcn_make_buffer_rsrc(const_cast<vec_t *>(vec), 0, nv * (int)sizeof(vec_t), kRawBuffer);
 #pragma unroll
-        for (int u = 0; u < U; ++u) tile_[1][u] = F::neg_inf();
-#pragma unroll
-        for (int d = 0; d < 2; ++d)
-            if (wave + d * nwaves < ntiles) load_tile<U, true, false>(vec, nv, wave + d * nwaves, lane, tile_[d], F::neg_inf());
+        for (int d = 0; d < 2; ++d) load(wave + d * nwaves, tile_[d]);
         lone = 0;
         if (wave == 0 && lane < head + tail) lone = row[lone_at(lane)];
     }
@@ -543,7 +515,8 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
     if (wave < ntiles) {
         // the first two tiles take part in the floor (8 KB per wave)
         float lane_max = -INFINITY;
-        auto offer = [&](const vec_t (&t)[U], int tile) {
+        auto offer = [&](vec_t (&t)[U], int tile) {
+            if (tile == nfull) blank(tile, t);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const uint32_t off = no_coord - (lane_coord + (uint32_t)(G * kWave * u) + (uint32_t)(G * U * kWave) * (uint32_t)tile);
@@ -555,8 +528,7 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
         if (wave + nwaves < ntiles) offer(tile_[1], wave + nwaves);
         asm volatile("" : "+v"(lane_max));                 // (both tiles are here before more is requested)
 #pragma unroll
-        for (int d = 2; d < D; ++d)
-            if (wave + d * nwaves < nfull) load_full<U>(vec, wave + d * nwaves, lane, tile_[d]);
+        for (int d = 2; d < D; ++d) load(wave + d * nwaves, tile_[d]);
         boot = ord_from_float(prev + lane_max);
     }
     // Any k values that different lanes hold give a valid floor
@@ -607,7 +579,8 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
     }
     const int parked_alone = parked;
     // one tile: test its U groups, set aside what may belong to the top k.  False: no room for them.
-    auto examine = [&](const vec_t (&t)[U], int tile) {
+    auto examine = [&](vec_t (&t)[U], int tile) {
+        if (tile == nfull) blank(tile, t);
         bool mine[U];
         u64 m[U], any = 0;
         int n = 0;
@@ -669,10 +642,6 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
                             : F::quick(prev, float_from_ord(bar + (ties == left ? 1u : 0u)));
     };
     int tl = wave;                        // tile to look at next
-#pragma unroll
-    for (int d = 2; d < D; ++d)           // the partial tile, if it is one of the first D
-        if (wave + d * nwaves >= nfull && wave + d * nwaves < ntiles)
-            load_partial<U>(vec, nv, wave + d * nwaves, lane, tile_[d], F::neg_inf());
     // a tile's registers are refilled as soon as it has been looked at, N tiles ahead
     auto stream = [&](auto &t) {
         constexpr int N = sizeof(t) / sizeof(t[0]);
@@ -683,7 +652,7 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
                 if (tl >= ntiles) break;
                 room = examine(t[d], tl);
                 if (!room) break;
-                if (tl + N * nwaves < ntiles) load_tile<U, false, (N > 2)>(vec, nv, tl + N * nwaves, lane, t[d], F::neg_inf());
+                if (tl + N * nwaves < ntiles) load(tl + N * nwaves, t[d]);
                 tl += nwaves;
             }
         }
@@ -715,7 +684,7 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
             }
             tl += nwaves;
 #pragma unroll
-            for (int d = 0; d < 2; ++d) load_tile<U, false, false>(vec, nv, tl + d * nwaves, lane, next[d], F::neg_inf());
+            for (int d = 0; d < 2; ++d) load(tl + d * nwaves, next[d]);
             stream(next);
         } while (tl < ntiles);
     }

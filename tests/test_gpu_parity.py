@@ -401,6 +401,18 @@ def test_floors_from_cells_and_from_sorted_lists(torch_gpu, V, fmt, ks):
         _harness().run_parity(wl, logp_format=fmt)
 
 
+@pytest.mark.parametrize("V,fmt", [(4, None), (1028, None), (2044, None), (4100, None), (8196, None), (9212, None), (32772, None), (33788, None),
+                                   (40959, None), (8, "f16"), (2056, "bf16"), (4088, "f16"), (18424, "bf16"), (67593, "f16")])
+def test_partial_tiles(torch_gpu, V, fmt):
+    """The last tile of a row holds one 16-byte group, or lacks one: as the only tile, among the first two of a wave, as
+    the third or fourth and behind those, with four and with eight waves a row.  (What a lane beyond the row gets is 0, better
+    than any log-prob here.)"""
+    wl = si.make_small(5800 + V, 3, 4, V, 4, max_phrases=2, max_len=2, dup_prob=0.3) if V > 100 else \
+        si.Workload(B=3, k=4, V=V, T=4, seed=5800 + V, constraints=[[], [], []])
+    wl.eos_switch = 2
+    _harness().run_parity(wl, logp_format=fmt)
+
+
 def test_many_sentences_long_decode(torch_gpu):
     """300 sentences (more workgroups in the merge phase than compute units), 150 steps of history,
     the set-up of Sec. 4 (per-word scores, pruning at 20), end-of-sentence likely from step 40 on."""
