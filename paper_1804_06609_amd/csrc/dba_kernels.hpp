@@ -770,7 +770,7 @@ __device__ __forceinline__ u64 finish_row(StreamSmem<NW> &sm, u64 list, int park
                 }
             key = sm.key[w][i - first];
         }
-        const u64 sorted = sort64_desc<u64, true>(key);
+        const u64 sorted = sort_first_desc<u64, true>(key, n - c * kWave);
         part = have ? merge_desc<u64, true>(part, sorted) : sorted;
         have = true;
     }
