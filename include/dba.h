@@ -14,9 +14,12 @@
  *   - "host" / "device" is said for every pointer.  Device pointers are plain
  *     hipMalloc-style addresses on the current device; no framework types.
  *   - The library allocates no device memory: state, history and scratch are
- *     carved from a caller-provided workspace.
- *   - dba_step only enqueues work on the stream given at init and returns;
- *     nothing is synchronised before dba_finalize / dba_get_state.
+ *     carved from a caller-provided workspace.  Each ctx holds a block of pinned host
+ *     memory (64 KB to 1 MB; none for more than about 3900 sentences), kept for
+ *     the next one by dba_destroy: at most 2 MB in all.
+ *   - dba_init and dba_step only enqueue work on the stream given at init and return
+ *     (dba_init waits where it has no block of host memory); nothing is
+ *     synchronised before dba_get_finished / dba_finalize / dba_get_state.
  *   - Every function returns DBA_OK (0) or a negative code; none throws or
  *     aborts.  dba_last_error gives the text of the last failure.
  *   - One ctx is used from one host thread at a time.

@@ -243,29 +243,69 @@ __global__ void dba_wave_select_kernel(int n_cases, const u64 *keys, const float
     fout[(size_t)i * 64 + lane] = float_from_ord(sort64_desc<uint32_t>(ord_from_float(vals[(size_t)i * 64 + lane])));
 }
 
-// decoder-init: slot 0 of every sentence is a live, empty hypothesis with score +0.0
-__global__ void dba_init_state_kernel(int B, int k, const int32_t *phr_off, const int32_t *nphr, float *score,
-                                      u64 *met, int32_t *ipq, int32_t *len, uint8_t *fin, u64 *inc,
-                                      int32_t *nxt, uint8_t *all_finished, BestCompleted *best)
+// The constraints of a sentence as the host hands them over: one word per place, token id | kBeginsPhrase, or kNoToken.
+constexpr uint32_t kBeginsPhrase = 0x80000000u, kNoToken = 0x40000000u;
+
+// decoder-init: slot 0 of every sentence is a live, empty hypothesis with score +0.0; and the sentence's tables, one
+// wave per sentence, lane = place of a token, then phrase.  Its time is one trip to host memory for the words.  seen
+// (may be null): host word per sentence, set once the sentence's words have been read.
+__global__ __launch_bounds__(kWave) void dba_init_kernel(int B, int k, const uint32_t *words, uint32_t *seen, StepParams p)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < B * k) {
-        const int b = i / k, h = i - b * k;
-        const int P = nphr[b];
-        const int C = phr_off[(size_t)b * (kMaxCons + 1) + P];
-        score[i] = h == 0 ? 0.0f : -INFINITY;
-        met[i] = 0;
-        ipq[i] = -1;
-        len[i] = 0;
-        fin[i] = (uint8_t)((h == 0 && C > 0) ? kFinEosBlocked : 0);
-        inc[i] = (h == 0 && P > 0) ? (P == 64 ? ~0ull : ((1ull << P) - 1ull)) : 0ull;
-        nxt[i] = -1;
+    __shared__ int off[kMaxCons], first[kMaxCons];
+    const int b = (int)blockIdx.x, lane = lane_id();
+    const size_t at = (size_t)b * kMaxCons + lane;
+    const uint32_t word = __hip_atomic_load(words + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const bool valid = (word & kNoToken) == 0, begins = valid && (word & kBeginsPhrase) != 0;
+    const int tok = valid ? (int)(word & ~kBeginsPhrase) : 0;
+    const u64 starts = __ballot(begins);
+    const int C = (int)__popcll(__ballot(valid)), P = (int)__popcll(starts);
+    if (seen && lane == 0) __hip_atomic_store(seen + b, (uint32_t)(1 + P), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (begins) {
+        off[lanes_before(starts)] = lane;
+        first[lanes_before(starts)] = tok;
     }
-    if (i < B) {
-        all_finished[i] = 0;
+    __syncthreads();
+    const int ftok = lane < P ? first[lane] : -1;
+    u64 same_lower = 0, bucket = 0;
+    int btok = -1;
+    for (int j = 0; j < P; ++j) {
+        const int f = __builtin_amdgcn_readlane(ftok, j);
+        if (j < lane && f == ftok) same_lower |= 1ull << j;
+        if ((f & 63) == lane) {
+            bucket |= 1ull << j;
+            btok = btok == -1 || btok == f ? f : -2;
+        }
+    }
+    const_cast<int32_t *>(p.cons_tok)[at] = tok;
+    int32_t *poff = const_cast<int32_t *>(p.phr_off) + (size_t)b * (kMaxCons + 1);
+    poff[lane] = lane < P ? off[lane] : lane == P ? C : 0;
+    const_cast<int32_t *>(p.first_tok)[at] = ftok;
+    const_cast<u64 *>(p.same_first_lower)[at] = same_lower;
+    const_cast<u64 *>(p.first_bucket)[at] = bucket;
+    const_cast<int32_t *>(p.bucket_tok)[at] = btok;
+    if (lane == 0) {
+        poff[kMaxCons] = P == kMaxCons ? C : 0;
+        const_cast<int32_t *>(p.nphr)[b] = P;
+        p.all_finished[b] = 0;
         BestCompleted none = {};
-        best[i] = none;
+        p.best[b] = none;
     }
+    if (lane < k) {
+        const size_t i = (size_t)b * k + lane;
+        p.score_nxt[i] = lane == 0 ? 0.0f : -INFINITY;
+        p.met_nxt[i] = 0;
+        p.ipq_nxt[i] = -1;
+        p.len_nxt[i] = 0;
+        p.fin_nxt[i] = (uint8_t)((lane == 0 && C > 0) ? kFinEosBlocked : 0);
+        p.inc_nxt[i] = (lane == 0 && P > 0) ? (P == 64 ? ~0ull : ((1ull << P) - 1ull)) : 0ull;
+        p.nxt_nxt[i] = -1;
+    }
+}
+
+// The stopping flags on their way to host memory, four sentences a word.
+__global__ __launch_bounds__(kBlock) void dba_flags_kernel(int words, const uint32_t *flags, uint32_t *out)
+{
+    for (int i = threadIdx.x; i < words; i += kBlock) out[i] = flags[i];
 }
 
 // End of decoding (Sec. 3.3, length normalisation of Sec. 4): one workgroup per sentence.
@@ -449,6 +489,11 @@ Layout make_layout(size_t B, size_t k, size_t N)
     return L;
 }
 
+// Up to this many bytes of tokens dba_finalize brings over together with the other results: 58 against 74 us with the
+// tokens on their own for 512000 bytes into ordinary memory, 57 against 50 into pinned memory; 78 / 75 and 77 / 53 at 716800,
+// 810 / 520 and 810 / 200 at 8 MB.
+bool staged_tokens(size_t B, size_t N) { return B * N * 4 <= 512 * 1024; }
+
 constexpr size_t kComputeUnits = 256;
 constexpr size_t kLdsPerUnit = 160 * 1024;
 
@@ -557,6 +602,117 @@ hipError_t static_scratch(void **out)
 
 }  // namespace
 
+namespace {
+
+// Pinned host memory that kernels read and write themselves: a copy to or from ordinary host memory costs about 8
+// us and a wait of its own (a decode with the stopping test asked for after each of its 21 steps, 8 x 10 x 32000: 814 -> 641
+// us; one of 100 steps, 64 x 20 x 32000: 3360 -> 3294).  A ctx holds one block from dba_init to dba_destroy; blocks are kept for the next ctx, of any
+// thread and device, up to kKeepBytes of them, and freed beyond.  A block whose dba_init may not have been
+// read by the GPU yet when its ctx goes waits aside until the words that say so are set.
+struct HostBlock {
+    unsigned char *p = nullptr;           // (host and device address)
+    size_t bytes = 0;
+};
+
+class HostBlocks {
+public:
+    static constexpr size_t kLeast = 64 * 1024, kMost = 1024 * 1024;
+    // an empty block if there is none to be had: its user does without
+    HostBlock get(size_t bytes) noexcept
+    {
+        HostBlock block;
+        if (bytes > kMost) return block;
+        size_t n = kLeast;
+        while (n < bytes) n *= 2;
+        {
+            std::lock_guard<std::mutex> hold(mutex_);
+            settle();
+            for (int i = 0; i < n_free_; ++i)
+                if (free_[i].bytes == n) {
+                    block = free_[i];
+                    free_[i] = free_[--n_free_];
+                    kept_ -= n;
+                    return block;
+                }
+        }
+        // (allocating is no part of a stream capture that this or another thread may have under way)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, n, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
+            block.p = static_cast<unsigned char *>(p);
+            block.bytes = n;
+        } else {
+            (void)hipGetLastError();
+        }
+        if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        return block;
+    }
+    // seen: the words of B sentences at the block's start, if they still have to be waited for (B = 0: not)
+    void put(HostBlock block, int B) noexcept
+    {
+        if (!block.p) return;
+        HostBlock extra;
+        {
+            std::lock_guard<std::mutex> hold(mutex_);
+            settle();
+            if (!read(block, B)) {
+                if (n_aside_ < kAside) {
+                    aside_[n_aside_] = block;
+                    aside_B_[n_aside_++] = B;
+                    return;
+                }
+                extra = block;
+            } else if (!keep(block)) {
+                extra = block;
+            }
+        }
+        if (extra.p) (void)hipHostFree(extra.p);           // (waits for the GPU)
+    }
+
+private:
+    static constexpr size_t kKeepBytes = 2 * 1024 * 1024;
+    static constexpr int kKeep = (int)(kKeepBytes / kLeast), kAside = 16;
+    static bool read(const HostBlock &block, int B)
+    {
+        const volatile uint32_t *seen = reinterpret_cast<const volatile uint32_t *>(block.p);
+        for (int b = 0; b < B; ++b)
+            if (seen[b] == 0) return false;
+        return true;
+    }
+    bool keep(const HostBlock &block)
+    {
+        if (kept_ + block.bytes > kKeepBytes) return false;
+        free_[n_free_++] = block;
+        kept_ += block.bytes;
+        return true;
+    }
+    void settle()
+    {
+        for (int i = 0; i < n_aside_;) {
+            if (read(aside_[i], aside_B_[i]) && keep(aside_[i])) {
+                aside_[i] = aside_[--n_aside_];
+                aside_B_[i] = aside_B_[n_aside_];
+            } else {
+                ++i;
+            }
+        }
+    }
+    std::mutex mutex_;
+    HostBlock free_[kKeep], aside_[kAside];
+    int aside_B_[kAside] = {};
+    int n_free_ = 0, n_aside_ = 0;
+    size_t kept_ = 0;
+};
+
+HostBlocks &host_blocks()
+{
+    static HostBlocks *blocks = new HostBlocks;            // (outlives every ctx: never destroyed)
+    return *blocks;
+}
+
+}  // namespace
+
 struct dba_ctx {
     int B, k, V, N, eos_id, pad_id;
     int met_bits;
@@ -573,6 +729,9 @@ struct dba_ctx {
     size_t dyn_smem;
     unsigned char *ws;
     Layout L;
+    HostBlock block;                    // seen words [B], stopping flags [B], then constraint words / results (p null: none)
+    size_t block_flags, block_data;     // offsets in it
+    int unread;                         // B while the GPU may still have to read the block's constraint words, 0 afterwards
     hipStream_t stream;
     char err[256];
 };
@@ -599,6 +758,33 @@ template <typename T>
 T *at(dba_ctx *c, size_t off)
 {
     return reinterpret_cast<T *>(c->ws + off);
+}
+
+void set_tables(dba_ctx *c, StepParams &p)
+{
+    const Layout &L = c->L;
+    p.cons_tok = at<int32_t>(c, L.cons_tok);
+    p.phr_off = at<int32_t>(c, L.phr_off);
+    p.nphr = at<int32_t>(c, L.nphr);
+    p.first_tok = at<int32_t>(c, L.ftok);
+    p.same_first_lower = at<u64>(c, L.sfl);
+    p.first_bucket = at<u64>(c, L.bloom);
+    p.bucket_tok = at<int32_t>(c, L.btok);
+    p.all_finished = at<uint8_t>(c, L.all_finished);
+    p.best = at<BestCompleted>(c, L.best);
+}
+
+// half: which of the two halves of the beam state the kernel writes
+void set_beam_after(dba_ctx *c, StepParams &p, int half)
+{
+    const Layout &L = c->L;
+    p.score_nxt = at<float>(c, L.score[half]);
+    p.met_nxt = at<u64>(c, L.met[half]);
+    p.ipq_nxt = at<int32_t>(c, L.ipq[half]);
+    p.len_nxt = at<int32_t>(c, L.len[half]);
+    p.fin_nxt = at<uint8_t>(c, L.fin[half]);
+    p.inc_nxt = at<u64>(c, L.inc[half]);
+    p.nxt_nxt = at<int32_t>(c, L.nxt[half]);
 }
 
 }  // namespace
@@ -638,18 +824,23 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     for (int b = 0; b < B; ++b)
         if (sent_offsets[b + 1] < sent_offsets[b])
             return fail(nullptr, DBA_EINVAL, "dba_init: sent_offsets decreases at %d", b);
-    // (an image of the tables' stretch of the workspace, so that one copy takes them all to the device: a copy from
-    // ordinary host memory costs about 8 us whatever its size)
+    // The constraint words go to a block of host memory that the kernel of dba_init reads itself, or, where there
+    // is none (large batches), through a copy to the workspace.  (Opening a session, the caller's allocations included, with
+    // all tables made on the host, copied and waited for / like this: one sentence 51 / 38 us, 64 sentences 119 / 48.)
     const Layout L = make_layout((size_t)B, (size_t)k, (size_t)N);
-    const size_t tables_bytes = L.rowlists - L.cons_tok;
-    std::vector<unsigned char> image(tables_bytes, 0);
-    auto table = [&](size_t off) { return image.data() + (off - L.cons_tok); };
-    int32_t *tok = reinterpret_cast<int32_t *>(table(L.cons_tok)), *off = reinterpret_cast<int32_t *>(table(L.phr_off));
-    int32_t *nph = reinterpret_cast<int32_t *>(table(L.nphr));
-    u64 *sfl = reinterpret_cast<u64 *>(table(L.sfl)), *bloom = reinterpret_cast<u64 *>(table(L.bloom));
-    int32_t *ftok = reinterpret_cast<int32_t *>(table(L.ftok)), *btok = reinterpret_cast<int32_t *>(table(L.btok));
-    std::fill(ftok, ftok + (size_t)B * kMaxCons, -1);
-    std::fill(btok, btok + (size_t)B * kMaxCons, -1);
+    const size_t words_bytes = (size_t)B * kMaxCons * sizeof(uint32_t);
+    struct Holder {
+        HostBlock block;
+        int unread = 0;
+        ~Holder() { host_blocks().put(block, unread); }
+    } held;
+    const size_t block_flags = (size_t)B * sizeof(uint32_t), block_data = align_up(block_flags + (size_t)B, 256);
+    const size_t results_bytes = L.fin_status + (size_t)B * 4 - (staged_tokens((size_t)B, (size_t)N) ? L.fin_tokens : L.fin_len);
+    held.block = host_blocks().get(block_data + std::max(words_bytes, results_bytes));
+    std::vector<uint32_t> own_words;
+    if (!held.block.p) own_words.resize((size_t)B * kMaxCons);
+    uint32_t *words = held.block.p ? reinterpret_cast<uint32_t *>(held.block.p + block_data) : own_words.data();
+    std::fill(words, words + (size_t)B * kMaxCons, kNoToken);
     int max_tokens = 0, max_phrases = 0;
     for (int b = 0; b < B; ++b) {
         const int p0 = sent_offsets[b], p1 = sent_offsets[b + 1];
@@ -664,30 +855,14 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
                 return fail(nullptr, DBA_EINVAL, "dba_init: sentence %d has more than %d constraint tokens", b,
                             DBA_MAX_CONS_TOKENS);
             if (!cons_tokens) return fail(nullptr, DBA_EINVAL, "dba_init: cons_tokens is NULL");
-            off[(size_t)b * (kMaxCons + 1) + (p - p0)] = n;
             for (int i = a; i < e; ++i) {
                 const int w = cons_tokens[i];
                 if (w < 0 || w >= V)
                     return fail(nullptr, DBA_EINVAL, "dba_init: constraint token %d outside [0,V)", w);
                 if (w == eos_id || w == pad_id)
                     return fail(nullptr, DBA_EINVAL, "dba_init: eos_id/pad_id cannot be a constraint token");
-                tok[(size_t)b * kMaxCons + n++] = w;
+                words[(size_t)b * kMaxCons + n++] = (uint32_t)w | (i == a ? kBeginsPhrase : 0u);
             }
-        }
-        off[(size_t)b * (kMaxCons + 1) + (p1 - p0)] = n;
-        nph[b] = p1 - p0;
-        // lookup aids for the kernels (layout only): which lower phrases share a phrase's first
-        // token; the phrases bucketed by the low six bits of their first token; and that token
-        // itself where all phrases of a bucket begin alike (-1 empty bucket, -2 they differ)
-        for (int j = 0; j < p1 - p0; ++j) {
-            const int fj = tok[(size_t)b * kMaxCons + off[(size_t)b * (kMaxCons + 1) + j]];
-            ftok[(size_t)b * kMaxCons + j] = fj;
-            bloom[(size_t)b * kMaxCons + (fj & 63)] |= 1ull << j;
-            int32_t &bt = btok[(size_t)b * kMaxCons + (fj & 63)];
-            bt = bt == -1 ? fj : (bt == fj ? fj : -2);
-            for (int j2 = 0; j2 < j; ++j2)
-                if (tok[(size_t)b * kMaxCons + off[(size_t)b * (kMaxCons + 1) + j2]] == fj)
-                    sfl[(size_t)b * kMaxCons + j] |= 1ull << j2;
         }
         if (n > max_tokens) max_tokens = n;
         if (p1 - p0 > max_phrases) max_phrases = p1 - p0;
@@ -705,9 +880,12 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     if (workspace_bytes < L.total)
         return fail(nullptr, DBA_ENOMEM, "dba_init: workspace has %zu bytes, %zu needed", workspace_bytes, L.total);
 
-    dba_ctx *c = new (std::nothrow) dba_ctx;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(static_cast<hipStream_t>(hip_stream), &capture) != hipSuccess) (void)hipGetLastError();
+    else if (capture != hipStreamCaptureStatusNone)
+        return fail(nullptr, DBA_EHIP, "dba_init: HIP error: %s", hipGetErrorString(hipErrorStreamCaptureUnsupported));
+    dba_ctx *c = new (std::nothrow) dba_ctx();
     if (!c) return fail(nullptr, DBA_ENOMEM, "dba_init: out of host memory");
-    memset(c, 0, sizeof *c);
     c->B = B; c->k = k; c->V = V; c->N = N; c->eos_id = eos_id; c->pad_id = pad_id;
     c->met_bits = met_bits;
     c->tok_bits = tok_bits;
@@ -731,22 +909,35 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     const int ncand_max = (k * (max_phrases + 2) + kWave - 1) / kWave * kWave;
     c->dyn_smem = (size_t)ncand_max * sizeof(u64);
 
-    hipError_t e = hipMemcpyAsync(c->ws + L.cons_tok, image.data(), tables_bytes, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) {
-        const int n = B * k;
-        dba_init_state_kernel<<<(n + 255) / 256, 256, 0, c->stream>>>(
-            B, k, at<int32_t>(c, L.phr_off), at<int32_t>(c, L.nphr), at<float>(c, L.score[0]),
-            at<u64>(c, L.met[0]), at<int32_t>(c, L.ipq[0]), at<int32_t>(c, L.len[0]),
-            at<uint8_t>(c, L.fin[0]), at<u64>(c, L.inc[0]), at<int32_t>(c, L.nxt[0]),
-            at<uint8_t>(c, L.all_finished), at<BestCompleted>(c, L.best));
-        e = hipGetLastError();
+    // (without a block the words pass through the row lists' place, which is large enough and not in use yet)
+    hipError_t e = hipSuccess;
+    uint32_t *seen = nullptr;
+    if (held.block.p) {
+        seen = reinterpret_cast<uint32_t *>(held.block.p);
+        memset(seen, 0, (size_t)B * sizeof(uint32_t));
+    } else {
+        e = hipMemcpyAsync(c->ws + L.rowlists, words, words_bytes, hipMemcpyHostToDevice, c->stream);
+        words = at<uint32_t>(c, L.rowlists);
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);   // the image is freed on return
+    if (e == hipSuccess) {
+        StepParams p = {};
+        set_tables(c, p);
+        set_beam_after(c, p, 0);
+        dba_init_kernel<<<(unsigned)B, kWave, 0, c->stream>>>(B, k, words, seen, p);
+        e = hipGetLastError();
+        if (e == hipSuccess && seen) held.unread = B;
+    }
+    if (e == hipSuccess && !seen) e = hipStreamSynchronize(c->stream);   // the words are freed on return
     if (e != hipSuccess) {
         const int rc = fail(nullptr, DBA_EHIP, "dba_init: HIP error: %s", hipGetErrorString(e));
         delete c;
         return rc;
     }
+    c->block = held.block;
+    c->block_flags = block_flags;
+    c->block_data = block_data;
+    c->unread = held.unread;
+    held.block.p = nullptr;
     *out = c;
     return DBA_OK;
 }
@@ -808,20 +999,8 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     p.fin_cur = at<uint8_t>(c, L.fin[cur]);
     p.inc_cur = at<u64>(c, L.inc[cur]);
     p.nxt_cur = at<int32_t>(c, L.nxt[cur]);
-    p.score_nxt = at<float>(c, L.score[nxt]);
-    p.met_nxt = at<u64>(c, L.met[nxt]);
-    p.ipq_nxt = at<int32_t>(c, L.ipq[nxt]);
-    p.len_nxt = at<int32_t>(c, L.len[nxt]);
-    p.fin_nxt = at<uint8_t>(c, L.fin[nxt]);
-    p.inc_nxt = at<u64>(c, L.inc[nxt]);
-    p.nxt_nxt = at<int32_t>(c, L.nxt[nxt]);
-    p.cons_tok = at<int32_t>(c, L.cons_tok);
-    p.phr_off = at<int32_t>(c, L.phr_off);
-    p.nphr = at<int32_t>(c, L.nphr);
-    p.first_tok = at<int32_t>(c, L.ftok);
-    p.same_first_lower = at<u64>(c, L.sfl);
-    p.first_bucket = at<u64>(c, L.bloom);
-    p.bucket_tok = at<int32_t>(c, L.btok);
+    set_beam_after(c, p, nxt);
+    set_tables(c, p);
     p.rowlists = own_scratch ? reinterpret_cast<u64 *>(own_scratch) : at<u64>(c, L.rowlists);
     p.conskeys = own_scratch ? reinterpret_cast<u64 *>(own_scratch + kStaticListBytes) : at<u64>(c, L.conskeys);
     p.out_token = out_token_dev;
@@ -831,8 +1010,6 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     const size_t hrow = (size_t)c->steps * c->B * c->k;
     p.hist_token = at<int32_t>(c, L.hist_token) + hrow;
     p.hist_backptr = at<int32_t>(c, L.hist_backptr) + hrow;
-    p.all_finished = at<uint8_t>(c, L.all_finished);
-    p.best = at<BestCompleted>(c, L.best);
 
     // one workgroup per beam row, 4 loads of 16 bytes per lane and tile, two or four 4 KB tiles in flight per wave
     const StreamPlan plan = stream_plan((size_t)c->B, (size_t)c->k, (size_t)c->V, elem);
@@ -926,11 +1103,6 @@ DBA_API int dba_step_noalloc(dba_ctx *c, const void *logp_dev, int logp_format, 
                      c->lib_scratch);
 }
 
-// Up to this many bytes of tokens dba_finalize brings over together with the other results: 58 against 74 us with the
-// tokens on their own for 512000 bytes into ordinary memory, 57 against 50 into pinned memory; 78 / 75 and 77 / 53 at 716800,
-// 810 / 520 and 810 / 200 at 8 MB.
-static const size_t kStagedTokens = 512 * 1024;
-
 DBA_API int dba_finalize(dba_ctx *c, int32_t *out_tokens_host, int32_t *out_len_host, float *out_score_host,
                  int32_t *out_status_host)
 {
@@ -939,42 +1111,41 @@ DBA_API int dba_finalize(dba_ctx *c, int32_t *out_tokens_host, int32_t *out_len_
         return fail(c, DBA_EINVAL, "dba_finalize: an output pointer is NULL");
     const Layout &L = c->L;
     const int cur = c->steps & 1;
+    const size_t B = (size_t)c->B, tokens_bytes = B * c->N * 4;
+    const bool staged = staged_tokens(B, (size_t)c->N);
+    // The four results lie side by side, small ones all in the block, where the kernel writes them; tokens beyond
+    // stay in the workspace and go straight to the caller's array.  Without a block each is copied.
+    const size_t first = staged ? L.fin_tokens : L.fin_len;
+    unsigned char *here = c->block.p ? c->block.p + c->block_data : nullptr;
+    auto place = [&](size_t off) {
+        return reinterpret_cast<int32_t *>(here && off >= first ? here + (off - first) : c->ws + off);
+    };
     dba_finalize_kernel<<<c->B, kFinWaves * kWave, 0, c->stream>>>(
         c->B, c->k, c->steps, c->N, c->pad_id, c->normalize, at<int32_t>(c, L.hist_token),
         at<int32_t>(c, L.hist_backptr),
         at<float>(c, L.score[cur]), at<u64>(c, L.met[cur]), at<int32_t>(c, L.len[cur]),
         at<uint8_t>(c, L.fin[cur]), c->track ? at<BestCompleted>(c, L.best) : nullptr,
-        at<int32_t>(c, L.fin_tokens), at<int32_t>(c, L.fin_len),
-        at<float>(c, L.fin_score), at<int32_t>(c, L.fin_status));
+        place(L.fin_tokens), place(L.fin_len), reinterpret_cast<float *>(place(L.fin_score)), place(L.fin_status));
     hipError_t e = hipGetLastError();
-    // The four results lie side by side.  Small ones come over in one copy (see dba_init) and are put apart here; tokens
-    // of more than kStagedTokens bytes go straight to the caller's array, and the three short results after them in
-    // one copy.  Without host memory for that, each goes straight.
-    const size_t B = (size_t)c->B, tokens_bytes = B * c->N * 4;
-    const bool staged = tokens_bytes <= kStagedTokens;
-    const size_t first = staged ? L.fin_tokens : L.fin_len, bytes = L.fin_status + B * 4 - first;
-    struct Free {
-        unsigned char *p;
-        ~Free() { free(p); }
-    } tmp{static_cast<unsigned char *>(malloc(bytes))};
-    auto fetch = [&](void *to, size_t from, size_t n) {
-        if (e == hipSuccess) e = hipMemcpyAsync(to, c->ws + from, n, hipMemcpyDeviceToHost, c->stream);
+    auto fetch = [&](void *to, size_t off, size_t n) {
+        if (e == hipSuccess && !(here && off >= first))
+            e = hipMemcpyAsync(to, c->ws + off, n, hipMemcpyDeviceToHost, c->stream);
     };
-    if (!staged || !tmp.p) fetch(out_tokens_host, L.fin_tokens, tokens_bytes);
-    if (tmp.p) {
-        fetch(tmp.p, first, bytes);
-    } else {
-        fetch(out_len_host, L.fin_len, B * 4);
-        fetch(out_score_host, L.fin_score, B * 4);
-        fetch(out_status_host, L.fin_status, B * 4);
-    }
+    fetch(out_tokens_host, L.fin_tokens, tokens_bytes);
+    fetch(out_len_host, L.fin_len, B * 4);
+    fetch(out_score_host, L.fin_score, B * 4);
+    fetch(out_status_host, L.fin_status, B * 4);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) return fail(c, DBA_EHIP, "dba_finalize: HIP error: %s", hipGetErrorString(e));
-    if (tmp.p) {
-        if (staged) memcpy(out_tokens_host, tmp.p, tokens_bytes);
-        memcpy(out_len_host, tmp.p + (L.fin_len - first), B * 4);
-        memcpy(out_score_host, tmp.p + (L.fin_score - first), B * 4);
-        memcpy(out_status_host, tmp.p + (L.fin_status - first), B * 4);
+    if (e != hipSuccess) {
+        if (here) c->block.p = nullptr;                    // (a kernel may still write to it: never used again)
+        return fail(c, DBA_EHIP, "dba_finalize: HIP error: %s", hipGetErrorString(e));
+    }
+    c->unread = 0;
+    if (here) {
+        if (staged) memcpy(out_tokens_host, place(L.fin_tokens), tokens_bytes);
+        memcpy(out_len_host, place(L.fin_len), B * 4);
+        memcpy(out_score_host, place(L.fin_score), B * 4);
+        memcpy(out_status_host, place(L.fin_status), B * 4);
     }
     return DBA_OK;
 }
@@ -1042,14 +1213,32 @@ DBA_API int dba_get_finished(dba_ctx *c, uint8_t *all_finished_host)
 {
     if (!c) return DBA_EINVAL;
     if (!all_finished_host) return fail(c, DBA_EINVAL, "dba_get_finished: the output pointer is NULL");
-    hipError_t e = hipMemcpyAsync(all_finished_host, at<uint8_t>(c, c->L.all_finished), (size_t)c->B,
-                                  hipMemcpyDeviceToHost, c->stream);
+    const uint8_t *flags = at<uint8_t>(c, c->L.all_finished);
+    uint8_t *here = c->block.p ? c->block.p + c->block_flags : nullptr;
+    hipError_t e;
+    if (here) {
+        dba_flags_kernel<<<1, kBlock, 0, c->stream>>>((c->B + 3) / 4, reinterpret_cast<const uint32_t *>(flags),
+                                                      reinterpret_cast<uint32_t *>(here));
+        e = hipGetLastError();
+    } else {
+        e = hipMemcpyAsync(all_finished_host, flags, (size_t)c->B, hipMemcpyDeviceToHost, c->stream);
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) return fail(c, DBA_EHIP, "dba_get_finished: HIP error: %s", hipGetErrorString(e));
+    if (e != hipSuccess) {
+        c->block.p = nullptr;                              // (a kernel may still write to it: never used again)
+        return fail(c, DBA_EHIP, "dba_get_finished: HIP error: %s", hipGetErrorString(e));
+    }
+    c->unread = 0;
+    if (here) memcpy(all_finished_host, here, (size_t)c->B);
     return DBA_OK;
 }
 
-DBA_API void dba_destroy(dba_ctx *c) { delete c; }
+DBA_API void dba_destroy(dba_ctx *c)
+{
+    if (!c) return;
+    host_blocks().put(c->block, c->unread);
+    delete c;
+}
 
 DBA_API const char *dba_last_error(const dba_ctx *c) { return c ? c->err : g_init_error; }
 

@@ -217,3 +217,65 @@ def test_a_decode_replayed_from_a_hip_graph_matches_eager_launches():
         assert ses.finished().tobytes() == want_stop, replay
         assert [np.asarray(a).tobytes() for a in ses.finalize()] == want_fin, replay
     ses.close()
+
+
+def test_ctxs_that_come_and_go_without_waiting():
+    """dba_init does not wait for the GPU: ctxs that are destroyed before it has read their constraints, on two
+    streams and from two threads, do not disturb those that follow, which get their host memory."""
+    import threading
+    import torch
+    from paper_1804_06609_amd.session import Session
+    jobs = []
+    for i, (B, k, V) in enumerate([(3, 5, 300), (40, 3, 200), (300, 2, 60), (2, 20, 500)]):
+        wl = si.make_small(8900 + i, B, k, V, 6, max_phrases=4, max_len=3, dup_prob=0.3)
+        wl.eos_switch = 3
+        dev = [torch.from_numpy(wl.logp(t)).cuda() for t in range(wl.T)]
+        ses = Session(B, k, V, wl.T, wl.eos_id, wl.pad_id, *wl.csr())
+        for t in range(wl.T):
+            ses.step(dev[t])
+        want = [np.asarray(a).tobytes() for a in ses.finalize()] + [ses.finished().tobytes()]
+        ses.close()
+        jobs.append((wl, dev, want))
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(first):
+        import paper_1804_06609_amd as dba
+        stream = torch.cuda.Stream()
+        for rep in range(12):
+            wl, dev, want = jobs[(first + rep) % len(jobs)]
+            other = jobs[(first + rep + 1) % len(jobs)][0]
+            keep = []                                      # (device memory outlives the ctxs below: theirs may still be under way)
+            with torch.cuda.stream(stream):
+                for _ in range(3):
+                    gone = Session(other.B, other.k, other.V, other.T, other.eos_id, other.pad_id, *other.csr(), stream=stream)
+                    dba.dba_destroy(gone.ctx)
+                    gone.ctx = None
+                    keep.append(gone)
+                ses = Session(wl.B, wl.k, wl.V, wl.T, wl.eos_id, wl.pad_id, *wl.csr(), stream=stream)
+                for t in range(wl.T):
+                    ses.step(dev[t])
+                    ses.finished()
+                got = [np.asarray(a).tobytes() for a in ses.finalize()] + [ses.finished().tobytes()]
+                ses.close()
+            if got != want:
+                wrong.append((first, rep))
+            stream.synchronize()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert not wrong
+
+
+@pytest.mark.parametrize("B,N", [(4000, 5), (4100, 5), (500, 400)])
+def test_batches_with_and_without_a_block_of_host_memory(B, N):
+    """Constraints, stopping flags and results pass through host memory that kernels use themselves, up to a megabyte;
+    beyond, and tokens of more than 512 KB, through copies."""
+    import harness
+    wl = si.make_small(8950, B, 2, 40, 5, max_phrases=2, max_len=2, dup_prob=0.3)
+    wl.T = N
+    wl.eos_switch = 2
+    harness.run_parity(wl, T=5, oracle_sentences=[0, 1, 63, 64, B // 2, B - 1])
