@@ -753,7 +753,8 @@ __device__ __forceinline__ u64 finish_row(StreamSmem<NW> &sm, u64 list, int park
         pre[w + 1] = pre[w] + sm.parked[w];
         any |= sm.has_list[w];
     }
-    const int n = pre[NW];
+    const int n = __builtin_amdgcn_readfirstlane(pre[NW]);
+    any = __builtin_amdgcn_readfirstlane(any);
     const int nchunks = (n + kWave - 1) >> 6;
     u64 part = 0;
     bool have = false;
