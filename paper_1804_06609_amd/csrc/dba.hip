@@ -726,6 +726,7 @@ struct dba_ctx {
     int merge_waves;                    // DBA_OPT_MERGE_WAVES (0: chosen here)
     int device;                         // the device that was current at dba_init
     unsigned char *lib_scratch;         // this device's copy of the library's own scratch (null: not resolved)
+    int cand_cap;                       // candidates of one sentence at most, in whole chunks of 64
     size_t dyn_smem;
     unsigned char *ws;
     Layout L;
@@ -907,7 +908,8 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     // candidates of one sentence: at most k best + k row bests + k * phrases constraint tokens,
     // in whole chunks of 64 keys (at most 4224 keys = 33 KB of LDS)
     const int ncand_max = (k * (max_phrases + 2) + kWave - 1) / kWave * kWave;
-    c->dyn_smem = (size_t)ncand_max * sizeof(u64);
+    c->cand_cap = ncand_max;
+    c->dyn_smem = (size_t)ncand_max * sizeof(u64) + (ncand_max > 4 * kWave ? kMostLeft * (sizeof(u64) + sizeof(int)) : 0);
 
     // (without a block the words pass through the row lists' place, which is large enough and not in use yet)
     hipError_t e = hipSuccess;
@@ -985,7 +987,7 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     p.met_bits = c->met_bits;
     p.tok_bits = c->tok_bits;
     p.first_step = c->steps == 0 ? 1 : 0;
-    p.cand_cap = (int)(c->dyn_smem / sizeof(u64));
+    p.cand_cap = c->cand_cap;
     p.adjust = c->adjust;
     p.normalize = c->normalize;
     p.prune = c->prune;

@@ -111,6 +111,7 @@ struct __attribute__((aligned(16))) HypState {
     int misc;      // finished flag | constraints met << 8
 };
 
+constexpr int kMostLeft = 1024;        // candidates there is room for after those that cannot be among their bank's best are gone
 constexpr int kMergeWavesMax = 8;     // most waves a merge-phase workgroup (one sentence) can have: 4 or 8 are used
 
 struct MergeSmem {
@@ -132,6 +133,7 @@ struct MergeSmem {
     int bar_need;                     // and the places left for keys that tie at that score (-1: no tie to settle)
     int ncand;
     int nsel;
+    int nleft;                        // candidates that can still be among their bank's best
     u64 kept;                         // pruning: bit i = the hypothesis at place i of the new beam stays
 };
 
@@ -1124,6 +1126,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     if (tid == 0) {
         sm.ncand = 0;
         sm.nsel = 0;
+        sm.nleft = 0;
         sm.kept = 0;
     }
     for (int i = tid; i < p.cand_cap; i += MW * kWave) cand[i] = 0;
@@ -1457,45 +1460,92 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         if (mine != 0 && lane < each) select(mine, rank);
     } else {
         // chunks of 64 are sorted by one wave each (wave 0, busy with the allocation, last); a
-        // candidate's rank is its place in its own chunk plus, by a search with three probes a round,
-        // the keys greater than it in every other chunk
+        // candidate's rank is the sum over the chunks of the keys greater than it, by a search with three probes a round
         const int my_first = MW - 1 - wave;
         for (int c = my_first; c < nchunks; c += MW) {
             const int i = c * kWave + lane;
             cand[i] = sort64_desc<u64, true>(i < ncand ? cand[i] : 0ull);
         }
         __syncthreads();
-        for (int c = my_first; c < nchunks; c += MW) {
-            const u64 mine = cand[c * kWave + lane];
-            int rank = lane;
-            // four searches at a time, so that their LDS reads overlap
-            for (int c0 = 0; c0 < nchunks; c0 += 4) {
-                int pos[4];
-                bool full[4];
+        // how many keys of chunks c0 .. c0 + 3 are greater; four searches at a time, so that their LDS reads overlap
+        auto greater = [&](u64 mine, int c0) {
+            int pos[4];
+            bool full[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int c2 = min(c0 + q, nchunks - 1);      // out of range: ignored below
+                pos[q] = 0;
+                full[q] = cand[c2 * kWave + 63] > mine;
+            }
+            // three probes a round (quarters, then sixteenths, then single places): three
+            // dependent trips to LDS instead of six
+#pragma unroll
+            for (int step = 16; step >= 1; step >>= 2) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int c2 = c0 + q < nchunks ? c0 + q : c;     // out of range: own chunk, ignored below
-                    pos[q] = 0;
-                    full[q] = cand[c2 * kWave + 63] > mine;
+                    const u64 *at0 = cand + min(c0 + q, nchunks - 1) * kWave + pos[q] - 1;
+                    const int above = (at0[step] > mine ? 1 : 0) + (at0[2 * step] > mine ? 1 : 0) +
+                                      (at0[3 * step] > mine ? 1 : 0);
+                    pos[q] += step * above;
                 }
-                // three probes a round (quarters, then sixteenths, then single places): three
-                // dependent trips to LDS instead of six
-#pragma unroll
-                for (int step = 16; step >= 1; step >>= 2) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int c2 = c0 + q < nchunks ? c0 + q : c;
-                        const u64 *at0 = cand + c2 * kWave + pos[q] - 1;
-                        const int above = (at0[step] > mine ? 1 : 0) + (at0[2 * step] > mine ? 1 : 0) +
-                                          (at0[3 * step] > mine ? 1 : 0);
-                        pos[q] += step * above;
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (c0 + q < nchunks && c0 + q != c) rank += full[q] ? 64 : pos[q];
             }
-            if (mine != 0) select(mine, rank);
+            int sum = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (c0 + q < nchunks) sum += full[q] ? 64 : pos[q];
+            return sum;
+        };
+        bool ranked = false;
+        if (nchunks > 4) {
+            // Many candidates (a wide beam with many constraints, up to a thousand early in a decode): only those
+            // that are among their bank's first alloc[bank] in their own chunk can be among them in all, and only those are ranked,
+            // a block of 64 of them against four chunks at a time.  (Every candidate against every chunk, five trips to LDS for
+            // a block and four chunks, took 6 of 17.6 us in the slowest of 128 sentences, k = 64, 32 constraint tokens; all its
+            // steps 145.5 -> 144.0 us in fp16.)  With four chunks or fewer the extra two barriers cost what they save.
+            u64 *left = cand + p.cand_cap;
+            int *ranks = reinterpret_cast<int *>(left + kMostLeft);
+            for (int c = my_first; c < nchunks; c += MW) {
+                const u64 mine = cand[c * kWave + lane];
+                const int bank = mb ? (int)(mine >> sel_shift) : 0;
+                const u64 starts = __ballot(lane == 0 || (int)dpp_mov<kDppWaveShr1>((uint32_t)bank) != bank);
+                const int first = 63 - __clzll((long long)(starts & (~0ull >> (63 - lane))));
+                const bool keep = mine != 0 && lane - first < sm.alloc[bank];
+                const u64 kept = __ballot(keep);
+                int at = 0;
+                if (lane == 0 && kept != 0) at = atomicAdd(&sm.nleft, (int)__popcll(kept));
+                const int to = __builtin_amdgcn_readfirstlane(at) + lanes_before(kept);
+                if (keep && to < kMostLeft) {
+                    left[to] = mine;
+                    ranks[to] = 0;
+                }
+            }
+            __syncthreads();
+            const int n = __builtin_amdgcn_readfirstlane(sm.nleft);
+            if (n <= kMostLeft) {
+                ranked = true;
+                const int blocks = (n + kWave - 1) >> 6;
+                int c0 = 0, block = wave;
+                for (;;) {
+                    while (block >= blocks && c0 < nchunks) {
+                        block -= blocks;
+                        c0 += 4;
+                    }
+                    if (c0 >= nchunks) break;
+                    const int i = block * kWave + lane;
+                    if (i < n) atomicAdd(&ranks[i], greater(left[i], c0));
+                    block += MW;
+                }
+                __syncthreads();
+                for (int i = tid; i < n; i += MW * kWave) select(left[i], ranks[i]);
+            }
+        }
+        if (!ranked) {
+            for (int c = my_first; c < nchunks; c += MW) {
+                const u64 mine = cand[c * kWave + lane];
+                int rank = 0;
+                for (int c0 = 0; c0 < nchunks; c0 += 4) rank += greater(mine, c0);
+                if (mine != 0) select(mine, rank);
+            }
         }
     }
     __syncthreads();

@@ -432,6 +432,20 @@ def test_most_candidates(torch_gpu):
     _harness().run_parity(wl)
 
 
+@pytest.mark.parametrize("k,C,max_len,waves", [(20, 14, 1, 0), (20, 32, 2, 0), (16, 40, 1, 4), (32, 24, 1, 8), (33, 12, 1, 0), (40, 40, 3, 0),
+                                               (64, 3, 1, 0), (64, 16, 1, 0), (64, 32, 2, 8), (64, 40, 1, 4), (64, 30, 1, 0)])
+def test_candidates_beyond_four_chunks(torch_gpu, k, C, max_len, waves):
+    """Around and beyond 256 candidates in a sentence: those that cannot be among their bank's best are left out
+    before the others are ranked; up to 1024 are, and where more remain (k = 64, early steps) all are."""
+    import paper_1804_06609_amd as dba
+    B, V, T = 3, 700, 7
+    cons = si.fixed_total_constraints(71 + k, B, V, C, max_len=max_len)
+    for boost in (0.0, 0.3):
+        wl = si.Workload(B=B, k=k, V=V, T=T, seed=72 + k, constraints=cons, boost_prob=boost, boost_value=5.0,
+                         boost_tokens=[[w for p in s for w in p] for s in cons])
+        _harness().run_parity(wl, options={dba.DBA_OPT_MERGE_WAVES: waves})
+
+
 @pytest.mark.parametrize("k,fmt", [(8, None), (33, None), (13, "bf16")])
 def test_first_tokens_that_share_a_table_bucket(torch_gpu, k, fmt):
     """The device looks a token's phrases up in a table bucketed by the low six bits of the first token.
