@@ -869,8 +869,20 @@ __device__ __forceinline__ int allocate_wave(int k, int C, int c, int c64, int &
     u64 donors = __ballot(a > c);                         // fixed before the hand-outs begin: a receiver never becomes one
     int need = max(0, c - a);
     u64 receivers = __ballot(need > 0);
+    const int last_donor = donors ? 63 - __clzll((long long)donors) : -1;
     while (donors != 0 && receivers != 0) {
         const int b = __ffsll((long long)donors) - 1;
+        const bool all_below = (receivers >> b) == 0, all_above = (receivers & (~0ull >> (63 - last_donor))) == 0;
+        if (all_below || all_above) {
+            // every donor that is left hands to the same banks in the same order, downwards from the highest or upwards
+            // from the lowest: early in a decode, when nearly all banks are empty donors above a few full ones, one prefix
+            // sum instead of up to 32 rounds (4.4 of the merge phase's 17 us with 128 sentences, k = 64)
+            const int spare = wave_inclusive_sum(((donors >> lane) & 1ull) ? a - c : 0);
+            const int incl = wave_inclusive_sum(need);
+            const int served = all_below ? __builtin_amdgcn_readlane(incl, kWave - 1) - incl : incl - need;
+            need -= min(need, max(0, __builtin_amdgcn_readlane(spare, kWave - 1) - served));
+            break;
+        }
         donors &= donors - 1;
         int e = __builtin_amdgcn_readlane(a - c, b);
         if (e > 2 && __popcll(receivers) > 2) {
