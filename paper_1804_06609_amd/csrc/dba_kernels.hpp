@@ -1519,7 +1519,8 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
             for (int c = my_first; c < nchunks; c += MW) {
                 const u64 mine = cand[c * kWave + lane];
                 const int bank = mb ? (int)(mine >> sel_shift) : 0;
-                const u64 starts = __ballot(lane == 0 || (int)dpp_mov<kDppWaveShr1>((uint32_t)bank) != bank);
+                const int below = (int)dpp_mov<kDppWaveShr1>((uint32_t)bank);    // (by every lane: a lane that is switched off reads as 0)
+                const u64 starts = __ballot(lane == 0 || below != bank);
                 const int first = 63 - __clzll((long long)(starts & (~0ull >> (63 - lane))));
                 const bool keep = mine != 0 && lane - first < sm.alloc[bank];
                 const u64 kept = __ballot(keep);

@@ -446,6 +446,15 @@ def test_candidates_beyond_four_chunks(torch_gpu, k, C, max_len, waves):
         _harness().run_parity(wl, options={dba.DBA_OPT_MERGE_WAVES: waves})
 
 
+def test_banks_that_begin_anywhere_in_a_chunk(torch_gpu):
+    """Two sentences of config 5 with some 800 candidates in few banks at the third step: in which chunk of 64 a
+    candidate is sorted depends on which wave came first, and a chunk may hold a single key of a higher bank before the first
+    of a bank that has one slot.  Decoded ten times over."""
+    wl = si.make_config(5, T=3)
+    for _ in range(10):
+        _harness().run_parity(wl, oracle_sentences=[37, 65], check_state_every=3)
+
+
 @pytest.mark.parametrize("k,fmt", [(8, None), (33, None), (13, "bf16")])
 def test_first_tokens_that_share_a_table_bucket(torch_gpu, k, fmt):
     """The device looks a token's phrases up in a table bucketed by the low six bits of the first token.
