@@ -211,7 +211,7 @@ DBA_API int dba_get_state(dba_ctx *ctx, float *score_host, uint64_t *met_mask_ho
  *                               workgroup that handles one sentence in the second launch of a step.
  *                               The results are the same for every setting; only the time differs.
  *                               0 lets the library choose for the shortest step of a single decode
- *                               (four up to k = 16, eight beyond).  Four-wave workgroups need less room
+ *                               (four up to k = 16, eight up to 32, sixteen beyond).  Four-wave workgroups need less room
  *                               at once on a GPU that is busy with other work.
  */
 #define DBA_OPT_ADJUSTMENT 2

@@ -1039,7 +1039,8 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
 #undef STREAM_ANY
 #undef STREAM
         // The merge phase is compiled for (rows per wave, waves, entries per lane).  Unless the caller fixes the
-        // waves: four up to k = 16, eight beyond (fewer lists per wave to merge and to scan, more waves to rank
+        // waves: four up to k = 16, eight up to 32, sixteen beyond (16 sentences of 2000 tokens, k = 64: 18.1 us per step with
+        // eight, 17.4 with sixteen; 4 of 32000 21.45 / 20.95; fewer lists per wave to merge and to scan, more waves to rank
         // candidates, at the price of a deeper tree where the waves' lists are joined; one decode, per step: 22.1 / 22.3 us with
         // four / eight waves at k = 12, 14.7 / 14.7 at k = 16; merge kernel 7.7 / 7.0 us at k = 20, 19.3 / 14.6 at k = 64).
         // Up to k = 11 every wave holds the k * k entries that matter, one or two a lane, and finds the bar by
@@ -1049,17 +1050,18 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         // k = 32 two rows share a register (k = 16: 14.9 against 15.4; k = 20: 32.6 against 33.1, with bf16 22.7 against
         // 23.4; k = 32: 49.1 against 49.6); beyond, a row's list needs all 64 lanes.
         const dim3 mgrid((unsigned)c->B);
-        const dim3 mblock8(8 * kWave), mblock4(4 * kWave);
-        const int mw = c->merge_waves ? c->merge_waves : (c->k <= 16 ? 4 : 8);
+        const int mw = c->merge_waves ? c->merge_waves : (c->k <= 16 ? 4 : c->k <= 32 ? 8 : 16);
         const uint32_t k_inv = (uint32_t)c->k | (uint32_t)(c->k == 1 ? 65535 : 65536 / c->k + 1) << 16;
 #define MERGE(ROWS, MW, J) \
-    dba_merge_kernel<ROWS, MW, J><<<mgrid, MW == 4 ? mblock4 : mblock8, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, k_inv, p)
+    dba_merge_kernel<ROWS, MW, J><<<mgrid, MW * kWave, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, k_inv, p)
         if (mw == 4) {
             if (c->k <= 8) MERGE(2, 4, 1);
             else if (c->k <= 11) MERGE(4, 4, 2);
             else if (c->k <= 16) MERGE(4, 4, -1);
             else if (c->k <= 32) MERGE(8, 4, -1);
             else MERGE(16, 4, 0);
+        } else if (mw == 16) {
+            MERGE(4, 16, 0);
         } else {
             if (c->k <= 8) MERGE(2, 8, 1);
             else if (c->k <= 11) MERGE(2, 8, 2);

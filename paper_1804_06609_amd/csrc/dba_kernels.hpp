@@ -112,7 +112,7 @@ struct __attribute__((aligned(16))) HypState {
 };
 
 constexpr int kMostLeft = 1024;        // candidates there is room for after those that cannot be among their bank's best are gone
-constexpr int kMergeWavesMax = 8;     // most waves a merge-phase workgroup (one sentence) can have: 4 or 8 are used
+constexpr int kMergeWavesMax = 16;    // most waves a merge-phase workgroup (one sentence) can have: 4, 8 or 16 are used
 
 struct MergeSmem {
     uint32_t ws[kMergeWavesMax][kWave];      // every wave's best score images
@@ -1229,8 +1229,18 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         // waves two share a SIMD, and the join is the same work in every wave: the first four (one
         // per SIMD) do it and hand the outcome to the others.
         constexpr int kJoiners = MW < 4 ? MW : 4;
+        if constexpr (MW > 8) {
+            // in two rounds: four lists in each of four waves, then the four results
+            if (wave < kJoiners) {
+                accs = merge32_desc(merge32_desc(sm.ws[4 * wave][lane], sm.ws[4 * wave + 1][lane], fell),
+                                    merge32_desc(sm.ws[4 * wave + 2][lane], sm.ws[4 * wave + 3][lane], fell), fell);
+                sm.wf[wave][lane] = fell;
+                sm.ws2[wave][lane] = accs;
+            }
+            __syncthreads();
+        }
         if (wave < kJoiners) {
-            accs = join_best64<MW>(sm.ws, wave, lane, fell);
+            accs = MW > 8 ? join_best64<4>(sm.ws2, wave, lane, fell) : join_best64<MW>(sm.ws, wave, lane, fell);
             tau_s = (uint32_t)__builtin_amdgcn_readlane((int)accs, k - 1);
             if (tau_s != 0) {
                 settled = (int)__popcll(__ballot(accs >= tau_s)) == k;  // places k.. hold lower scores
@@ -1449,7 +1459,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     // searches in the other chunks; at twice as many candidates it is longer (64 sentences, k = 32, 100 to 200
     // candidates: merge kernel 7.7 us with this limit, 8.3 with twice it, 7.6 sorted throughout; k = 20, about 80 of
     // them in most steps: 6.6 against 7.2 us sorted throughout).
-    constexpr int kCountLimit = MW == 8 ? 112 : 96;
+    constexpr int kCountLimit = MW >= 8 ? 112 : 96;
     if (ncand <= kCountLimit) {
         // Few candidates (the usual case): the rank is the number of greater keys, counted over all of them.  A wave
         // takes 16 or 32 candidates, four or two lanes each, the lanes of a candidate each count a share.
