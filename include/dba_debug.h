@@ -47,6 +47,14 @@ DBA_API int dba_debug_wave_select(int n_cases, const uint64_t *keys_host, const 
 DBA_API int dba_debug_stream_plan(int B, int k, int V, int logp_format, int32_t *plan_host);
 
 /*
+ * Diagnostic: on != 0: steps of this ctx that take one launch number the sentences' workgroups before the
+ * rows' and let them wait for no row to start, so that rows take the sentences on themselves, which otherwise
+ * happens on a busy GPU only.  The results are the same.  Returns 1 if steps of this ctx take one launch,
+ * else 0.
+ */
+DBA_API int dba_debug_sentences_first(dba_ctx *ctx, int on);
+
+/*
  * Diagnostic: the reference read.  out_max_dev[r] = largest of the V floats of row r of
  * src_dev [rows, V] (device, 16-byte aligned, V a multiple of 4), one workgroup per row,
  * with the loads and the tile order of the step's streaming phase and no other work.  The

@@ -44,6 +44,7 @@ _SIGNATURES = {
     "dba_debug_allocate": (_I, [_I, _I] + [_P] * 5 + [ctypes.c_size_t, _P]),
     "dba_debug_wave_select": (_I, [_I] + [_P] * 5 + [ctypes.c_size_t, _P]),
     "dba_debug_stream_plan": (_I, [_I] * 4 + [_P]),
+    "dba_debug_sentences_first": (_I, [_P, _I]),
     "dba_debug_row_max": (_I, [_P, _I, _I, _P, _P]),
 }
 
@@ -184,3 +185,10 @@ def dba_debug_stream_plan(B: int, k: int, V: int, logp_format: int = DBA_LOGP_F3
     plan = np.zeros(4, np.int32)
     _check(load().dba_debug_stream_plan(B, k, V, logp_format, _host(plan, np.int32)))
     return tuple(int(x) for x in plan)
+
+
+def dba_debug_sentences_first(ctx, on: bool) -> bool:
+    """True if steps of this ctx take one launch."""
+    rc = load().dba_debug_sentences_first(ctx, int(on))
+    _check(min(rc, DBA_OK), ctx)
+    return rc == 1

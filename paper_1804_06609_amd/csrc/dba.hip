@@ -25,7 +25,7 @@ using namespace dba;
 // logp, V, k, first_step are what the first loads need; the kernels take them as leading scalar
 // arguments, which the hardware hands over in registers at wave start (kernel-argument preload),
 // so that the first two tiles are requested before any argument has been read from memory.
-template <int U, int FMT, int NW, int D>
+template <int U, int FMT, int NW, int D, bool ONE>
 __device__ __forceinline__ void stream_phase(const StepParams &p, const void *logp, int V, int k, int first_step,
                                              int b, int h, StreamSmem<NW> &sm)
 {
@@ -100,7 +100,11 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
         st.list = make_key(prev + 0.0f, code_base | (uint32_t)p.pad_id);
     }
     if (gatherer) {
-        p.conskeys[(size_t)row * kMaxCons + lane] = ckey;
+        if constexpr (ONE) {
+            if (lane < g_P) hand_over(p.conskeys + (size_t)row * kMaxCons + lane, ckey ? ckey : kNoKey);
+        } else {
+            p.conskeys[(size_t)row * kMaxCons + lane] = ckey;
+        }
     }
     const u64 acc = finish_row(sm, st.list, parked, wave, fin_wave);
     if (finisher) {
@@ -126,7 +130,12 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
         const int bank = !extends ? nmet
                                   : nmet_after(nmet, g_ipq < 0 ? -1 : (g_ipq >> 8), g_ipq < 0 ? 0 : (g_ipq & 255),
                                                w == g_nxt, match, g_inc);
-        p.rowlists[(size_t)row * kWave + lane] = sel_from_rowkey(p.met_bits, bank, acc);
+        const u64 key = sel_from_rowkey(p.met_bits, bank, acc);
+        if constexpr (ONE) {
+            if (lane < k) hand_over(p.rowlists + (size_t)row * kWave + lane, key ? key : kNoKey);
+        } else {
+            p.rowlists[(size_t)row * kWave + lane] = key;
+        }
     }
 }
 
@@ -149,7 +158,75 @@ __global__ __launch_bounds__(NW * kWave) void dba_stream_kernel(const void *logp
     const uint32_t m = abreast ? n >> 3 : n;
     const uint32_t q = k == 1 ? m : __umulhi(m, inv_k);
     const int b = (int)(abreast ? q * 8u + (n & 7u) : q), h = (int)(m - q * k);
-    stream_phase<U, FMT, NW, D>(p, logp, V, (int)k, k_first >> 16, b, h, sm);
+    stream_phase<U, FMT, NW, D, false>(p, logp, V, (int)k, k_first >> 16, b, h, sm);
+}
+
+// Both phases in one launch, for steps of few rows.  Grid: B * k workgroups for the rows, then B that each take a
+// sentence through the merge phase.  Such a step is a chain of latencies, and the end of one kernel, the start of the
+// next and its wait for the row lists were 2.2 us of it; here a sentence's workgroup has its tables in LDS before the
+// rows are through and reads their places in the row lists again and again until all are filled (a store is seen
+// there after 0.7 to 1.2 us).  Per step, two launches / one: 5 rows of 1000 9.2 / 8.4 us, 160 of 32000 13.05 / 12.75, 168 of 50001
+// 14.2 / 13.45, 240 of 9000 10.95 / 9.95, 192 with k = 16 13.85 / 12.85, one sentence of ten rows 11.15 / 11.05.
+//
+// Every wait ends.  A row waits for nothing.  A sentence's workgroup looks for the lists only once all rows of the sentence have
+// started, from where they run to their end by themselves.  If they do not start soon - other work may hold the chip - it
+// says so and leaves, in the same atomic step in which it sees their number once more; the row that then starts last finds
+// that said and takes the sentence on itself when it is through.  (The one that ends first or last could be elected instead,
+// without a workgroup for it; its tables and its code then come cold: as slow as two launches.)
+// rows_order: B * k, and from bit 31 whether the sentences' workgroups are numbered first (for tests of the other way).
+template <int U, int FMT, int NW, int D, int ROWS, int MW, int J>
+__global__ __launch_bounds__(NW * kWave) void dba_step_kernel(const void *logp, int V, int k_first, uint32_t rows_abreast,
+                                                             uint32_t inv_k, uint32_t rows_order, uint32_t inv_k16, const StepParams p)
+{
+    extern __shared__ __align__(16) unsigned char dyn_smem[];
+    __shared__ int role;
+    StreamSmem<NW> &ss = *reinterpret_cast<StreamSmem<NW> *>(dyn_smem);
+    MergeSmem &ms = *reinterpret_cast<MergeSmem *>(dyn_smem);
+    u64 *cand = reinterpret_cast<u64 *>(dyn_smem + (sizeof(MergeSmem) + 15) / 16 * 16);
+    const uint32_t k = (uint32_t)k_first & 0xFFFFu, rows = rows_order & 0x7FFFFFFFu;
+    const uint32_t n = blockIdx.x - (rows_order >> 31 ? (k == 1 ? rows : __umulhi(rows, inv_k)) : 0u);     // (wraps below the first row)
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), tid = (int)threadIdx.x;
+    int b;
+    if (n < rows) {
+        const bool abreast = n < rows_abreast;
+        const uint32_t m = abreast ? n >> 3 : n;
+        const uint32_t q = k == 1 ? m : __umulhi(m, inv_k);
+        b = (int)(abreast ? q * 8u + (n & 7u) : q);
+        const int h = (int)(m - q * k);
+        int before = 0;
+        if (wave == 1 && lane_id() == 0)
+            before = __hip_atomic_fetch_add(&p.best[b].started, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        stream_phase<U, FMT, NW, D, true>(p, logp, V, (int)k, k_first >> 16, b, h, ss);
+        // the last row to start takes the sentence on if its workgroup has given up waiting for the rows to start
+        if (wave == 1 && lane_id() == 0) role = before == (kDeclined | (int)(k - 1));
+        __syncthreads();
+        if (!role) return;
+        __syncthreads();                                   // (everyone has left the row's LDS)
+    } else {
+        b = (int)((rows_order >> 31) ? blockIdx.x : n - rows);
+    }
+    MergeTables tables;
+    int P = 0;
+    if (wave < MW) {
+        P = tables.request(p, b, (int)k, tid);
+        clear_for_merge(p, tid, MW * kWave, ms, cand);
+        tables.store((int)k, tid, ms);
+    }
+    if (wave == 0 && lane_id() == 0) {
+        int ready = 1;
+        if (n >= rows) {
+            ready = 0;
+            for (int i = (rows_order >> 31) ? kMostWaits : 0; i < kMostWaits && !ready; ++i)
+                ready = __hip_atomic_load(&p.best[b].started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)k;
+            if (!ready)
+                ready = __hip_atomic_fetch_or(&p.best[b].started, kDeclined, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)k;
+        }
+        if (ready) __hip_atomic_store(&p.best[b].started, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        role = ready;
+    }
+    __syncthreads();
+    if (!role || wave >= MW) return;
+    merge_phase<ROWS, MW, J, true>(p, p.rowlists, p.conskeys, (int)k, inv_k16, b, ms, cand, P);
 }
 
 // Second launch of a step: the merge phase.  Grid: one workgroup of MW waves per sentence, each wave
@@ -162,8 +239,8 @@ __global__ __launch_bounds__(MW * kWave) void dba_merge_kernel(const u64 *rowlis
 {
     extern __shared__ __align__(16) unsigned char dyn_smem[];
     __shared__ MergeSmem sm;
-    merge_phase<ROWS, MW, J>(p, rowlists, conskeys, (int)(k_inv & 0xFFFFu), k_inv >> 16, (int)blockIdx.x, sm,
-                             reinterpret_cast<u64 *>(dyn_smem));
+    merge_phase<ROWS, MW, J, false>(p, rowlists, conskeys, (int)(k_inv & 0xFFFFu), k_inv >> 16, (int)blockIdx.x, sm,
+                                    reinterpret_cast<u64 *>(dyn_smem), 0);
 }
 
 // Reference read: the largest element of each row, one workgroup per row, with the tile order and
@@ -290,6 +367,11 @@ __global__ __launch_bounds__(kWave) void dba_init_kernel(int B, int k, const uin
         BestCompleted none = {};
         p.best[b] = none;
     }
+    if (p.rowlists)                                        // steps of one launch: all places empty
+        for (int h = 0; h < k; ++h) {
+            p.rowlists[((size_t)b * k + h) * kWave + lane] = 0;
+            p.conskeys[((size_t)b * k + h) * kWave + lane] = 0;
+        }
     if (lane < k) {
         const size_t i = (size_t)b * k + lane;
         p.score_nxt[i] = lane == 0 ? 0.0f : -INFINITY;
@@ -554,6 +636,10 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem)
     return plan;
 }
 
+// Where a step is one launch: every row has a compute unit to itself and its latencies show.  (Wider beams have more to merge
+// than a row's workgroup has waves for.)
+bool one_launch_shape(size_t B, size_t k) { return B * k <= kComputeUnits && k <= 32; }
+
 int bits_for(int v)   // bits needed to hold values 0..v
 {
     int n = 0;
@@ -732,6 +818,8 @@ struct dba_ctx {
     Layout L;
     HostBlock block;                    // seen words [B], stopping flags [B], then constraint words / results (p null: none)
     size_t block_flags, block_data;     // offsets in it
+    bool one_launch;                    // the row lists are empty between steps, which may then be one launch each
+    bool sentences_first;               // dba_debug_sentences_first
     int unread;                         // B while the GPU may still have to read the block's constraint words, 0 afterwards
     hipStream_t stream;
     char err[256];
@@ -925,6 +1013,11 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
         StepParams p = {};
         set_tables(c, p);
         set_beam_after(c, p, 0);
+        c->one_launch = seen != nullptr && one_launch_shape((size_t)B, (size_t)k);
+        if (c->one_launch) {
+            p.rowlists = at<u64>(c, L.rowlists);
+            p.conskeys = at<u64>(c, L.conskeys);
+        }
         dba_init_kernel<<<(unsigned)B, kWave, 0, c->stream>>>(B, k, words, seen, p);
         e = hipGetLastError();
         if (e == hipSuccess && seen) held.unread = B;
@@ -1018,7 +1111,36 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     const dim3 grid((unsigned)c->B * (unsigned)c->k);
     const uint32_t inv_k = (uint32_t)(((1ull << 32) + (unsigned)c->k - 1) / (unsigned)c->k);
     const int kf = p.k | (p.first_step << 16);
-    {
+    const uint32_t inv_k16 = (uint32_t)(c->k == 1 ? 65535 : 65536 / c->k + 1);
+    if (c->one_launch && c->merge_waves == 0) {
+        // (the places are empty between steps, which only the ctx's own are)
+        p.rowlists = at<u64>(c, L.rowlists);
+        p.conskeys = at<u64>(c, L.conskeys);
+        const dim3 sblock((unsigned)(plan.waves * kWave)), sgrid((unsigned)c->B * (unsigned)(c->k + 1));
+        const size_t lds = std::max((plan.waves == 8 ? sizeof(StreamSmem<8>) : sizeof(StreamSmem<4>)), align_up(sizeof(MergeSmem), 16) + c->dyn_smem);
+#define ONE(FMT, NW, D, ROWS, MW, J)                                                                      \
+    dba_step_kernel<kTileLoads, FMT, NW, D, ROWS, MW, J><<<sgrid, sblock, lds, c->stream>>>(p.logp, p.V, kf, plan.rows_abreast, \
+                                                                                       inv_k, (unsigned)c->B * (unsigned)c->k | (c->sentences_first ? 0x80000000u : 0u), inv_k16, p)
+#define ONE_ANY(NW, D, ROWS, MW, J)                                       \
+    switch (logp_format) {                                      \
+        case DBA_LOGP_F16: ONE(kFmtF16, NW, D, ROWS, MW, J); break;       \
+        case DBA_LOGP_BF16: ONE(kFmtBF16, NW, D, ROWS, MW, J); break;     \
+        default: ONE(kFmtF32, NW, D, ROWS, MW, J); break;                 \
+    }
+        if (plan.waves == 8) {
+            if (c->k <= 8) ONE_ANY(8, 4, 2, 4, 1)
+            else if (c->k <= 11) ONE_ANY(8, 4, 4, 4, 2)
+            else if (c->k <= 16) ONE_ANY(8, 4, 4, 4, -1)
+            else ONE_ANY(8, 4, 4, 8, -1)
+        } else {
+            if (c->k <= 8) ONE_ANY(4, 2, 2, 4, 1)
+            else if (c->k <= 11) ONE_ANY(4, 2, 4, 4, 2)
+            else if (c->k <= 16) ONE_ANY(4, 2, 4, 4, -1)
+            else ONE_ANY(4, 2, 8, 4, -1)
+        }
+#undef ONE_ANY
+#undef ONE
+    } else {
         const dim3 sblock((unsigned)(plan.waves * kWave));
 #define STREAM(FMT, NW, D)                                                                                              \
     dba_stream_kernel<kTileLoads, FMT, NW, D><<<grid, sblock, plan.spare_lds, c->stream>>>(p.logp, p.V, kf, plan.rows_abreast, \
@@ -1051,7 +1173,7 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         // 23.4; k = 32: 49.1 against 49.6); beyond, a row's list needs all 64 lanes.
         const dim3 mgrid((unsigned)c->B);
         const int mw = c->merge_waves ? c->merge_waves : (c->k <= 16 ? 4 : c->k <= 32 ? 8 : 16);
-        const uint32_t k_inv = (uint32_t)c->k | (uint32_t)(c->k == 1 ? 65535 : 65536 / c->k + 1) << 16;
+        const uint32_t k_inv = (uint32_t)c->k | inv_k16 << 16;
 #define MERGE(ROWS, MW, J) \
     dba_merge_kernel<ROWS, MW, J><<<mgrid, MW * kWave, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, k_inv, p)
         if (mw == 4) {
@@ -1299,6 +1421,13 @@ DBA_API int dba_debug_wave_select(int n_cases, const uint64_t *keys_host, const 
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail(nullptr, DBA_EHIP, "dba_debug_wave_select: HIP error: %s", hipGetErrorString(e));
     return DBA_OK;
+}
+
+DBA_API int dba_debug_sentences_first(dba_ctx *c, int on)
+{
+    if (!c) return DBA_EINVAL;
+    c->sentences_first = on != 0;
+    return c->one_launch && c->merge_waves == 0 ? 1 : 0;
 }
 
 DBA_API int dba_debug_stream_plan(int B, int k, int V, int logp_format, int32_t *plan_host)

@@ -92,7 +92,8 @@ struct __attribute__((aligned(32))) BestCompleted {
     int len;           // its length, end-of-sentence included
     float q;           // its score per word
     float score;       // its score as that beam held it
-    int pad[2];
+    int started;       // workgroups of the step under way that have started (steps of one launch; 0 between steps)
+    int pad;
 };
 
 // constraints of one sentence: token ids phrase after phrase, phrase p = tok[poff[p] .. poff[p+1])
@@ -1038,6 +1039,84 @@ __device__ __forceinline__ uint32_t best32_of(uint32_t (&o)[N], uint32_t &fell)
     return join32_halves(o[0], fell);
 }
 
+// ---- hand-over inside one launch --------------------------------------------------------
+// A place of the row lists and constraint keys is 0 while it is empty, kNoKey if there is no key for it.
+constexpr u64 kNoKey = 1;             // (no key is 1: the score image of a finite sum is not 0)
+constexpr int kMostTries = 1 << 16;   // an end to every wait, whatever happens; one try is a trip to memory
+constexpr int kMostWaits = 48;
+constexpr int kDeclined = 1 << 16;    // in BestCompleted::started
+
+__device__ __forceinline__ void hand_over(u64 *to, u64 key)
+{
+    __hip_atomic_store(to, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ u64 handed_over(const u64 *from)
+{
+    return __hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The sentence's tables and beam on their way from memory to LDS, one entry a thread: every load
+// is issued before the first one is waited for (clamped indices instead of branches).
+struct MergeTables {
+    int poff, tok, btok, ipq, nxt, len, fin;
+    u64 bucket, met, inc;
+    __device__ __forceinline__ int request(const StepParams &p, int b, int k, int tid)
+    {
+        const int lane = lane_id(), t64 = tid < kMaxCons ? tid : kMaxCons;
+        const size_t rs = (size_t)b * k + (tid < k ? tid : k - 1);
+        poff = p.phr_off[(size_t)b * (kMaxCons + 1) + t64];
+        tok = p.cons_tok[(size_t)b * kMaxCons + lane];
+        const int P = p.nphr[b];
+        bucket = p.first_bucket[(size_t)b * kMaxCons + lane];
+        btok = p.bucket_tok[(size_t)b * kMaxCons + lane];
+        met = p.met_cur[rs];
+        inc = p.inc_cur[rs];
+        ipq = p.ipq_cur[rs];
+        nxt = p.nxt_cur[rs];
+        len = p.len_cur[rs];
+        fin = p.fin_cur[rs];
+        return P;
+    }
+    __device__ __forceinline__ void store(int k, int tid, MergeSmem &sm) const
+    {
+        if (tid <= kMaxCons) sm.ct.poff[tid] = poff;
+        if (tid < kMaxCons) {
+            sm.ct.tok[tid] = tok;
+            sm.fbucket[tid] = bucket;
+            sm.btok[tid] = btok;
+        }
+        if (tid < k) {
+            HypState hs;
+            hs.met = met;
+            hs.inc = inc;
+            hs.ipq = ipq;
+            hs.nxt = nxt;
+            hs.len = len;
+            hs.misc = (fin & kFinFinished) | (__popcll(met) << 8);
+            sm.hyp[tid] = hs;
+        }
+    }
+};
+
+// the counters and the candidate buffer, by the first `threads` threads
+__device__ __forceinline__ void clear_for_merge(const StepParams &p, int tid, int threads, MergeSmem &sm, u64 *cand)
+{
+    if (tid < 2 * kMaxCons) {
+        sm.cnt[tid] = 0;
+        sm.alloc[tid] = 0;                             // banks beyond the sentence's get no slot
+        sm.start[tid] = 0;
+        sm.first[tid] = 0;
+    }
+    if (tid < kMaxCons) sm.sel[tid] = 0;               // places beyond the last selected key compare as empty
+    if (tid == 0) {
+        sm.ncand = 0;
+        sm.nsel = 0;
+        sm.nleft = 0;
+        sm.kept = 0;
+    }
+    for (int i = tid; i < p.cand_cap; i += threads) cand[i] = 0;
+}
+
 // MW: waves of the sentence's workgroup; ROWS: beam rows per wave the code is laid out for
 // (k <= MW * ROWS; wave w takes rows w, w + MW, ...): the loops over a wave's rows are unrolled, so a
 // smaller bound keeps the code of small beams short.
@@ -1047,9 +1126,9 @@ __device__ __forceinline__ uint32_t best32_of(uint32_t (&o)[N], uint32_t &fell)
 // halves the merges, the registers looked through for candidates and the LDS they pass through.
 // rowlists, conskeys, k, inv_k: what the first loads need (p.rowlists, p.conskeys, p.k; floor(2^16 / k) + 1,
 // with which i * inv_k >> 16 is i / k for i < k * k, k <= 32).
-template <int ROWS, int MW, int J>
+template <int ROWS, int MW, int J, bool ONE>
 __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowlists, const u64 *conskeys, int k,
-                                            uint32_t inv_k, int b, MergeSmem &sm, u64 *cand)
+                                            uint32_t inv_k, int b, MergeSmem &sm, u64 *cand, int P_here)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // in a scalar register: row guards are scalar branches
@@ -1062,6 +1141,60 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     u64 rl[kLists], ck[kRowsPerWave];
     u64 hd[kPacked ? kRowsPerWave : 1];                    // packed: the heads of the lists of the wave's rows
     uint32_t head_bits = 0;                                // packed: bit j = this lane's entry j is a row's best
+    if constexpr (ONE) {
+        // handed over by workgroups that run now: read again until every place this wave looks at is filled (ONE's tables
+        // and counters are in LDS already)
+        for (int tries = 0; tries < kMostTries; ++tries) {
+            bool there = true;
+            if constexpr (kPacked) {
+                head_bits = 0;
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const uint32_t i = (uint32_t)(j * kWave + lane);
+                    rl[j] = kNoKey;
+                    if (i < (uint32_t)(k * k)) {
+                        const uint32_t h = (i * inv_k) >> 16, at = i - h * (uint32_t)k;
+                        head_bits |= (at == 0 ? 1u : 0u) << j;
+                        rl[j] = handed_over(rowlists + ((size_t)b * k + h) * kWave + at);
+                    }
+                }
+            } else {
+                static_assert(kPacked || kHalves, "lists of up to 32 keys");
+#pragma unroll
+                for (int i = 0; i < kLists; ++i) {
+                    const int h = wave + (2 * i + (lane >> 5)) * MW;
+                    rl[i] = kNoKey;
+                    if (h < k && (lane & 31) < k) rl[i] = handed_over(rowlists + ((size_t)b * k + h) * kWave + (lane & 31));
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < kRowsPerWave; ++i) {
+                const int h = wave + i * MW;
+                ck[i] = kNoKey;
+                if (kPacked) hd[kPacked ? i : 0] = kNoKey;
+                if (h < k) {
+                    const size_t o = ((size_t)b * k + h) * kWave;
+                    if (lane < P_here) ck[i] = handed_over(conskeys + o + lane);
+                    if (kPacked) hd[kPacked ? i : 0] = handed_over(rowlists + o);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < kLists; ++i) there &= rl[i] != 0;
+#pragma unroll
+            for (int i = 0; i < kRowsPerWave; ++i) {
+                there &= ck[i] != 0;
+                if (kPacked) there &= hd[kPacked ? i : 0] != 0;
+            }
+            if (__ballot(!there) == 0) break;
+        }
+#pragma unroll
+        for (int i = 0; i < kLists; ++i) rl[i] = rl[i] == kNoKey ? 0 : rl[i];
+#pragma unroll
+        for (int i = 0; i < kRowsPerWave; ++i) {
+            ck[i] = ck[i] == kNoKey ? 0 : ck[i];
+            if (kPacked) hd[kPacked ? i : 0] = hd[kPacked ? i : 0] == kNoKey ? 0 : hd[kPacked ? i : 0];
+        }
+    } else {
     if constexpr (kPacked) {
 #pragma unroll
         for (int j = 0; j < J; ++j) {
@@ -1103,6 +1236,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
             if (kPacked) hd[kPacked ? i : 0] = rowlists[o];
         }
     }
+    }
     __builtin_amdgcn_sched_barrier(0);
     const int mb = p.met_bits;
     const int sel_shift = 64 - mb;
@@ -1111,45 +1245,20 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     const uint32_t flatmask = fb >= 32 ? 0xFFFFFFFFu : ((1u << fb) - 1u);
     const uint32_t tokmask = (1u << p.tok_bits) - 1u;
 
-    // ---- everything this sentence needs from memory, requested at once: every load is issued
-    // before the first one is waited for (clamped indices instead of branches) --------------
-    const int t64 = tid < kMaxCons ? tid : kMaxCons;
-    const int hs = tid < k ? tid : k - 1;
-    const size_t rs = (size_t)b * k + hs;
-    const int ld_poff = p.phr_off[(size_t)b * (kMaxCons + 1) + t64];
-    const int ld_tok = p.cons_tok[(size_t)b * kMaxCons + lane];
-    const int P = p.nphr[b];
-    const u64 ld_bucket = p.first_bucket[(size_t)b * kMaxCons + lane];
-    const int ld_btok = p.bucket_tok[(size_t)b * kMaxCons + lane];
-    const u64 ld_met = p.met_cur[rs];
-    const u64 ld_inc = p.inc_cur[rs];
-    const int ld_ipq = p.ipq_cur[rs];
-    const int ld_nxt = p.nxt_cur[rs];
-    const int ld_len = p.len_cur[rs];
-    const int ld_fin = p.fin_cur[rs];
-    // while the loads above are on their way, the counters and the candidate buffer are cleared
-    if (tid < 2 * kMaxCons) {
-        sm.cnt[tid] = 0;
-        sm.alloc[tid] = 0;                             // banks beyond the sentence's get no slot
-        sm.start[tid] = 0;
-        sm.first[tid] = 0;
-    }
-    if (tid < kMaxCons) sm.sel[tid] = 0;               // places beyond the last selected key compare as empty
-    if (tid == 0) {
-        sm.ncand = 0;
-        sm.nsel = 0;
-        sm.nleft = 0;
-        sm.kept = 0;
-    }
-    for (int i = tid; i < p.cand_cap; i += MW * kWave) cand[i] = 0;
-    if (kPacked) __syncthreads();
-    // the lists are pinned here, or their loads would be moved down to the conditional code that uses them
+    MergeTables tables;
+    int P = P_here;
+    if constexpr (!ONE) {
+        P = tables.request(p, b, k, tid);
+        clear_for_merge(p, tid, MW * kWave, sm, cand);
+        if (kPacked) __syncthreads();
+        // the lists are pinned here, or their loads would be moved down to the conditional code that uses them
 #pragma unroll
-    for (int i = 0; i < kLists; ++i) asm volatile("" : "+v"(rl[i]));
+        for (int i = 0; i < kLists; ++i) asm volatile("" : "+v"(rl[i]));
 #pragma unroll
-    for (int i = 0; i < kRowsPerWave; ++i) {
-        asm volatile("" : "+v"(ck[i]));
-        if (kPacked) asm volatile("" : "+v"(hd[kPacked ? i : 0]));
+        for (int i = 0; i < kRowsPerWave; ++i) {
+            asm volatile("" : "+v"(ck[i]));
+            if (kPacked) asm volatile("" : "+v"(hd[kPacked ? i : 0]));
+        }
     }
     // ---- source 1: the sentence's k best (Sec. 3.1 item 1) = top k of the union of the row
     // lists.  All that is needed of them is the bar tau a key has to reach to be among them.
@@ -1180,22 +1289,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     }
     // the sentence's tables and beam go to LDS only now: their loads were issued after those of the
     // row lists and arrive later, and the merges above needed none of them
-    if (tid <= kMaxCons) sm.ct.poff[tid] = ld_poff;
-    if (tid < kMaxCons) {
-        sm.ct.tok[tid] = ld_tok;
-        sm.fbucket[tid] = ld_bucket;
-        sm.btok[tid] = ld_btok;
-    }
-    if (tid < k) {
-        HypState hs;
-        hs.met = ld_met;
-        hs.inc = ld_inc;
-        hs.ipq = ld_ipq;
-        hs.nxt = ld_nxt;
-        hs.len = ld_len;
-        hs.misc = (ld_fin & kFinFinished) | (__popcll(ld_met) << 8);
-        sm.hyp[tid] = hs;
-    }
+    if constexpr (!ONE) tables.store(k, tid, sm);
     // the waves' lists of 32, two to a register
     auto joined32 = [&](uint32_t *buf, uint32_t mine) {
         if (lane < 32) buf[wave * 32 + lane] = mine;
@@ -1356,6 +1450,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
                 const u64 body = ck[i] & body_mask;
                 // (places from k on cannot be among the k best)
                 const u64 listed = lane >= k ? 0ull
+                                   : ONE ? handed_over(rowlists + ((size_t)b * k + h) * kWave + lane)
                                    : (kPacked || kHalves) ? rowlists[((size_t)b * k + h) * kWave + lane] : rl[kPacked ? 0 : i];
                 u64 tied = __ballot(((cm >> i) & 1u) != 0 && body >= tau);
                 while (tied) {
@@ -1572,6 +1667,17 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         }
     }
     __syncthreads();
+
+    if constexpr (ONE) {
+        // the next step finds the places empty
+        if (wave >= 2) {
+            for (int h = wave - 2; h < k; h += MW - 2) {
+                const size_t o = ((size_t)b * k + h) * kWave + lane;
+                if (lane < k) hand_over(p.rowlists + o, 0);
+                if (lane < P) hand_over(p.conskeys + o, 0);
+            }
+        }
+    }
 
     // ---- new beam, best first (Sec. 3.1); empty slots last ---------------------------------
     // One lane per selected candidate.  Its place in the new beam is the number of selected keys greater

@@ -279,3 +279,78 @@ def test_batches_with_and_without_a_block_of_host_memory(B, N):
     wl.T = N
     wl.eos_switch = 2
     harness.run_parity(wl, T=5, oracle_sentences=[0, 1, 63, 64, B // 2, B - 1])
+
+
+def _one_launch_decode(wl, dev, stream, first, waves=0):
+    import paper_1804_06609_amd as dba
+    from paper_1804_06609_amd.session import Session
+    ses = Session(wl.B, wl.k, wl.V, wl.T, wl.eos_id, wl.pad_id, *wl.csr(), stream=stream,
+                  options={dba.DBA_OPT_MERGE_WAVES: waves})
+    return ses, dba.dba_debug_sentences_first(ses.ctx, first)
+
+
+@pytest.mark.parametrize("B,k,V,fmt,one", [
+    (256, 1, 300, None, True), (257, 1, 300, None, False), (85, 3, 1200, "f16", True), (32, 8, 1000, None, True), (28, 9, 4100, "bf16", True),
+    (23, 11, 8200, None, True), (21, 12, 2000, None, True), (16, 16, 16500, "f16", True), (15, 17, 700, None, True), (8, 32, 8300, None, True),
+    (7, 33, 600, None, False), (3, 20, 33001, None, True), (1, 5, 1000, None, True), (2, 32, 40000, "bf16", True)])
+def test_steps_of_one_launch(B, k, V, fmt, one):
+    """Small steps take one launch, whose sentences wait for their rows; or, if the rows are slow to start (forced here by
+    numbering the sentences first), a row takes the sentence on.  Both against the two launches, every step; the
+    formats and the step with its own scratch mixed."""
+    import torch
+    wl = si.make_small(9100 + V, B, k, V, 6, max_phrases=4, max_len=3, dup_prob=0.3)
+    wl.eos_switch = 3
+    tdt = {None: torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[fmt]
+    dev = [torch.from_numpy(wl.logp(t)).cuda().to(tdt) for t in range(wl.T)]
+    stream = torch.cuda.current_stream()
+    two, is_one = _one_launch_decode(wl, dev, stream, False, waves=8)
+    assert not is_one
+    others = [_one_launch_decode(wl, dev, stream, first) for first in (False, True)]
+    assert all(o[1] == one for o in others)
+    for t in range(wl.T):
+        two.step(dev[t])
+        want = [a.tobytes() for a in two.outputs()] + [a.tobytes() for a in two.state().values()]
+        for i, (ses, _) in enumerate(others):
+            ses.step(dev[t], noalloc=(t + i) % 3 == 2)
+            got = [a.tobytes() for a in ses.outputs()] + [a.tobytes() for a in ses.state().values()]
+            assert got == want, (t, i)
+    want = [np.asarray(a).tobytes() for a in two.finalize()]
+    for ses, _ in others:
+        assert [np.asarray(a).tobytes() for a in ses.finalize()] == want
+        ses.close()
+    two.close()
+
+
+def test_steps_of_one_launch_side_by_side():
+    """Six decodes on six streams, interleaved, two of them with the sentences first, beside a seventh that keeps
+    the GPU busy with many rows: the results of each alone."""
+    import torch
+    from paper_1804_06609_amd.session import Session
+    jobs = []
+    for i, (B, k, V) in enumerate([(16, 10, 8200), (50, 5, 900), (1, 20, 33000), (8, 32, 3000), (85, 3, 500), (24, 7, 9001)]):
+        wl = si.make_small(9200 + i, B, k, V, 8, max_phrases=4, max_len=3, dup_prob=0.3)
+        wl.eos_switch = 5
+        jobs.append((wl, [torch.from_numpy(wl.logp(t)).cuda() for t in range(wl.T)]))
+    big = si.make_small(9300, 200, 20, 2000, 40, max_phrases=4, max_len=3)
+    big_lp = torch.from_numpy(big.logp(0)).cuda()
+    alone = []
+    for wl, dev in jobs:
+        ses, _ = _one_launch_decode(wl, dev, torch.cuda.current_stream(), False)
+        for t in range(wl.T):
+            ses.step(dev[t])
+        alone.append([a.tobytes() for a in ses.outputs()] + [np.asarray(a).tobytes() for a in ses.finalize()])
+        ses.close()
+    torch.cuda.synchronize()
+    for rep in range(4):
+        streams = [torch.cuda.Stream() for _ in range(7)]
+        busy = Session(big.B, big.k, big.V, big.T, big.eos_id, big.pad_id, *big.csr(), stream=streams[6])
+        running = [_one_launch_decode(wl, dev, s, i % 3 == 2)[0] for i, ((wl, dev), s) in enumerate(zip(jobs, streams))]
+        for t in range(8):
+            for _ in range(5):
+                busy.step(big_lp)
+            for ses, (wl, dev) in zip(running, jobs):
+                ses.step(dev[t])
+        for ses, want in zip(running, alone):
+            assert [a.tobytes() for a in ses.outputs()] + [np.asarray(a).tobytes() for a in ses.finalize()] == want, rep
+            ses.close()
+        busy.close()
