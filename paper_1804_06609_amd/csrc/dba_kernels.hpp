@@ -1,6 +1,6 @@
 // Device side of the DBA step (Post & Vilar 2018, Alg. 2, Sec. 3.1-3.3) for gfx950.
 //
-// Two phases per step:
+// Two phases per step, one launch each, or both in one where rows are few:
 //   stream phase  one workgroup per beam row (b,h): a single pass over the V
 //                 log-probs of that row - score add, end-of-sentence mask,
 //                 exact top-k of the row (which holds the row's best token
