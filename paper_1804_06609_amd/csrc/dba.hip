@@ -636,9 +636,11 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem)
     return plan;
 }
 
-// Where a step is one launch: every row has a compute unit to itself and its latencies show.  (Wider beams have more to merge
+// Where a step is one launch: a compute unit has one or two rows and their latencies show (per step, two launches / one: 400 rows
+// of 8000 fp32 12.75 / 12.4 us, 480 of 4000 bf16 12.3 / 11.7, 320 of 2000 10.25 / 9.85, 260 of 32000 16.65 / 16.45; from 500 rows
+// of 32000 on there is little left to gain, 19.8 / 19.7 and 17.7 / 17.7).  (Wider beams have more to merge
 // than a row's workgroup has waves for.)
-bool one_launch_shape(size_t B, size_t k) { return B * k <= kComputeUnits && k <= 32; }
+bool one_launch_shape(size_t B, size_t k) { return B * k <= 2 * kComputeUnits && k <= 32; }
 
 int bits_for(int v)   // bits needed to hold values 0..v
 {

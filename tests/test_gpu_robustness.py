@@ -290,7 +290,7 @@ def _one_launch_decode(wl, dev, stream, first, waves=0):
 
 
 @pytest.mark.parametrize("B,k,V,fmt,one", [
-    (256, 1, 300, None, True), (257, 1, 300, None, False), (85, 3, 1200, "f16", True), (32, 8, 1000, None, True), (28, 9, 4100, "bf16", True),
+    (256, 1, 300, None, True), (512, 1, 300, None, True), (513, 1, 300, None, False), (34, 15, 9000, None, True), (16, 32, 2100, "bf16", True), (17, 31, 700, None, False), (85, 3, 1200, "f16", True), (32, 8, 1000, None, True), (28, 9, 4100, "bf16", True),
     (23, 11, 8200, None, True), (21, 12, 2000, None, True), (16, 16, 16500, "f16", True), (15, 17, 700, None, True), (8, 32, 8300, None, True),
     (7, 33, 600, None, False), (3, 20, 33001, None, True), (1, 5, 1000, None, True), (2, 32, 40000, "bf16", True)])
 def test_steps_of_one_launch(B, k, V, fmt, one):
