@@ -187,7 +187,7 @@ def dba_debug_stream_plan(B: int, k: int, V: int, logp_format: int = DBA_LOGP_F3
     return tuple(int(x) for x in plan)
 
 
-def dba_debug_sentences_first(ctx, on: bool) -> bool:
+def dba_debug_sentences_first(ctx, on: int) -> bool:
     """True if steps of this ctx take one launch."""
     rc = load().dba_debug_sentences_first(ctx, int(on))
     _check(min(rc, DBA_OK), ctx)

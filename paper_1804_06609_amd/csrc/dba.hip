@@ -168,15 +168,17 @@ __global__ __launch_bounds__(NW * kWave) void dba_stream_kernel(const void *logp
 // there after 0.7 to 1.2 us).  Per step, two launches / one: 5 rows of 1000 9.2 / 8.4 us, 160 of 32000 13.05 / 12.75, 168 of 50001
 // 14.2 / 13.45, 240 of 9000 10.95 / 9.95, 192 with k = 16 13.85 / 12.85, one sentence of ten rows 11.15 / 11.05.
 //
-// Every wait ends.  A row waits for nothing.  A sentence's workgroup looks for the lists only once all rows of the sentence have
-// started, from where they run to their end by themselves.  If they do not start soon - other work may hold the chip - it
-// says so and leaves, in the same atomic step in which it sees their number once more; the row that then starts last finds
-// that said and takes the sentence on itself when it is through.  (The one that ends first or last could be elected instead,
-// without a workgroup for it; its tables and its code then come cold: as slow as two launches.)
+// Every wait ends, and with the right answer.  A row waits for nothing; when its keys have reached memory it counts itself
+// among the sentence's ended rows.  A sentence's workgroup that has looked for the keys most_tries times - the rows may be
+// long, or have not started because other work holds the chip - says so in the atomic step that tells it how many rows have ended.  If all
+// have, their keys are there; if not, it leaves, and the row that ends last finds that said and takes the sentence on itself.
+// (Rows could always do so, without a workgroup for the sentence; its tables and its code then come cold: as slow as two
+// launches.)
 // rows_order: B * k, and from bit 31 whether the sentences' workgroups are numbered first (for tests of the other way).
 template <int U, int FMT, int NW, int D, int ROWS, int MW, int J>
 __global__ __launch_bounds__(NW * kWave) void dba_step_kernel(const void *logp, int V, int k_first, uint32_t rows_abreast,
-                                                             uint32_t inv_k, uint32_t rows_order, uint32_t inv_k16, const StepParams p)
+                                                             uint32_t inv_k, uint32_t rows_order, uint32_t inv_k16, int most_tries,
+                                                             const StepParams p)
 {
     extern __shared__ __align__(16) unsigned char dyn_smem[];
     __shared__ int role;
@@ -187,21 +189,24 @@ __global__ __launch_bounds__(NW * kWave) void dba_step_kernel(const void *logp, 
     const uint32_t n = blockIdx.x - (rows_order >> 31 ? (k == 1 ? rows : __umulhi(rows, inv_k)) : 0u);     // (wraps below the first row)
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), tid = (int)threadIdx.x;
     int b;
+    bool all_ended = false;
     if (n < rows) {
         const bool abreast = n < rows_abreast;
         const uint32_t m = abreast ? n >> 3 : n;
         const uint32_t q = k == 1 ? m : __umulhi(m, inv_k);
         b = (int)(abreast ? q * 8u + (n & 7u) : q);
         const int h = (int)(m - q * k);
-        int before = 0;
-        if (wave == 1 && lane_id() == 0)
-            before = __hip_atomic_fetch_add(&p.best[b].started, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         stream_phase<U, FMT, NW, D, true>(p, logp, V, (int)k, k_first >> 16, b, h, ss);
-        // the last row to start takes the sentence on if its workgroup has given up waiting for the rows to start
-        if (wave == 1 && lane_id() == 0) role = before == (kDeclined | (int)(k - 1));
+        // (each wave waits until the keys it has handed over are in memory, where their agent-scope stores put them)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
+        __syncthreads();                                   // (and everyone has left the row's LDS)
+        if (wave == 0 && lane_id() == 0)
+            role = __hip_atomic_fetch_add(&p.best[b].ended, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                   (kGivenUp | (int)(k - 1));
         __syncthreads();
         if (!role) return;
-        __syncthreads();                                   // (everyone has left the row's LDS)
+        all_ended = true;
     } else {
         b = (int)((rows_order >> 31) ? blockIdx.x : n - rows);
     }
@@ -212,21 +217,9 @@ __global__ __launch_bounds__(NW * kWave) void dba_step_kernel(const void *logp, 
         clear_for_merge(p, tid, MW * kWave, ms, cand);
         tables.store((int)k, tid, ms);
     }
-    if (wave == 0 && lane_id() == 0) {
-        int ready = 1;
-        if (n >= rows) {
-            ready = 0;
-            for (int i = (rows_order >> 31) ? kMostWaits : 0; i < kMostWaits && !ready; ++i)
-                ready = __hip_atomic_load(&p.best[b].started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)k;
-            if (!ready)
-                ready = __hip_atomic_fetch_or(&p.best[b].started, kDeclined, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)k;
-        }
-        if (ready) __hip_atomic_store(&p.best[b].started, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        role = ready;
-    }
     __syncthreads();
-    if (!role || wave >= MW) return;
-    merge_phase<ROWS, MW, J, true>(p, p.rowlists, p.conskeys, (int)k, inv_k16, b, ms, cand, P);
+    if (wave >= MW) return;
+    merge_phase<ROWS, MW, J, true>(p, p.rowlists, p.conskeys, (int)k, inv_k16, b, ms, cand, P, most_tries, all_ended);
 }
 
 // Second launch of a step: the merge phase.  Grid: one workgroup of MW waves per sentence, each wave
@@ -240,7 +233,7 @@ __global__ __launch_bounds__(MW * kWave) void dba_merge_kernel(const u64 *rowlis
     extern __shared__ __align__(16) unsigned char dyn_smem[];
     __shared__ MergeSmem sm;
     merge_phase<ROWS, MW, J, false>(p, rowlists, conskeys, (int)(k_inv & 0xFFFFu), k_inv >> 16, (int)blockIdx.x, sm,
-                                    reinterpret_cast<u64 *>(dyn_smem), 0);
+                                    reinterpret_cast<u64 *>(dyn_smem), 0, 0, false);
 }
 
 // Reference read: the largest element of each row, one workgroup per row, with the tile order and
@@ -642,6 +635,11 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem)
 // than a row's workgroup has waves for.)
 bool one_launch_shape(size_t B, size_t k) { return B * k <= 2 * kComputeUnits && k <= 32; }
 
+// How often a sentence's workgroup looks for the rows' keys: a look takes about a microsecond, and the rows two to four times
+// less than these, as many as at 2 TB/s.  Beyond, the row that ends last takes the sentence on, which costs the step the 2 us
+// that one launch saves.
+int most_tries(size_t rows, size_t row_bytes) { return 64 + (int)std::min(rows * row_bytes >> 21, (size_t)1 << 20); }
+
 int bits_for(int v)   // bits needed to hold values 0..v
 {
     int n = 0;
@@ -821,7 +819,7 @@ struct dba_ctx {
     HostBlock block;                    // seen words [B], stopping flags [B], then constraint words / results (p null: none)
     size_t block_flags, block_data;     // offsets in it
     bool one_launch;                    // the row lists are empty between steps, which may then be one launch each
-    bool sentences_first;               // dba_debug_sentences_first
+    int give_up;                        // dba_debug_sentences_first
     int unread;                         // B while the GPU may still have to read the block's constraint words, 0 afterwards
     hipStream_t stream;
     char err[256];
@@ -1120,9 +1118,10 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         p.conskeys = at<u64>(c, L.conskeys);
         const dim3 sblock((unsigned)(plan.waves * kWave)), sgrid((unsigned)c->B * (unsigned)(c->k + 1));
         const size_t lds = std::max((plan.waves == 8 ? sizeof(StreamSmem<8>) : sizeof(StreamSmem<4>)), align_up(sizeof(MergeSmem), 16) + c->dyn_smem);
+        const int tries = c->give_up ? 0 : most_tries((size_t)c->B * (size_t)c->k, (size_t)c->V * elem);
 #define ONE(FMT, NW, D, ROWS, MW, J)                                                                      \
     dba_step_kernel<kTileLoads, FMT, NW, D, ROWS, MW, J><<<sgrid, sblock, lds, c->stream>>>(p.logp, p.V, kf, plan.rows_abreast, \
-                                                                                       inv_k, (unsigned)c->B * (unsigned)c->k | (c->sentences_first ? 0x80000000u : 0u), inv_k16, p)
+                                                                                       inv_k, (unsigned)c->B * (unsigned)c->k | ((c->give_up & 1) ? 0x80000000u : 0u), inv_k16, tries, p)
 #define ONE_ANY(NW, D, ROWS, MW, J)                                       \
     switch (logp_format) {                                      \
         case DBA_LOGP_F16: ONE(kFmtF16, NW, D, ROWS, MW, J); break;       \
@@ -1428,7 +1427,7 @@ DBA_API int dba_debug_wave_select(int n_cases, const uint64_t *keys_host, const 
 DBA_API int dba_debug_sentences_first(dba_ctx *c, int on)
 {
     if (!c) return DBA_EINVAL;
-    c->sentences_first = on != 0;
+    c->give_up = on;
     return c->one_launch && c->merge_waves == 0 ? 1 : 0;
 }
 

@@ -92,7 +92,7 @@ struct __attribute__((aligned(32))) BestCompleted {
     int len;           // its length, end-of-sentence included
     float q;           // its score per word
     float score;       // its score as that beam held it
-    int started;       // workgroups of the step under way that have started (steps of one launch; 0 between steps)
+    int ended;         // rows of the step under way that have ended (steps of one launch; 0 between steps)
     int pad;
 };
 
@@ -135,6 +135,7 @@ struct MergeSmem {
     int ncand;
     int nsel;
     int nleft;                        // candidates that can still be among their bank's best
+    int verdict;                      // steps of one launch, once a wave has run out of looks for the rows' keys (below)
     u64 kept;                         // pruning: bit i = the hypothesis at place i of the new beam stays
 };
 
@@ -1042,9 +1043,27 @@ __device__ __forceinline__ uint32_t best32_of(uint32_t (&o)[N], uint32_t &fell)
 // ---- hand-over inside one launch --------------------------------------------------------
 // A place of the row lists and constraint keys is 0 while it is empty, kNoKey if there is no key for it.
 constexpr u64 kNoKey = 1;             // (no key is 1: the score image of a finite sum is not 0)
-constexpr int kMostTries = 1 << 16;   // an end to every wait, whatever happens; one try is a trip to memory
-constexpr int kMostWaits = 48;
-constexpr int kDeclined = 1 << 16;    // in BestCompleted::started
+constexpr int kGivenUp = 1 << 16;     // in BestCompleted::ended: the sentence is left to the row that ends last
+constexpr int kLastTries = 1 << 16;   // where all rows have ended: their keys are in memory, the first look finds them (a damaged
+                                      // workspace costs a wrong beam, not an endless wait)
+constexpr int kAsked = 1, kGoesOn = 2, kLeaves = 3;    // MergeSmem::verdict
+
+// A wave of sentence b's workgroup has run out of looks for its rows' keys.  The first one to do so tells the rows, in the
+// atomic step that tells it how many have ended: if all, their keys are there (true); if not, the last one will find
+// that said and take the sentence on (false).  The other waves go by what it was told.
+__device__ __forceinline__ bool all_rows_ended(const StepParams &p, int b, int k, MergeSmem &sm)
+{
+    int verdict = 0;
+    if (lane_id() == 0) {
+        if (atomicCAS(&sm.verdict, 0, kAsked) == 0) {
+            const int ended = __hip_atomic_fetch_or(&p.best[b].ended, kGivenUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&sm.verdict, ended == k ? kGoesOn : kLeaves, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        do verdict = __hip_atomic_load(&sm.verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        while (verdict == kAsked);
+    }
+    return __builtin_amdgcn_readfirstlane(verdict) == kGoesOn;
+}
 
 __device__ __forceinline__ void hand_over(u64 *to, u64 key)
 {
@@ -1112,6 +1131,7 @@ __device__ __forceinline__ void clear_for_merge(const StepParams &p, int tid, in
         sm.ncand = 0;
         sm.nsel = 0;
         sm.nleft = 0;
+        sm.verdict = 0;
         sm.kept = 0;
     }
     for (int i = tid; i < p.cand_cap; i += threads) cand[i] = 0;
@@ -1126,9 +1146,12 @@ __device__ __forceinline__ void clear_for_merge(const StepParams &p, int tid, in
 // halves the merges, the registers looked through for candidates and the LDS they pass through.
 // rowlists, conskeys, k, inv_k: what the first loads need (p.rowlists, p.conskeys, p.k; floor(2^16 / k) + 1,
 // with which i * inv_k >> 16 is i / k for i < k * k, k <= 32).
+// ONE: most_tries, how often a wave looks for the rows' keys before it asks whether to go on (if not, the workgroup leaves and
+// has written nothing); all_ended, the sentence was left to this workgroup, a row's, as every row has ended.
 template <int ROWS, int MW, int J, bool ONE>
 __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowlists, const u64 *conskeys, int k,
-                                            uint32_t inv_k, int b, MergeSmem &sm, u64 *cand, int P_here)
+                                            uint32_t inv_k, int b, MergeSmem &sm, u64 *cand, int P_here, int most_tries,
+                                            bool all_ended)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // in a scalar register: row guards are scalar branches
@@ -1144,7 +1167,8 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     if constexpr (ONE) {
         // handed over by workgroups that run now: read again until every place this wave looks at is filled (ONE's tables
         // and counters are in LDS already)
-        for (int tries = 0; tries < kMostTries; ++tries) {
+        bool last = all_ended;
+        for (int tries = last ? kLastTries : most_tries;; --tries) {
             bool there = true;
             if constexpr (kPacked) {
                 head_bits = 0;
@@ -1186,6 +1210,11 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
                 if (kPacked) there &= hd[kPacked ? i : 0] != 0;
             }
             if (__ballot(!there) == 0) break;
+            if (tries <= 0) {
+                if (last || !all_rows_ended(p, b, k, sm)) break;
+                last = true;
+                tries = kLastTries;
+            }
         }
 #pragma unroll
         for (int i = 0; i < kLists; ++i) rl[i] = rl[i] == kNoKey ? 0 : rl[i];
@@ -1668,9 +1697,15 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     }
     __syncthreads();
 
+    const int nsel = min(sm.nsel, k);
     if constexpr (ONE) {
-        // the next step finds the places empty
+        const int verdict = __builtin_amdgcn_readfirstlane(sm.verdict);
+        if (verdict == kLeaves) return;
+        // the next step finds the places empty, and once the last row has counted itself, no row ended
         if (wave >= 2) {
+            if (wave == 2 && lane == 0)
+                __hip_atomic_fetch_add(&p.best[b].ended, -(k + (all_ended || verdict == kGoesOn ? kGivenUp : 0)), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
             for (int h = wave - 2; h < k; h += MW - 2) {
                 const size_t o = ((size_t)b * k + h) * kWave + lane;
                 if (lane < k) hand_over(p.rowlists + o, 0);
@@ -1683,7 +1718,6 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     // One lane per selected candidate.  Its place in the new beam is the number of selected keys greater
     // than its own (at most 64 uniform LDS reads: cheaper than a 64-lane sort); wave 1 counts that
     // while wave 0 takes the hypotheses through add().
-    const int nsel = min(sm.nsel, k);
     const bool live = lane < nsel;
     const u64 mine = (wave <= 1 && live) ? sm.sel[lane] : 0ull;
     if (wave == 1) {

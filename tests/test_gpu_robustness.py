@@ -354,3 +354,32 @@ def test_steps_of_one_launch_side_by_side():
             assert [a.tobytes() for a in ses.outputs()] + [np.asarray(a).tobytes() for a in ses.finalize()] == want, rep
             ses.close()
         busy.close()
+
+
+@pytest.mark.parametrize("first", [1, 2])
+@pytest.mark.parametrize("B,k,V,fmt", [(8, 5, 200, None), (40, 12, 500, None), (16, 10, 32000, None), (20, 24, 3000, None),
+                                       (2, 32, 40000, "bf16"), (26, 10, 33000, "f16"), (3, 20, 300001, None), (512, 1, 700, None)])
+def test_sentences_that_give_up_waiting(B, k, V, fmt, first):
+    """A sentence's workgroup that looks for the rows' keys once and gives up (a limit of 0 looks set by the host; in
+    earnest it runs out where rows take unusually long): the row that ends last takes the sentence on, or the
+    workgroup goes on if all have ended.  Nothing is lost or left behind: the results of two launches, at every step
+    and with the ordinary limit after."""
+    import torch
+    wl = si.make_small(9400 + V, B, k, V, 12, max_phrases=4, max_len=3, dup_prob=0.3)
+    wl.eos_switch = 7
+    tdt = {None: torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[fmt]
+    dev = [torch.from_numpy(wl.logp(t)).cuda().to(tdt) for t in range(wl.T)]
+    stream = torch.cuda.current_stream()
+    import paper_1804_06609_amd as dba
+    two, _ = _one_launch_decode(wl, dev, stream, 0, waves=8)
+    ses, one = _one_launch_decode(wl, dev, stream, first)
+    assert one
+    for t in range(wl.T):
+        dba.dba_debug_sentences_first(ses.ctx, first if t % 4 != 3 else 0)
+        two.step(dev[t])
+        ses.step(dev[t])
+        want = [a.tobytes() for a in two.outputs()] + [a.tobytes() for a in two.state().values()]
+        assert [a.tobytes() for a in ses.outputs()] + [a.tobytes() for a in ses.state().values()] == want, t
+    assert [np.asarray(a).tobytes() for a in ses.finalize()] == [np.asarray(a).tobytes() for a in two.finalize()]
+    ses.close()
+    two.close()
