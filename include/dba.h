@@ -76,7 +76,8 @@ DBA_API size_t dba_workspace_bytes(int B, int k, int V, int N, int max_cons_toke
  *   sent_offsets     host [B+1]            sentence b owns phrases sent_offsets[b] .. sent_offsets[b+1]
  *                    (a sentence may have none).  The three arrays are copied; the caller may free them.
  *   workspace_dev    device, 256-byte aligned, >= dba_workspace_bytes(...) bytes; owned by the
- *                    caller, must stay valid and untouched until dba_destroy
+ *                    caller, must stay valid and untouched until dba_destroy, and until the stream has
+ *                    passed the last step
  *   hip_stream       a hipStream_t (NULL = default stream); all work of this ctx is enqueued on it
  *
  * The initial beam of every sentence is one live, empty hypothesis in slot 0
@@ -237,7 +238,9 @@ DBA_API int dba_get_finished(dba_ctx *ctx, uint8_t *all_finished_host);
 /* Number of dba_step calls made so far (or DBA_EINVAL). */
 DBA_API int dba_steps_done(const dba_ctx *ctx);
 
-/* Frees the host-side ctx only; device memory belongs to the caller. */
+/* Frees the host-side ctx only; device memory belongs to the caller.  Waits for the work of dba_init, if that is
+ * still under way; steps that are still under way need the workspace and the step's buffers until the stream has
+ * passed them. */
 DBA_API void dba_destroy(dba_ctx *ctx);
 
 /* Text of the last error on this ctx, or of the last failed dba_init of the

@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "../../include/dba.h"
@@ -318,7 +319,8 @@ constexpr uint32_t kBeginsPhrase = 0x80000000u, kNoToken = 0x40000000u;
 
 // decoder-init: slot 0 of every sentence is a live, empty hypothesis with score +0.0; and the sentence's tables, one
 // wave per sentence, lane = place of a token, then phrase.  Its time is one trip to host memory for the words.  seen
-// (may be null): host word per sentence, set once the sentence's words have been read.
+// (may be null): host word per sentence, set once the sentence's words have been read and all that is written for it here is in
+// memory, where no later write-back can land on what a next owner of the workspace puts there.
 __global__ __launch_bounds__(kWave) void dba_init_kernel(int B, int k, const uint32_t *words, uint32_t *seen, StepParams p)
 {
     __shared__ int off[kMaxCons], first[kMaxCons];
@@ -329,7 +331,6 @@ __global__ __launch_bounds__(kWave) void dba_init_kernel(int B, int k, const uin
     const int tok = valid ? (int)(word & ~kBeginsPhrase) : 0;
     const u64 starts = __ballot(begins);
     const int C = (int)__popcll(__ballot(valid)), P = (int)__popcll(starts);
-    if (seen && lane == 0) __hip_atomic_store(seen + b, (uint32_t)(1 + P), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (begins) {
         off[lanes_before(starts)] = lane;
         first[lanes_before(starts)] = tok;
@@ -346,34 +347,41 @@ __global__ __launch_bounds__(kWave) void dba_init_kernel(int B, int k, const uin
             btok = btok == -1 || btok == f ? f : -2;
         }
     }
-    const_cast<int32_t *>(p.cons_tok)[at] = tok;
+    // (past the L2, like every store here)
+    auto put = [](auto *to, auto value) { __hip_atomic_store(to, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    put(const_cast<int32_t *>(p.cons_tok) + at, tok);
     int32_t *poff = const_cast<int32_t *>(p.phr_off) + (size_t)b * (kMaxCons + 1);
-    poff[lane] = lane < P ? off[lane] : lane == P ? C : 0;
-    const_cast<int32_t *>(p.first_tok)[at] = ftok;
-    const_cast<u64 *>(p.same_first_lower)[at] = same_lower;
-    const_cast<u64 *>(p.first_bucket)[at] = bucket;
-    const_cast<int32_t *>(p.bucket_tok)[at] = btok;
+    put(poff + lane, lane < P ? off[lane] : lane == P ? C : 0);
+    put(const_cast<int32_t *>(p.first_tok) + at, ftok);
+    put(const_cast<u64 *>(p.same_first_lower) + at, same_lower);
+    put(const_cast<u64 *>(p.first_bucket) + at, bucket);
+    put(const_cast<int32_t *>(p.bucket_tok) + at, btok);
     if (lane == 0) {
-        poff[kMaxCons] = P == kMaxCons ? C : 0;
-        const_cast<int32_t *>(p.nphr)[b] = P;
-        p.all_finished[b] = 0;
-        BestCompleted none = {};
-        p.best[b] = none;
+        put(poff + kMaxCons, P == kMaxCons ? C : 0);
+        put(const_cast<int32_t *>(p.nphr) + b, P);
+        put(p.all_finished + b, (uint8_t)0);
     }
+    static_assert(sizeof(BestCompleted) == 4 * sizeof(u64), "four words");
+    if (lane < 4) put(reinterpret_cast<u64 *>(p.best + b) + lane, (u64)0);
     if (p.rowlists)                                        // steps of one launch: all places empty
         for (int h = 0; h < k; ++h) {
-            p.rowlists[((size_t)b * k + h) * kWave + lane] = 0;
-            p.conskeys[((size_t)b * k + h) * kWave + lane] = 0;
+            put(p.rowlists + ((size_t)b * k + h) * kWave + lane, (u64)0);
+            put(p.conskeys + ((size_t)b * k + h) * kWave + lane, (u64)0);
         }
     if (lane < k) {
         const size_t i = (size_t)b * k + lane;
-        p.score_nxt[i] = lane == 0 ? 0.0f : -INFINITY;
-        p.met_nxt[i] = 0;
-        p.ipq_nxt[i] = -1;
-        p.len_nxt[i] = 0;
-        p.fin_nxt[i] = (uint8_t)((lane == 0 && C > 0) ? kFinEosBlocked : 0);
-        p.inc_nxt[i] = (lane == 0 && P > 0) ? (P == 64 ? ~0ull : ((1ull << P) - 1ull)) : 0ull;
-        p.nxt_nxt[i] = -1;
+        put(p.score_nxt + i, lane == 0 ? 0.0f : -INFINITY);
+        put(p.met_nxt + i, (u64)0);
+        put(p.ipq_nxt + i, -1);
+        put(p.len_nxt + i, 0);
+        put(p.fin_nxt + i, (uint8_t)((lane == 0 && C > 0) ? kFinEosBlocked : 0));
+        put(p.inc_nxt + i, (lane == 0 && P > 0) ? (P == 64 ? ~0ull : ((1ull << P) - 1ull)) : 0ull);
+        put(p.nxt_nxt + i, -1);
+    }
+    if (seen) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): all of it is in memory
+        if (lane == 0) __hip_atomic_store(seen + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -693,11 +701,23 @@ namespace {
 // Pinned host memory that kernels read and write themselves: a copy to or from ordinary host memory costs about 8
 // us and a wait of its own (a decode with the stopping test asked for after each of its 21 steps, 8 x 10 x 32000: 814 -> 641
 // us; one of 100 steps, 64 x 20 x 32000: 3360 -> 3294).  A ctx holds one block from dba_init to dba_destroy; blocks are kept for the next ctx, of any
-// thread and device, up to kKeepBytes of them, and freed beyond.  A block whose dba_init may not have been
-// read by the GPU yet when its ctx goes waits aside until the words that say so are set.
+// thread and device, up to kKeepBytes of them, and freed beyond.  No kernel uses a block any more when it comes back.
 struct HostBlock {
     unsigned char *p = nullptr;           // (host and device address)
     size_t bytes = 0;
+};
+
+// For calls that are no part of a stream capture which this or another thread may have under way.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    RelaxedCapture() = default;
+    RelaxedCapture(const RelaxedCapture &) = delete;
+    RelaxedCapture &operator=(const RelaxedCapture &) = delete;
+    ~RelaxedCapture()
+    {
+        if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
 };
 
 class HostBlocks {
@@ -712,7 +732,6 @@ public:
         while (n < bytes) n *= 2;
         {
             std::lock_guard<std::mutex> hold(mutex_);
-            settle();
             for (int i = 0; i < n_free_; ++i)
                 if (free_[i].bytes == n) {
                     block = free_[i];
@@ -721,9 +740,7 @@ public:
                     return block;
                 }
         }
-        // (allocating is no part of a stream capture that this or another thread may have under way)
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        const RelaxedCapture relaxed;
         void *p = nullptr;
         if (hipHostMalloc(&p, n, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
             block.p = static_cast<unsigned char *>(p);
@@ -731,41 +748,21 @@ public:
         } else {
             (void)hipGetLastError();
         }
-        if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
         return block;
     }
-    // seen: the words of B sentences at the block's start, if they still have to be waited for (B = 0: not)
-    void put(HostBlock block, int B) noexcept
+    void put(HostBlock block) noexcept
     {
         if (!block.p) return;
-        HostBlock extra;
         {
             std::lock_guard<std::mutex> hold(mutex_);
-            settle();
-            if (!read(block, B)) {
-                if (n_aside_ < kAside) {
-                    aside_[n_aside_] = block;
-                    aside_B_[n_aside_++] = B;
-                    return;
-                }
-                extra = block;
-            } else if (!keep(block)) {
-                extra = block;
-            }
+            if (keep(block)) return;
         }
-        if (extra.p) (void)hipHostFree(extra.p);           // (waits for the GPU)
+        (void)hipHostFree(block.p);                        // (waits for the GPU)
     }
 
 private:
     static constexpr size_t kKeepBytes = 2 * 1024 * 1024;
-    static constexpr int kKeep = (int)(kKeepBytes / kLeast), kAside = 16;
-    static bool read(const HostBlock &block, int B)
-    {
-        const volatile uint32_t *seen = reinterpret_cast<const volatile uint32_t *>(block.p);
-        for (int b = 0; b < B; ++b)
-            if (seen[b] == 0) return false;
-        return true;
-    }
+    static constexpr int kKeep = (int)(kKeepBytes / kLeast);
     bool keep(const HostBlock &block)
     {
         if (kept_ + block.bytes > kKeepBytes) return false;
@@ -773,21 +770,9 @@ private:
         kept_ += block.bytes;
         return true;
     }
-    void settle()
-    {
-        for (int i = 0; i < n_aside_;) {
-            if (read(aside_[i], aside_B_[i]) && keep(aside_[i])) {
-                aside_[i] = aside_[--n_aside_];
-                aside_B_[i] = aside_B_[n_aside_];
-            } else {
-                ++i;
-            }
-        }
-    }
     std::mutex mutex_;
-    HostBlock free_[kKeep], aside_[kAside];
-    int aside_B_[kAside] = {};
-    int n_free_ = 0, n_aside_ = 0;
+    HostBlock free_[kKeep];
+    int n_free_ = 0;
     size_t kept_ = 0;
 };
 
@@ -820,7 +805,7 @@ struct dba_ctx {
     size_t block_flags, block_data;     // offsets in it
     bool one_launch;                    // the row lists are empty between steps, which may then be one launch each
     int give_up;                        // dba_debug_sentences_first
-    int unread;                         // B while the GPU may still have to read the block's constraint words, 0 afterwards
+    bool init_under_way;                // the kernel of dba_init may not be through: nothing has waited for it yet
     hipStream_t stream;
     char err[256];
 };
@@ -861,6 +846,15 @@ void set_tables(dba_ctx *c, StepParams &p)
     p.bucket_tok = at<int32_t>(c, L.btok);
     p.all_finished = at<uint8_t>(c, L.all_finished);
     p.best = at<BestCompleted>(c, L.best);
+}
+
+// the kernel of dba_init sets a word of the block for every sentence when it is through with it
+bool init_is_through(const dba_ctx *c)
+{
+    const uint32_t *seen = reinterpret_cast<const uint32_t *>(c->block.p);
+    for (int b = 0; seen && b < c->B; ++b)
+        if (__atomic_load_n(seen + b, __ATOMIC_RELAXED) == 0) return false;
+    return true;
 }
 
 // half: which of the two halves of the beam state the kernel writes
@@ -920,8 +914,7 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     const size_t words_bytes = (size_t)B * kMaxCons * sizeof(uint32_t);
     struct Holder {
         HostBlock block;
-        int unread = 0;
-        ~Holder() { host_blocks().put(block, unread); }
+        ~Holder() { host_blocks().put(block); }
     } held;
     const size_t block_flags = (size_t)B * sizeof(uint32_t), block_data = align_up(block_flags + (size_t)B, 256);
     const size_t results_bytes = L.fin_status + (size_t)B * 4 - (staged_tokens((size_t)B, (size_t)N) ? L.fin_tokens : L.fin_len);
@@ -1020,7 +1013,6 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
         }
         dba_init_kernel<<<(unsigned)B, kWave, 0, c->stream>>>(B, k, words, seen, p);
         e = hipGetLastError();
-        if (e == hipSuccess && seen) held.unread = B;
     }
     if (e == hipSuccess && !seen) e = hipStreamSynchronize(c->stream);   // the words are freed on return
     if (e != hipSuccess) {
@@ -1031,7 +1023,7 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     c->block = held.block;
     c->block_flags = block_flags;
     c->block_data = block_data;
-    c->unread = held.unread;
+    c->init_under_way = seen != nullptr;
     held.block.p = nullptr;
     *out = c;
     return DBA_OK;
@@ -1267,7 +1259,7 @@ DBA_API int dba_finalize(dba_ctx *c, int32_t *out_tokens_host, int32_t *out_len_
         if (here) c->block.p = nullptr;                    // (a kernel may still write to it: never used again)
         return fail(c, DBA_EHIP, "dba_finalize: HIP error: %s", hipGetErrorString(e));
     }
-    c->unread = 0;
+    c->init_under_way = false;
     if (here) {
         if (staged) memcpy(out_tokens_host, place(L.fin_tokens), tokens_bytes);
         memcpy(out_len_host, place(L.fin_len), B * 4);
@@ -1305,6 +1297,7 @@ DBA_API int dba_get_state(dba_ctx *c, float *score_host, uint64_t *met_mask_host
         e = hipMemcpyAsync(length_host, at<int32_t>(c, L.len[cur]), n * 4, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return fail(c, DBA_EHIP, "dba_get_state: HIP error: %s", hipGetErrorString(e));
+    c->init_under_way = false;
     for (size_t i = 0; i < n; ++i) {
         if (score_host) score_host[i] = score[i];
         if (inprog_phrase_host) inprog_phrase_host[i] = ipq[i] < 0 ? -1 : (ipq[i] >> 8);
@@ -1355,7 +1348,7 @@ DBA_API int dba_get_finished(dba_ctx *c, uint8_t *all_finished_host)
         c->block.p = nullptr;                              // (a kernel may still write to it: never used again)
         return fail(c, DBA_EHIP, "dba_get_finished: HIP error: %s", hipGetErrorString(e));
     }
-    c->unread = 0;
+    c->init_under_way = false;
     if (here) memcpy(all_finished_host, here, (size_t)c->B);
     return DBA_OK;
 }
@@ -1363,7 +1356,19 @@ DBA_API int dba_get_finished(dba_ctx *c, uint8_t *all_finished_host)
 DBA_API void dba_destroy(dba_ctx *c)
 {
     if (!c) return;
-    host_blocks().put(c->block, c->unread);
+    // a ctx that goes before the GPU is through with its dba_init: the workspace and the block are given back only then
+    if (c->init_under_way && !init_is_through(c)) {
+        const RelaxedCapture relaxed;
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
+        if (capture != hipStreamCaptureStatusNone) {       // (what was enqueued before the capture began runs all the same)
+            while (!init_is_through(c)) std::this_thread::yield();
+        } else if (hipStreamSynchronize(c->stream) != hipSuccess) {
+            (void)hipGetLastError();
+            c->block.p = nullptr;                          // (never used again)
+        }
+    }
+    host_blocks().put(c->block);
     delete c;
 }
 

@@ -383,3 +383,60 @@ def test_sentences_that_give_up_waiting(B, k, V, fmt, first):
     assert [np.asarray(a).tobytes() for a in ses.finalize()] == [np.asarray(a).tobytes() for a in two.finalize()]
     ses.close()
     two.close()
+
+
+@pytest.mark.parametrize("B,k,V", [(3, 5, 300), (60, 20, 500), (300, 2, 60)])
+def test_a_workspace_is_free_once_its_ctx_is_destroyed(B, k, V):
+    """dba_init returns before the GPU has come to it; a ctx that is destroyed without a step gives its workspace back
+    only when nothing of dba_init can write to it any more, on whatever stream it is used next."""
+    import torch
+    import paper_1804_06609_amd as dba
+    wl = si.make_small(9500 + B, B, k, V, 4, max_phrases=3, max_len=3)
+    nbytes = dba.dba_workspace_bytes(B, k, V, 4, dba.DBA_MAX_CONS_TOKENS)
+    ws = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
+    base = (ws.data_ptr() + 255) // 256 * 256
+    stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+    a = torch.randn(4096, 4096, device="cuda")
+    a @ a
+    torch.cuda.synchronize()
+    for option in (None, 99):
+        with torch.cuda.stream(stream):
+            for _ in range(20):                            # some milliseconds ahead of dba_init on its stream
+                a @ a
+        ctx = dba.dba_init(B, k, V, 4, wl.eos_id, wl.pad_id, *wl.csr(), base, nbytes, stream.cuda_stream)
+        if option is not None:                             # (why a ctx may go without a step)
+            with pytest.raises(dba.DbaError):
+                dba.dba_set_option(ctx, option, 1.0)
+        dba.dba_destroy(ctx)
+        with torch.cuda.stream(other):
+            ws.fill_(0x5A)
+        other.synchronize()
+        torch.cuda.synchronize()
+        assert bool((ws == 0x5A).all()), option
+
+
+def test_destroying_a_ctx_leaves_a_capture_alone():
+    """dba_destroy between the begin and the end of a capture on the ctx's own stream, while dba_init is still under way."""
+    import torch
+    import paper_1804_06609_amd as dba
+    wl = si.make_small(9550, 4, 5, 300, 4, max_phrases=3, max_len=3)
+    nbytes = dba.dba_workspace_bytes(4, 5, 300, 4, dba.DBA_MAX_CONS_TOKENS)
+    ws = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
+    base = (ws.data_ptr() + 255) // 256 * 256
+    a, x = torch.randn(4096, 4096, device="cuda"), torch.zeros(64, device="cuda")
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        a @ a
+        x.add_(0)
+        stream.synchronize()
+        for _ in range(20):
+            a @ a
+        ctx = dba.dba_init(4, 5, 300, 4, wl.eos_id, wl.pad_id, *wl.csr(), base, nbytes, stream.cuda_stream)
+        graph.capture_begin()
+        x.add_(1)
+        dba.dba_destroy(ctx)
+        graph.capture_end()
+        for _ in range(3):
+            graph.replay()
+    torch.cuda.synchronize()
+    assert bool((x == 3).all())
