@@ -16,7 +16,8 @@
  *   - The library allocates no device memory: state, history and scratch are
  *     carved from a caller-provided workspace.  Each ctx holds a block of pinned host
  *     memory (64 KB to 1 MB; none for more than about 3900 sentences), kept for
- *     the next one by dba_destroy: at most 2 MB in all.
+ *     the next one by dba_destroy: at most 2 MB in all, beyond which dba_destroy frees
+ *     the blocks that have not been used for longest (that waits for the GPU).
  *   - dba_init and dba_step only enqueue work on the stream given at init and return
  *     (dba_init waits where it has no block of host memory); nothing is
  *     synchronised before dba_get_finished / dba_finalize / dba_get_state.

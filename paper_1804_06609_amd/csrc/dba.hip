@@ -14,6 +14,7 @@
 #include "../../include/dba.h"
 #include "../../include/dba_debug.h"
 #include "dba_kernels.hpp"
+#include "host_blocks.hpp"
 
 using namespace dba;
 
@@ -698,15 +699,6 @@ hipError_t static_scratch(void **out)
 
 namespace {
 
-// Pinned host memory that kernels read and write themselves: a copy to or from ordinary host memory costs about 8
-// us and a wait of its own (a decode with the stopping test asked for after each of its 21 steps, 8 x 10 x 32000: 814 -> 641
-// us; one of 100 steps, 64 x 20 x 32000: 3360 -> 3294).  A ctx holds one block from dba_init to dba_destroy; blocks are kept for the next ctx, of any
-// thread and device, up to kKeepBytes of them, and freed beyond.  No kernel uses a block any more when it comes back.
-struct HostBlock {
-    unsigned char *p = nullptr;           // (host and device address)
-    size_t bytes = 0;
-};
-
 // For calls that are no part of a stream capture which this or another thread may have under way.
 struct RelaxedCapture {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
@@ -720,65 +712,29 @@ struct RelaxedCapture {
     }
 };
 
-class HostBlocks {
-public:
-    static constexpr size_t kLeast = 64 * 1024, kMost = 1024 * 1024;
-    // an empty block if there is none to be had: its user does without
-    HostBlock get(size_t bytes) noexcept
+// Pinned host memory that kernels read and write themselves: a copy to or from ordinary host memory costs about 8
+// us and a wait of its own (a decode with the stopping test asked for after each of its 21 steps, 8 x 10 x 32000: 814 -> 641
+// us; one of 100 steps, 64 x 20 x 32000: 3360 -> 3294).  A ctx holds one block from dba_init to dba_destroy; blocks are kept for the next
+// ctx, of any thread and device, and what is more than the store keeps is freed.  No kernel uses a block any more when it comes back.
+struct PinnedMemory {
+    static void *allocate(size_t n)
     {
-        HostBlock block;
-        if (bytes > kMost) return block;
-        size_t n = kLeast;
-        while (n < bytes) n *= 2;
-        {
-            std::lock_guard<std::mutex> hold(mutex_);
-            for (int i = 0; i < n_free_; ++i)
-                if (free_[i].bytes == n) {
-                    block = free_[i];
-                    free_[i] = free_[--n_free_];
-                    kept_ -= n;
-                    return block;
-                }
-        }
         const RelaxedCapture relaxed;
         void *p = nullptr;
-        if (hipHostMalloc(&p, n, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
-            block.p = static_cast<unsigned char *>(p);
-            block.bytes = n;
-        } else {
-            (void)hipGetLastError();
-        }
-        return block;
+        if (hipHostMalloc(&p, n, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) return p;
+        (void)hipGetLastError();
+        return nullptr;
     }
-    void put(HostBlock block) noexcept
+    static void release(void *p)                           // (waits for the GPU)
     {
-        if (!block.p) return;
-        {
-            std::lock_guard<std::mutex> hold(mutex_);
-            if (keep(block)) return;
-        }
-        (void)hipHostFree(block.p);                        // (waits for the GPU)
+        const RelaxedCapture relaxed;
+        if (hipHostFree(p) != hipSuccess) (void)hipGetLastError();
     }
-
-private:
-    static constexpr size_t kKeepBytes = 2 * 1024 * 1024;
-    static constexpr int kKeep = (int)(kKeepBytes / kLeast);
-    bool keep(const HostBlock &block)
-    {
-        if (kept_ + block.bytes > kKeepBytes) return false;
-        free_[n_free_++] = block;
-        kept_ += block.bytes;
-        return true;
-    }
-    std::mutex mutex_;
-    HostBlock free_[kKeep];
-    int n_free_ = 0;
-    size_t kept_ = 0;
 };
 
-HostBlocks &host_blocks()
+HostBlocks<PinnedMemory> &host_blocks()
 {
-    static HostBlocks *blocks = new HostBlocks;            // (outlives every ctx: never destroyed)
+    static auto *blocks = new HostBlocks<PinnedMemory>;    // (outlives every ctx: never destroyed)
     return *blocks;
 }
 

@@ -440,3 +440,43 @@ def test_destroying_a_ctx_leaves_a_capture_alone():
             graph.replay()
     torch.cuda.synchronize()
     assert bool((x == 3).all())
+
+
+def test_blocks_of_host_memory_are_freed_beside_a_capture():
+    """Four ctxs with a megabyte of host memory each are destroyed, two megabytes of it freed, while another stream is being
+    captured: the capture is none the worse, nor is the decode that comes next."""
+    import torch
+    from paper_1804_06609_amd.session import Session
+    wl = si.make_small(9560, 3000, 2, 40, 2, max_phrases=2, max_len=2)
+    lp = [torch.from_numpy(wl.logp(t)).cuda() for t in range(2)]
+    mine, other = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def decode():
+        ses = Session(wl.B, wl.k, wl.V, wl.T, wl.eos_id, wl.pad_id, *wl.csr(), stream=mine)
+        for t in range(2):
+            ses.step(lp[t])
+        return ses
+
+    torch.cuda.synchronize()
+    held = [decode() for _ in range(4)]
+    want = [[np.asarray(a).tobytes() for a in s.finalize()] for s in held]
+    assert all(w == want[0] for w in want)
+    mine.synchronize()
+    x, graph = torch.zeros(64, device="cuda"), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    import paper_1804_06609_amd as dba
+    with torch.cuda.stream(other):
+        graph.capture_begin(capture_error_mode="global")
+        x.add_(1)
+        for s in held:
+            dba.dba_destroy(s.ctx)
+            s.ctx = None
+        x.add_(1)
+        graph.capture_end()
+        for _ in range(2):
+            graph.replay()
+    torch.cuda.synchronize()
+    assert bool((x == 4).all())
+    ses = decode()
+    assert [np.asarray(a).tobytes() for a in ses.finalize()] == want[0]
+    ses.close()
