@@ -39,8 +39,8 @@ DBA_API int dba_debug_wave_select(int n_cases, const uint64_t *keys_host, const 
                                   size_t scratch_bytes, void *hip_stream);
 
 /*
- * Diagnostic: how the first launch of a step is laid out for a shape (host only, no GPU needed), so that
- * tests can tell which kernel a shape reaches.  plan_host [4]: wavefronts per beam row, 4 KB tiles each
+ * Diagnostic: how the stream phase of a step is laid out for a shape at the default options (host only, no GPU
+ * needed), so that tests can tell which kernel a shape reaches.  plan_host [4]: wavefronts per beam row, 4 KB tiles each
  * wavefront keeps in flight, bytes of LDS a workgroup asks for (its own and what it leaves unused to
  * keep other workgroups off its compute unit), beam rows numbered eight sentences abreast.
  */

@@ -597,7 +597,8 @@ struct StreamPlan {
     uint32_t rows_abreast;  // rows of the sentences that are numbered eight abreast
 };
 
-StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem)
+// one: the step takes one launch
+StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem, bool one)
 {
     StreamPlan plan;
     const size_t rows = B * k, row_bytes = V * elem;
@@ -633,8 +634,14 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem)
                                                 : spread_lds<4, 7>(share < 8 ? share : 6);
     // Tiles in flight per wave: four where every row has a compute unit to itself and its latencies show
     // (per step: 14.7 -> 13.7 us for 160 rows of 32000 fp32, 16.0 -> 15.0 for 168 of 50001, 26.6 -> 25.0 for 240 of
-    // 100000); two beyond (480 rows of 50000: 24.8 against 25.8 with four).
-    plan.tiles = plan.waves == 8 && rows <= kComputeUnits ? 4 : 2;
+    // 100000); two beyond (480 rows of 50000: 24.8 against 25.8 with four).  In one launch the registers of two tiles leave
+    // room for a sentence's workgroup beside two rows (59 against 89; per step, four / two: 400 rows of 32000 fp32 18.3 / 17.65 us, 320
+    // 17.1 / 16.8, 480 of 50000 25.7 / 25.05, 400 of 58000 26.1 / 25.25, 400 of 32000 bf16 16.25 / 15.75, 480 of 65000 bf16 20.35 / 19.45; four
+    // decodes of 512 rows of 32000 bf16 side by side 35.1 / 29.7), but long rows are traffic more than latency again, from
+    // seven tiles a wave on, six with two elements in the place of one (240 KB: fp32 22.55 / 22.65 and 28.1 / 28.25, bf16 21.55 / 22.85;
+    // 200 KB: bf16 20.35 / 20.85 and 26.55 / 26.8; 400 KB: fp32 30.05 / 31.2 and 39.45 / 40.0, at 260 and 500 rows).
+    const bool long_rows = row_bytes >= (elem == 4 ? 7u : 6u) * 8 * 4096;
+    plan.tiles = plan.waves == 8 && (rows <= kComputeUnits || (one && long_rows)) ? 4 : 2;
     return plan;
 }
 
@@ -1055,12 +1062,13 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     p.hist_backptr = at<int32_t>(c, L.hist_backptr) + hrow;
 
     // one workgroup per beam row, 4 loads of 16 bytes per lane and tile, two or four 4 KB tiles in flight per wave
-    const StreamPlan plan = stream_plan((size_t)c->B, (size_t)c->k, (size_t)c->V, elem);
+    const bool one = c->one_launch && c->merge_waves == 0;
+    const StreamPlan plan = stream_plan((size_t)c->B, (size_t)c->k, (size_t)c->V, elem, one);
     const dim3 grid((unsigned)c->B * (unsigned)c->k);
     const uint32_t inv_k = (uint32_t)(((1ull << 32) + (unsigned)c->k - 1) / (unsigned)c->k);
     const int kf = p.k | (p.first_step << 16);
     const uint32_t inv_k16 = (uint32_t)(c->k == 1 ? 65535 : 65536 / c->k + 1);
-    if (c->one_launch && c->merge_waves == 0) {
+    if (one) {
         // (the places are empty between steps, which only the ctx's own are)
         p.rowlists = at<u64>(c, L.rowlists);
         p.conskeys = at<u64>(c, L.conskeys);
@@ -1076,11 +1084,16 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         case DBA_LOGP_BF16: ONE(kFmtBF16, NW, D, ROWS, MW, J); break;     \
         default: ONE(kFmtF32, NW, D, ROWS, MW, J); break;                 \
     }
-        if (plan.waves == 8) {
+        if (plan.waves == 8 && plan.tiles == 4) {
             if (c->k <= 8) ONE_ANY(8, 4, 2, 4, 1)
             else if (c->k <= 11) ONE_ANY(8, 4, 4, 4, 2)
             else if (c->k <= 16) ONE_ANY(8, 4, 4, 4, -1)
             else ONE_ANY(8, 4, 4, 8, -1)
+        } else if (plan.waves == 8) {
+            if (c->k <= 8) ONE_ANY(8, 2, 2, 4, 1)
+            else if (c->k <= 11) ONE_ANY(8, 2, 4, 4, 2)
+            else if (c->k <= 16) ONE_ANY(8, 2, 4, 4, -1)
+            else ONE_ANY(8, 2, 4, 8, -1)
         } else {
             if (c->k <= 8) ONE_ANY(4, 2, 2, 4, 1)
             else if (c->k <= 11) ONE_ANY(4, 2, 4, 4, 2)
@@ -1396,7 +1409,8 @@ DBA_API int dba_debug_stream_plan(int B, int k, int V, int logp_format, int32_t 
 {
     if (!shape_ok(B, k, V, 1, 0) || !plan_host || logp_format < DBA_LOGP_F32 || logp_format > DBA_LOGP_BF16)
         return fail(nullptr, DBA_EINVAL, "dba_debug_stream_plan: bad argument");
-    const StreamPlan plan = stream_plan((size_t)B, (size_t)k, (size_t)V, logp_format == DBA_LOGP_F32 ? 4u : 2u);
+    const StreamPlan plan = stream_plan((size_t)B, (size_t)k, (size_t)V, logp_format == DBA_LOGP_F32 ? 4u : 2u,
+                                        one_launch_shape((size_t)B, (size_t)k));
     plan_host[0] = plan.waves;
     plan_host[1] = plan.tiles;
     plan_host[2] = (int32_t)((plan.waves == 8 ? sizeof(StreamSmem<8>) : sizeof(StreamSmem<4>)) + plan.spare_lds);

@@ -378,6 +378,27 @@ def test_room_runs_out_behind_the_floor(torch_gpu, B, k, V, fmt, plan, shape):
     _harness().run_parity(wl, logp_format=fmt)
 
 
+@pytest.mark.parametrize("shape", ["rise", "ties", "rising", "stairs", "equal", "plateau"])
+@pytest.mark.parametrize("B,k,V,fmt,plan,merge_waves", [
+    (9, 30, 40003, None, (8, 2), 8), (11, 24, 70001, "bf16", (8, 2), 8), (9, 29, 40003, "f16", (8, 2), 4), (8, 33, 40003, None, (8, 2), 0),
+    (26, 20, 41003, None, (8, 2), 0), (30, 9, 58001, None, (8, 4), 0), (270, 1, 100001, "bf16", (8, 4), 0), (22, 12, 40003, None, (8, 2), 0),
+    (2, 20, 40003, None, (8, 4), 8), (5, 33, 70001, "f16", (8, 4), 0)])
+def test_room_runs_out_in_both_forms_of_a_step(torch_gpu, B, k, V, fmt, plan, merge_waves, shape):
+    """The same for the kernels that the cases above do not reach: two launches where those take one (fixed merge waves, more
+    than 512 rows or k > 32), one launch with two tiles and with four beyond 256 rows."""
+    import paper_1804_06609_amd as dba
+    code = {None: dba.DBA_LOGP_F32, "f16": dba.DBA_LOGP_F16, "bf16": dba.DBA_LOGP_BF16}[fmt]
+    waves, tiles = dba.dba_debug_stream_plan(B, k, V, code)[:2]
+    tile = 1024 if fmt is None else 2048
+    assert (waves, tiles) == plan
+    base = si.make_small(5550 + k, B, k, V, 2, max_phrases=3, max_len=2, dup_prob=0.3, boost=False)
+    wl = (_Shaped if shape == "rising" else _Late)(B=B, k=k, V=V, T=2, seed=base.seed, constraints=base.constraints)
+    wl.shape, wl.first = shape, 2 * waves * tile
+    wl.eos_switch = 1
+    _harness().run_parity(wl, logp_format=fmt, options={dba.DBA_OPT_MERGE_WAVES: merge_waves},
+                          oracle_sentences=sorted({0, 1, B // 2, B - 1}) if B > 40 else None)
+
+
 @pytest.mark.parametrize("k,V,fmt", [(20, 1000, None), (33, 700, None), (48, 1031, None), (64, 256, None), (64, 500, None),
                                      (64, 1000, None), (64, 1024, None), (64, 3000, None), (40, 900, "bf16"), (64, 300, "bf16"),
                                      (64, 1000, "f16"), (64, 2000, "bf16"), (64, 2048, "f16"), (32, 400, "bf16")])

@@ -58,3 +58,15 @@ def test_only_long_rows_that_follow_one_another_are_held_to_six_waves_a_simd():
                                (110, 20, 32000, dba.DBA_LOGP_F32, True), (64, 32, 32000, dba.DBA_LOGP_F32, False)):
         waves, _, lds, _ = dba.dba_debug_stream_plan(B, k, V, fmt)
         assert waves == 4 and UNIT_LDS // lds == (6 if held else 9), (B, k, V, fmt, lds)
+
+
+def test_tiles_in_flight_beyond_a_row_per_compute_unit():
+    """One launch keeps two tiles there too, and four only for rows of seven tiles a wave (six with 16-bit elements);
+    two launches (k > 32 here) always two."""
+    f32, bf16 = dba.DBA_LOGP_F32, dba.DBA_LOGP_BF16
+    for B, k, V, fmt, tiles in ((16, 16, 32000, f32, 4), (257, 1, 32000, f32, 2), (26, 10, 32000, f32, 2), (16, 30, 50000, f32, 2),
+                                (26, 10, 57343, f32, 2), (26, 10, 57344, f32, 4), (16, 32, 100000, f32, 4), (30, 16, 65000, bf16, 2),
+                                (26, 10, 98303, bf16, 2), (26, 10, 98304, bf16, 4), (8, 33, 100000, f32, 2), (52, 10, 100000, f32, 2),
+                                (4, 33, 100000, f32, 4)):
+        waves, got = dba.dba_debug_stream_plan(B, k, V, fmt)[:2]
+        assert (waves, got) == (8, tiles), (B, k, V, fmt, got)
