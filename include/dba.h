@@ -143,8 +143,8 @@ DBA_API int dba_step_fmt(dba_ctx *ctx, const void *logp_dev, int logp_format, in
  * overwrites what it reads.
  * Limits: B*k <= DBA_NOALLOC_MAX_ROWS, else DBA_EINVAL with a message (no launch).  All contexts on
  * one GPU share that GPU's array: steps of different contexts that overlap in time (different
- * streams) race on it - keep such steps on one stream or use dba_step.  (Steps of at most 512 beam
- * rows with k <= 32 take one launch and hand over through the workspace in every form.)  The device that was current
+ * streams) race on it - keep such steps on one stream or use dba_step.  (Steps that take one
+ * launch, see DBA_OPT_MERGE_WAVES, hand over through the workspace in every form.)  The device that was current
  * at dba_init must be current.  Calls no hipMalloc / hipFree.
  */
 #define DBA_NOALLOC_MAX_ROWS 8192
@@ -214,7 +214,8 @@ DBA_API int dba_get_state(dba_ctx *ctx, float *score_host, uint64_t *met_mask_ho
  *                               workgroup that handles one sentence in the second launch of a step.
  *                               The results are the same for every setting; only the time differs.
  *                               0 lets the library choose for the shortest step of a single decode: one
- *                               launch for both parts of a small step (B*k <= 512, k <= 32), else so many
+ *                               launch for both parts of a small step (B*k <= 512, and k <= 16, or k <= 32
+ *                               with rows of at least 32 KB), else so many
  *                               (four up to k = 16, eight up to 32, sixteen beyond).  Four-wave workgroups need less room
  *                               at once on a GPU that is busy with other work.
  */

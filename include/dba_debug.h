@@ -46,12 +46,15 @@ DBA_API int dba_debug_wave_select(int n_cases, const uint64_t *keys_host, const 
  */
 DBA_API int dba_debug_stream_plan(int B, int k, int V, int logp_format, int32_t *plan_host);
 
+/* Diagnostic: launches of a step of this shape at the default options, 1 or 2 (host only). */
+DBA_API int dba_debug_launches(int B, int k, int V, int logp_format);
+
 /*
  * Diagnostic: on != 0: in steps of this ctx that take one launch the sentences' workgroups look for the rows' keys once
  * and then give up, so that rows take the sentences on themselves, which otherwise happens on a busy GPU or with
  * rows that take unusually long; on = 1: numbered before the rows', they all do; on = 2: numbered behind them as usual,
- * so that some may find all rows ended.  The results are the same.  Returns 1 if steps of this ctx take
- * one launch, else 0.
+ * so that some may find all rows ended.  The results are the same.  Returns 1 if steps of this ctx may take
+ * one launch (dba_debug_launches), else 0.
  */
 DBA_API int dba_debug_sentences_first(dba_ctx *ctx, int on);
 

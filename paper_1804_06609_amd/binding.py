@@ -44,6 +44,7 @@ _SIGNATURES = {
     "dba_debug_allocate": (_I, [_I, _I] + [_P] * 5 + [ctypes.c_size_t, _P]),
     "dba_debug_wave_select": (_I, [_I] + [_P] * 5 + [ctypes.c_size_t, _P]),
     "dba_debug_stream_plan": (_I, [_I] * 4 + [_P]),
+    "dba_debug_launches": (_I, [_I] * 4),
     "dba_debug_sentences_first": (_I, [_P, _I]),
     "dba_debug_row_max": (_I, [_P, _I, _I, _P, _P]),
 }
@@ -187,8 +188,15 @@ def dba_debug_stream_plan(B: int, k: int, V: int, logp_format: int = DBA_LOGP_F3
     return tuple(int(x) for x in plan)
 
 
+def dba_debug_launches(B: int, k: int, V: int, logp_format: int = DBA_LOGP_F32) -> int:
+    """Launches of a step of this shape at the default options."""
+    rc = load().dba_debug_launches(B, k, V, logp_format)
+    _check(min(rc, DBA_OK))
+    return rc
+
+
 def dba_debug_sentences_first(ctx, on: int) -> bool:
-    """True if steps of this ctx take one launch."""
+    """True if steps of this ctx may take one launch."""
     rc = load().dba_debug_sentences_first(ctx, int(on))
     _check(min(rc, DBA_OK), ctx)
     return rc == 1

@@ -221,21 +221,21 @@ __global__ __launch_bounds__(NW * kWave) void dba_step_kernel(const void *logp, 
     }
     __syncthreads();
     if (wave >= MW) return;
-    merge_phase<ROWS, MW, J, true>(p, p.rowlists, p.conskeys, (int)k, inv_k16, b, ms, cand, P, most_tries, all_ended);
+    merge_phase<ROWS, MW, J, true, true>(p, p.rowlists, p.conskeys, (int)k, inv_k16, b, ms, cand, P, most_tries, all_ended);
 }
 
 // Second launch of a step: the merge phase.  Grid: one workgroup of MW waves per sentence, each wave
 // taking up to ROWS beam rows (k <= ROWS * MW); J > 0: and holding J entries per lane of all the sentence's lists
 // (k * k <= 64 * J).  The pointers to the row lists and the beam width (k_inv = k | inv_k << 16) come first:
 // they are all the first loads need.
-template <int ROWS, int MW, int J>
+template <int ROWS, int MW, int J, bool EMPTY>
 __global__ __launch_bounds__(MW * kWave) void dba_merge_kernel(const u64 *rowlists, const u64 *conskeys, uint32_t k_inv,
                                                                const StepParams p)
 {
     extern __shared__ __align__(16) unsigned char dyn_smem[];
     __shared__ MergeSmem sm;
-    merge_phase<ROWS, MW, J, false>(p, rowlists, conskeys, (int)(k_inv & 0xFFFFu), k_inv >> 16, (int)blockIdx.x, sm,
-                                    reinterpret_cast<u64 *>(dyn_smem), 0, 0, false);
+    merge_phase<ROWS, MW, J, false, EMPTY>(p, rowlists, conskeys, (int)(k_inv & 0xFFFFu), k_inv >> 16, (int)blockIdx.x, sm,
+                                           reinterpret_cast<u64 *>(dyn_smem), 0, 0, false);
 }
 
 // Reference read: the largest element of each row, one workgroup per row, with the tile order and
@@ -589,16 +589,21 @@ constexpr size_t spread_lds(size_t n)
     return align_up(kLdsPerUnit / (n + 1) + 1 - sizeof(StreamSmem<NW>), 256);
 }
 
+// Where steps may take one launch: a compute unit has one or two rows and their latencies show.  (Wider beams have more
+// to merge than a row's workgroup has waves for.)
+bool one_launch_shape(size_t B, size_t k) { return B * k <= 2 * kComputeUnits && k <= 32; }
+
 // How the stream phase of a step is launched: one workgroup per beam row, and
 struct StreamPlan {
+    bool one;               // launch does for the whole step, if the options leave it open
     int waves;              // of a workgroup: 4 or 8
     int tiles;              // of 4 KB that each wave keeps in flight
     size_t spare_lds;       // LDS a workgroup asks for and does not use, which keeps others off its compute unit
     uint32_t rows_abreast;  // rows of the sentences that are numbered eight abreast
 };
 
-// one: the step takes one launch
-StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem, bool one)
+// free: the options leave the number of launches open
+StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem, bool free)
 {
     StreamPlan plan;
     const size_t rows = B * k, row_bytes = V * elem;
@@ -617,6 +622,12 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem, bool one)
     // row and fewer sums are looked at closely); four otherwise - with rows of 64-128 KB and
     // thousands of them, twice the workgroups per compute unit stream faster than twice the waves.
     plan.waves = ((rows <= 512 && row_bytes >= 32768) || row_bytes >= 163840) ? 8 : 4;
+    // One launch for the whole step where the shape allows it and a row's workgroup has the waves to merge with: beyond k = 16
+    // eight.  Per step, two launches / one, 16 to 512 rows of 100 to 32000 elements: with k up to 8 0.4 to 1.4 us less, 9 to 11 0.1 to 0.9,
+    // 12 to 16 0.6 to 1.4; k = 17 to 32 with eight waves 0.7 to 1.35 (500 rows of 32000, k = 20, 19.95 / 18.8; 256 rows, k = 32,
+    // 16.5 / 15.45), but with four up to 0.35 more at k = 18, 0.5 at 24, 0.9 at 28 and 1.2 at 32 (256 rows of 2000, k = 32: 11.7 / 13.4
+    // before this line was drawn; with bf16 0.25 less to 0.3 more up to 24, beyond as with fp32).
+    plan.one = free && one_launch_shape(B, k) && (k <= 16 || plan.waves == 8);
     // Rows side by side on a compute unit.  More than a unit's even share leaves others short, and lets a
     // second decode's rows in beside the first one's: where the grid fills the chip, no more than that share
     // (three decodes of 64 x 20 rows of 32000 in flight: 84 against 94 us for three steps, one of them alone
@@ -641,15 +652,9 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem, bool one)
     // seven tiles a wave on, six with two elements in the place of one (240 KB: fp32 22.55 / 22.65 and 28.1 / 28.25, bf16 21.55 / 22.85;
     // 200 KB: bf16 20.35 / 20.85 and 26.55 / 26.8; 400 KB: fp32 30.05 / 31.2 and 39.45 / 40.0, at 260 and 500 rows).
     const bool long_rows = row_bytes >= (elem == 4 ? 7u : 6u) * 8 * 4096;
-    plan.tiles = plan.waves == 8 && (rows <= kComputeUnits || (one && long_rows)) ? 4 : 2;
+    plan.tiles = plan.waves == 8 && (rows <= kComputeUnits || (plan.one && long_rows)) ? 4 : 2;
     return plan;
 }
-
-// Where a step is one launch: a compute unit has one or two rows and their latencies show (per step, two launches / one: 400 rows
-// of 8000 fp32 12.75 / 12.4 us, 480 of 4000 bf16 12.3 / 11.7, 320 of 2000 10.25 / 9.85, 260 of 32000 16.65 / 16.45; from 500 rows
-// of 32000 on there is little left to gain, 19.8 / 19.7 and 17.7 / 17.7).  (Wider beams have more to merge
-// than a row's workgroup has waves for.)
-bool one_launch_shape(size_t B, size_t k) { return B * k <= 2 * kComputeUnits && k <= 32; }
 
 // How often a sentence's workgroup looks for the rows' keys: a look takes about a microsecond, and the rows two to four times
 // less than these, as many as at 2 TB/s.  Beyond, the row that ends last takes the sentence on, which costs the step the 2 us
@@ -1027,6 +1032,8 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         return fail(c, DBA_EINVAL, "dba_step: logp_dev must be aligned to its element size (%u bytes)", elem);
     if (c->steps >= c->N) return fail(c, DBA_ESTATE, "dba_step: all N=%d steps have been taken", c->N);
 
+    // one workgroup per beam row, 4 loads of 16 bytes per lane and tile, two or four 4 KB tiles in flight per wave
+    const StreamPlan plan = stream_plan((size_t)c->B, (size_t)c->k, (size_t)c->V, elem, c->one_launch && c->merge_waves == 0);
     const int cur = c->steps & 1, nxt = cur ^ 1;
     const Layout &L = c->L;
     StepParams p;
@@ -1053,6 +1060,8 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     set_tables(c, p);
     p.rowlists = own_scratch ? reinterpret_cast<u64 *>(own_scratch) : at<u64>(c, L.rowlists);
     p.conskeys = own_scratch ? reinterpret_cast<u64 *>(own_scratch + kStaticListBytes) : at<u64>(c, L.conskeys);
+    // (k > 16: what a step's rows are made of decides how many launches it takes; one must find the places empty after two)
+    const bool leave_empty = c->one_launch && c->merge_waves == 0 && !plan.one && !own_scratch;
     p.out_token = out_token_dev;
     p.out_backptr = out_backptr_dev;
     p.out_score = out_score_dev;
@@ -1061,14 +1070,11 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     p.hist_token = at<int32_t>(c, L.hist_token) + hrow;
     p.hist_backptr = at<int32_t>(c, L.hist_backptr) + hrow;
 
-    // one workgroup per beam row, 4 loads of 16 bytes per lane and tile, two or four 4 KB tiles in flight per wave
-    const bool one = c->one_launch && c->merge_waves == 0;
-    const StreamPlan plan = stream_plan((size_t)c->B, (size_t)c->k, (size_t)c->V, elem, one);
     const dim3 grid((unsigned)c->B * (unsigned)c->k);
     const uint32_t inv_k = (uint32_t)(((1ull << 32) + (unsigned)c->k - 1) / (unsigned)c->k);
     const int kf = p.k | (p.first_step << 16);
     const uint32_t inv_k16 = (uint32_t)(c->k == 1 ? 65535 : 65536 / c->k + 1);
-    if (one) {
+    if (plan.one) {
         // (the places are empty between steps, which only the ctx's own are)
         p.rowlists = at<u64>(c, L.rowlists);
         p.conskeys = at<u64>(c, L.conskeys);
@@ -1097,8 +1103,7 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         } else {
             if (c->k <= 8) ONE_ANY(4, 2, 2, 4, 1)
             else if (c->k <= 11) ONE_ANY(4, 2, 4, 4, 2)
-            else if (c->k <= 16) ONE_ANY(4, 2, 4, 4, -1)
-            else ONE_ANY(4, 2, 8, 4, -1)
+            else ONE_ANY(4, 2, 4, 4, -1)
         }
 #undef ONE_ANY
 #undef ONE
@@ -1136,21 +1141,22 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         const dim3 mgrid((unsigned)c->B);
         const int mw = c->merge_waves ? c->merge_waves : (c->k <= 16 ? 4 : c->k <= 32 ? 8 : 16);
         const uint32_t k_inv = (uint32_t)c->k | inv_k16 << 16;
-#define MERGE(ROWS, MW, J) \
-    dba_merge_kernel<ROWS, MW, J><<<mgrid, MW * kWave, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, k_inv, p)
+#define MERGE(ROWS, MW, J, EMPTY) \
+    dba_merge_kernel<ROWS, MW, J, EMPTY><<<mgrid, MW * kWave, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, k_inv, p)
         if (mw == 4) {
-            if (c->k <= 8) MERGE(2, 4, 1);
-            else if (c->k <= 11) MERGE(4, 4, 2);
-            else if (c->k <= 16) MERGE(4, 4, -1);
-            else if (c->k <= 32) MERGE(8, 4, -1);
-            else MERGE(16, 4, 0);
+            if (c->k <= 8) MERGE(2, 4, 1, false);
+            else if (c->k <= 11) MERGE(4, 4, 2, false);
+            else if (c->k <= 16) MERGE(4, 4, -1, false);
+            else if (c->k <= 32) MERGE(8, 4, -1, false);
+            else MERGE(16, 4, 0, false);
         } else if (mw == 16) {
-            MERGE(4, 16, 0);
+            MERGE(4, 16, 0, false);
         } else {
-            if (c->k <= 8) MERGE(2, 8, 1);
-            else if (c->k <= 11) MERGE(2, 8, 2);
-            else if (c->k <= 32) MERGE(4, 8, -1);
-            else MERGE(8, 8, 0);
+            if (c->k <= 8) MERGE(2, 8, 1, false);
+            else if (c->k <= 11) MERGE(2, 8, 2, false);
+            else if (c->k <= 32 && leave_empty) MERGE(4, 8, -1, true);
+            else if (c->k <= 32) MERGE(4, 8, -1, false);
+            else MERGE(8, 8, 0, false);
         }
 #undef MERGE
     }
@@ -1405,12 +1411,18 @@ DBA_API int dba_debug_sentences_first(dba_ctx *c, int on)
     return c->one_launch && c->merge_waves == 0 ? 1 : 0;
 }
 
+DBA_API int dba_debug_launches(int B, int k, int V, int logp_format)
+{
+    if (!shape_ok(B, k, V, 1, 0) || logp_format < DBA_LOGP_F32 || logp_format > DBA_LOGP_BF16)
+        return fail(nullptr, DBA_EINVAL, "dba_debug_launches: bad argument");
+    return stream_plan((size_t)B, (size_t)k, (size_t)V, logp_format == DBA_LOGP_F32 ? 4u : 2u, true).one ? 1 : 2;
+}
+
 DBA_API int dba_debug_stream_plan(int B, int k, int V, int logp_format, int32_t *plan_host)
 {
     if (!shape_ok(B, k, V, 1, 0) || !plan_host || logp_format < DBA_LOGP_F32 || logp_format > DBA_LOGP_BF16)
         return fail(nullptr, DBA_EINVAL, "dba_debug_stream_plan: bad argument");
-    const StreamPlan plan = stream_plan((size_t)B, (size_t)k, (size_t)V, logp_format == DBA_LOGP_F32 ? 4u : 2u,
-                                        one_launch_shape((size_t)B, (size_t)k));
+    const StreamPlan plan = stream_plan((size_t)B, (size_t)k, (size_t)V, logp_format == DBA_LOGP_F32 ? 4u : 2u, true);
     plan_host[0] = plan.waves;
     plan_host[1] = plan.tiles;
     plan_host[2] = (int32_t)((plan.waves == 8 ? sizeof(StreamSmem<8>) : sizeof(StreamSmem<4>)) + plan.spare_lds);

@@ -1148,7 +1148,8 @@ __device__ __forceinline__ void clear_for_merge(const StepParams &p, int tid, in
 // with which i * inv_k >> 16 is i / k for i < k * k, k <= 32).
 // ONE: most_tries, how often a wave looks for the rows' keys before it asks whether to go on (if not, the workgroup leaves and
 // has written nothing); all_ended, the sentence was left to this workgroup, a row's, as every row has ended.
-template <int ROWS, int MW, int J, bool ONE>
+// EMPTY: the row lists are left empty, as a step of one launch finds and leaves them.
+template <int ROWS, int MW, int J, bool ONE, bool EMPTY>
 __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowlists, const u64 *conskeys, int k,
                                             uint32_t inv_k, int b, MergeSmem &sm, u64 *cand, int P_here, int most_tries,
                                             bool all_ended)
@@ -1701,11 +1702,14 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     if constexpr (ONE) {
         const int verdict = __builtin_amdgcn_readfirstlane(sm.verdict);
         if (verdict == kLeaves) return;
-        // the next step finds the places empty, and once the last row has counted itself, no row ended
+        // once the last row has counted itself, the next step finds no row ended,
+        if (wave == 2 && lane == 0)
+            __hip_atomic_fetch_add(&p.best[b].ended, -(k + (all_ended || verdict == kGoesOn ? kGivenUp : 0)), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if constexpr (EMPTY) {
+        // and the places empty
         if (wave >= 2) {
-            if (wave == 2 && lane == 0)
-                __hip_atomic_fetch_add(&p.best[b].ended, -(k + (all_ended || verdict == kGoesOn ? kGivenUp : 0)), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
             for (int h = wave - 2; h < k; h += MW - 2) {
                 const size_t o = ((size_t)b * k + h) * kWave + lane;
                 if (lane < k) hand_over(p.rowlists + o, 0);

@@ -480,3 +480,43 @@ def test_blocks_of_host_memory_are_freed_beside_a_capture():
     ses = decode()
     assert [np.asarray(a).tobytes() for a in ses.finalize()] == want[0]
     ses.close()
+
+
+def test_one_launch_and_two_by_turns():
+    """With k > 16 the element type decides (32 KB a row): steps of one ctx that take one launch and two by turns, eager
+    and replayed from a graph, leave nothing behind for each other; an element type and back, the library's own scratch among them."""
+    import torch
+    import paper_1804_06609_amd as dba
+    B, k, V, T = 6, 20, 9000, 9
+    assert (dba.dba_debug_launches(B, k, V, dba.DBA_LOGP_F32), dba.dba_debug_launches(B, k, V, dba.DBA_LOGP_F16)) == (1, 2)
+    wl = si.make_small(9600, B, k, V, 3 * T, max_phrases=4, max_len=3, dup_prob=0.3)
+    wl.eos_switch = 7
+    dev = [torch.from_numpy(wl.logp(t)).cuda().to(torch.float16 if t % 3 == 1 else torch.float32) for t in range(T)]
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        two, _ = _one_launch_decode(wl, dev, stream, 0, waves=8)
+        ses, one = _one_launch_decode(wl, dev, stream, 0)
+        assert one
+        for t in range(T):
+            two.step(dev[t])
+            ses.step(dev[t], noalloc=t % 4 == 1)
+            want = [a.tobytes() for a in two.outputs()] + [a.tobytes() for a in two.state().values()]
+            assert [a.tobytes() for a in ses.outputs()] + [a.tobytes() for a in ses.state().values()] == want, t
+        # a step of one launch from a graph, behind eager steps of two
+        graph = torch.cuda.CUDAGraph()
+        stream.synchronize()
+        graph.capture_begin()
+        ses.step(dev[0])
+        graph.capture_end()
+        two.step(dev[0])
+        want = [a.tobytes() for a in two.outputs()]
+        for _ in range(3):
+            graph.replay()
+            assert [a.tobytes() for a in ses.outputs()] == want
+        for t in (1, 2):
+            two.step(dev[t])
+            ses.step(dev[t])
+            assert [a.tobytes() for a in ses.outputs()] == [a.tobytes() for a in two.outputs()], t
+        ses.close()
+        two.close()

@@ -70,3 +70,18 @@ def test_tiles_in_flight_beyond_a_row_per_compute_unit():
                                 (4, 33, 100000, f32, 4)):
         waves, got = dba.dba_debug_stream_plan(B, k, V, fmt)[:2]
         assert (waves, got) == (8, tiles), (B, k, V, fmt, got)
+
+
+def test_a_step_takes_one_launch_where_its_rows_have_the_waves_to_merge_with():
+    """Up to 512 rows: always to k = 16, from there to k = 32 with eight waves a row, which rows of 32 KB and more have."""
+    f32, f16 = dba.DBA_LOGP_F32, dba.DBA_LOGP_F16
+    for B, k, V, fmt, launches in ((1, 1, 1, f32, 1), (512, 1, 100, f32, 1), (513, 1, 100, f32, 2), (32, 16, 100, f16, 1), (33, 16, 100, f32, 2),
+                                   (1, 17, 8191, f32, 2), (1, 17, 8192, f32, 1), (30, 17, 16383, f16, 2), (30, 17, 16384, f16, 1),
+                                   (16, 32, 2000, f32, 2), (16, 32, 32000, f32, 1), (17, 32, 32000, f32, 2), (1, 33, 32000, f32, 2)):
+        assert dba.dba_debug_launches(B, k, V, fmt) == launches, (B, k, V, fmt)
+    for bad in ((0, 1, 100, 0), (1, 65, 100, 0), (1, 5, 100, 3)):
+        try:
+            dba.dba_debug_launches(*bad)
+        except dba.DbaError:
+            continue
+        raise AssertionError(bad)
