@@ -483,12 +483,14 @@ struct RowStream {
         vec = reinterpret_cast<const vec_t *>(row + head);
         ntiles = (nv + kWave * U - 1) / (kWave * U);
         body = __builtin_amdgcn_make_buffer_rsrc(const_cast<vec_t *>(vec), 0, nv * (int)sizeof(vec_t), kRawBuffer);
-        // (a tile that is not there is not requested: it would read nothing, but its requests take their turn.  Per step, many
-        // rows of one tile or two: 2010 of 1296 fp32 with most of them empty 9.45 -> 8.45 us, 4000 of 1000 26.2 -> 25.45, 8192
-        // of 1000, k = 64, 56.1 -> 54.8; 320 of 2000 9.55 -> 9.25)
+        // (A wave that has no tile requests none: its requests would read nothing, but take their turn.  Per step, many rows of one
+        // tile or two: 2010 of 1296 fp32 with most of them empty 9.5 -> 8.6 us, 8192 of 1000, k = 64, 55.8 -> 54.4, 320 of 2000 9.8 ->
+        // 9.4.  The second tile shares the branch: in one of its own the wait for the first would be for both, 2123
+        // rows of 6910 bf16 19.8 -> 20.0.)
+        if (wave < ntiles) {
 #pragma unroll
-        for (int d = 0; d < 2; ++d)
-            if (wave + d * nwaves < ntiles) load(wave + d * nwaves, tile_[d]);
+            for (int d = 0; d < 2; ++d) load(wave + d * nwaves, tile_[d]);
+        }
         lone = 0;
         if (wave == 0 && lane < head + tail) lone = row[lone_at(lane)];
     }
