@@ -174,9 +174,14 @@ constexpr int kKeyCap = 128;          // and keys it can park there
 // rests on the whole row (2400 rows of 9000 fp16, k = 20: 22.5 / 23.5; 2048 of 8000 fp32, k = 32: 22.8 / 23.4; but 1280 of 32000 bf16, k =
 // 20: 23.5 / 23.2; 2048 of 32000 fp32, k = 32: 49.3 / 49.0).  160 rows of 32000 fp32, k = 10: 13.4 / 13.9; with eight waves 192, k = 32,
 // 15.8 / 17.2, 1024 of 100000 bf16, k = 32, 42.2 / 44.4.
-__device__ __forceinline__ bool floor_from_cells(int k, int ntiles, int nwaves)
+// Nor for more than the cells that hold an element, which can be fewer in rows of one tile or two (1872 rows of 131 fp16, k = 8:
+// four cells hold any, and a floor from sixteen was none, 15.6 us against 14.15): groups are dealt out lane by lane, and
+// with three tiles more lanes have one than five eighths of the cells need.  (Eight waves have rows of eight tiles and more.)
+template <int NW, int U>
+__device__ __forceinline__ bool floor_from_cells(int k, int ngroups, int ntiles)
 {
-    return 8 * k <= 5 * (kWave / nwaves) * min(nwaves, ntiles) && (nwaves == 8 || k <= 16 || ntiles <= 2 * nwaves);
+    return 8 * k <= 5 * (kWave / NW) * min(NW, ntiles) && (NW == 8 || k <= 16 || ntiles <= 2 * NW) &&
+           (NW == 8 || k * NW <= ngroups - (ntiles - 1) * (kWave * (U - 1)));
 }
 
 // Keys of one wave folded into its sorted list 64 at a time: one 64-lane sort and one merge per
@@ -543,14 +548,14 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
     }
     // Any k values that different lanes hold give a valid floor
     constexpr int share = kWave / nwaves;              // entries of every wave that fit one 64-lane sort
-    if (floor_from_cells(kk, ntiles, nwaves)) {
+    if (floor_from_cells<NW, U>(kk, nv, ntiles)) {
         boot = max_of_lanes<nwaves>(boot);
         if (lane % nwaves == 0) sm.boot[wave][lane / nwaves] = boot;
         __syncthreads();
         boot = sm.boot[lane / share][lane % share];
         boot = LL ? sort64_minmax_desc(boot) : sort64_desc<uint32_t, false>(boot);
     } else {
-        boot = sort64_desc<uint32_t, LL>(boot);
+        if (NW == 8 || wave < ntiles) boot = sort64_desc<uint32_t, LL>(boot);      // (the others hold the same in every lane)
         sm.boot[wave][lane] = boot;
         __syncthreads();
         if (kk <= 3 * share) {

@@ -422,6 +422,18 @@ def test_floors_from_cells_and_from_sorted_lists(torch_gpu, V, fmt, ks):
         _harness().run_parity(wl, logp_format=fmt)
 
 
+@pytest.mark.parametrize("V,fmt,ks", [(40, None, (1, 2, 3)), (102, None, (6, 7, 9)), (255, None, (9, 10, 11)), (131, "f16", (4, 5, 8)), (88, "bf16", (2, 3, 6)),
+                                      (1032, None, (16, 17, 20)), (1060, None, (18, 19, 20)), (1100, None, (20, 21)), (2100, None, (30, 31)),
+                                      (2074, "f16", (16, 17)), (3300, None, (33, 40)), (32788, None, (40, 41)), (16400, "bf16", (40, 41))])
+def test_floors_from_rows_that_do_not_reach_all_cells(torch_gpu, V, fmt, ks):
+    """The last of a workgroup's first tiles holds a few groups, some of its cells none: beams on either side of what
+    the filled cells allow."""
+    for k in ks:
+        wl = si.make_small(5750 + k, 2, k, V, 3, max_phrases=2, max_len=2, dup_prob=0.3)
+        wl.eos_switch = 2
+        _harness().run_parity(wl, logp_format=fmt)
+
+
 @pytest.mark.parametrize("V,fmt", [(4, None), (1028, None), (2044, None), (4100, None), (8196, None), (9212, None), (32772, None), (33788, None),
                                    (40959, None), (8, "f16"), (2056, "bf16"), (4088, "f16"), (18424, "bf16"), (67593, "f16")])
 def test_partial_tiles(torch_gpu, V, fmt):
