@@ -1129,7 +1129,9 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
 #undef STREAM
         // The merge phase is compiled for (rows per wave, waves, entries per lane).  Unless the caller fixes the
         // waves: four up to k = 16, eight up to 32, sixteen beyond (16 sentences of 2000 tokens, k = 64: 18.1 us per step with
-        // eight, 17.4 with sixteen; 4 of 32000 21.45 / 20.95; fewer lists per wave to merge and to scan, more waves to rank
+        // eight, 17.4 with sixteen; 4 of 32000 21.45 / 20.95 - as long as every
+        // sentence has a compute unit to itself, since no second workgroup of sixteen fits there (seven waves a SIMD, by scalar registers): 256 of 1000, k = 64, 91.8 / 91.0, 257
+        // 93.8 / 98.4, 1000 315.6 / 329.3; fewer lists per wave to merge and to scan, more waves to rank
         // candidates, at the price of a deeper tree where the waves' lists are joined; one decode, per step: 22.1 / 22.3 us with
         // four / eight waves at k = 12, 14.7 / 14.7 at k = 16; merge kernel 7.7 / 7.0 us at k = 20, 19.3 / 14.6 at k = 64).
         // Up to k = 11 every wave holds the k * k entries that matter, one or two a lane, and finds the bar by
@@ -1139,7 +1141,7 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         // k = 32 two rows share a register (k = 16: 14.9 against 15.4; k = 20: 32.6 against 33.1, with bf16 22.7 against
         // 23.4; k = 32: 49.1 against 49.6); beyond, a row's list needs all 64 lanes.
         const dim3 mgrid((unsigned)c->B);
-        const int mw = c->merge_waves ? c->merge_waves : (c->k <= 16 ? 4 : c->k <= 32 ? 8 : 16);
+        const int mw = c->merge_waves ? c->merge_waves : (c->k <= 16 ? 4 : c->k <= 32 || c->B > (int)kComputeUnits ? 8 : 16);
         const uint32_t k_inv = (uint32_t)c->k | inv_k16 << 16;
 #define MERGE(ROWS, MW, J, EMPTY) \
     dba_merge_kernel<ROWS, MW, J, EMPTY><<<mgrid, MW * kWave, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, k_inv, p)

@@ -455,6 +455,14 @@ def test_many_sentences_long_decode(torch_gpu):
     _harness().run_parity(wl, check_state_every=10, normalize=True, prune=20.0)
 
 
+@pytest.mark.parametrize("B,k", [(256, 33), (257, 33), (300, 64)])
+def test_wide_beams_of_more_sentences_than_compute_units(torch_gpu, B, k):
+    """Sixteen merge waves a sentence up to 256 sentences, eight beyond."""
+    wl = si.make_small(5900 + B, B, k, 90, 4, max_phrases=4, max_len=2, dup_prob=0.3)
+    wl.eos_switch = 2
+    _harness().run_parity(wl, oracle_sentences=[0, 1, 100, 255, B - 1])
+
+
 def test_most_candidates(torch_gpu):
     """The widest beam with 64 one-token constraints: k * (64 + 2) candidates per sentence at most,
     the largest candidate buffer the merge phase can need."""
