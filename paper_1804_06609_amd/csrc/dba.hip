@@ -580,6 +580,7 @@ bool staged_tokens(size_t B, size_t N) { return B * N * 4 <= 512 * 1024; }
 
 constexpr size_t kComputeUnits = 256;
 constexpr size_t kLdsPerUnit = 160 * 1024;
+constexpr size_t kLdsPerLaunch = 64 * 1024;   // what a launch may ask for as it is
 
 // LDS to add to a stream-phase workgroup of NW waves so that no more than n <= MOST of them fit a compute unit
 template <int NW, int MOST>
@@ -955,9 +956,11 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     (void)static_scratch(&own);          // dba_step_noalloc asks again (and reports) if this failed
     c->lib_scratch = static_cast<unsigned char *>(own);
     // candidates of one sentence: at most k best + k row bests + k * phrases constraint tokens,
-    // in whole chunks of 64 keys (at most 4224 keys = 33 KB of LDS)
+    // in whole chunks of 64 keys
     const int ncand_max = (k * (max_phrases + 2) + kWave - 1) / kWave * kWave;
     c->cand_cap = ncand_max;
+    constexpr size_t most_cand = (size_t)DBA_MAX_BEAM * (DBA_MAX_CONS_TOKENS + 2) * sizeof(u64) + kMostLeft * (sizeof(u64) + sizeof(int));
+    static_assert(sizeof(MergeSmem) + 16 + most_cand <= kLdsPerLaunch, "k = 64 with 64 phrases: 45 KB beside the merge phase's own 18");
     c->dyn_smem = (size_t)ncand_max * sizeof(u64) + (ncand_max > 4 * kWave ? kMostLeft * (sizeof(u64) + sizeof(int)) : 0);
 
     // (without a block the words pass through the row lists' place, which is large enough and not in use yet)
