@@ -93,6 +93,9 @@ def guarded_decode(case):
         cons = si.fixed_total_constraints(61, B, V, 64, max_len=4)
         wl = si.Workload(B=B, k=k, V=V, T=T, seed=61, constraints=cons,
                          boost_tokens=[[w for p in s for w in p] for s in cons], boost_prob=0.3, boost_value=6.0)
+    elif case == "noalloc_two_launches":                   # (the library's own scratch passes the keys on)
+        wl = si.make_small(9962, 4, 35, 4099, 10, max_phrases=5, max_len=3, dup_prob=0.3)
+        assert dba.dba_debug_launches(wl.B, wl.k, wl.V) == 2
     else:
         wl = si.make_small(9961, 4, 13, 4099, 10, max_phrases=5, max_len=3, dup_prob=0.3)
     wl.eos_switch = wl.T // 2
@@ -118,7 +121,7 @@ def guarded_decode(case):
             else:
                 dev = torch.from_numpy(si.narrow16(lp, fmt).view(np.int16)).cuda().view(torch.bfloat16)
                 code = dba.DBA_LOGP_BF16
-            step = dba.dba_step_noalloc if case == "noalloc" else dba.dba_step_fmt
+            step = dba.dba_step_noalloc if case.startswith("noalloc") else dba.dba_step_fmt
             step(ctx, dev.data_ptr(), code, o_tok.ptr, o_bp.ptr, o_sc.ptr, o_fl.ptr)
             torch.cuda.synchronize()
             got.append(o_tok.body().cpu().numpy().tobytes())
@@ -173,7 +176,7 @@ def test_the_end_of_a_decode_is_the_same_however_long_its_token_rows_are(N):
 
 
 def test_a_decode_replayed_from_a_hip_graph_matches_eager_launches():
-    """A step enqueues two kernels and nothing else (no allocation, no memset, no copy), so a decode can
+    """A step enqueues one kernel (here) or two and nothing else (no allocation, no memset, no copy), so a decode can
     be recorded into a HIP graph by a caller who wants to.  Steps 1..T-1 of a decode are recorded once and replayed three times, each
     time from the device state after step 0 (the workspace is copied back, with eager work and
     synchronisations in between); every replay must leave the beam, the state and the end of
