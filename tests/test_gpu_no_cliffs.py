@@ -7,7 +7,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def step_us(B, k, V, dtype="float32", steps=24, skip=4, repeats=7, equal=0.0):
+def step_us(B, k, V, dtype="float32", steps=24, skip=4, repeats=7, equal=0.0, options=None):
     """Least time of a step (stream and merge kernel), in us, over a few decodes of random log-probs, the share
     `equal` of every row equal and best."""
     import torch
@@ -20,7 +20,8 @@ def step_us(B, k, V, dtype="float32", steps=24, skip=4, repeats=7, equal=0.0):
         lp[..., :int(equal * V)] = -0.5
     best = np.inf
     for _ in range(repeats):
-        ses = Session(B, k, V, steps, 2, 0, np.zeros(0, np.int32), np.zeros(1, np.int32), np.zeros(B + 1, np.int32))
+        ses = Session(B, k, V, steps, 2, 0, np.zeros(0, np.int32), np.zeros(1, np.int32), np.zeros(B + 1, np.int32),
+                      options=options)
         start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         for t in range(steps):
             if t == skip:
@@ -54,6 +55,25 @@ def test_rows_that_tie_take_little_longer_than_others(equal, dtype):
     since ties beyond the first k are passed over."""
     plain, tied = step_us(64, 20, 32000, dtype), step_us(64, 20, 32000, dtype, equal=equal)
     assert tied < 1.75 * plain, (plain, tied)
+
+
+@pytest.mark.parametrize("B,k,V,dtype,bound", [(8, 32, 2000, "float32", 1.045), (16, 32, 2000, "float32", 1.04), (25, 20, 32000, "bfloat16", 1.0),
+                                               (40, 10, 8000, "float32", 1.01), (4, 5, 1000, "float32", 1.0), (1000, 33, 1000, "float32", 1.025)])
+def test_the_default_is_no_slower_than_two_launches_with_eight_merge_waves(B, k, V, dtype, bound):
+    """1.09 and 1.07 times their time with k = 32 and rows of 2000 when those took one launch, 1.01 since they take two; 0.92,
+    0.95 and 0.9 where one launch is ahead; and 1.05 with more sentences than compute units when they got sixteen merge waves
+    each, the same since they get eight."""
+    import paper_1804_06609_amd as dba
+    default, eight = step_us(B, k, V, dtype), step_us(B, k, V, dtype, options={dba.DBA_OPT_MERGE_WAVES: 8})
+    assert default < bound * eight, (default, eight)
+
+
+@pytest.mark.parametrize("B,k,bound", [(234, 8, 1.1), (217, 10, 1.16)])
+def test_rows_that_do_not_reach_all_cells_take_little_longer_than_longer_ones(B, k, bound):
+    """Rows of 131 fp16 against 400: 1.14 and 1.21 times the time when the floor was taken from cells most of which held nothing,
+    1.05 and 1.11 since it is not."""
+    few, more = step_us(B, k, 131, "float16"), step_us(B, k, 400, "float16")
+    assert few < bound * more, (few, more)
 
 
 def test_many_tokens_reach_pinned_memory_at_the_speed_of_a_copy():
