@@ -37,8 +37,8 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E peak
 # rocprofv3 FETCH_SIZE / WRITE_SIZE runs summarised in profiles/ (scaled against a plain copy), and
 # the digest of the kernel sources those counters were taken with: the line carries the figure only
 # while the sources are still those, null otherwise.
-TRAFFIC_BYTES_PER_LAUNCH = 167104336
-TRAFFIC_KERNEL_SHA16 = "a2675bb49afe5d64"
+TRAFFIC_BYTES_PER_LAUNCH = 167110738
+TRAFFIC_KERNEL_SHA16 = "ef247d2649da62b6"
 
 
 def kernel_sources_sha16() -> str:
