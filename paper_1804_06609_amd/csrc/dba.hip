@@ -167,8 +167,9 @@ __global__ __launch_bounds__(NW * kWave) void dba_stream_kernel(const void *logp
 // sentence through the merge phase.  Such a step is a chain of latencies, and the end of one kernel, the start of the
 // next and its wait for the row lists were 2.2 us of it; here a sentence's workgroup has its tables in LDS before the
 // rows are through and reads their places in the row lists again and again until all are filled (a store is seen
-// there after 0.7 to 1.2 us).  Per step, two launches / one: 5 rows of 1000 9.2 / 8.4 us, 160 of 32000 13.05 / 12.75, 168 of 50001
-// 14.2 / 13.45, 240 of 9000 10.95 / 9.95, 192 with k = 16 13.85 / 12.85, one sentence of ten rows 11.15 / 11.05.
+// there after 0.7 to 1.2 us).  Per step, two launches / one: 5 rows of 1000 9.25 / 8.65 us, 160 of 32000 13.05 / 12.55, 168 of 50001
+// 14.3 / 13.35, 240 of 9000 10.95 / 10.2, 192 with k = 16 13.9 / 12.7, 256 with k = 32 16.4 / 15.5, one sentence of ten rows 11.7 / 11.5,
+// 400 rows of 8000 12.75 / 12.35, 500 of 32000 19.9 / 18.7.
 //
 // Every wait ends, and with the right answer.  A row waits for nothing; when its keys have reached memory it counts itself
 // among the sentence's ended rows.  A sentence's workgroup that has looked for the keys most_tries times - the rows may be
