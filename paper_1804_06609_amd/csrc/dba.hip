@@ -1214,9 +1214,14 @@ DBA_API int dba_finalize(dba_ctx *c, int32_t *out_tokens_host, int32_t *out_len_
     const size_t B = (size_t)c->B, tokens_bytes = B * c->N * 4;
     const bool staged = staged_tokens(B, (size_t)c->N);
     // The four results lie side by side, small ones all in the block, where the kernel writes them; tokens beyond
-    // stay in the workspace and go straight to the caller's array.  Without a block each is copied.
-    const size_t first = staged ? L.fin_tokens : L.fin_len;
+    // stay in the workspace and go straight to the caller's array.  Without a block one copy takes what the block would
+    // hold (5000 sentences, 20 steps: 71 us, 91 with a copy each); without host memory for that, each goes straight.
+    const size_t first = staged ? L.fin_tokens : L.fin_len, bytes = L.fin_status + B * 4 - first;
     unsigned char *here = c->block.p ? c->block.p + c->block_data : nullptr;
+    struct Free {
+        unsigned char *p;
+        ~Free() { free(p); }
+    } copied{here ? nullptr : static_cast<unsigned char *>(malloc(bytes))};
     auto place = [&](size_t off) {
         return reinterpret_cast<int32_t *>(here && off >= first ? here + (off - first) : c->ws + off);
     };
@@ -1228,24 +1233,25 @@ DBA_API int dba_finalize(dba_ctx *c, int32_t *out_tokens_host, int32_t *out_len_
         place(L.fin_tokens), place(L.fin_len), reinterpret_cast<float *>(place(L.fin_score)), place(L.fin_status));
     hipError_t e = hipGetLastError();
     auto fetch = [&](void *to, size_t off, size_t n) {
-        if (e == hipSuccess && !(here && off >= first))
+        if (e == hipSuccess && !((here || copied.p) && off >= first))
             e = hipMemcpyAsync(to, c->ws + off, n, hipMemcpyDeviceToHost, c->stream);
     };
     fetch(out_tokens_host, L.fin_tokens, tokens_bytes);
     fetch(out_len_host, L.fin_len, B * 4);
     fetch(out_score_host, L.fin_score, B * 4);
     fetch(out_status_host, L.fin_status, B * 4);
+    if (e == hipSuccess && copied.p) e = hipMemcpyAsync(copied.p, c->ws + first, bytes, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
         if (here) c->block.p = nullptr;                    // (a kernel may still write to it: never used again)
         return fail(c, DBA_EHIP, "dba_finalize: HIP error: %s", hipGetErrorString(e));
     }
     c->init_under_way = false;
-    if (here) {
-        if (staged) memcpy(out_tokens_host, place(L.fin_tokens), tokens_bytes);
-        memcpy(out_len_host, place(L.fin_len), B * 4);
-        memcpy(out_score_host, place(L.fin_score), B * 4);
-        memcpy(out_status_host, place(L.fin_status), B * 4);
+    if (const unsigned char *from = here ? here : copied.p) {
+        if (staged) memcpy(out_tokens_host, from, tokens_bytes);
+        memcpy(out_len_host, from + (L.fin_len - first), B * 4);
+        memcpy(out_score_host, from + (L.fin_score - first), B * 4);
+        memcpy(out_status_host, from + (L.fin_status - first), B * 4);
     }
     return DBA_OK;
 }
