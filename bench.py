@@ -38,7 +38,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E peak
 # the digest of the kernel sources those counters were taken with: the line carries the figure only
 # while the sources are still those, null otherwise.
 TRAFFIC_BYTES_PER_LAUNCH = 167110738
-TRAFFIC_KERNEL_SHA16 = "384e1836e09ade84"
+TRAFFIC_KERNEL_SHA16 = "523eb1ab61234472"
 
 
 def kernel_sources_sha16() -> str:
