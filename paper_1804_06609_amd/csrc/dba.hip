@@ -47,34 +47,34 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
     if (!known_empty) rs.begin(logp_row, V, wave, nwaves);
     __builtin_amdgcn_sched_barrier(0);
     // then the hypothesis and its constraint bookkeeping (one wave, one lane per phrase)
-    const float prev_ld = p.score_cur[row];
-    const int fin_ld = p.fin_cur[row];
+    const Sentence &sent = p.sentences[b];
+    const Hyp hyp = p.beam[row];
+    const int phrases = sent.nphr;
+    // The flags come by a vector load, which returns after those of the two tiles: whatever depends on them, the scattered
+    // gathers of the constraint tokens' log-probs above all, is then behind the tiles of the rows beside this one and not among
+    // them (per step, by a scalar load / like this: 798 rows of 16760 fp32 23.6 / 22.6 us, 768 of 16000 23.45 / 22.0, 800, k = 20,
+    // 19.6 / 18.6, 160 of 32000 12.25 / 12.1; ten rows of 32000, which have the chip to themselves, 10.15 / 10.4).
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    const uint32_t state_ld = (&p.beam[row].state)[zero];
     // workgroups are dealt out round-robin over the 256 compute units, so the ones sharing a
     // compute unit differ in (number / 256): let that pick the wave (hence the SIMD) that finishes the row
     const int fin_wave = (int)(blockIdx.x >> 8) & (nwaves - 1);
     const bool finisher = wave == fin_wave;
-    u64 g_met = 0, g_inc = 0, g_sfl = 0, t_bucket = 0;
-    int g_ipq = -1, g_nxt = -1, g_ftok = -1, g_P = 0, t_btok = -1;
-    if (gatherer || finisher) {
-        g_met = p.met_cur[row];
-        g_inc = p.inc_cur[row];
-        g_ipq = p.ipq_cur[row];
-        g_nxt = p.nxt_cur[row];
-        g_ftok = p.first_tok[(size_t)b * kMaxCons + lane];
-    }
-    if (gatherer) {
-        g_P = p.nphr[b];
-        g_sfl = p.same_first_lower[(size_t)b * kMaxCons + lane];
-    }
+    u64 g_sfl = 0, t_bucket = 0;
+    int g_ftok = -1, t_btok = -1;
+    if (gatherer || finisher) g_ftok = sent.first_tok[lane];
+    if (gatherer) g_sfl = sent.same_first_lower[lane];
     if (finisher) {
         // lane j: the phrases whose first token has low six bits j, and that token where they agree on it
-        t_bucket = p.first_bucket[(size_t)b * kMaxCons + lane];
-        t_btok = p.bucket_tok[(size_t)b * kMaxCons + lane];
+        t_bucket = sent.first_bucket[lane];
+        t_btok = sent.bucket_tok[lane];
     }
 
-    // the row's hypothesis: wave-uniform by construction, made so for the compiler
-    const float prev = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(prev_ld)));
-    const int fin = __builtin_amdgcn_readfirstlane(fin_ld);
+    asm volatile("" : : "s"(phrases));                   // (waited for together with the hypothesis)
+    const float prev = hyp.score;
+    const uint32_t state = (uint32_t)__builtin_amdgcn_readfirstlane((int)state_ld);
+    const int fin = flags_of(state), ipq = ipq_of(state);
     const uint32_t code_base = (uint32_t)h << p.tok_bits;
 
     RowTop st;
@@ -87,8 +87,8 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
         // it may place now; the log-prob is one 4-byte read per token, in flight during the stream
         int cw = -1, cbank = 0;
         if (gatherer)
-            cw = expandable_entry(g_P, __popcll(g_met), g_inc, g_ipq < 0 ? -1 : (g_ipq >> 8),
-                                  g_ipq < 0 ? 0 : (g_ipq & 255), g_nxt, g_ftok, g_sfl, cbank);
+            cw = expandable_entry(phrases, __popcll(hyp.met), hyp.inc, ipq < 0 ? -1 : (ipq >> 8), ipq < 0 ? 0 : (ipq & 255), hyp.nxt,
+                                  g_ftok, g_sfl, cbank);
         const float cx = cw >= 0 ? Logp<FMT>::widen_one(logp_row[cw]) : -INFINITY;
         // Sec. 3.3: no end-of-sentence before all constraints are met
         const int eos_block = (fin & kFinEosBlocked) ? p.eos_id : -1;
@@ -103,7 +103,7 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
     }
     if (gatherer) {
         if constexpr (ONE) {
-            if (lane < g_P) hand_over(p.conskeys + (size_t)row * kMaxCons + lane, ckey ? ckey : kNoKey);
+            if (lane < phrases) hand_over(p.conskeys + (size_t)row * kMaxCons + lane, ckey ? ckey : kNoKey);
         } else {
             p.conskeys[(size_t)row * kMaxCons + lane] = ckey;
         }
@@ -115,7 +115,7 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
         // looks its own token up in the sentence's table of first tokens, which the lanes of this
         // wave hold (lane j = bucket j): the phrases it could begin, then the count.
         // (every lane takes every step, so that any lane's table entry can be read)
-        const int nmet = __popcll(g_met);
+        const int nmet = __popcll(hyp.met);
         const bool extends = !(fin & kFinFinished) && acc != 0;      // not the carried-over key of a finished row
         const int w = extends ? (int)(key_flat(acc) & ((1u << p.tok_bits) - 1u)) : 0;
         const int same = __shfl(t_btok, w & 63, kWave);
@@ -130,8 +130,8 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
             todo &= todo - 1;
         }
         const int bank = !extends ? nmet
-                                  : nmet_after(nmet, g_ipq < 0 ? -1 : (g_ipq >> 8), g_ipq < 0 ? 0 : (g_ipq & 255),
-                                               w == g_nxt, match, g_inc);
+                                  : nmet_after(nmet, ipq < 0 ? -1 : (ipq >> 8), ipq < 0 ? 0 : (ipq & 255), w == hyp.nxt, match,
+                                               hyp.inc);
         const u64 key = sel_from_rowkey(p.met_bits, bank, acc);
         if constexpr (ONE) {
             if (lane < k) hand_over(p.rowlists + (size_t)row * kWave + lane, key ? key : kNoKey);
@@ -351,16 +351,16 @@ __global__ __launch_bounds__(kWave) void dba_init_kernel(int B, int k, const uin
     }
     // (past the L2, like every store here)
     auto put = [](auto *to, auto value) { __hip_atomic_store(to, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-    put(const_cast<int32_t *>(p.cons_tok) + at, tok);
-    int32_t *poff = const_cast<int32_t *>(p.phr_off) + (size_t)b * (kMaxCons + 1);
-    put(poff + lane, lane < P ? off[lane] : lane == P ? C : 0);
-    put(const_cast<int32_t *>(p.first_tok) + at, ftok);
-    put(const_cast<u64 *>(p.same_first_lower) + at, same_lower);
-    put(const_cast<u64 *>(p.first_bucket) + at, bucket);
-    put(const_cast<int32_t *>(p.bucket_tok) + at, btok);
+    Sentence *s = const_cast<Sentence *>(p.sentences) + b;
+    put(s->tok + lane, tok);
+    put(s->phr_off + lane, lane < P ? off[lane] : lane == P ? C : 0);
+    put(s->first_tok + lane, ftok);
+    put(s->same_first_lower + lane, same_lower);
+    put(s->first_bucket + lane, bucket);
+    put(s->bucket_tok + lane, btok);
     if (lane == 0) {
-        put(poff + kMaxCons, P == kMaxCons ? C : 0);
-        put(const_cast<int32_t *>(p.nphr) + b, P);
+        put(s->phr_off + kMaxCons, P == kMaxCons ? C : 0);
+        put(&s->nphr, P);
         put(p.all_finished + b, (uint8_t)0);
     }
     static_assert(sizeof(BestCompleted) == 4 * sizeof(u64), "four words");
@@ -372,13 +372,12 @@ __global__ __launch_bounds__(kWave) void dba_init_kernel(int B, int k, const uin
         }
     if (lane < k) {
         const size_t i = (size_t)b * k + lane;
-        put(p.score_nxt + i, lane == 0 ? 0.0f : -INFINITY);
-        put(p.met_nxt + i, (u64)0);
-        put(p.ipq_nxt + i, -1);
-        put(p.len_nxt + i, 0);
-        put(p.fin_nxt + i, (uint8_t)((lane == 0 && C > 0) ? kFinEosBlocked : 0));
-        put(p.inc_nxt + i, (lane == 0 && P > 0) ? (P == 64 ? ~0ull : ((1ull << P) - 1ull)) : 0ull);
-        put(p.nxt_nxt + i, -1);
+        put(&p.beam_nxt[i].score, lane == 0 ? 0.0f : -INFINITY);
+        put(&p.beam_nxt[i].state, state_word((lane == 0 && C > 0) ? kFinEosBlocked : 0, -1));
+        put(&p.beam_nxt[i].len, 0);
+        put(&p.beam_nxt[i].nxt, -1);
+        put(&p.beam_nxt[i].met, (u64)0);
+        put(&p.beam_nxt[i].inc, (lane == 0 && P > 0) ? (P == 64 ? ~0ull : ((1ull << P) - 1ull)) : 0ull);
     }
     if (seen) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -405,7 +404,7 @@ constexpr int kFinWaves = 8, kFinRows = 16, kFinSteps = kFinWaves * kFinRows;
 
 __global__ __launch_bounds__(kFinWaves * kWave) void dba_finalize_kernel(
     int B, int k, int T, int N, int pad_id, int normalized, const int32_t *hist_token, const int32_t *hist_backptr,
-    const float *score, const u64 *met, const int32_t *len, const uint8_t *fin, const BestCompleted *best_rec,
+    const Hyp *beam, const BestCompleted *best_rec,
     int32_t *out_tokens, int32_t *out_len, float *out_score, int32_t *out_status)
 {
     __shared__ uint8_t parent[kFinSteps][kWave];
@@ -438,9 +437,9 @@ __global__ __launch_bounds__(kFinWaves * kWave) void dba_finalize_kernel(
             slot = r.slot;
         } else {
             const size_t o = (size_t)b * k + (lane < k ? lane : 0);
-            const float s = score[o];
-            const int l = len[o];
-            const bool live = lane < k && s > -INFINITY, done = live && (fin[o] & kFinFinished) != 0;
+            const float s = beam[o].score;
+            const int l = beam[o].len;
+            const bool live = lane < k && s > -INFINITY, done = live && (flags_of(beam[o].state) & kFinFinished) != 0;
             const u64 any_done = __ballot(done), any_live = __ballot(live);
             u64 among = any_live;                          // slots still in question; ties go to the lowest
             uint32_t image = 0;
@@ -450,7 +449,7 @@ __global__ __launch_bounds__(kFinWaves * kWave) void dba_finalize_kernel(
                 if (done) image = ord_from_float(normalized ? s : __fdiv_rn(s, (float)l));
                 among = any_done;
             } else if (any_live) {
-                const uint32_t n = live ? 1u + (uint32_t)__popcll(met[o]) : 0u;
+                const uint32_t n = live ? 1u + (uint32_t)__popcll(beam[o].met) : 0u;
                 const uint32_t most = wave_max_uniform(n);     // (every lane takes part)
                 among = __ballot(live && n == most);
                 if ((among >> lane) & 1ull) image = ord_from_float(s);
@@ -528,8 +527,7 @@ thread_local char g_init_error[256] = "";
 constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 struct Layout {
-    size_t score[2], met[2], ipq[2], len[2], fin[2], inc[2], nxt[2];
-    size_t cons_tok, phr_off, nphr, ftok, sfl, bloom, btok, rowlists, conskeys;
+    size_t beam[2], sentences, rowlists, conskeys;
     size_t hist_token, hist_backptr;
     size_t fin_tokens, fin_len, fin_score, fin_status, all_finished, best;
     size_t total;
@@ -544,22 +542,8 @@ Layout make_layout(size_t B, size_t k, size_t N)
         off = align_up(off + bytes, 256);
         return at;
     };
-    for (int i = 0; i < 2; ++i) {
-        L.score[i] = take(B * k * sizeof(float));
-        L.met[i] = take(B * k * sizeof(u64));
-        L.ipq[i] = take(B * k * sizeof(int32_t));
-        L.len[i] = take(B * k * sizeof(int32_t));
-        L.fin[i] = take(B * k);
-        L.inc[i] = take(B * k * sizeof(u64));
-        L.nxt[i] = take(B * k * sizeof(int32_t));
-    }
-    L.cons_tok = take(B * kMaxCons * sizeof(int32_t));
-    L.phr_off = take(B * (kMaxCons + 1) * sizeof(int32_t));
-    L.nphr = take(B * sizeof(int32_t));
-    L.ftok = take(B * kMaxCons * sizeof(int32_t));
-    L.sfl = take(B * kMaxCons * sizeof(u64));
-    L.bloom = take(B * kMaxCons * sizeof(u64));
-    L.btok = take(B * kMaxCons * sizeof(int32_t));
+    for (int i = 0; i < 2; ++i) L.beam[i] = take(B * k * sizeof(Hyp));
+    L.sentences = take(B * sizeof(Sentence));
     L.rowlists = take(B * k * kWave * sizeof(u64));
     L.conskeys = take(B * k * kMaxCons * sizeof(u64));
     L.hist_token = take(N * B * k * sizeof(int32_t));
@@ -807,13 +791,7 @@ T *at(dba_ctx *c, size_t off)
 void set_tables(dba_ctx *c, StepParams &p)
 {
     const Layout &L = c->L;
-    p.cons_tok = at<int32_t>(c, L.cons_tok);
-    p.phr_off = at<int32_t>(c, L.phr_off);
-    p.nphr = at<int32_t>(c, L.nphr);
-    p.first_tok = at<int32_t>(c, L.ftok);
-    p.same_first_lower = at<u64>(c, L.sfl);
-    p.first_bucket = at<u64>(c, L.bloom);
-    p.bucket_tok = at<int32_t>(c, L.btok);
+    p.sentences = at<Sentence>(c, L.sentences);
     p.all_finished = at<uint8_t>(c, L.all_finished);
     p.best = at<BestCompleted>(c, L.best);
 }
@@ -825,19 +803,6 @@ bool init_is_through(const dba_ctx *c)
     for (int b = 0; seen && b < c->B; ++b)
         if (__atomic_load_n(seen + b, __ATOMIC_RELAXED) == 0) return false;
     return true;
-}
-
-// half: which of the two halves of the beam state the kernel writes
-void set_beam_after(dba_ctx *c, StepParams &p, int half)
-{
-    const Layout &L = c->L;
-    p.score_nxt = at<float>(c, L.score[half]);
-    p.met_nxt = at<u64>(c, L.met[half]);
-    p.ipq_nxt = at<int32_t>(c, L.ipq[half]);
-    p.len_nxt = at<int32_t>(c, L.len[half]);
-    p.fin_nxt = at<uint8_t>(c, L.fin[half]);
-    p.inc_nxt = at<u64>(c, L.inc[half]);
-    p.nxt_nxt = at<int32_t>(c, L.nxt[half]);
 }
 
 }  // namespace
@@ -977,7 +942,7 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     if (e == hipSuccess) {
         StepParams p = {};
         set_tables(c, p);
-        set_beam_after(c, p, 0);
+        p.beam_nxt = at<Hyp>(c, L.beam[0]);
         c->one_launch = seen != nullptr && one_launch_shape((size_t)B, (size_t)k);
         if (c->one_launch) {
             p.rowlists = at<u64>(c, L.rowlists);
@@ -1038,7 +1003,7 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
 
     // one workgroup per beam row, 4 loads of 16 bytes per lane and tile, two or four 4 KB tiles in flight per wave
     const StreamPlan plan = stream_plan((size_t)c->B, (size_t)c->k, (size_t)c->V, elem, c->one_launch && c->merge_waves == 0);
-    const int cur = c->steps & 1, nxt = cur ^ 1;
+    const int cur = c->steps & 1;
     const Layout &L = c->L;
     StepParams p;
     p.B = c->B; p.k = c->k; p.V = c->V;
@@ -1053,14 +1018,8 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     p.track = c->track;
     p.step = c->steps;
     p.logp = logp_dev;
-    p.score_cur = at<float>(c, L.score[cur]);
-    p.met_cur = at<u64>(c, L.met[cur]);
-    p.ipq_cur = at<int32_t>(c, L.ipq[cur]);
-    p.len_cur = at<int32_t>(c, L.len[cur]);
-    p.fin_cur = at<uint8_t>(c, L.fin[cur]);
-    p.inc_cur = at<u64>(c, L.inc[cur]);
-    p.nxt_cur = at<int32_t>(c, L.nxt[cur]);
-    set_beam_after(c, p, nxt);
+    p.beam = at<Hyp>(c, L.beam[cur]);
+    p.beam_nxt = at<Hyp>(c, L.beam[cur ^ 1]);
     set_tables(c, p);
     p.rowlists = own_scratch ? reinterpret_cast<u64 *>(own_scratch) : at<u64>(c, L.rowlists);
     p.conskeys = own_scratch ? reinterpret_cast<u64 *>(own_scratch + kStaticListBytes) : at<u64>(c, L.conskeys);
@@ -1228,8 +1187,7 @@ DBA_API int dba_finalize(dba_ctx *c, int32_t *out_tokens_host, int32_t *out_len_
     dba_finalize_kernel<<<c->B, kFinWaves * kWave, 0, c->stream>>>(
         c->B, c->k, c->steps, c->N, c->pad_id, c->normalize, at<int32_t>(c, L.hist_token),
         at<int32_t>(c, L.hist_backptr),
-        at<float>(c, L.score[cur]), at<u64>(c, L.met[cur]), at<int32_t>(c, L.len[cur]),
-        at<uint8_t>(c, L.fin[cur]), c->track ? at<BestCompleted>(c, L.best) : nullptr,
+        at<Hyp>(c, L.beam[cur]), c->track ? at<BestCompleted>(c, L.best) : nullptr,
         place(L.fin_tokens), place(L.fin_len), reinterpret_cast<float *>(place(L.fin_score)), place(L.fin_status));
     hipError_t e = hipGetLastError();
     auto fetch = [&](void *to, size_t off, size_t n) {
@@ -1263,34 +1221,26 @@ DBA_API int dba_get_state(dba_ctx *c, float *score_host, uint64_t *met_mask_host
     const Layout &L = c->L;
     const int cur = c->steps & 1;
     const size_t n = (size_t)c->B * c->k;
-    // one host block for the three arrays this call decodes: n floats, n ints, n bytes
-    unsigned char *tmp = static_cast<unsigned char *>(malloc(n * 9 + 16));
-    if (!tmp) return fail(c, DBA_ENOMEM, "dba_get_state: out of host memory");
+    Hyp *beam = static_cast<Hyp *>(malloc(n * sizeof(Hyp)));
+    if (!beam) return fail(c, DBA_ENOMEM, "dba_get_state: out of host memory");
     struct Free {
-        unsigned char *p;
+        Hyp *p;
         ~Free() { free(p); }
-    } guard{tmp};
-    float *score = reinterpret_cast<float *>(tmp);
-    int32_t *ipq = reinterpret_cast<int32_t *>(tmp + n * 4);
-    uint8_t *fin = tmp + n * 8;
-    hipError_t e = hipMemcpyAsync(score, at<float>(c, L.score[cur]), n * 4, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ipq, at<int32_t>(c, L.ipq[cur]), n * 4, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(fin, at<uint8_t>(c, L.fin[cur]), n, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess && met_mask_host)
-        e = hipMemcpyAsync(met_mask_host, at<u64>(c, L.met[cur]), n * 8, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess && length_host)
-        e = hipMemcpyAsync(length_host, at<int32_t>(c, L.len[cur]), n * 4, hipMemcpyDeviceToHost, c->stream);
+    } guard{beam};
+    hipError_t e = hipMemcpyAsync(beam, at<Hyp>(c, L.beam[cur]), n * sizeof(Hyp), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return fail(c, DBA_EHIP, "dba_get_state: HIP error: %s", hipGetErrorString(e));
     c->init_under_way = false;
     for (size_t i = 0; i < n; ++i) {
-        if (score_host) score_host[i] = score[i];
-        if (inprog_phrase_host) inprog_phrase_host[i] = ipq[i] < 0 ? -1 : (ipq[i] >> 8);
-        if (inprog_pos_host) inprog_pos_host[i] = ipq[i] < 0 ? 0 : (ipq[i] & 255);
+        const Hyp &y = beam[i];
+        const int ipq = ipq_of(y.state);
+        if (score_host) score_host[i] = y.score;
+        if (met_mask_host) met_mask_host[i] = y.met;
+        if (inprog_phrase_host) inprog_phrase_host[i] = ipq < 0 ? -1 : (ipq >> 8);
+        if (inprog_pos_host) inprog_pos_host[i] = ipq < 0 ? 0 : (ipq & 255);
+        if (length_host) length_host[i] = y.len;
         if (flags_host)
-            flags_host[i] = (uint8_t)(((fin[i] & kFinFinished) ? DBA_FLAG_FINISHED : 0) | (score[i] > -INFINITY ? 0 : DBA_FLAG_DEAD));
+            flags_host[i] = (uint8_t)(((flags_of(y.state) & kFinFinished) ? DBA_FLAG_FINISHED : 0) | (y.score > -INFINITY ? 0 : DBA_FLAG_DEAD));
     }
     return DBA_OK;
 }

@@ -22,6 +22,9 @@
 
 namespace dba {
 
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
 constexpr int kMaxBeam = 64;
 constexpr int kMaxCons = 64;          // constraint tokens (and phrases) per sentence
 constexpr int kBlock = 256;           // threads per workgroup of the small helper kernels
@@ -32,6 +35,35 @@ constexpr int kFmtF16 = 1;            // IEEE binary16,
 constexpr int kFmtBF16 = 2;           // bfloat16 (the 16-bit types are widened exactly; the sum is fp32)
 constexpr int kFinFinished = 1;       // beam-state flag: the hypothesis has generated end-of-sentence
 constexpr int kFinEosBlocked = 4;     // beam-state flag: constraints unmet, end-of-sentence not allowed (Sec. 3.3)
+
+// One hypothesis of a beam in memory, two 16-byte words: who needs all of it has two loads or stores, and a kernel one pointer (an
+// array for each member, seven loads and stores and seven pointers, and seven pointers to the constraints' tables filled the scalar
+// registers of both phases: 15 to 51 of them spilled in the kernels of one launch, now 2 to 12, none in the second of two.  Per step,
+// before / now: one sentence of five rows of 1000 8.55 / 8.2 us, ten of 32000 10.6 / 10.4, 160 rows 12.4 / 12.1, 168 of 50001 13.0 / 12.7,
+// 595 of 24157 18.95 / 18.35, 1280 of 32000 32.2 / 32.0).
+struct __attribute__((aligned(16))) Hyp {
+    float score;                      // -inf: empty slot
+    uint32_t state;                   // kFin* flags | (phrase under way * 256 + tokens met in it, + 1; 0: none) << 8
+    int len;
+    int nxt;                          // next token of the phrase under way (-1: none)
+    u64 met;                          // bit i = constraint token i met
+    u64 inc;                          // bit j = phrase j is not complete
+};
+__host__ __device__ __forceinline__ uint32_t state_word(int flags, int ipq) { return (uint32_t)flags | (uint32_t)(ipq + 1) << 8; }
+__host__ __device__ __forceinline__ int flags_of(uint32_t state) { return (int)(state & 255u); }
+// phrase under way * 256 + tokens met in it, or -1
+__host__ __device__ __forceinline__ int ipq_of(uint32_t state) { return (int)(state >> 8) - 1; }
+
+// The constraints of one sentence in memory, made by dba_init.
+struct __attribute__((aligned(64))) Sentence {
+    u64 same_first_lower[kMaxCons];   // phrase j: the lower phrases with the same first token
+    u64 first_bucket[kMaxCons];       // bucket w & 63: the phrases whose first token has these low six bits
+    int32_t bucket_tok[kMaxCons];     // that first token if the bucket's phrases agree on it; -1 none, -2 they differ
+    int32_t first_tok[kMaxCons];      // first token of phrase j
+    int32_t tok[kMaxCons];            // the tokens, phrase after phrase
+    int32_t phr_off[kMaxCons + 1];    // token offset of each phrase, phr_off[nphr] = tokens in all
+    int32_t nphr;                     // phrases
+};
 
 struct StepParams {
     int B, k, V;
@@ -46,30 +78,9 @@ struct StepParams {
     int track;                        // 1: keep a record of the best completed hypothesis seen on any beam (Sec. 3.3)
     int step;                         // index of this step, from 0
     const void *logp;                 // [B,k,V] in the element type the kernel is instantiated for
-    // beam before the step
-    const float *score_cur;           // [B,k]  (-inf: empty slot)
-    const u64 *met_cur;               // [B,k]  bit i = constraint token i met
-    const int32_t *ipq_cur;           // [B,k]  phrase under way * 256 + tokens met in it, or -1
-    const int32_t *len_cur;           // [B,k]
-    const uint8_t *fin_cur;           // [B,k]  kFin* flags
-    const u64 *inc_cur;               // [B,k]  bit j = phrase j is not complete
-    const int32_t *nxt_cur;           // [B,k]  next token of the phrase under way (-1: none)
-    // beam after the step
-    float *score_nxt;
-    u64 *met_nxt;
-    int32_t *ipq_nxt;
-    int32_t *len_nxt;
-    uint8_t *fin_nxt;
-    u64 *inc_nxt;
-    int32_t *nxt_nxt;
-    // constraints
-    const int32_t *cons_tok;          // [B,64]
-    const int32_t *phr_off;           // [B,65] token offset of each phrase, phr_off[b][P] = C
-    const int32_t *nphr;              // [B]
-    const int32_t *first_tok;         // [B,64] first token of phrase j
-    const u64 *same_first_lower;      // [B,64] phrase j: the lower phrases with the same first token
-    const u64 *first_bucket;          // [B,64] bucket w & 63: the phrases whose first token has these low six bits
-    const int32_t *bucket_tok;        // [B,64] that first token if the bucket's phrases agree on it; -1 none, -2 they differ
+    const Hyp *beam;                  // [B,k]  before the step,
+    Hyp *beam_nxt;                    //        and after it
+    const Sentence *sentences;        // [B]    the constraints
     // scratch
     u64 *rowlists;                    // [B*k,64] every row's best sums, decreasing, as selection-key bodies
     u64 *conskeys;                    // [B*k,64] selection keys (bank, score image, ~flat) of the
@@ -196,9 +207,6 @@ __device__ __forceinline__ u64 fold_keys(u64 list, const u64 *keys, int cnt)
     return list;
 }
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-
 // max of four finite-or-infinite floats in two instructions (the inputs are never NaN, so the
 // quieting moves a generic fmaxf would add are not needed)
 __device__ __forceinline__ float max4(const v4f &x)
@@ -259,6 +267,8 @@ struct Logp<kFmtF32> {
     }
     static __device__ __forceinline__ float some_element_at_most_max(const vec_t &x) { return max4(x); }
     static __device__ __forceinline__ float widen_one(elem_t e) { return e; }
+    typedef float lone_t;
+    static __device__ __forceinline__ float widen_lone(lone_t e) { return e; }
 };
 
 // The two 16-bit formats are sign-magnitude like fp32, so among negative values a greater bit
@@ -286,6 +296,8 @@ struct Logp16 {
         else return (float)__builtin_bit_cast(_Float16, (unsigned short)h);
     }
     static __device__ __forceinline__ float widen_one(elem_t e) { return widen_bits(e); }
+    typedef uint32_t lone_t;
+    static __device__ __forceinline__ float widen_lone(lone_t e) { return widen_bits(e); }
     // round-to-nearest pattern of a negative finite fp32 (a starting point only: quick() corrects it)
     static __device__ __forceinline__ uint32_t narrow_bits(float d)
     {
@@ -450,7 +462,7 @@ struct RowStream {
     int V, head, nv, tail, ntiles;        // nv: groups in the row's aligned body
     __amdgpu_buffer_rsrc_t body;
     vec_t tile_[D][U];
-    elem_t lone;          // wave 0: this lane's element outside the aligned body, if there is one
+    typename F::lone_t lone;   // wave 0: this lane's element outside the aligned body, if there is one, as it is read
 
     // Requests a tile.  The descriptor ends with the row's aligned body, so lanes beyond it read nothing and get 0:
     // a partial tile needs neither a branch nor switched-off lanes when it is requested, only to be blanked when it is looked at,
@@ -587,7 +599,10 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
     // the elements outside the aligned body (fewer than two groups of them) are parked as keys at once
     if (wave == 0 && head + tail > 0) {
         const uint32_t at = flat_base + (uint32_t)lone_at(lane);
-        const float s = lane < head + tail && at != no_coord ? prev + F::widen_one(lone) : -INFINITY;
+        // (16 bits are widened here and not where they are read: the wait for them there would also be one for the tiles
+        // requested before; 1152 rows of 32003 bf16 21.1 -> 20.75 us per step)
+        if constexpr (G > 4) asm volatile("" : "+v"(lone));
+        const float s = lane < head + tail && at != no_coord ? prev + F::widen_lone(lone) : -INFINITY;
         const u64 m = __ballot(s >= st.thr);
         if ((m >> lane) & 1ull) key[lanes_before(m)] = make_key(s, at);
         parked = __popcll(m);
@@ -1088,23 +1103,21 @@ __device__ __forceinline__ u64 handed_over(const u64 *from)
 // The sentence's tables and beam on their way from memory to LDS, one entry a thread: every load
 // is issued before the first one is waited for (clamped indices instead of branches).
 struct MergeTables {
-    int poff, tok, btok, ipq, nxt, len, fin;
-    u64 bucket, met, inc;
+    int poff, tok, btok;
+    u64 bucket;
+    v4u lo, hi;                        // the two halves of a Hyp
     __device__ __forceinline__ int request(const StepParams &p, int b, int k, int tid)
     {
         const int lane = lane_id(), t64 = tid < kMaxCons ? tid : kMaxCons;
-        const size_t rs = (size_t)b * k + (tid < k ? tid : k - 1);
-        poff = p.phr_off[(size_t)b * (kMaxCons + 1) + t64];
-        tok = p.cons_tok[(size_t)b * kMaxCons + lane];
-        const int P = p.nphr[b];
-        bucket = p.first_bucket[(size_t)b * kMaxCons + lane];
-        btok = p.bucket_tok[(size_t)b * kMaxCons + lane];
-        met = p.met_cur[rs];
-        inc = p.inc_cur[rs];
-        ipq = p.ipq_cur[rs];
-        nxt = p.nxt_cur[rs];
-        len = p.len_cur[rs];
-        fin = p.fin_cur[rs];
+        const v4u *hyp = reinterpret_cast<const v4u *>(p.beam + ((size_t)b * k + (tid < k ? tid : k - 1)));
+        const Sentence &s = p.sentences[b];
+        poff = s.phr_off[t64];
+        tok = s.tok[lane];
+        const int P = s.nphr;
+        bucket = s.first_bucket[lane];
+        btok = s.bucket_tok[lane];
+        lo = hyp[0];
+        hi = hyp[1];
         return P;
     }
     __device__ __forceinline__ void store(int k, int tid, MergeSmem &sm) const
@@ -1117,12 +1130,12 @@ struct MergeTables {
         }
         if (tid < k) {
             HypState hs;
-            hs.met = met;
-            hs.inc = inc;
-            hs.ipq = ipq;
-            hs.nxt = nxt;
-            hs.len = len;
-            hs.misc = (fin & kFinFinished) | (__popcll(met) << 8);
+            hs.met = (u64)hi.y << 32 | hi.x;
+            hs.inc = (u64)hi.w << 32 | hi.z;
+            hs.ipq = ipq_of(lo.y);
+            hs.nxt = (int)lo.w;
+            hs.len = (int)lo.z;
+            hs.misc = (flags_of(lo.y) & kFinFinished) | (__popcll(hs.met) << 8);
             sm.hyp[tid] = hs;
         }
     }
@@ -1824,13 +1837,8 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         const u64 open = __ballot(keep && !fin2);
         if (keep) {
             const size_t o = (size_t)b * k + slot;
-            p.score_nxt[o] = score;
-            p.met_nxt[o] = met2;
-            p.inc_nxt[o] = inc2;
-            p.ipq_nxt[o] = ipq2;
-            p.nxt_nxt[o] = nxt2;
-            p.len_nxt[o] = length;
-            p.fin_nxt[o] = (uint8_t)(fin2 | ((!fin2 && (int)__popcll(met2) < C) ? kFinEosBlocked : 0));
+            p.beam_nxt[o] = Hyp{score, state_word(fin2 | ((!fin2 && (int)__popcll(met2) < C) ? kFinEosBlocked : 0), ipq2),
+                                length, nxt2, met2, inc2};
             p.hist_token[o] = token;
             p.hist_backptr[o] = parent;
             if (p.out_token) p.out_token[o] = token;
@@ -1840,13 +1848,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         }
         if (lane >= nlive && lane < k) {                  // empty slots
             const size_t o = (size_t)b * k + lane;
-            p.score_nxt[o] = -INFINITY;
-            p.met_nxt[o] = 0;
-            p.inc_nxt[o] = 0;
-            p.ipq_nxt[o] = -1;
-            p.nxt_nxt[o] = -1;
-            p.len_nxt[o] = 0;
-            p.fin_nxt[o] = 0;
+            p.beam_nxt[o] = Hyp{-INFINITY, state_word(0, -1), 0, -1, 0, 0};
             p.hist_token[o] = p.pad_id;
             p.hist_backptr[o] = -1;
             if (p.out_token) p.out_token[o] = p.pad_id;
