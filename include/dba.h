@@ -215,7 +215,8 @@ DBA_API int dba_get_state(dba_ctx *ctx, float *score_host, uint64_t *met_mask_ho
  *                               The results are the same for every setting; only the time differs.
  *                               0 lets the library choose for the shortest step of a single decode: one
  *                               launch for both parts of a small step (B*k <= 512, and k <= 16, or k <= 32
- *                               with rows of at least 32 KB), else so many
+ *                               with rows of at least 32 KB, or k <= 28 with fp32 rows of at most 28 KB; k <= 16 and B*k <= 1408,
+ *                               or 704 with rows of 160 KB and more), else so many
  *                               (four up to k = 16, eight up to 32 or for more than 256 sentences, sixteen beyond).  Four-wave workgroups need less room
  *                               at once on a GPU that is busy with other work.
  */

@@ -186,8 +186,8 @@ __global__ __launch_bounds__(NW * kWave) void dba_step_kernel(const void *logp, 
     extern __shared__ __align__(16) unsigned char dyn_smem[];
     __shared__ int role;
     StreamSmem<NW> &ss = *reinterpret_cast<StreamSmem<NW> *>(dyn_smem);
-    MergeSmem &ms = *reinterpret_cast<MergeSmem *>(dyn_smem);
-    u64 *cand = reinterpret_cast<u64 *>(dyn_smem + (sizeof(MergeSmem) + 15) / 16 * 16);
+    MergeSmem<MW> &ms = *reinterpret_cast<MergeSmem<MW> *>(dyn_smem);
+    u64 *cand = reinterpret_cast<u64 *>(dyn_smem + (sizeof(MergeSmem<MW>) + 15) / 16 * 16);
     const uint32_t k = (uint32_t)k_first & 0xFFFFu, rows = rows_order & 0x7FFFFFFFu;
     const uint32_t n = blockIdx.x - (rows_order >> 31 ? (k == 1 ? rows : __umulhi(rows, inv_k)) : 0u);     // (wraps below the first row)
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), tid = (int)threadIdx.x;
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(MW * kWave) void dba_merge_kernel(const u64 *rowlis
                                                                const StepParams p)
 {
     extern __shared__ __align__(16) unsigned char dyn_smem[];
-    __shared__ MergeSmem sm;
+    __shared__ MergeSmem<MW> sm;
     merge_phase<ROWS, MW, J, false, EMPTY>(p, rowlists, conskeys, (int)(k_inv & 0xFFFFu), k_inv >> 16, (int)blockIdx.x, sm,
                                            reinterpret_cast<u64 *>(dyn_smem), 0, 0, false);
 }
@@ -575,9 +575,18 @@ constexpr size_t spread_lds(size_t n)
     return align_up(kLdsPerUnit / (n + 1) + 1 - sizeof(StreamSmem<NW>), 256);
 }
 
-// Where steps may take one launch: a compute unit has one or two rows and their latencies show.  (Wider beams have more
-// to merge than a row's workgroup has waves for.)
-bool one_launch_shape(size_t B, size_t k) { return B * k <= 2 * kComputeUnits && k <= 32; }
+// Where steps may take one launch, whatever their rows are made of: up to k = 16, where four waves merge as fast as eight, while a
+// compute unit has five or six rows of four waves (seven waves of this kernel fit a SIMD, by its scalar registers, and the sentences'
+// workgroups need room beside the rows); with two rows a unit up to k = 32, where the rows have eight waves.  Per step, two launches /
+// one: 768 rows of 32000 fp32, k = 12, 24.2 / 23.2 us, 1152 of 32003 bf16 20.9 / 19.5, 1280, k = 16, 32.8 / 32.2, 1275 of 16000 22.0 / 20.8, 1024
+// of 8000 14.5 / 13.9, 960 of 2000 11.7 / 10.8, 600 of 1000 11.0 / 10.5; but 1700 of 32000 41.6 / 43.3, 1600 of 2000 13.2 / 14.6, 5000 of 2000
+// 22.0 / 24.5, and with k = 20 to 32 and four waves 1280 of 32000 34.2 / 34.3, 2048 49.6 / 51.1.  (More than two rows a unit of a tile's eighth
+// or less, vocabularies of a few hundred, keep two launches.)
+bool one_launch_shape(size_t B, size_t k, size_t V)
+{
+    const size_t rows = B * k;
+    return rows <= 2 * kComputeUnits ? k <= 32 : k <= 16 && V >= 512 && rows * 4 <= 22 * kComputeUnits;
+}
 
 // How the stream phase of a step is launched: one workgroup per beam row, and
 struct StreamPlan {
@@ -607,13 +616,17 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem, bool free)
     // them, and where rows are long (from 160 KB on: the floor then rests on a larger share of the
     // row and fewer sums are looked at closely); four otherwise - with rows of 64-128 KB and
     // thousands of them, twice the workgroups per compute unit stream faster than twice the waves.
-    plan.waves = ((rows <= 512 && row_bytes >= 32768) || row_bytes >= 163840) ? 8 : 4;
+    // Eight also where that lets a step of k = 17 to 28 with short rows take one launch (see below).
+    const bool wide_short = free && rows <= 2 * kComputeUnits && k > 16 && k <= 28 && elem == 4 && row_bytes <= 28 * 1024;
+    plan.waves = ((rows <= 2 * kComputeUnits && (row_bytes >= 32768 || wide_short)) || row_bytes >= 163840) ? 8 : 4;
     // One launch for the whole step where the shape allows it and a row's workgroup has the waves to merge with: beyond k = 16
-    // eight.  Per step, two launches / one, 16 to 512 rows of 100 to 32000 elements: with k up to 8 0.4 to 1.4 us less, 9 to 11 0.1 to 0.9,
-    // 12 to 16 0.6 to 1.4; k = 17 to 32 with eight waves 0.7 to 1.35 (500 rows of 32000, k = 20, 19.95 / 18.8; 256 rows, k = 32,
-    // 16.5 / 15.45), but with four up to 0.35 more at k = 18, 0.5 at 24, 0.9 at 28 and 1.2 at 32 (256 rows of 2000, k = 32: 11.7 / 13.4
-    // before this line was drawn; with bf16 0.25 less to 0.3 more up to 24, beyond as with fp32).
-    plan.one = free && one_launch_shape(B, k) && (k <= 16 || plan.waves == 8);
+    // eight; beyond two rows a compute unit as long as their waves leave room.  Per step, two launches / one, 16 to 512 rows of 100 to 32000 elements:
+    // with k up to 8 0.4 to 1.4 us less, 9 to 11 0.1 to 0.9, 12 to 16 0.6 to 1.4; k = 17 to 32 with eight waves 0.7 to 1.35 (500 rows of
+    // 32000, k = 20, 19.95 / 18.8; 256 rows, k = 32, 16.5 / 15.45), but with four waves up to 0.35 more at k = 18, 0.5 at 24, 0.9 at 28 and 1.2 at
+    // 32.  So short rows get eight too, though most of these have no tile, to k = 28 (fp32, two launches with four / one with eight: 200
+    // rows of 2000, k = 20, 10.3 / 9.7 us, 126 of 4000, k = 18, 10.8 / 9.75, 504 11.7 / 10.8, 448 of 7000, k = 28, 13.0 / 12.2; 512 of 5000, k = 32, 12.8 /
+    // 13.5; 16-bit rows gain less, 240 of 6000, k = 20, 11.15 / 10.7, and are left as they are, like rows of 28 to 32 KB).
+    plan.one = free && one_launch_shape(B, k, V) && (k <= 16 || plan.waves == 8) && (rows <= 2 * kComputeUnits || rows * plan.waves <= 22 * kComputeUnits);
     // Rows side by side on a compute unit.  More than a unit's even share leaves others short, and lets a
     // second decode's rows in beside the first one's: where the grid fills the chip, no more than that share
     // (three decodes of 64 x 20 rows of 32000 in flight: 84 against 94 us for three steps, one of them alone
@@ -638,7 +651,7 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem, bool free)
     // seven tiles a wave on, six with two elements in the place of one (240 KB: fp32 22.55 / 22.65 and 28.1 / 28.25, bf16 21.55 / 22.85;
     // 200 KB: bf16 20.35 / 20.85 and 26.55 / 26.8; 400 KB: fp32 30.05 / 31.2 and 39.45 / 40.0, at 260 and 500 rows).
     const bool long_rows = row_bytes >= (elem == 4 ? 7u : 6u) * 8 * 4096;
-    plan.tiles = plan.waves == 8 && (rows <= kComputeUnits || (plan.one && long_rows)) ? 4 : 2;
+    plan.tiles = plan.waves == 8 && (rows <= kComputeUnits || (plan.one && rows <= 2 * kComputeUnits && long_rows)) ? 4 : 2;
     return plan;
 }
 
@@ -926,7 +939,7 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     const int ncand_max = (k * (max_phrases + 2) + kWave - 1) / kWave * kWave;
     c->cand_cap = ncand_max;
     constexpr size_t most_cand = (size_t)DBA_MAX_BEAM * (DBA_MAX_CONS_TOKENS + 2) * sizeof(u64) + kMostLeft * (sizeof(u64) + sizeof(int));
-    static_assert(sizeof(MergeSmem) + 16 + most_cand <= kLdsPerLaunch, "k = 64 with 64 phrases: 45 KB beside the merge phase's own 18");
+    static_assert(sizeof(MergeSmem<16>) + 16 + most_cand <= kLdsPerLaunch, "k = 64 with 64 phrases: 45 KB beside the merge phase's own 18");
     c->dyn_smem = (size_t)ncand_max * sizeof(u64) + (ncand_max > 4 * kWave ? kMostLeft * (sizeof(u64) + sizeof(int)) : 0);
 
     // (without a block the words pass through the row lists' place, which is large enough and not in use yet)
@@ -943,7 +956,7 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
         StepParams p = {};
         set_tables(c, p);
         p.beam_nxt = at<Hyp>(c, L.beam[0]);
-        c->one_launch = seen != nullptr && one_launch_shape((size_t)B, (size_t)k);
+        c->one_launch = seen != nullptr && one_launch_shape((size_t)B, (size_t)k, (size_t)V);
         if (c->one_launch) {
             p.rowlists = at<u64>(c, L.rowlists);
             p.conskeys = at<u64>(c, L.conskeys);
@@ -1023,7 +1036,7 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     set_tables(c, p);
     p.rowlists = own_scratch ? reinterpret_cast<u64 *>(own_scratch) : at<u64>(c, L.rowlists);
     p.conskeys = own_scratch ? reinterpret_cast<u64 *>(own_scratch + kStaticListBytes) : at<u64>(c, L.conskeys);
-    // (k > 16: what a step's rows are made of decides how many launches it takes; one must find the places empty after two)
+    // (what a step's rows are made of may decide how many launches it takes; one must find the places empty after two)
     const bool leave_empty = c->one_launch && c->merge_waves == 0 && !plan.one && !own_scratch;
     p.out_token = out_token_dev;
     p.out_backptr = out_backptr_dev;
@@ -1042,7 +1055,9 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         p.rowlists = at<u64>(c, L.rowlists);
         p.conskeys = at<u64>(c, L.conskeys);
         const dim3 sblock((unsigned)(plan.waves * kWave)), sgrid((unsigned)c->B * (unsigned)(c->k + 1));
-        const size_t lds = std::max((plan.waves == 8 ? sizeof(StreamSmem<8>) : sizeof(StreamSmem<4>)), align_up(sizeof(MergeSmem), 16) + c->dyn_smem);
+        const int mw = c->k <= 16 || plan.waves == 4 ? 4 : 8;
+        const size_t lds = std::max(plan.waves == 8 ? sizeof(StreamSmem<8>) : sizeof(StreamSmem<4>),
+                                    align_up(mw == 4 ? sizeof(MergeSmem<4>) : sizeof(MergeSmem<8>), 16) + c->dyn_smem);
         const int tries = c->give_up ? 0 : most_tries((size_t)c->B * (size_t)c->k, (size_t)c->V * elem);
 #define ONE(FMT, NW, D, ROWS, MW, J)                                                                      \
     dba_step_kernel<kTileLoads, FMT, NW, D, ROWS, MW, J><<<sgrid, sblock, lds, c->stream>>>(p.logp, p.V, kf, plan.rows_abreast, \
@@ -1092,9 +1107,8 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
 #undef STREAM
         // The merge phase is compiled for (rows per wave, waves, entries per lane).  Unless the caller fixes the
         // waves: four up to k = 16, eight up to 32, sixteen beyond (16 sentences of 2000 tokens, k = 64: 18.1 us per step with
-        // eight, 17.4 with sixteen; 4 of 32000 21.45 / 20.95 - as long as every
-        // sentence has a compute unit to itself, since no second workgroup of sixteen fits there (seven waves a SIMD, by scalar registers): 256 of 1000, k = 64, 91.8 / 91.0, 257
-        // 93.8 / 98.4, 1000 315.6 / 329.3; fewer lists per wave to merge and to scan, more waves to rank
+        // eight, 17.4 with sixteen; 4 of 32000 21.45 / 20.95 - as long as every sentence has a compute unit to itself: 256 of 1000, k =
+        // 64, 91.8 / 91.0, but 257 87.9 / 92.3, 1000 292.9 / 306.2, 300 of 8000 bf16 100.4 / 105.0; fewer lists per wave to merge and to scan, more waves to rank
         // candidates, at the price of a deeper tree where the waves' lists are joined; one decode, per step: 22.1 / 22.3 us with
         // four / eight waves at k = 12, 14.7 / 14.7 at k = 16; merge kernel 7.7 / 7.0 us at k = 20, 19.3 / 14.6 at k = 64).
         // Up to k = 11 every wave holds the k * k entries that matter, one or two a lane, and finds the bar by
@@ -1109,7 +1123,10 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
 #define MERGE(ROWS, MW, J, EMPTY) \
     dba_merge_kernel<ROWS, MW, J, EMPTY><<<mgrid, MW * kWave, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, k_inv, p)
         if (mw == 4) {
-            if (c->k <= 8) MERGE(2, 4, 1, false);
+            if (leave_empty && c->k <= 8) MERGE(2, 4, 1, true);
+            else if (leave_empty && c->k <= 11) MERGE(4, 4, 2, true);
+            else if (leave_empty && c->k <= 16) MERGE(4, 4, -1, true);
+            else if (c->k <= 8) MERGE(2, 4, 1, false);
             else if (c->k <= 11) MERGE(4, 4, 2, false);
             else if (c->k <= 16) MERGE(4, 4, -1, false);
             else if (c->k <= 32) MERGE(8, 4, -1, false);

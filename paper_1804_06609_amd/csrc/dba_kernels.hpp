@@ -124,12 +124,12 @@ struct __attribute__((aligned(16))) HypState {
 };
 
 constexpr int kMostLeft = 1024;        // candidates there is room for after those that cannot be among their bank's best are gone
-constexpr int kMergeWavesMax = 16;    // most waves a merge-phase workgroup (one sentence) can have: 4, 8 or 16 are used
-
+// LDS of a merge-phase workgroup of MW waves (one sentence): 4, 8 or 16 are used
+template <int MW>
 struct MergeSmem {
-    uint32_t ws[kMergeWavesMax][kWave];      // every wave's best score images
-    uint32_t wf[kMergeWavesMax][kWave];      // and the greatest images its merges dropped
-    uint32_t ws2[kMergeWavesMax][kWave];     // every wave's best low words among tied keys
+    uint32_t ws[MW][kWave];           // every wave's best score images
+    uint32_t wf[MW][kWave];           // and the greatest images its merges dropped
+    uint32_t ws2[MW][kWave];          // every wave's best low words among tied keys
     HypState hyp[kMaxBeam];
     u64 sel[kMaxBeam];
     int slot[kMaxBeam];               // place in the new beam of the selected key i
@@ -187,12 +187,12 @@ constexpr int kKeyCap = 128;          // and keys it can park there
 // 15.8 / 17.2, 1024 of 100000 bf16, k = 32, 42.2 / 44.4.
 // Nor for more than the cells that hold an element, which can be fewer in rows of one tile or two (1872 rows of 131 fp16, k = 8:
 // four cells hold any, and a floor from sixteen was none, 15.6 us against 14.15): groups are dealt out lane by lane, and
-// with three tiles more lanes have one than five eighths of the cells need.  (Eight waves have rows of eight tiles and more.)
+// with three tiles more lanes have one than five eighths of the cells need.
 template <int NW, int U>
 __device__ __forceinline__ bool floor_from_cells(int k, int ngroups, int ntiles)
 {
     return 8 * k <= 5 * (kWave / NW) * min(NW, ntiles) && (NW == 8 || k <= 16 || ntiles <= 2 * NW) &&
-           (NW == 8 || k * NW <= ngroups - (ntiles - 1) * (kWave * (U - 1)));
+           k * NW <= ngroups - (ntiles - 1) * (kWave * (U - 1));
 }
 
 // Keys of one wave folded into its sorted list 64 at a time: one 64-lane sort and one merge per
@@ -570,13 +570,18 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
         if (NW == 8 || wave < ntiles) boot = sort64_desc<uint32_t, LL>(boot);      // (the others hold the same in every lane)
         sm.boot[wave][lane] = boot;
         __syncthreads();
-        if (kk <= 3 * share) {
+        const int lists = min(nwaves, ntiles);             // (the other waves hold nothing)
+        if (lists > 3 && 4 * kk <= 3 * lists * share) {
             // the best `share` of every wave's list, sorted once: the k-th of them is the k-th of all unless one
-            // wave holds more than `share` of the k greatest (then it is a little lower)
+            // wave holds more than `share` of the k greatest (then it is a little lower).  Of one to three lists, as rows of so
+            // many tiles have, all is kept: a merge each is no longer than the sort, and `share` of each would be fewer than k, no floor
+            // at all (per step, rows of one tile, k = 20 to 32: 96 of 1000 fp32 12.7 -> 9.7 us, 512 14.2 -> 11.5, 500 of 2000 bf16 15.6 -> 12.0)
             boot = sort64_desc<uint32_t, LL>(sm.boot[lane / share][lane % share]);
         } else {
-            for (int w = 0; w < nwaves; ++w)
-                if (w != wave) boot = merge_desc<uint32_t, LL>(boot, sm.boot[w][lane]);
+            const int own = wave < lists ? wave : 0;
+            if (wave >= lists) boot = sm.boot[0][lane];
+            for (int w = 0; w < lists; ++w)
+                if (w != own) boot = merge_desc<uint32_t, LL>(boot, sm.boot[w][lane]);
         }
     }
     st.thr = fmaxf(float_from_ord((uint32_t)__builtin_amdgcn_readlane((int)boot, kk - 1)), kLowestFinite);
@@ -961,7 +966,8 @@ __device__ __forceinline__ u64 sel_from_rowkey(int met_bits, int bank, u64 key)
 // The phrases whose first token is w (w < 0: none), as a bit mask.  Every lane looks its own
 // token up in the bucket of the token's low six bits: one trip to LDS where the bucket's
 // phrases all begin with the same token (nearly always), else they are compared one by one.
-__device__ __forceinline__ u64 first_token_matches(int w, const MergeSmem &sm)
+template <typename Smem>
+__device__ __forceinline__ u64 first_token_matches(int w, const Smem &sm)
 {
     if (w < 0) return 0;
     const int same = sm.btok[w & 63];
@@ -1024,8 +1030,7 @@ __device__ __forceinline__ uint32_t wave_best64(int wave, int k, int kth, List l
 // The 64 greatest keys of the lists the MW waves have left in buf (after a barrier), for the
 // calling wave: a tree of merges whose independent pairs run side by side.
 template <int MW>
-__device__ __forceinline__ uint32_t join_best64(const uint32_t (&buf)[kMergeWavesMax][kWave], int wave, int lane,
-                                                uint32_t &fell)
+__device__ __forceinline__ uint32_t join_best64(const uint32_t (*buf)[kWave], int wave, int lane, uint32_t &fell)
 {
     uint32_t o[MW];
 #pragma unroll
@@ -1040,7 +1045,7 @@ __device__ __forceinline__ uint32_t join_best64(const uint32_t (&buf)[kMergeWave
 // The same where most lists are expected to be empty (an empty list costs nothing), in every
 // wave; one barrier.
 template <int MW>
-__device__ __forceinline__ uint32_t block_best64_sparse(uint32_t (&buf)[kMergeWavesMax][kWave], int wave, int lane,
+__device__ __forceinline__ uint32_t block_best64_sparse(uint32_t (&buf)[MW][kWave], int wave, int lane,
                                                         uint32_t mine, uint32_t &fell)
 {
     buf[wave][lane] = mine;
@@ -1077,15 +1082,15 @@ constexpr int kAsked = 1, kGoesOn = 2, kLeaves = 3;    // MergeSmem::verdict
 // A wave of sentence b's workgroup has run out of looks for its rows' keys.  The first one to do so tells the rows, in the
 // atomic step that tells it how many have ended: if all, their keys are there (true); if not, the last one will find
 // that said and take the sentence on (false).  The other waves go by what it was told.
-__device__ __forceinline__ bool all_rows_ended(const StepParams &p, int b, int k, MergeSmem &sm)
+__device__ __forceinline__ bool all_rows_ended(const StepParams &p, int b, int k, int &told)
 {
     int verdict = 0;
     if (lane_id() == 0) {
-        if (atomicCAS(&sm.verdict, 0, kAsked) == 0) {
+        if (atomicCAS(&told, 0, kAsked) == 0) {
             const int ended = __hip_atomic_fetch_or(&p.best[b].ended, kGivenUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&sm.verdict, ended == k ? kGoesOn : kLeaves, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_store(&told, ended == k ? kGoesOn : kLeaves, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        do verdict = __hip_atomic_load(&sm.verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        do verdict = __hip_atomic_load(&told, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         while (verdict == kAsked);
     }
     return __builtin_amdgcn_readfirstlane(verdict) == kGoesOn;
@@ -1120,7 +1125,8 @@ struct MergeTables {
         hi = hyp[1];
         return P;
     }
-    __device__ __forceinline__ void store(int k, int tid, MergeSmem &sm) const
+    template <typename Smem>
+    __device__ __forceinline__ void store(int k, int tid, Smem &sm) const
     {
         if (tid <= kMaxCons) sm.ct.poff[tid] = poff;
         if (tid < kMaxCons) {
@@ -1142,7 +1148,8 @@ struct MergeTables {
 };
 
 // the counters and the candidate buffer, by the first `threads` threads
-__device__ __forceinline__ void clear_for_merge(const StepParams &p, int tid, int threads, MergeSmem &sm, u64 *cand)
+template <typename Smem>
+__device__ __forceinline__ void clear_for_merge(const StepParams &p, int tid, int threads, Smem &sm, u64 *cand)
 {
     if (tid < 2 * kMaxCons) {
         sm.cnt[tid] = 0;
@@ -1175,7 +1182,7 @@ __device__ __forceinline__ void clear_for_merge(const StepParams &p, int tid, in
 // EMPTY: the row lists are left empty, as a step of one launch finds and leaves them.
 template <int ROWS, int MW, int J, bool ONE, bool EMPTY>
 __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowlists, const u64 *conskeys, int k,
-                                            uint32_t inv_k, int b, MergeSmem &sm, u64 *cand, int P_here, int most_tries,
+                                            uint32_t inv_k, int b, MergeSmem<MW> &sm, u64 *cand, int P_here, int most_tries,
                                             bool all_ended)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -1236,7 +1243,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
             }
             if (__ballot(!there) == 0) break;
             if (tries <= 0) {
-                if (last || !all_rows_ended(p, b, k, sm)) break;
+                if (last || !all_rows_ended(p, b, k, sm.verdict)) break;
                 last = true;
                 tries = kLastTries;
             }

@@ -1,0 +1,62 @@
+"""-m gpu: steps of one launch at the edges of the rule that chooses it, against two launches and the oracle."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+def _session(wl, waves, first=0):
+    import torch
+    import paper_1804_06609_amd as dba
+    from paper_1804_06609_amd.session import Session
+    ses = Session(wl.B, wl.k, wl.V, wl.T, wl.eos_id, wl.pad_id, *wl.csr(), stream=torch.cuda.current_stream(),
+                  options={dba.DBA_OPT_MERGE_WAVES: waves})
+    return ses, dba.dba_debug_sentences_first(ses.ctx, first)
+
+
+def _bytes(ses):
+    return [a.tobytes() for a in ses.outputs()] + [a.tobytes() for a in ses.state().values()]
+
+
+@pytest.mark.parametrize("B,k,V,fmts,one", [
+    (88, 16, 512, ("f32",), True), (89, 16, 512, ("f32",), False), (88, 16, 511, ("f32",), False), (1408, 1, 700, ("f16",), True),
+    (176, 8, 1031, ("bf16", "f32"), True), (127, 11, 2049, ("f32", "f16"), True), (93, 15, 3001, ("f32",), True), (64, 11, 41001, ("f32", "bf16"), True),
+    (65, 11, 41001, ("f32", "bf16"), True), (89, 8, 41001, ("bf16", "f32"), True), (46, 16, 41001, ("f16", "f32"), True),
+    (18, 28, 7168, ("f32", "f16"), True), (18, 28, 7169, ("f32",), True), (30, 17, 1000, ("f32",), True), (1, 17, 17, ("f32",), True), (5, 24, 1024, ("f32", "bf16"), True)])
+def test_one_launch_and_two(B, k, V, fmts, one):
+    """Every step against the two launches, with the element types by turns (where they decide how many launches a step takes,
+    the places that rows hand their keys over in are left empty by both), the step with its own scratch among them, and with the
+    sentences' workgroups giving up at once."""
+    import torch
+    tdt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
+    wl = si.make_small(9700 + V + k, B, k, V, 6, max_phrases=4, max_len=3, dup_prob=0.3)
+    wl.eos_switch = 4
+    dev = [torch.from_numpy(wl.logp(t)).cuda().to(tdt[fmts[t // 2 % len(fmts)]]) for t in range(wl.T)]
+    two, is_one = _session(wl, 8)
+    assert not is_one
+    others = [_session(wl, 0, first) for first in (0, 1, 2)]
+    assert all(o[1] == one for o in others)
+    for t in range(wl.T):
+        two.step(dev[t])
+        want = _bytes(two)
+        for i, (ses, _) in enumerate(others):
+            ses.step(dev[t], noalloc=(t + i) % 3 == 2)
+            assert _bytes(ses) == want, (t, i)
+    want = [np.asarray(a).tobytes() for a in two.finalize()]
+    for ses, _ in others:
+        assert [np.asarray(a).tobytes() for a in ses.finalize()] == want
+        ses.close()
+    two.close()
+
+
+@pytest.mark.parametrize("k,fmt", [(13, None), (16, None), (17, None), (24, None), (28, None), (32, None), (36, None), (48, None), (64, "bf16"), (20, "f16")])
+def test_floors_of_rows_of_one_tile_to_six(k, fmt):
+    """The floor of a row comes from as many lists as it has tiles: sorted pools of their best, or all of them merged."""
+    import harness
+    tile = 1024 if fmt is None else 2048
+    for tiles in (1, 2, 3, 4, 6):
+        wl = si.make_small(9800 + tiles, 2, k, tiles * tile - 3, 3, max_phrases=2, max_len=2, dup_prob=0.3)
+        wl.eos_switch = 2
+        harness.run_parity(wl, logp_format=fmt)

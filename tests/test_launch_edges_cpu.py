@@ -1,0 +1,19 @@
+"""Which steps take one launch, at the edges of the rule (worked out on the host, no GPU)."""
+import paper_1804_06609_amd as dba
+
+
+def test_steps_beyond_two_rows_a_compute_unit():
+    """k <= 16, up to 1408 rows of four waves or 704 of eight; not for vocabularies below 512."""
+    f32, bf16 = dba.DBA_LOGP_F32, dba.DBA_LOGP_BF16
+    for B, k, V, fmt, launches in ((88, 16, 512, f32, 1), (88, 16, 511, f32, 2), (89, 16, 512, f32, 2), (1408, 1, 32000, bf16, 1), (1409, 1, 32000, bf16, 2),
+                                   (31, 17, 32000, f32, 2), (64, 11, 40959, f32, 1), (64, 11, 40960, f32, 1), (65, 11, 40960, f32, 2),
+                                   (65, 11, 40960, bf16, 1), (513, 1, 100000, f32, 1), (705, 1, 100000, f32, 2)):
+        assert dba.dba_debug_launches(B, k, V, fmt) == launches, (B, k, V, fmt)
+
+
+def test_short_rows_of_beams_of_17_to_28():
+    f32, f16 = dba.DBA_LOGP_F32, dba.DBA_LOGP_F16
+    for B, k, V, fmt, launches, waves in ((1, 17, 17, f32, 1, 8), (18, 28, 7168, f32, 1, 8), (18, 28, 7169, f32, 2, 4), (18, 29, 2000, f32, 2, 4), (19, 28, 2000, f32, 2, 4),
+                                          (18, 28, 2000, f16, 2, 4), (32, 16, 2000, f32, 1, 4)):
+        assert dba.dba_debug_launches(B, k, V, fmt) == launches, (B, k, V, fmt)
+        assert dba.dba_debug_stream_plan(B, k, V, fmt)[0] == waves, (B, k, V, fmt)
