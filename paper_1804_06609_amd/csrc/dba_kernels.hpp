@@ -1194,54 +1194,55 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     constexpr int kRowsPerWave = ROWS;
     constexpr int kLists = kPacked ? J : (kHalves ? ROWS / 2 : ROWS);
     u64 rl[kLists], ck[kRowsPerWave];
-    u64 hd[kPacked ? kRowsPerWave : 1];                    // packed: the heads of the lists of the wave's rows
     uint32_t head_bits = 0;                                // packed: bit j = this lane's entry j is a row's best
     if constexpr (ONE) {
-        // handed over by workgroups that run now: read again until every place this wave looks at is filled (ONE's tables
-        // and counters are in LDS already)
+        // Handed over by workgroups that run now: read again until every place this wave looks at is filled (ONE's tables
+        // and counters are in LDS already).  Only places that are still empty are asked for again: a look takes as long as its
+        // requests, the keys are seen half a look late, and at the end it is one row that all wait for.  (Per step, all places asked for in
+        // every look / this, and the heads of the lists by lane reads instead of loads of their own: 5 rows of 1000 8.5 / 7.9 us, ten of
+        // 32000 10.5 / 10.2, 160 12.15 / 11.75, 168 of 50001 12.9 / 12.65, 612 of 4872 12.05 / 11.4, 595 of 24157 17.2 / 16.8.)
+        static_assert(kPacked || kHalves, "lists of up to 32 keys");
+        u64 miss[kLists], cmiss[kRowsPerWave];             // lanes whose place is empty
+        const u64 *from[kLists], *cfrom[kRowsPerWave];
+#pragma unroll
+        for (int i = 0; i < kLists; ++i) {
+            bool mine;
+            uint32_t at;
+            if constexpr (kPacked) {
+                const uint32_t e = (uint32_t)(i * kWave + lane), h = (e * inv_k) >> 16;
+                mine = e < (uint32_t)(k * k);
+                head_bits |= (mine && e == h * (uint32_t)k ? 1u : 0u) << i;
+                at = h * kWave + (e - h * (uint32_t)k);
+            } else {
+                const int h = wave + (2 * i + (lane >> 5)) * MW;
+                mine = h < k && (lane & 31) < k;
+                at = (uint32_t)(h * kWave + (lane & 31));
+            }
+            rl[i] = kNoKey;
+            miss[i] = __ballot(mine);
+            from[i] = rowlists + ((size_t)b * k * kWave + at);
+        }
+#pragma unroll
+        for (int i = 0; i < kRowsPerWave; ++i) {
+            const int h = wave + i * MW;
+            ck[i] = kNoKey;
+            cmiss[i] = __ballot(h < k && lane < P_here);
+            cfrom[i] = conskeys + (((size_t)b * k + h) * kWave + lane);
+        }
         bool last = all_ended;
         for (int tries = last ? kLastTries : most_tries;; --tries) {
-            bool there = true;
-            if constexpr (kPacked) {
-                head_bits = 0;
 #pragma unroll
-                for (int j = 0; j < J; ++j) {
-                    const uint32_t i = (uint32_t)(j * kWave + lane);
-                    rl[j] = kNoKey;
-                    if (i < (uint32_t)(k * k)) {
-                        const uint32_t h = (i * inv_k) >> 16, at = i - h * (uint32_t)k;
-                        head_bits |= (at == 0 ? 1u : 0u) << j;
-                        rl[j] = handed_over(rowlists + ((size_t)b * k + h) * kWave + at);
-                    }
-                }
-            } else {
-                static_assert(kPacked || kHalves, "lists of up to 32 keys");
+            for (int i = 0; i < kLists; ++i)
+                if (miss[i] != 0 && ((miss[i] >> lane) & 1ull)) rl[i] = handed_over(from[i]);
 #pragma unroll
-                for (int i = 0; i < kLists; ++i) {
-                    const int h = wave + (2 * i + (lane >> 5)) * MW;
-                    rl[i] = kNoKey;
-                    if (h < k && (lane & 31) < k) rl[i] = handed_over(rowlists + ((size_t)b * k + h) * kWave + (lane & 31));
-                }
-            }
+            for (int i = 0; i < kRowsPerWave; ++i)
+                if (cmiss[i] != 0 && ((cmiss[i] >> lane) & 1ull)) ck[i] = handed_over(cfrom[i]);
+            u64 any = 0;
 #pragma unroll
-            for (int i = 0; i < kRowsPerWave; ++i) {
-                const int h = wave + i * MW;
-                ck[i] = kNoKey;
-                if (kPacked) hd[kPacked ? i : 0] = kNoKey;
-                if (h < k) {
-                    const size_t o = ((size_t)b * k + h) * kWave;
-                    if (lane < P_here) ck[i] = handed_over(conskeys + o + lane);
-                    if (kPacked) hd[kPacked ? i : 0] = handed_over(rowlists + o);
-                }
-            }
+            for (int i = 0; i < kLists; ++i) any |= miss[i] = __ballot(rl[i] == 0);
 #pragma unroll
-            for (int i = 0; i < kLists; ++i) there &= rl[i] != 0;
-#pragma unroll
-            for (int i = 0; i < kRowsPerWave; ++i) {
-                there &= ck[i] != 0;
-                if (kPacked) there &= hd[kPacked ? i : 0] != 0;
-            }
-            if (__ballot(!there) == 0) break;
+            for (int i = 0; i < kRowsPerWave; ++i) any |= cmiss[i] = __ballot(ck[i] == 0);
+            if (any == 0) break;
             if (tries <= 0) {
                 if (last || !all_rows_ended(p, b, k, sm.verdict)) break;
                 last = true;
@@ -1251,10 +1252,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
 #pragma unroll
         for (int i = 0; i < kLists; ++i) rl[i] = rl[i] == kNoKey ? 0 : rl[i];
 #pragma unroll
-        for (int i = 0; i < kRowsPerWave; ++i) {
-            ck[i] = ck[i] == kNoKey ? 0 : ck[i];
-            if (kPacked) hd[kPacked ? i : 0] = hd[kPacked ? i : 0] == kNoKey ? 0 : hd[kPacked ? i : 0];
-        }
+        for (int i = 0; i < kRowsPerWave; ++i) ck[i] = ck[i] == kNoKey ? 0 : ck[i];
     } else {
     if constexpr (kPacked) {
 #pragma unroll
@@ -1290,11 +1288,9 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     for (int i = 0; i < kRowsPerWave; ++i) {
         const int h = wave + i * MW;
         ck[i] = 0;
-        if (kPacked) hd[kPacked ? i : 0] = 0;
         if (h < k) {
             const size_t o = ((size_t)b * k + h) * kWave;
             ck[i] = conskeys[o + lane];
-            if (kPacked) hd[kPacked ? i : 0] = rowlists[o];
         }
     }
     }
@@ -1316,10 +1312,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
 #pragma unroll
         for (int i = 0; i < kLists; ++i) asm volatile("" : "+v"(rl[i]));
 #pragma unroll
-        for (int i = 0; i < kRowsPerWave; ++i) {
-            asm volatile("" : "+v"(ck[i]));
-            if (kPacked) asm volatile("" : "+v"(hd[kPacked ? i : 0]));
-        }
+        for (int i = 0; i < kRowsPerWave; ++i) asm volatile("" : "+v"(ck[i]));
     }
     // ---- source 1: the sentence's k best (Sec. 3.1 item 1) = top k of the union of the row
     // lists.  All that is needed of them is the bar tau a key has to reach to be among them.
@@ -1494,8 +1487,16 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
 #pragma unroll
         for (int i = 0; i < kRowsPerWave; ++i) {
             if (wave + i * MW < k) {
-                const u64 best = (kPacked ? hd[kPacked ? i : 0] : kHalves ? read_lane(rl[i / 2], (i & 1) * 32)
-                                                                          : read_lane(rl[kPacked ? 0 : i], 0)) & body_mask;
+                u64 best;
+                if constexpr (kPacked) {
+                    const int e = (wave + i * MW) * k;
+                    best = read_lane(rl[0], e & (kWave - 1));
+#pragma unroll
+                    for (int j = 1; j < J; ++j) best = e >= j * kWave ? read_lane(rl[j], e & (kWave - 1)) : best;
+                } else {
+                    best = kHalves ? read_lane(rl[i / 2], (i & 1) * 32) : read_lane(rl[kPacked ? 0 : i], 0);
+                }
+                best &= body_mask;
                 const u64 body = ck[i] & body_mask;
                 const bool valid = body - 1 < below - 1 && body != best;      // (an empty place holds 0)
                 cm |= (valid ? 1u : 0u) << i;
