@@ -27,14 +27,16 @@ using namespace dba;
 // logp, V, k, first_step are what the first loads need; the kernels take them as leading scalar
 // arguments, which the hardware hands over in registers at wave start (kernel-argument preload),
 // so that the first two tiles are requested before any argument has been read from memory.
-template <int U, int FMT, int NW, int D, bool ONE>
-__device__ __forceinline__ void stream_phase(const StepParams &p, const void *logp, int V, int k, int first_step,
-                                             int b, int h, StreamSmem<NW> &sm)
+// TO: where the keys go.  kInMemory; kHandedOver, the same to a workgroup that runs now; kInLds, sm.key[slot] (rows of one wave).
+// wave: of the row's NW; turn: which of them finishes the row, modulo NW; early: what else to request, right behind the first two tiles.
+template <int U, int FMT, int NW, int D, int TO, typename Smem, typename Early>
+__device__ __forceinline__ void stream_phase(const StepParams &p, const void *logp, int V, int k, int first_step, int b, int h,
+                                             int wave, int turn, int slot, Smem &sm, Early early)
 {
     typedef typename Logp<FMT>::elem_t elem_t;
+    static_assert((TO == kInLds) == (NW == 1), "a row of one wave");
     const int row = b * k + h;
     const int lane = lane_id();
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     constexpr int nwaves = NW;
     const bool gatherer = wave == nwaves - 1;     // this wave also fetches the constraint tokens
 
@@ -46,6 +48,7 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
     const bool known_empty = first_step && h != 0;   // decoder-init leaves slots 1.. empty
     if (!known_empty) rs.begin(logp_row, V, wave, nwaves);
     __builtin_amdgcn_sched_barrier(0);
+    early();
     // then the hypothesis and its constraint bookkeeping (one wave, one lane per phrase)
     const Sentence &sent = p.sentences[b];
     const Hyp hyp = p.beam[row];
@@ -57,9 +60,7 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
     int zero = 0;
     asm volatile("" : "+v"(zero));
     const uint32_t state_ld = (&p.beam[row].state)[zero];
-    // workgroups are dealt out round-robin over the 256 compute units, so the ones sharing a
-    // compute unit differ in (number / 256): let that pick the wave (hence the SIMD) that finishes the row
-    const int fin_wave = (int)(blockIdx.x >> 8) & (nwaves - 1);
+    const int fin_wave = turn & (nwaves - 1);
     const bool finisher = wave == fin_wave;
     u64 g_sfl = 0, t_bucket = 0;
     int g_ftok = -1, t_btok = -1;
@@ -92,7 +93,7 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
         const float cx = cw >= 0 ? Logp<FMT>::widen_one(logp_row[cw]) : -INFINITY;
         // Sec. 3.3: no end-of-sentence before all constraints are met
         const int eos_block = (fin & kFinEosBlocked) ? p.eos_id : -1;
-        parked = rs.run(prev, eos_block, code_base, k, wave, sm, st);
+        parked = rs.template run<NW>(prev, eos_block, code_base, k, wave, slot, sm, st);
         const float cs = prev + cx;
         if (cw >= 0 && cs > -INFINITY)
             ckey = pack_sel(p.met_bits, cbank, ord_from_float(cs), code_base | (uint32_t)cw);
@@ -101,14 +102,16 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
         // at log-prob +0.0, score carried unchanged
         st.list = make_key(prev + 0.0f, code_base | (uint32_t)p.pad_id);
     }
-    if (gatherer) {
-        if constexpr (ONE) {
+    if (gatherer && TO != kInLds) {
+        if constexpr (TO == kHandedOver) {
             if (lane < phrases) hand_over(p.conskeys + (size_t)row * kMaxCons + lane, ckey ? ckey : kNoKey);
         } else {
             p.conskeys[(size_t)row * kMaxCons + lane] = ckey;
         }
     }
-    const u64 acc = finish_row(sm, st.list, parked, wave, fin_wave);
+    u64 acc;
+    if constexpr (NW == 1) acc = finish_row_of_one_wave(sm.key[slot], st.list, parked);
+    else acc = finish_row(sm, st.list, parked, wave, fin_wave);
     if (finisher) {
         // Handed on as selection keys: every listed sum with the bank it would land in - the
         // constraints met once the hypothesis has emitted that token (add(), Sec. 3.1).  Each lane
@@ -133,7 +136,10 @@ __device__ __forceinline__ void stream_phase(const StepParams &p, const void *lo
                                   : nmet_after(nmet, ipq < 0 ? -1 : (ipq >> 8), ipq < 0 ? 0 : (ipq & 255), w == hyp.nxt, match,
                                                hyp.inc);
         const u64 key = sel_from_rowkey(p.met_bits, bank, acc);
-        if constexpr (ONE) {
+        if constexpr (TO == kInLds) {
+            sm.key[slot][lane] = key;
+            sm.key[slot][kWave + lane] = ckey;
+        } else if constexpr (TO == kHandedOver) {
             if (lane < k) hand_over(p.rowlists + (size_t)row * kWave + lane, key ? key : kNoKey);
         } else {
             p.rowlists[(size_t)row * kWave + lane] = key;
@@ -160,7 +166,10 @@ __global__ __launch_bounds__(NW * kWave) void dba_stream_kernel(const void *logp
     const uint32_t m = abreast ? n >> 3 : n;
     const uint32_t q = k == 1 ? m : __umulhi(m, inv_k);
     const int b = (int)(abreast ? q * 8u + (n & 7u) : q), h = (int)(m - q * k);
-    stream_phase<U, FMT, NW, D, false>(p, logp, V, (int)k, k_first >> 16, b, h, sm);
+    // workgroups are dealt out round-robin over the 256 compute units, so the ones sharing a
+    // compute unit differ in (number / 256): let that pick the wave (hence the SIMD) that finishes the row
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    stream_phase<U, FMT, NW, D, kInMemory>(p, logp, V, (int)k, k_first >> 16, b, h, wave, (int)(blockIdx.x >> 8), wave, sm, [] {});
 }
 
 // Both phases in one launch, for steps of few rows.  Grid: B * k workgroups for the rows, then B that each take a
@@ -199,7 +208,8 @@ __global__ __launch_bounds__(NW * kWave) void dba_step_kernel(const void *logp, 
         const uint32_t q = k == 1 ? m : __umulhi(m, inv_k);
         b = (int)(abreast ? q * 8u + (n & 7u) : q);
         const int h = (int)(m - q * k);
-        stream_phase<U, FMT, NW, D, true>(p, logp, V, (int)k, k_first >> 16, b, h, ss);
+        stream_phase<U, FMT, NW, D, kHandedOver>(p, logp, V, (int)k, k_first >> 16, b, h, wave, (int)(blockIdx.x >> 8), wave, ss,
+                                                 [] {});
         // (each wave waits until the keys it has handed over are in memory, where their agent-scope stores put them)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
@@ -222,7 +232,40 @@ __global__ __launch_bounds__(NW * kWave) void dba_step_kernel(const void *logp, 
     }
     __syncthreads();
     if (wave >= MW) return;
-    merge_phase<ROWS, MW, J, true, true>(p, p.rowlists, p.conskeys, (int)k, inv_k16, b, ms, cand, P, most_tries, all_ended);
+    merge_phase<ROWS, MW, J, kHandedOver, true>(p, p.rowlists, p.conskeys, (int)k, inv_k16, b, ms, cand, P, most_tries, all_ended);
+}
+
+// Both phases of steps of short rows and narrow beams: one workgroup per sentence, a wave per row (k <= 8), so that nothing is
+// handed over through memory and no wave of a row waits for another.  Such a step is one chain of latencies; here it is as long as
+// one wave takes for a row, with eight on four SIMDs, which is why it pays only for few bytes a sentence.  Per step, one launch with a
+// workgroup per row and one per sentence / this: 5 rows of 1000 fp32 7.95 / 6.9 us, one of 1000 7.45 / 6.25, 8 of 1024 7.75 / 7.3, 256 x 5 of 1000
+// 9.95 / 8.2; but 5 of 3000 7.75 / 8.1, 8 of 2000 7.85 / 8.35, 8 of 4000 8.1 / 9.6, and with sixteen waves 10 of 2000 8.8 / 9.7, 16 of 4000
+// 9.1 / 11.0.
+template <int FMT>
+__global__ __launch_bounds__(kSentenceWaves * kWave) void dba_sentence_kernel(const void *logp, int V, int k_first, uint32_t inv_k16,
+                                                                             const StepParams p)
+{
+    extern __shared__ __align__(16) unsigned char dyn_smem[];
+    __shared__ SentenceSmem sm;
+    constexpr int MW = 4;
+    MergeSmem<MW> &ms = *reinterpret_cast<MergeSmem<MW> *>(dyn_smem);
+    u64 *cand = reinterpret_cast<u64 *>(dyn_smem + (sizeof(MergeSmem<MW>) + 15) / 16 * 16);
+    const int k = k_first & 0xFFFF, b = (int)blockIdx.x, tid = (int)threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    MergeTables tables;
+    int P = 0;
+    auto early = [&] {
+        if (wave < MW) P = tables.request(p, b, k, tid);
+    };
+    if (wave < k) stream_phase<kTileLoads, FMT, 1, 2, kInLds>(p, logp, V, k, k_first >> 16, b, wave, 0, 0, wave, sm, early);
+    else early();
+    if (wave < MW) {
+        clear_for_merge(p, tid, MW * kWave, ms, cand);
+        tables.store(k, tid, ms);
+    }
+    __syncthreads();
+    if (wave >= MW) return;
+    merge_phase<2, MW, 1, kInLds, false>(p, sm.key[0], sm.key[0] + kWave, k, inv_k16, b, ms, cand, P, 0, false);
 }
 
 // Second launch of a step: the merge phase.  Grid: one workgroup of MW waves per sentence, each wave
@@ -235,7 +278,7 @@ __global__ __launch_bounds__(MW * kWave) void dba_merge_kernel(const u64 *rowlis
 {
     extern __shared__ __align__(16) unsigned char dyn_smem[];
     __shared__ MergeSmem<MW> sm;
-    merge_phase<ROWS, MW, J, false, EMPTY>(p, rowlists, conskeys, (int)(k_inv & 0xFFFFu), k_inv >> 16, (int)blockIdx.x, sm,
+    merge_phase<ROWS, MW, J, kInMemory, EMPTY>(p, rowlists, conskeys, (int)(k_inv & 0xFFFFu), k_inv >> 16, (int)blockIdx.x, sm,
                                            reinterpret_cast<u64 *>(dyn_smem), 0, 0, false);
 }
 
@@ -590,7 +633,8 @@ bool one_launch_shape(size_t B, size_t k, size_t V)
 
 // How the stream phase of a step is launched: one workgroup per beam row, and
 struct StreamPlan {
-    bool one;               // launch does for the whole step, if the options leave it open
+    bool one;               // launch does for the whole step, if the options leave it open,
+    bool sentence;          // with one workgroup per sentence
     int waves;              // of a workgroup: 4 or 8
     int tiles;              // of 4 KB that each wave keeps in flight
     size_t spare_lds;       // LDS a workgroup asks for and does not use, which keeps others off its compute unit
@@ -627,6 +671,11 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem, bool free)
     // rows of 2000, k = 20, 10.3 / 9.7 us, 126 of 4000, k = 18, 10.8 / 9.75, 504 11.7 / 10.8, 448 of 7000, k = 28, 13.0 / 12.2; 512 of 5000, k = 32, 12.8 /
     // 13.5; 16-bit rows gain less, 240 of 6000, k = 20, 11.15 / 10.7, and are left as they are, like rows of 28 to 32 KB).
     plan.one = free && one_launch_shape(B, k, V) && (k <= 16 || plan.waves == 8) && (rows <= 2 * kComputeUnits || rows * plan.waves <= 22 * kComputeUnits);
+    // One workgroup for a whole sentence where its rows are short and few: eight tiles in all (a partial one takes as long as a whole one; per step,
+    // a workgroup per row / per sentence, 40 sentences, fp32: k = 8, 1024 tokens 8.15 / 7.75 us, 4, 2048 7.85 / 7.6, 5, 1000 8.2 / 7.55, but 5, 1638 8.3 / 8.55,
+    // 3, 2730 8.1 / 8.25), and no more sentences than three for a compute unit (700, k = 2, 1000 tokens 10.5 / 8.95; 1300, k = 1, 11.3 / 14.5).
+    const size_t tiles = (row_bytes + 4095) / 4096;
+    plan.sentence = plan.one && k * tiles <= kSentenceWaves && tiles <= 4 && B <= 3 * kComputeUnits;
     // Rows side by side on a compute unit.  More than a unit's even share leaves others short, and lets a
     // second decode's rows in beside the first one's: where the grid fills the chip, no more than that share
     // (three decodes of 64 x 20 rows of 32000 in flight: 84 against 94 us for three steps, one of them alone
@@ -1050,7 +1099,18 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     const uint32_t inv_k = (uint32_t)(((1ull << 32) + (unsigned)c->k - 1) / (unsigned)c->k);
     const int kf = p.k | (p.first_step << 16);
     const uint32_t inv_k16 = (uint32_t)(c->k == 1 ? 65535 : 65536 / c->k + 1);
-    if (plan.one) {
+    if (plan.sentence) {
+        const size_t lds = align_up(sizeof(MergeSmem<4>), 16) + c->dyn_smem;
+        static_assert(sizeof(SentenceSmem) + sizeof(MergeSmem<4>) + 16 + (size_t)kSentenceWaves * (DBA_MAX_CONS_TOKENS + 2) * sizeof(u64) + 64 * sizeof(u64) +
+                      kMostLeft * (sizeof(u64) + sizeof(int)) <= kLdsPerLaunch, "beside the rows' LDS");
+#define SENTENCE(FMT) dba_sentence_kernel<FMT><<<(unsigned)c->B, kSentenceWaves * kWave, lds, c->stream>>>(p.logp, p.V, kf, inv_k16, p)
+        switch (logp_format) {
+            case DBA_LOGP_F16: SENTENCE(kFmtF16); break;
+            case DBA_LOGP_BF16: SENTENCE(kFmtBF16); break;
+            default: SENTENCE(kFmtF32); break;
+        }
+#undef SENTENCE
+    } else if (plan.one) {
         // (the places are empty between steps, which only the ctx's own are)
         p.rowlists = at<u64>(c, L.rowlists);
         p.conskeys = at<u64>(c, L.conskeys);

@@ -382,6 +382,16 @@ struct StreamSmem {
     int has_list[NW];                   // and whether it holds a list from earlier folds
 };
 
+// LDS of a workgroup that streams all rows of a sentence, a wave each.  At the end of its row a wave leaves the row's list in the
+// first 64 of its keys and the keys of its constraint tokens in the others.
+constexpr int kSentenceWaves = 8;
+struct SentenceSmem {
+    v4u group[kSentenceWaves][kGroupCap];
+    uint32_t coord[kSentenceWaves][kGroupCap];
+    u64 key[kSentenceWaves][kKeyCap];
+};
+static_assert(kKeyCap == kWave + kMaxCons, "a list and the constraint keys");
+
 // The groups a wave has set aside, element by element: sums that reach the threshold are parked as keys,
 // and the keys are folded into the wave's list whenever they would overflow (the threshold then
 // rises).  Reached only where the k best groups hold more keys than there is room for (few elements, many ties): kept
@@ -519,19 +529,20 @@ struct RowStream {
         return lane < head ? lane : head + nv * G + (lane - head);
     }
 
-    // Returns the number of keys left parked in sm.key[wave] (not yet folded into st.list).
-    template <int NW>
-    __device__ __forceinline__ int run(float prev, int eos_block, uint32_t flat_base, int kk, int wave,
-                                       StreamSmem<NW> &sm, RowTop &st);
+    // slot: the wave's places in sm (which other rows' waves may share).
+    // Returns the number of keys left parked in sm.key[slot] (not yet folded into st.list).
+    template <int NW, typename Smem>
+    __device__ __forceinline__ int run(float prev, int eos_block, uint32_t flat_base, int kk, int wave, int slot, Smem &sm,
+                                       RowTop &st);
 };
 
 template <int U, int FMT, int D>
-template <int NW>
+template <int NW, typename Smem>
 __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_block, uint32_t flat_base, int kk,
-                                                         int wave, StreamSmem<NW> &sm, RowTop &st)
+                                                         int wave, int slot, Smem &sm, RowTop &st)
 {
     constexpr int nwaves = NW;
-    constexpr bool LL = D > 2;            // few waves about: exchanges of the shortest latency
+    constexpr bool LL = D > 2 || NW == 1; // few waves about: exchanges of the shortest latency
     const int lane = lane_id();
     const int nfull = nv / (kWave * U);
     const uint32_t lane_coord = flat_base + (uint32_t)(head + G * lane);
@@ -560,7 +571,9 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
     }
     // Any k values that different lanes hold give a valid floor
     constexpr int share = kWave / nwaves;              // entries of every wave that fit one 64-lane sort
-    if (floor_from_cells<NW, U>(kk, nv, ntiles)) {
+    if constexpr (NW == 1) {
+        boot = sort64_minmax_desc(boot);
+    } else if (floor_from_cells<NW, U>(kk, nv, ntiles)) {
         boot = max_of_lanes<nwaves>(boot);
         if (lane % nwaves == 0) sm.boot[wave][lane / nwaves] = boot;
         __syncthreads();
@@ -586,9 +599,9 @@ __device__ __forceinline__ int RowStream<U, FMT, D>::run(float prev, int eos_blo
     }
     st.thr = fmaxf(float_from_ord((uint32_t)__builtin_amdgcn_readlane((int)boot, kk - 1)), kLowestFinite);
     typename F::Quick quick = F::quick(prev, st.thr);
-    v4u *group = sm.group[wave];
-    uint32_t *coord = sm.coord[wave];
-    u64 *key = sm.key[wave];
+    v4u *group = sm.group[slot];
+    uint32_t *coord = sm.coord[slot];
+    u64 *key = sm.key[slot];
     int cnt = 0, parked = 0;              // groups set aside, keys parked
     auto set_aside = [&](const vec_t &x, bool mine, u64 m, uint32_t at) {
         if (mine) {
@@ -827,6 +840,17 @@ __device__ __forceinline__ u64 finish_row(StreamSmem<NW> &sm, u64 list, int park
         }
     }
     return part;
+}
+
+// The same for a row of one wave.
+__device__ __forceinline__ u64 finish_row_of_one_wave(const u64 *keys, u64 list, int parked)
+{
+    const int lane = lane_id(), n = __builtin_amdgcn_readfirstlane(parked);
+    for (int base = 0; base < n; base += kWave) {
+        const u64 sorted = sort_first_desc<u64, true>(base + lane < n ? keys[base + lane] : 0ull, n - base);
+        list = read_lane(list, 0) != 0 ? merge_desc<u64, true>(list, sorted) : sorted;
+    }
+    return list;
 }
 
 // ---------------------------------------------------------------------------
@@ -1177,16 +1201,22 @@ __device__ __forceinline__ void clear_for_merge(const StepParams &p, int tid, in
 // halves the merges, the registers looked through for candidates and the LDS they pass through.
 // rowlists, conskeys, k, inv_k: what the first loads need (p.rowlists, p.conskeys, p.k; floor(2^16 / k) + 1,
 // with which i * inv_k >> 16 is i / k for i < k * k, k <= 32).
-// ONE: most_tries, how often a wave looks for the rows' keys before it asks whether to go on (if not, the workgroup leaves and
-// has written nothing); all_ended, the sentence was left to this workgroup, a row's, as every row has ended.
+// SRC: where the keys come from.  kInMemory, an earlier launch has left them there; kHandedOver, workgroups that run now (most_tries: how
+// often a wave looks for them before it asks whether to go on; if not, the workgroup leaves and has written nothing.  all_ended:
+// the sentence was left to this workgroup, a row's, as every row has ended); kInLds, the other waves of this workgroup, rowlists
+// and conskeys point to those of its first row.  Tables and counters are in LDS already, but for kInMemory.
 // EMPTY: the row lists are left empty, as a step of one launch finds and leaves them.
-template <int ROWS, int MW, int J, bool ONE, bool EMPTY>
+constexpr int kInMemory = 0, kHandedOver = 1, kInLds = 2;
+
+template <int ROWS, int MW, int J, int SRC, bool EMPTY>
 __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowlists, const u64 *conskeys, int k,
                                             uint32_t inv_k, int b, MergeSmem<MW> &sm, u64 *cand, int P_here, int most_tries,
                                             bool all_ended)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // in a scalar register: row guards are scalar branches
+    // places of the lists of the sentence's row h
+    auto at_row = [&](int h) { return SRC == kInLds ? (size_t)(h * kKeyCap) : ((size_t)b * k + h) * kWave; };
     // the row lists first: the chain of this phase starts with them, and their addresses need nothing
     // that has to be read from memory first
     constexpr bool kPacked = J > 0;
@@ -1195,7 +1225,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     constexpr int kLists = kPacked ? J : (kHalves ? ROWS / 2 : ROWS);
     u64 rl[kLists], ck[kRowsPerWave];
     uint32_t head_bits = 0;                                // packed: bit j = this lane's entry j is a row's best
-    if constexpr (ONE) {
+    if constexpr (SRC == kHandedOver) {
         // Handed over by workgroups that run now: read again until every place this wave looks at is filled (ONE's tables
         // and counters are in LDS already).  Only places that are still empty are asked for again: a look takes as long as its
         // requests, the keys are seen half a look late, and at the end it is one row that all wait for.  (Per step, all places asked for in
@@ -1262,7 +1292,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
             if (i < (uint32_t)(k * k)) {
                 const uint32_t h = (i * inv_k) >> 16, at = i - h * (uint32_t)k;
                 head_bits |= (at == 0 ? 1u : 0u) << j;
-                rl[j] = rowlists[((size_t)b * k + h) * kWave + at];
+                rl[j] = rowlists[at_row((int)h) + at];
             }
         }
     } else if constexpr (kHalves) {
@@ -1271,27 +1301,21 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         for (int i = 0; i < kLists; ++i) {
             const int h = wave + (2 * i + (lane >> 5)) * MW;
             rl[i] = 0;
-            if (h < k && (lane & 31) < k) rl[i] = rowlists[((size_t)b * k + h) * kWave + (lane & 31)];
+            if (h < k && (lane & 31) < k) rl[i] = rowlists[at_row(h) + (lane & 31)];
         }
     } else {
 #pragma unroll
         for (int i = 0; i < kLists; ++i) {
             const int h = wave + i * MW;
             rl[i] = 0;
-            if (h < k) {
-                const size_t o = ((size_t)b * k + h) * kWave + lane;
-                rl[i] = rowlists[o];
-            }
+            if (h < k) rl[i] = rowlists[at_row(h) + lane];
         }
     }
 #pragma unroll
     for (int i = 0; i < kRowsPerWave; ++i) {
         const int h = wave + i * MW;
         ck[i] = 0;
-        if (h < k) {
-            const size_t o = ((size_t)b * k + h) * kWave;
-            ck[i] = conskeys[o + lane];
-        }
+        if (h < k) ck[i] = conskeys[at_row(h) + lane];
     }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -1304,7 +1328,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
 
     MergeTables tables;
     int P = P_here;
-    if constexpr (!ONE) {
+    if constexpr (SRC == kInMemory) {
         P = tables.request(p, b, k, tid);
         clear_for_merge(p, tid, MW * kWave, sm, cand);
         if (kPacked) __syncthreads();
@@ -1343,7 +1367,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     }
     // the sentence's tables and beam go to LDS only now: their loads were issued after those of the
     // row lists and arrive later, and the merges above needed none of them
-    if constexpr (!ONE) tables.store(k, tid, sm);
+    if constexpr (SRC == kInMemory) tables.store(k, tid, sm);
     // the waves' lists of 32, two to a register
     auto joined32 = [&](uint32_t *buf, uint32_t mine) {
         if (lane < 32) buf[wave * 32 + lane] = mine;
@@ -1512,8 +1536,8 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
                 const u64 body = ck[i] & body_mask;
                 // (places from k on cannot be among the k best)
                 const u64 listed = lane >= k ? 0ull
-                                   : ONE ? handed_over(rowlists + ((size_t)b * k + h) * kWave + lane)
-                                   : (kPacked || kHalves) ? rowlists[((size_t)b * k + h) * kWave + lane] : rl[kPacked ? 0 : i];
+                                   : SRC == kHandedOver ? handed_over(rowlists + at_row(h) + lane)
+                                   : (kPacked || kHalves) ? rowlists[at_row(h) + lane] : rl[kPacked ? 0 : i];
                 u64 tied = __ballot(((cm >> i) & 1u) != 0 && body >= tau);
                 while (tied) {
                     const int l = __ffsll((long long)tied) - 1;
@@ -1731,7 +1755,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
     __syncthreads();
 
     const int nsel = min(sm.nsel, k);
-    if constexpr (ONE) {
+    if constexpr (SRC == kHandedOver) {
         const int verdict = __builtin_amdgcn_readfirstlane(sm.verdict);
         if (verdict == kLeaves) return;
         // once the last row has counted itself, the next step finds no row ended,

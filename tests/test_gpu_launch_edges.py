@@ -24,7 +24,9 @@ def _bytes(ses):
     (88, 16, 512, ("f32",), True), (89, 16, 512, ("f32",), False), (88, 16, 511, ("f32",), False), (1408, 1, 700, ("f16",), True),
     (176, 8, 1031, ("bf16", "f32"), True), (127, 11, 2049, ("f32", "f16"), True), (93, 15, 3001, ("f32",), True), (64, 11, 41001, ("f32", "bf16"), True),
     (65, 11, 41001, ("f32", "bf16"), True), (89, 8, 41001, ("bf16", "f32"), True), (46, 16, 41001, ("f16", "f32"), True),
-    (18, 28, 7168, ("f32", "f16"), True), (18, 28, 7169, ("f32",), True), (30, 17, 1000, ("f32",), True), (1, 17, 17, ("f32",), True), (5, 24, 1024, ("f32", "bf16"), True)])
+    (18, 28, 7168, ("f32", "f16"), True), (18, 28, 7169, ("f32",), True), (30, 17, 1000, ("f32",), True), (1, 17, 17, ("f32",), True), (5, 24, 1024, ("f32", "bf16"), True),
+    (3, 8, 1024, ("f32", "bf16"), True), (3, 8, 1023, ("f32", "f16"), True), (41, 4, 2047, ("f32", "bf16"), True), (5, 2, 4093, ("f32",), True), (2, 1, 8190, ("bf16", "f32"), True),
+    (7, 5, 700, ("f16",), True), (768, 1, 600, ("f32",), True), (769, 1, 600, ("f32",), True), (6, 8, 60, ("f32", "bf16"), True), (2, 7, 9, ("f32",), True)])
 def test_one_launch_and_two(B, k, V, fmts, one):
     """Every step against the two launches, with the element types by turns (where they decide how many launches a step takes,
     the places that rows hand their keys over in are left empty by both), the step with its own scratch among them, and with the
@@ -60,3 +62,26 @@ def test_floors_of_rows_of_one_tile_to_six(k, fmt):
         wl = si.make_small(9800 + tiles, 2, k, tiles * tile - 3, 3, max_phrases=2, max_len=2, dup_prob=0.3)
         wl.eos_switch = 2
         harness.run_parity(wl, logp_format=fmt)
+
+
+@pytest.mark.parametrize("B,k,V,fmt", [(3, 8, 1024, None), (2, 8, 1021, "f16"), (4, 5, 1000, None), (3, 4, 4096, "bf16"), (3, 2, 4095, None), (2, 1, 4001, None), (5, 3, 40, "bf16"), (3, 8, 11, None)])
+@pytest.mark.parametrize("shape", ["zipf", "rising", "equal"])
+def test_a_sentence_in_one_workgroup(B, k, V, fmt, shape):
+    """Rows of up to four tiles, one wave each, against the oracle: rising rows and equal elements fill a wave's room for groups and for keys."""
+    import harness
+    base = si.make_small(9850 + V, B, k, V, 8, max_phrases=4, max_len=3, dup_prob=0.3)
+    if shape == "zipf":
+        wl = base
+    else:
+        class Shaped(si.Workload):
+            def logp(self, t, out=None):
+                lp = super().logp(t, out=out)
+                if shape == "rising":
+                    lp.sort(axis=-1)
+                else:
+                    lp.fill(np.float32(-3.0))
+                return lp
+        wl = Shaped(B=B, k=k, V=V, T=8, seed=base.seed, constraints=base.constraints)
+    wl.eos_switch = 5
+    harness.run_parity(wl, logp_format=fmt)
+    harness.run_parity(wl, logp_format=fmt, normalize=True, prune=20.0, track=True)
