@@ -822,6 +822,12 @@ struct dba_ctx {
     bool one_launch;                    // the row lists are empty between steps, which may then be one launch each
     int give_up;                        // dba_debug_sentences_first
     bool init_under_way;                // the kernel of dba_init may not be through: nothing has waited for it yet
+    // Once the stopping flags have been asked for, steps write them to the block themselves: no kernel of its own has to bring them over.
+    // (a decode of 21 steps asked after each, 8 x 10 x 32000: 614 -> 589 us; the rest of a question is the wait for the stream, 8 us of it
+    // after the last store).  Not those recorded into a graph, which may run when the ctx is gone, and none from there on: a replay may be what ran last.
+    bool asked, recorded;
+    int told;                           // steps taken when the last one that did so had been launched (0: none),
+    bool told_under_way;                // and whether nothing has waited for it yet
     hipStream_t stream;
     char err[256];
 };
@@ -1063,6 +1069,12 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         return fail(c, DBA_EINVAL, "dba_step: logp_dev must be aligned to its element size (%u bytes)", elem);
     if (c->steps >= c->N) return fail(c, DBA_ESTATE, "dba_step: all N=%d steps have been taken", c->N);
 
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (!c->recorded && (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
+        if (capture == hipStreamCaptureStatusNone) (void)hipGetLastError();
+        c->recorded = true;
+    }
+    const bool tells = c->asked && !c->recorded && c->block.p;
     // one workgroup per beam row, 4 loads of 16 bytes per lane and tile, two or four 4 KB tiles in flight per wave
     const StreamPlan plan = stream_plan((size_t)c->B, (size_t)c->k, (size_t)c->V, elem, c->one_launch && c->merge_waves == 0);
     const int cur = c->steps & 1;
@@ -1087,6 +1099,7 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     p.conskeys = own_scratch ? reinterpret_cast<u64 *>(own_scratch + kStaticListBytes) : at<u64>(c, L.conskeys);
     // (what a step's rows are made of may decide how many launches it takes; one must find the places empty after two)
     const bool leave_empty = c->one_launch && c->merge_waves == 0 && !plan.one && !own_scratch;
+    p.told = tells ? c->block.p + c->block_flags : nullptr;
     p.out_token = out_token_dev;
     p.out_backptr = out_backptr_dev;
     p.out_score = out_score_dev;
@@ -1203,8 +1216,16 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
 #undef MERGE
     }
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(c, DBA_EHIP, "dba_step: launch failed: %s", hipGetErrorString(e));
+    if (e != hipSuccess) {
+        c->recorded = c->recorded || tells;                // (what has been launched is not known)
+        c->told_under_way = c->told_under_way || tells;
+        return fail(c, DBA_EHIP, "dba_step: launch failed: %s", hipGetErrorString(e));
+    }
     c->steps += 1;
+    if (tells) {
+        c->told = c->steps;
+        c->told_under_way = true;
+    }
     return DBA_OK;
 }
 
@@ -1281,7 +1302,7 @@ DBA_API int dba_finalize(dba_ctx *c, int32_t *out_tokens_host, int32_t *out_len_
         if (here) c->block.p = nullptr;                    // (a kernel may still write to it: never used again)
         return fail(c, DBA_EHIP, "dba_finalize: HIP error: %s", hipGetErrorString(e));
     }
-    c->init_under_way = false;
+    c->init_under_way = c->told_under_way = false;
     if (const unsigned char *from = here ? here : copied.p) {
         if (staged) memcpy(out_tokens_host, from, tokens_bytes);
         memcpy(out_len_host, from + (L.fin_len - first), B * 4);
@@ -1307,7 +1328,7 @@ DBA_API int dba_get_state(dba_ctx *c, float *score_host, uint64_t *met_mask_host
     hipError_t e = hipMemcpyAsync(beam, at<Hyp>(c, L.beam[cur]), n * sizeof(Hyp), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return fail(c, DBA_EHIP, "dba_get_state: HIP error: %s", hipGetErrorString(e));
-    c->init_under_way = false;
+    c->init_under_way = c->told_under_way = false;
     for (size_t i = 0; i < n; ++i) {
         const Hyp &y = beam[i];
         const int ipq = ipq_of(y.state);
@@ -1349,8 +1370,10 @@ DBA_API int dba_get_finished(dba_ctx *c, uint8_t *all_finished_host)
     if (!all_finished_host) return fail(c, DBA_EINVAL, "dba_get_finished: the output pointer is NULL");
     const uint8_t *flags = at<uint8_t>(c, c->L.all_finished);
     uint8_t *here = c->block.p ? c->block.p + c->block_flags : nullptr;
-    hipError_t e;
-    if (here) {
+    hipError_t e = hipSuccess;
+    if (here && !c->recorded && c->steps > 0 && c->told == c->steps) {
+        // the last step has written them
+    } else if (here) {
         dba_flags_kernel<<<1, kBlock, 0, c->stream>>>((c->B + 3) / 4, reinterpret_cast<const uint32_t *>(flags),
                                                       reinterpret_cast<uint32_t *>(here));
         e = hipGetLastError();
@@ -1362,24 +1385,27 @@ DBA_API int dba_get_finished(dba_ctx *c, uint8_t *all_finished_host)
         c->block.p = nullptr;                              // (a kernel may still write to it: never used again)
         return fail(c, DBA_EHIP, "dba_get_finished: HIP error: %s", hipGetErrorString(e));
     }
-    c->init_under_way = false;
+    c->init_under_way = c->told_under_way = false;
     if (here) memcpy(all_finished_host, here, (size_t)c->B);
+    c->asked = true;
     return DBA_OK;
 }
 
 DBA_API void dba_destroy(dba_ctx *c)
 {
     if (!c) return;
-    // a ctx that goes before the GPU is through with its dba_init: the workspace and the block are given back only then
-    if (c->init_under_way && !init_is_through(c)) {
+    // a ctx that goes before the GPU is through with its dba_init, or with steps that write to the block: the workspace and
+    // the block are given back only then
+    if (c->told_under_way || (c->init_under_way && !init_is_through(c))) {
         const RelaxedCapture relaxed;
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
         if (capture != hipStreamCaptureStatusNone) {       // (what was enqueued before the capture began runs all the same)
-            while (!init_is_through(c)) std::this_thread::yield();
+            while (c->init_under_way && !init_is_through(c)) std::this_thread::yield();
+            if (c->told_under_way) c->block.p = nullptr;   // (never used again)
         } else if (hipStreamSynchronize(c->stream) != hipSuccess) {
             (void)hipGetLastError();
-            c->block.p = nullptr;                          // (never used again)
+            c->block.p = nullptr;
         }
     }
     host_blocks().put(c->block);
