@@ -232,7 +232,7 @@ __global__ __launch_bounds__(NW * kWave) void dba_step_kernel(const void *logp, 
     }
     __syncthreads();
     if (wave >= MW) return;
-    merge_phase<ROWS, MW, J, kHandedOver, true>(p, p.rowlists, p.conskeys, (int)k, inv_k16, b, ms, cand, P, most_tries, all_ended);
+    merge_phase<ROWS, MW, J, kHandedOver>(p, p.rowlists, p.conskeys, (int)k, inv_k16, b, ms, cand, P, most_tries, all_ended);
 }
 
 // Both phases of steps of short rows and narrow beams: one workgroup per sentence, a wave per row (k <= 8), so that nothing is
@@ -265,20 +265,20 @@ __global__ __launch_bounds__(kSentenceWaves * kWave) void dba_sentence_kernel(co
     }
     __syncthreads();
     if (wave >= MW) return;
-    merge_phase<2, MW, 1, kInLds, false>(p, sm.key[0], sm.key[0] + kWave, k, inv_k16, b, ms, cand, P, 0, false);
+    merge_phase<2, MW, 1, kInLds>(p, sm.key[0], sm.key[0] + kWave, k, inv_k16, b, ms, cand, P, 0, false);
 }
 
 // Second launch of a step: the merge phase.  Grid: one workgroup of MW waves per sentence, each wave
 // taking up to ROWS beam rows (k <= ROWS * MW); J > 0: and holding J entries per lane of all the sentence's lists
 // (k * k <= 64 * J).  The pointers to the row lists and the beam width (k_inv = k | inv_k << 16) come first:
 // they are all the first loads need.
-template <int ROWS, int MW, int J, bool EMPTY>
+template <int ROWS, int MW, int J>
 __global__ __launch_bounds__(MW * kWave) void dba_merge_kernel(const u64 *rowlists, const u64 *conskeys, uint32_t k_inv,
                                                                const StepParams p)
 {
     extern __shared__ __align__(16) unsigned char dyn_smem[];
     __shared__ MergeSmem<MW> sm;
-    merge_phase<ROWS, MW, J, kInMemory, EMPTY>(p, rowlists, conskeys, (int)(k_inv & 0xFFFFu), k_inv >> 16, (int)blockIdx.x, sm,
+    merge_phase<ROWS, MW, J, kInMemory>(p, rowlists, conskeys, (int)(k_inv & 0xFFFFu), k_inv >> 16, (int)blockIdx.x, sm,
                                            reinterpret_cast<u64 *>(dyn_smem), 0, 0, false);
 }
 
@@ -571,12 +571,15 @@ constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 struct Layout {
     size_t beam[2], sentences, rowlists, conskeys;
+    size_t place_lists, place_keys;     // the same for steps of one launch, empty between steps (where the shape has such steps)
     size_t hist_token, hist_backptr;
     size_t fin_tokens, fin_len, fin_score, fin_status, all_finished, best;
     size_t total;
 };
 
-Layout make_layout(size_t B, size_t k, size_t N)
+bool one_launch_shape(size_t B, size_t k, size_t V);
+
+Layout make_layout(size_t B, size_t k, size_t V, size_t N)
 {
     Layout L;
     size_t off = 0;
@@ -589,6 +592,9 @@ Layout make_layout(size_t B, size_t k, size_t N)
     L.sentences = take(B * sizeof(Sentence));
     L.rowlists = take(B * k * kWave * sizeof(u64));
     L.conskeys = take(B * k * kMaxCons * sizeof(u64));
+    const size_t places = one_launch_shape(B, k, V) ? B * k : 0;
+    L.place_lists = take(places * kWave * sizeof(u64));
+    L.place_keys = take(places * kMaxCons * sizeof(u64));
     L.hist_token = take(N * B * k * sizeof(int32_t));
     L.hist_backptr = take(N * B * k * sizeof(int32_t));
     L.fin_tokens = take(B * N * sizeof(int32_t));
@@ -628,7 +634,8 @@ constexpr size_t spread_lds(size_t n)
 bool one_launch_shape(size_t B, size_t k, size_t V)
 {
     const size_t rows = B * k;
-    return rows <= 2 * kComputeUnits ? k <= 32 : k <= 16 && V >= 512 && rows * 4 <= 22 * kComputeUnits;
+    if (rows <= 2 * kComputeUnits) return k <= 32;
+    return rows * 4 <= 22 * kComputeUnits && (k <= 16 ? V >= 512 : k <= 28 && V >= 4096);
 }
 
 // How the stream phase of a step is launched: one workgroup per beam row, and
@@ -670,7 +677,12 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem, bool free)
     // 32.  So short rows get eight too, though most of these have no tile, to k = 28 (fp32, two launches with four / one with eight: 200
     // rows of 2000, k = 20, 10.3 / 9.7 us, 126 of 4000, k = 18, 10.8 / 9.75, 504 11.7 / 10.8, 448 of 7000, k = 28, 13.0 / 12.2; 512 of 5000, k = 32, 12.8 /
     // 13.5; 16-bit rows gain less, 240 of 6000, k = 20, 11.15 / 10.7, and are left as they are, like rows of 28 to 32 KB).
-    plan.one = free && one_launch_shape(B, k, V) && (k <= 16 || plan.waves == 8) && (rows <= 2 * kComputeUnits || rows * plan.waves <= 22 * kComputeUnits);
+    // Beyond two rows a unit 16-bit rows also with k = 17 to 28 and four waves: there are half the bytes in front of what one launch
+    // saves (bf16, 544 rows of 32000, k = 17, 18.35 / 17.6, 1080, k = 24, 22.75 / 22.0, 1200 of 8000, k = 20, 15.9 / 15.2, 1400 of 16000, k =
+    // 28, 21.45 / 20.9; k = 32 equal; fp32 1080 of 12000, k = 18, 18.05 / 17.9, 1200 of 16000 21.6 / 21.3, but 1400 of 24000, k = 28, 31.9 / 32.65, 600 of 8000 13.9 / 14.05).
+    plan.one = free && one_launch_shape(B, k, V) &&
+               (rows <= 2 * kComputeUnits ? k <= 16 || plan.waves == 8
+                                          : rows * plan.waves <= 22 * kComputeUnits && (k <= 16 || (elem == 2 && plan.waves == 4)));
     // One workgroup for a whole sentence where its rows are short and few: eight tiles in all (a partial one takes as long as a whole one; per step,
     // a workgroup per row / per sentence, 40 sentences, fp32: k = 8, 1024 tokens 8.15 / 7.75 us, 4, 2048 7.85 / 7.6, 5, 1000 8.2 / 7.55, but 5, 1638 8.3 / 8.55,
     // 3, 2730 8.1 / 8.25), and no more sentences than three for a compute unit (700, k = 2, 1000 tokens 10.5 / 8.95; 1300, k = 1, 11.3 / 14.5).
@@ -880,7 +892,7 @@ extern "C" {
 DBA_API size_t dba_workspace_bytes(int B, int k, int V, int N, int max_cons_tokens)
 {
     if (!shape_ok(B, k, V, N, max_cons_tokens)) return 0;
-    return make_layout((size_t)B, (size_t)k, (size_t)N).total;
+    return make_layout((size_t)B, (size_t)k, (size_t)V, (size_t)N).total;
 }
 
 // dba_init proper; may throw std::bad_alloc from its host tables (caught by dba_init)
@@ -913,7 +925,7 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     // The constraint words go to a block of host memory that the kernel of dba_init reads itself, or, where there
     // is none (large batches), through a copy to the workspace.  (Opening a session, the caller's allocations included, with
     // all tables made on the host, copied and waited for / like this: one sentence 51 / 38 us, 64 sentences 119 / 48.)
-    const Layout L = make_layout((size_t)B, (size_t)k, (size_t)N);
+    const Layout L = make_layout((size_t)B, (size_t)k, (size_t)V, (size_t)N);
     const size_t words_bytes = (size_t)B * kMaxCons * sizeof(uint32_t);
     struct Holder {
         HostBlock block;
@@ -1013,8 +1025,8 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
         p.beam_nxt = at<Hyp>(c, L.beam[0]);
         c->one_launch = seen != nullptr && one_launch_shape((size_t)B, (size_t)k, (size_t)V);
         if (c->one_launch) {
-            p.rowlists = at<u64>(c, L.rowlists);
-            p.conskeys = at<u64>(c, L.conskeys);
+            p.rowlists = at<u64>(c, L.place_lists);
+            p.conskeys = at<u64>(c, L.place_keys);
         }
         dba_init_kernel<<<(unsigned)B, kWave, 0, c->stream>>>(B, k, words, seen, p);
         e = hipGetLastError();
@@ -1097,8 +1109,6 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     set_tables(c, p);
     p.rowlists = own_scratch ? reinterpret_cast<u64 *>(own_scratch) : at<u64>(c, L.rowlists);
     p.conskeys = own_scratch ? reinterpret_cast<u64 *>(own_scratch + kStaticListBytes) : at<u64>(c, L.conskeys);
-    // (what a step's rows are made of may decide how many launches it takes; one must find the places empty after two)
-    const bool leave_empty = c->one_launch && c->merge_waves == 0 && !plan.one && !own_scratch;
     p.told = tells ? c->block.p + c->block_flags : nullptr;
     p.out_token = out_token_dev;
     p.out_backptr = out_backptr_dev;
@@ -1124,9 +1134,9 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         }
 #undef SENTENCE
     } else if (plan.one) {
-        // (the places are empty between steps, which only the ctx's own are)
-        p.rowlists = at<u64>(c, L.rowlists);
-        p.conskeys = at<u64>(c, L.conskeys);
+        // (places that no step of two launches writes to: they are empty between steps, whatever the steps before took)
+        p.rowlists = at<u64>(c, L.place_lists);
+        p.conskeys = at<u64>(c, L.place_keys);
         const dim3 sblock((unsigned)(plan.waves * kWave)), sgrid((unsigned)c->B * (unsigned)(c->k + 1));
         const int mw = c->k <= 16 || plan.waves == 4 ? 4 : 8;
         const size_t lds = std::max(plan.waves == 8 ? sizeof(StreamSmem<8>) : sizeof(StreamSmem<4>),
@@ -1141,6 +1151,11 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         case DBA_LOGP_BF16: ONE(kFmtBF16, NW, D, ROWS, MW, J); break;     \
         default: ONE(kFmtF32, NW, D, ROWS, MW, J); break;                 \
     }
+#define ONE_16(NW, D, ROWS, MW, J)                                        \
+    switch (logp_format) {                                      \
+        case DBA_LOGP_F16: ONE(kFmtF16, NW, D, ROWS, MW, J); break;       \
+        default: ONE(kFmtBF16, NW, D, ROWS, MW, J); break;                \
+    }
         if (plan.waves == 8 && plan.tiles == 4) {
             if (c->k <= 8) ONE_ANY(8, 4, 2, 4, 1)
             else if (c->k <= 11) ONE_ANY(8, 4, 4, 4, 2)
@@ -1154,8 +1169,10 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         } else {
             if (c->k <= 8) ONE_ANY(4, 2, 2, 4, 1)
             else if (c->k <= 11) ONE_ANY(4, 2, 4, 4, 2)
-            else ONE_ANY(4, 2, 4, 4, -1)
+            else if (c->k <= 16) ONE_ANY(4, 2, 4, 4, -1)
+            else ONE_16(4, 2, 8, 4, -1)
         }
+#undef ONE_16
 #undef ONE_ANY
 #undef ONE
     } else {
@@ -1193,25 +1210,21 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         const dim3 mgrid((unsigned)c->B);
         const int mw = c->merge_waves ? c->merge_waves : (c->k <= 16 ? 4 : c->k <= 32 || c->B > (int)kComputeUnits ? 8 : 16);
         const uint32_t k_inv = (uint32_t)c->k | inv_k16 << 16;
-#define MERGE(ROWS, MW, J, EMPTY) \
-    dba_merge_kernel<ROWS, MW, J, EMPTY><<<mgrid, MW * kWave, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, k_inv, p)
+#define MERGE(ROWS, MW, J) \
+    dba_merge_kernel<ROWS, MW, J><<<mgrid, MW * kWave, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, k_inv, p)
         if (mw == 4) {
-            if (leave_empty && c->k <= 8) MERGE(2, 4, 1, true);
-            else if (leave_empty && c->k <= 11) MERGE(4, 4, 2, true);
-            else if (leave_empty && c->k <= 16) MERGE(4, 4, -1, true);
-            else if (c->k <= 8) MERGE(2, 4, 1, false);
-            else if (c->k <= 11) MERGE(4, 4, 2, false);
-            else if (c->k <= 16) MERGE(4, 4, -1, false);
-            else if (c->k <= 32) MERGE(8, 4, -1, false);
-            else MERGE(16, 4, 0, false);
+            if (c->k <= 8) MERGE(2, 4, 1);
+            else if (c->k <= 11) MERGE(4, 4, 2);
+            else if (c->k <= 16) MERGE(4, 4, -1);
+            else if (c->k <= 32) MERGE(8, 4, -1);
+            else MERGE(16, 4, 0);
         } else if (mw == 16) {
-            MERGE(4, 16, 0, false);
+            MERGE(4, 16, 0);
         } else {
-            if (c->k <= 8) MERGE(2, 8, 1, false);
-            else if (c->k <= 11) MERGE(2, 8, 2, false);
-            else if (c->k <= 32 && leave_empty) MERGE(4, 8, -1, true);
-            else if (c->k <= 32) MERGE(4, 8, -1, false);
-            else MERGE(8, 8, 0, false);
+            if (c->k <= 8) MERGE(2, 8, 1);
+            else if (c->k <= 11) MERGE(2, 8, 2);
+            else if (c->k <= 32) MERGE(4, 8, -1);
+            else MERGE(8, 8, 0);
         }
 #undef MERGE
     }

@@ -1206,10 +1206,10 @@ __device__ __forceinline__ void clear_for_merge(const StepParams &p, int tid, in
 // often a wave looks for them before it asks whether to go on; if not, the workgroup leaves and has written nothing.  all_ended:
 // the sentence was left to this workgroup, a row's, as every row has ended); kInLds, the other waves of this workgroup, rowlists
 // and conskeys point to those of its first row.  Tables and counters are in LDS already, but for kInMemory.
-// EMPTY: the row lists are left empty, as a step of one launch finds and leaves them.
+// (kHandedOver leaves the places empty, as it found them.)
 constexpr int kInMemory = 0, kHandedOver = 1, kInLds = 2;
 
-template <int ROWS, int MW, int J, int SRC, bool EMPTY>
+template <int ROWS, int MW, int J, int SRC>
 __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowlists, const u64 *conskeys, int k,
                                             uint32_t inv_k, int b, MergeSmem<MW> &sm, u64 *cand, int P_here, int most_tries,
                                             bool all_ended)
@@ -1764,7 +1764,7 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
             __hip_atomic_fetch_add(&p.best[b].ended, -(k + (all_ended || verdict == kGoesOn ? kGivenUp : 0)), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
     }
-    if constexpr (EMPTY) {
+    if constexpr (SRC == kHandedOver) {
         // and the places empty
         if (wave >= 2) {
             for (int h = wave - 2; h < k; h += MW - 2) {

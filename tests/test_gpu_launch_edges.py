@@ -25,6 +25,7 @@ def _bytes(ses):
     (176, 8, 1031, ("bf16", "f32"), True), (127, 11, 2049, ("f32", "f16"), True), (93, 15, 3001, ("f32",), True), (64, 11, 41001, ("f32", "bf16"), True),
     (65, 11, 41001, ("f32", "bf16"), True), (89, 8, 41001, ("bf16", "f32"), True), (46, 16, 41001, ("f16", "f32"), True),
     (18, 28, 7168, ("f32", "f16"), True), (18, 28, 7169, ("f32",), True), (30, 17, 1000, ("f32",), True), (1, 17, 17, ("f32",), True), (5, 24, 1024, ("f32", "bf16"), True),
+    (50, 28, 4096, ("f16", "f32"), True), (31, 17, 9001, ("bf16", "f32"), True), (50, 28, 4095, ("f16",), False), (25, 24, 16387, ("f32", "f16", "bf16"), True),
     (3, 8, 1024, ("f32", "bf16"), True), (3, 8, 1023, ("f32", "f16"), True), (41, 4, 2047, ("f32", "bf16"), True), (5, 2, 4093, ("f32",), True), (2, 1, 8190, ("bf16", "f32"), True),
     (7, 5, 700, ("f16",), True), (768, 1, 600, ("f32",), True), (769, 1, 600, ("f32",), True), (6, 8, 60, ("f32", "bf16"), True), (2, 7, 9, ("f32",), True)])
 def test_one_launch_and_two(B, k, V, fmts, one):

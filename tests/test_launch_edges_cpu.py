@@ -17,3 +17,17 @@ def test_short_rows_of_beams_of_17_to_28():
                                           (18, 28, 2000, f16, 2, 4), (32, 16, 2000, f32, 1, 4)):
         assert dba.dba_debug_launches(B, k, V, fmt) == launches, (B, k, V, fmt)
         assert dba.dba_debug_stream_plan(B, k, V, fmt)[0] == waves, (B, k, V, fmt)
+
+
+def test_wide_beams_with_16_bit_rows_beyond_two_rows_a_compute_unit():
+    f32, f16, bf16 = dba.DBA_LOGP_F32, dba.DBA_LOGP_F16, dba.DBA_LOGP_BF16
+    for B, k, V, fmt, launches in ((50, 28, 4096, f16, 1), (50, 28, 4096, f32, 2), (50, 28, 4095, f16, 2), (50, 29, 4096, f16, 2), (51, 28, 4096, bf16, 2),
+                                   (31, 17, 81919, bf16, 1), (31, 17, 81920, bf16, 2), (88, 16, 4096, bf16, 1)):
+        assert dba.dba_debug_launches(B, k, V, fmt) == launches, (B, k, V, fmt)
+
+
+def test_only_shapes_with_steps_of_one_launch_have_places_of_their_own():
+    """1024 bytes a row in the workspace, for steps whose keys no step of two launches may write over."""
+    for B, k, without, beyond in ((88, 16, 511, 512), (50, 28, 4095, 4096)):
+        more = dba.dba_workspace_bytes(B, k, beyond, 1, 0) - dba.dba_workspace_bytes(B, k, without, 1, 0)
+        assert more == B * k * 1024, (B, k, more)
