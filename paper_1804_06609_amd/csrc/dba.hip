@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <mutex>
 #include <new>
 #include <thread>
@@ -172,13 +173,12 @@ __global__ __launch_bounds__(NW * kWave) void dba_stream_kernel(const void *logp
     stream_phase<U, FMT, NW, D, kInMemory>(p, logp, V, (int)k, k_first >> 16, b, h, wave, (int)(blockIdx.x >> 8), wave, sm, [] {});
 }
 
-// Both phases in one launch, for steps of few rows.  Grid: B * k workgroups for the rows, then B that each take a
-// sentence through the merge phase.  Such a step is a chain of latencies, and the end of one kernel, the start of the
-// next and its wait for the row lists were 2.2 us of it; here a sentence's workgroup has its tables in LDS before the
+// Both phases in one launch, where the sentences' workgroups find room beside the rows (one_launch_shape).  Grid: B * k workgroups for
+// the rows, then B that each take a sentence through the merge phase.  Such a step is a chain of latencies, and the end of one kernel,
+// the start of the next and its wait for the row lists were 2.2 us of it; here a sentence's workgroup has its tables in LDS before the
 // rows are through and reads their places in the row lists again and again until all are filled (a store is seen
-// there after 0.7 to 1.2 us).  Per step, two launches / one: 5 rows of 1000 9.25 / 8.65 us, 160 of 32000 13.05 / 12.55, 168 of 50001
-// 14.3 / 13.35, 240 of 9000 10.95 / 10.2, 192 with k = 16 13.9 / 12.7, 256 with k = 32 16.4 / 15.5, one sentence of ten rows 11.7 / 11.5,
-// 400 rows of 8000 12.75 / 12.35, 500 of 32000 19.9 / 18.7.
+// there after 0.6 to 0.9 us).  Per step, two launches / one: ten rows of 32000 11.1 / 10.2 us, 160 13.0 / 11.8, 168 of 50001 14.05 / 12.9, 240 of
+// 9000 11.45 / 10.5, 192 of 32000 with k = 16 13.6 / 12.5, 256 with k = 32 16.15 / 15.2, 400 rows of 8000 12.6 / 11.45, 500 of 32000 18.75 / 17.65.
 //
 // Every wait ends, and with the right answer.  A row waits for nothing; when its keys have reached memory it counts itself
 // among the sentence's ended rows.  A sentence's workgroup that has looked for the keys most_tries times - the rows may be
@@ -829,7 +829,7 @@ struct dba_ctx {
     size_t dyn_smem;
     unsigned char *ws;
     Layout L;
-    HostBlock block;                    // seen words [B], stopping flags [B], then constraint words / results (p null: none)
+    HostBlock block;                    // seen words [B] (then what steps tell), stopping flags [B], then constraint words / results (p null: none)
     size_t block_flags, block_data;     // offsets in it
     bool one_launch;                    // the row lists are empty between steps, which may then be one launch each
     int give_up;                        // dba_debug_sentences_first
@@ -882,6 +882,15 @@ bool init_is_through(const dba_ctx *c)
     const uint32_t *seen = reinterpret_cast<const uint32_t *>(c->block.p);
     for (int b = 0; seen && b < c->B; ++b)
         if (__atomic_load_n(seen + b, __ATOMIC_RELAXED) == 0) return false;
+    return true;
+}
+
+// every sentence's word is the one that the last step which writes them leaves there
+bool told_is_through(const dba_ctx *c)
+{
+    const uint32_t *told = reinterpret_cast<const uint32_t *>(c->block.p), last = (uint32_t)c->told << 2;
+    for (int b = 0; told && b < c->B; ++b)
+        if ((__atomic_load_n(told + b, __ATOMIC_RELAXED) & ~3u) != last) return false;
     return true;
 }
 
@@ -1109,7 +1118,7 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     set_tables(c, p);
     p.rowlists = own_scratch ? reinterpret_cast<u64 *>(own_scratch) : at<u64>(c, L.rowlists);
     p.conskeys = own_scratch ? reinterpret_cast<u64 *>(own_scratch + kStaticListBytes) : at<u64>(c, L.conskeys);
-    p.told = tells ? c->block.p + c->block_flags : nullptr;
+    p.told = tells ? reinterpret_cast<uint32_t *>(c->block.p) : nullptr;
     p.out_token = out_token_dev;
     p.out_backptr = out_backptr_dev;
     p.out_score = out_score_dev;
@@ -1383,14 +1392,13 @@ DBA_API int dba_get_finished(dba_ctx *c, uint8_t *all_finished_host)
     if (!all_finished_host) return fail(c, DBA_EINVAL, "dba_get_finished: the output pointer is NULL");
     const uint8_t *flags = at<uint8_t>(c, c->L.all_finished);
     uint8_t *here = c->block.p ? c->block.p + c->block_flags : nullptr;
+    const bool told = here && !c->recorded && c->steps > 0 && c->told == c->steps;     // the last step has written them
     hipError_t e = hipSuccess;
-    if (here && !c->recorded && c->steps > 0 && c->told == c->steps) {
-        // the last step has written them
-    } else if (here) {
+    if (here && !told) {
         dba_flags_kernel<<<1, kBlock, 0, c->stream>>>((c->B + 3) / 4, reinterpret_cast<const uint32_t *>(flags),
                                                       reinterpret_cast<uint32_t *>(here));
         e = hipGetLastError();
-    } else {
+    } else if (!here) {
         e = hipMemcpyAsync(all_finished_host, flags, (size_t)c->B, hipMemcpyDeviceToHost, c->stream);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -1399,7 +1407,9 @@ DBA_API int dba_get_finished(dba_ctx *c, uint8_t *all_finished_host)
         return fail(c, DBA_EHIP, "dba_get_finished: HIP error: %s", hipGetErrorString(e));
     }
     c->init_under_way = c->told_under_way = false;
-    if (here) memcpy(all_finished_host, here, (size_t)c->B);
+    const uint32_t *words = reinterpret_cast<const uint32_t *>(c->block.p);
+    for (int b = 0; told && b < c->B; ++b) all_finished_host[b] = (uint8_t)(__atomic_load_n(words + b, __ATOMIC_RELAXED) & 3u);
+    if (here && !told) memcpy(all_finished_host, here, (size_t)c->B);
     c->asked = true;
     return DBA_OK;
 }
@@ -1407,18 +1417,28 @@ DBA_API int dba_get_finished(dba_ctx *c, uint8_t *all_finished_host)
 DBA_API void dba_destroy(dba_ctx *c)
 {
     if (!c) return;
-    // a ctx that goes before the GPU is through with its dba_init, or with steps that write to the block: the workspace and
-    // the block are given back only then
-    if (c->told_under_way || (c->init_under_way && !init_is_through(c))) {
+    // a ctx that goes before the GPU is through with its dba_init: the workspace and the block are given back only then
+    if (c->init_under_way && !init_is_through(c)) {
         const RelaxedCapture relaxed;
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
         if (capture != hipStreamCaptureStatusNone) {       // (what was enqueued before the capture began runs all the same)
-            while (c->init_under_way && !init_is_through(c)) std::this_thread::yield();
-            if (c->told_under_way) c->block.p = nullptr;   // (never used again)
+            while (!init_is_through(c)) std::this_thread::yield();
         } else if (hipStreamSynchronize(c->stream) != hipSuccess) {
             (void)hipGetLastError();
-            c->block.p = nullptr;
+            c->block.p = nullptr;                          // (never used again)
+        }
+    }
+    // nor is the block while a step may still write to it.  (By the words: the stream may be gone by now, and nothing has to be
+    // known of it.  A step that does not come, behind work that waits for this thread, keeps the block, not the caller.)
+    if (c->told_under_way && c->block.p) {
+        const auto begin = std::chrono::steady_clock::now();
+        while (!told_is_through(c)) {
+            if (std::chrono::steady_clock::now() - begin > std::chrono::seconds(2)) {
+                c->block.p = nullptr;
+                break;
+            }
+            std::this_thread::yield();
         }
     }
     host_blocks().put(c->block);

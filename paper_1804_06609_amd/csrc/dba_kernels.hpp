@@ -92,7 +92,7 @@ struct StepParams {
     int32_t *hist_token, *hist_backptr;   // row t of the history, [B,k]
     uint8_t *all_finished;            // [B] bit 0: the new beam is not empty and every hypothesis on it is completed;
                                       //     bit 1: some hypothesis on it is completed
-    uint8_t *told;                    // [B] host memory that takes the same (null: the host does not ask)
+    uint32_t *told;                   // [B] host memory that takes the same, | steps taken << 2 (null: the host does not ask)
     struct BestCompleted *best;       // [B] the record kept under `track`
 };
 
@@ -1918,7 +1918,8 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
         if (lane == 0) {                                  // stopping tests: Sec. 4 (all), Sec. 6.3 (any)
             const uint8_t stop = (uint8_t)(((nlive > 0 && open == 0) ? 1 : 0) | (closed != 0 ? 2 : 0));
             p.all_finished[b] = stop;
-            if (p.told) __hip_atomic_store(p.told + b, stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            if (p.told)
+                __hip_atomic_store(p.told + b, (uint32_t)(p.step + 1) << 2 | stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
 }
