@@ -1043,6 +1043,7 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     if (e == hipSuccess && !seen) e = hipStreamSynchronize(c->stream);   // the words are freed on return
     if (e != hipSuccess) {
         const int rc = fail(nullptr, DBA_EHIP, "dba_init: HIP error: %s", hipGetErrorString(e));
+        held.block.p = nullptr;                            // (the kernel may have been launched all the same: never used again)
         delete c;
         return rc;
     }
@@ -1239,8 +1240,7 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
-        c->recorded = c->recorded || tells;                // (what has been launched is not known)
-        c->told_under_way = c->told_under_way || tells;
+        if (tells) c->block.p = nullptr;                   // (what has been launched is not known, and may still write to it: never used again)
         return fail(c, DBA_EHIP, "dba_step: launch failed: %s", hipGetErrorString(e));
     }
     c->steps += 1;
