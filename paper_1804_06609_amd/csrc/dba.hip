@@ -810,6 +810,19 @@ HostBlocks<PinnedMemory> &host_blocks()
     return *blocks;
 }
 
+// A launch that tells how it went: hipGetLastError, behind the <<< >>> form, may tell of an earlier call on this thread, of whomever,
+// and takes that error from its owner.  (Nor does this one pass its grid through the runtime first: a step's call takes 2.85 instead of 3.05
+// us with one launch and 5.27 instead of 5.65 with two, which is the time of a step where short ones of several decodes alternate.)
+template <typename... P, typename... A>
+hipError_t launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t stream, const A &...a)
+{
+    auto with = [&](P... arg) {
+        void *args[] = {&arg...};
+        return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, args, lds, stream);
+    };
+    return with(a...);
+}
+
 }  // namespace
 
 struct dba_ctx {
@@ -1037,13 +1050,12 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
             p.rowlists = at<u64>(c, L.place_lists);
             p.conskeys = at<u64>(c, L.place_keys);
         }
-        dba_init_kernel<<<(unsigned)B, kWave, 0, c->stream>>>(B, k, words, seen, p);
-        e = hipGetLastError();
+        e = launch(dba_init_kernel, (unsigned)B, kWave, 0, c->stream, B, k, words, seen, p);
     }
     if (e == hipSuccess && !seen) e = hipStreamSynchronize(c->stream);   // the words are freed on return
     if (e != hipSuccess) {
         const int rc = fail(nullptr, DBA_EHIP, "dba_init: HIP error: %s", hipGetErrorString(e));
-        held.block.p = nullptr;                            // (the kernel may have been launched all the same: never used again)
+        held.block.p = nullptr;                            // (never used again: whatever went wrong, nothing is known to wait for)
         delete c;
         return rc;
     }
@@ -1128,6 +1140,7 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     p.hist_token = at<int32_t>(c, L.hist_token) + hrow;
     p.hist_backptr = at<int32_t>(c, L.hist_backptr) + hrow;
 
+    hipError_t e = hipSuccess;
     const dim3 grid((unsigned)c->B * (unsigned)c->k);
     const uint32_t inv_k = (uint32_t)(((1ull << 32) + (unsigned)c->k - 1) / (unsigned)c->k);
     const int kf = p.k | (p.first_step << 16);
@@ -1136,7 +1149,7 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         const size_t lds = align_up(sizeof(MergeSmem<4>), 16) + c->dyn_smem;
         static_assert(sizeof(SentenceSmem) + sizeof(MergeSmem<4>) + 16 + (size_t)kSentenceWaves * (DBA_MAX_CONS_TOKENS + 2) * sizeof(u64) + 64 * sizeof(u64) +
                       kMostLeft * (sizeof(u64) + sizeof(int)) <= kLdsPerLaunch, "beside the rows' LDS");
-#define SENTENCE(FMT) dba_sentence_kernel<FMT><<<(unsigned)c->B, kSentenceWaves * kWave, lds, c->stream>>>(p.logp, p.V, kf, inv_k16, p)
+#define SENTENCE(FMT) e = launch(dba_sentence_kernel<FMT>, (unsigned)c->B, kSentenceWaves * kWave, lds, c->stream, p.logp, p.V, kf, inv_k16, p)
         switch (logp_format) {
             case DBA_LOGP_F16: SENTENCE(kFmtF16); break;
             case DBA_LOGP_BF16: SENTENCE(kFmtBF16); break;
@@ -1152,9 +1165,10 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         const size_t lds = std::max(plan.waves == 8 ? sizeof(StreamSmem<8>) : sizeof(StreamSmem<4>),
                                     align_up(mw == 4 ? sizeof(MergeSmem<4>) : sizeof(MergeSmem<8>), 16) + c->dyn_smem);
         const int tries = c->give_up ? 0 : most_tries((size_t)c->B * (size_t)c->k, (size_t)c->V * elem);
-#define ONE(FMT, NW, D, ROWS, MW, J)                                                                      \
-    dba_step_kernel<kTileLoads, FMT, NW, D, ROWS, MW, J><<<sgrid, sblock, lds, c->stream>>>(p.logp, p.V, kf, plan.rows_abreast, \
-                                                                                       inv_k, (unsigned)c->B * (unsigned)c->k | ((c->give_up & 1) ? 0x80000000u : 0u), inv_k16, tries, p)
+        const uint32_t rows_order = (unsigned)c->B * (unsigned)c->k | ((c->give_up & 1) ? 0x80000000u : 0u);
+#define ONE(FMT, NW, D, ROWS, MW, J)                                                                                       \
+    e = launch(dba_step_kernel<kTileLoads, FMT, NW, D, ROWS, MW, J>, sgrid, sblock, lds, c->stream, p.logp, p.V, kf, plan.rows_abreast, \
+               inv_k, rows_order, inv_k16, tries, p)
 #define ONE_ANY(NW, D, ROWS, MW, J)                                       \
     switch (logp_format) {                                      \
         case DBA_LOGP_F16: ONE(kFmtF16, NW, D, ROWS, MW, J); break;       \
@@ -1188,8 +1202,7 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
     } else {
         const dim3 sblock((unsigned)(plan.waves * kWave));
 #define STREAM(FMT, NW, D)                                                                                              \
-    dba_stream_kernel<kTileLoads, FMT, NW, D><<<grid, sblock, plan.spare_lds, c->stream>>>(p.logp, p.V, kf, plan.rows_abreast, \
-                                                                                           inv_k, p)
+    e = launch(dba_stream_kernel<kTileLoads, FMT, NW, D>, grid, sblock, plan.spare_lds, c->stream, p.logp, p.V, kf, plan.rows_abreast, inv_k, p)
 #define STREAM_ANY(NW, D)                                       \
     switch (logp_format) {                                      \
         case DBA_LOGP_F16: STREAM(kFmtF16, NW, D); break;       \
@@ -1221,8 +1234,10 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         const int mw = c->merge_waves ? c->merge_waves : (c->k <= 16 ? 4 : c->k <= 32 || c->B > (int)kComputeUnits ? 8 : 16);
         const uint32_t k_inv = (uint32_t)c->k | inv_k16 << 16;
 #define MERGE(ROWS, MW, J) \
-    dba_merge_kernel<ROWS, MW, J><<<mgrid, MW * kWave, c->dyn_smem, c->stream>>>(p.rowlists, p.conskeys, k_inv, p)
-        if (mw == 4) {
+    e = launch(dba_merge_kernel<ROWS, MW, J>, mgrid, MW * kWave, c->dyn_smem, c->stream, p.rowlists, p.conskeys, k_inv, p)
+        if (e != hipSuccess) {
+            // (nothing to merge)
+        } else if (mw == 4) {
             if (c->k <= 8) MERGE(2, 4, 1);
             else if (c->k <= 11) MERGE(4, 4, 2);
             else if (c->k <= 16) MERGE(4, 4, -1);
@@ -1238,9 +1253,8 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         }
 #undef MERGE
     }
-    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
-        if (tells) c->block.p = nullptr;                   // (what has been launched is not known, and may still write to it: never used again)
+        if (tells) c->block.p = nullptr;                   // (never used again: whatever went wrong, its words are not to be relied upon)
         return fail(c, DBA_EHIP, "dba_step: launch failed: %s", hipGetErrorString(e));
     }
     c->steps += 1;
@@ -1304,12 +1318,10 @@ DBA_API int dba_finalize(dba_ctx *c, int32_t *out_tokens_host, int32_t *out_len_
     auto place = [&](size_t off) {
         return reinterpret_cast<int32_t *>(here && off >= first ? here + (off - first) : c->ws + off);
     };
-    dba_finalize_kernel<<<c->B, kFinWaves * kWave, 0, c->stream>>>(
-        c->B, c->k, c->steps, c->N, c->pad_id, c->normalize, at<int32_t>(c, L.hist_token),
-        at<int32_t>(c, L.hist_backptr),
-        at<Hyp>(c, L.beam[cur]), c->track ? at<BestCompleted>(c, L.best) : nullptr,
-        place(L.fin_tokens), place(L.fin_len), reinterpret_cast<float *>(place(L.fin_score)), place(L.fin_status));
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch(dba_finalize_kernel, (unsigned)c->B, kFinWaves * kWave, 0, c->stream, c->B, c->k, c->steps, c->N, c->pad_id,
+                          c->normalize, at<int32_t>(c, L.hist_token), at<int32_t>(c, L.hist_backptr), at<Hyp>(c, L.beam[cur]),
+                          c->track ? at<BestCompleted>(c, L.best) : nullptr, place(L.fin_tokens), place(L.fin_len),
+                          reinterpret_cast<float *>(place(L.fin_score)), place(L.fin_status));
     auto fetch = [&](void *to, size_t off, size_t n) {
         if (e == hipSuccess && !((here || copied.p) && off >= first))
             e = hipMemcpyAsync(to, c->ws + off, n, hipMemcpyDeviceToHost, c->stream);
@@ -1395,9 +1407,8 @@ DBA_API int dba_get_finished(dba_ctx *c, uint8_t *all_finished_host)
     const bool told = here && !c->recorded && c->steps > 0 && c->told == c->steps;     // the last step has written them
     hipError_t e = hipSuccess;
     if (here && !told) {
-        dba_flags_kernel<<<1, kBlock, 0, c->stream>>>((c->B + 3) / 4, reinterpret_cast<const uint32_t *>(flags),
-                                                      reinterpret_cast<uint32_t *>(here));
-        e = hipGetLastError();
+        e = launch(dba_flags_kernel, 1, kBlock, 0, c->stream, (c->B + 3) / 4, reinterpret_cast<const uint32_t *>(flags),
+                   reinterpret_cast<uint32_t *>(here));
     } else if (!here) {
         e = hipMemcpyAsync(all_finished_host, flags, (size_t)c->B, hipMemcpyDeviceToHost, c->stream);
     }
@@ -1465,10 +1476,7 @@ DBA_API int dba_debug_allocate(int n_cases, int adjust, const int32_t *k_host, c
     hipError_t e = hipMemcpyAsync(d_k, k_host, n * 4, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(d_C, C_host, n * 4, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(d_cnt, cnt_host, n * 65 * 4, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) {
-        dba_allocate_kernel<<<dim3((unsigned)n_cases), dim3(kWave), 0, s>>>(n_cases, adjust, d_k, d_C, d_cnt, d_alloc);
-        e = hipGetLastError();
-    }
+    if (e == hipSuccess) e = launch(dba_allocate_kernel, (unsigned)n_cases, kWave, 0, s, n_cases, adjust, d_k, d_C, d_cnt, d_alloc);
     if (e == hipSuccess) e = hipMemcpyAsync(alloc_host, d_alloc, n * 65 * 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail(nullptr, DBA_EHIP, "dba_debug_allocate: HIP error: %s", hipGetErrorString(e));
@@ -1491,10 +1499,7 @@ DBA_API int dba_debug_wave_select(int n_cases, const uint64_t *keys_host, const 
     float *d_fout = d_vals + n * 64;
     hipError_t e = hipMemcpyAsync(d_keys, keys_host, n * 128 * 8, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(d_vals, vals_host, n * 64 * 4, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) {
-        dba_wave_select_kernel<<<dim3((unsigned)n_cases), dim3(kWave), 0, s>>>(n_cases, d_keys, d_vals, d_out, d_fout);
-        e = hipGetLastError();
-    }
+    if (e == hipSuccess) e = launch(dba_wave_select_kernel, (unsigned)n_cases, kWave, 0, s, n_cases, d_keys, d_vals, d_out, d_fout);
     if (e == hipSuccess) e = hipMemcpyAsync(out_host, d_out, n * 256 * 8, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipMemcpyAsync(fout_host, d_fout, n * 64 * 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -1535,8 +1540,7 @@ DBA_API int dba_debug_row_max(const float *src_dev, int rows, int V, float *out_
     if (reinterpret_cast<uintptr_t>(src_dev) & 15)
         return fail(nullptr, DBA_EINVAL, "dba_debug_row_max: src_dev must be 16-byte aligned");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    dba_row_max_kernel<<<dim3((unsigned)rows), dim3(kBlock), 0, s>>>(src_dev, V, out_max_dev);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = launch(dba_row_max_kernel, (unsigned)rows, kBlock, 0, s, src_dev, V, out_max_dev);
     if (e != hipSuccess) return fail(nullptr, DBA_EHIP, "dba_debug_row_max: HIP error: %s", hipGetErrorString(e));
     return DBA_OK;
 }

@@ -232,10 +232,36 @@ static void launch_errors()
     }
 }
 
+// A step asks whether its stream is being captured and launches its kernels: the error that another call has left on the
+// thread is not looked at, and stays there.
+static void calls_of_a_step()
+{
+    const struct { int B, k, V, launches; } shapes[] = {{1, 5, 1000, 1}, {16, 10, 32000, 1}, {2, 40, 1000, 2}};
+    for (auto &s : shapes) {
+        dba_ctx *c = nullptr;
+        g_last_error = kErrorInvalidValue;
+        CHECK(init(&c, s.B, s.k, s.V, 9) == DBA_OK);
+        for (int t = 0; t < 4; ++t) {
+            const int calls = g_calls, launches = g_launches;
+            CHECK(step(c) == DBA_OK);
+            CHECK(g_launches == launches + s.launches && g_calls == calls + 1 + s.launches);
+        }
+        ask(c);
+        CHECK(g_last_error == kErrorInvalidValue);
+        // the first of two launches fails: there is nothing for the second
+        g_fail_launch = 0;
+        const int launches = g_launches;
+        CHECK(step(c) == DBA_EHIP && g_launches == launches && LIB(dba_steps_done)(c) == 4);
+        gpu_runs();
+        LIB(dba_destroy)(c);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> scenarios = {
         {"launch_errors", launch_errors},
+        {"calls_of_a_step", calls_of_a_step},
     };
     if (argc != 3 || !scenarios.count(argv[2])) return 2;
     g_lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);
