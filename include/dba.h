@@ -242,8 +242,8 @@ DBA_API int dba_get_finished(dba_ctx *ctx, uint8_t *all_finished_host);
 DBA_API int dba_steps_done(const dba_ctx *ctx);
 
 /* Frees the host-side ctx only; device memory belongs to the caller.  Waits for the work of dba_init, if that is
- * still under way, and, once dba_get_finished has been called, for the steps since; other steps that are still
- * under way need the workspace and the step's buffers until the stream has passed them. */
+ * still under way, and for nothing else: steps that are still under way need the workspace and the step's buffers until
+ * the stream has passed them. */
 DBA_API void dba_destroy(dba_ctx *ctx);
 
 /* Text of the last error on this ctx, or of the last failed dba_init of the

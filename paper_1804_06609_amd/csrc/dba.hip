@@ -6,7 +6,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <chrono>
 #include <mutex>
 #include <new>
 #include <thread>
@@ -787,7 +786,8 @@ struct RelaxedCapture {
 // Pinned host memory that kernels read and write themselves: a copy to or from ordinary host memory costs about 8
 // us and a wait of its own (a decode with the stopping test asked for after each of its 21 steps, 8 x 10 x 32000: 814 -> 641
 // us; one of 100 steps, 64 x 20 x 32000: 3360 -> 3294).  A ctx holds one block from dba_init to dba_destroy; blocks are kept for the next
-// ctx, of any thread and device, and what is more than the store keeps is freed.  No kernel uses a block any more when it comes back.
+// ctx, of any thread and device, and what is more than the store keeps is freed.  No kernel uses a block any more when it
+// comes back, or its words tell when (put_when).
 struct PinnedMemory {
     static void *allocate(size_t n)
     {
@@ -895,15 +895,6 @@ bool init_is_through(const dba_ctx *c)
     const uint32_t *seen = reinterpret_cast<const uint32_t *>(c->block.p);
     for (int b = 0; seen && b < c->B; ++b)
         if (__atomic_load_n(seen + b, __ATOMIC_RELAXED) == 0) return false;
-    return true;
-}
-
-// every sentence's word is the one that the last step which writes them leaves there
-bool told_is_through(const dba_ctx *c)
-{
-    const uint32_t *told = reinterpret_cast<const uint32_t *>(c->block.p), last = (uint32_t)c->told << 2;
-    for (int b = 0; told && b < c->B; ++b)
-        if ((__atomic_load_n(told + b, __ATOMIC_RELAXED) & ~3u) != last) return false;
     return true;
 }
 
@@ -1440,19 +1431,10 @@ DBA_API void dba_destroy(dba_ctx *c)
             c->block.p = nullptr;                          // (never used again)
         }
     }
-    // nor is the block while a step may still write to it.  (By the words: the stream may be gone by now, and nothing has to be
-    // known of it.  A step that does not come, behind work that waits for this thread, keeps the block, not the caller.)
-    if (c->told_under_way && c->block.p) {
-        const auto begin = std::chrono::steady_clock::now();
-        while (!told_is_through(c)) {
-            if (std::chrono::steady_clock::now() - begin > std::chrono::seconds(2)) {
-                c->block.p = nullptr;
-                break;
-            }
-            std::this_thread::yield();
-        }
-    }
-    host_blocks().put(c->block);
+    // Nor does the block go to the next ctx while a step may still write to it: it goes when every sentence's word is the one that the
+    // last such step leaves there.  (The stream may be gone by now, and a step may be behind work that waits for this thread.)
+    if (c->told_under_way) host_blocks().put_when(c->block, (uint32_t)c->B, (uint32_t)c->told << 2, ~3u);
+    else host_blocks().put(c->block);
     delete c;
 }
 

@@ -107,6 +107,81 @@ int main()
         CHECK(g_bytes - before <= Store::kKeepBytes);
     }
     {
+        // blocks that somebody still writes to: nothing waits for them, they are not handed out before their words have come, and then are
+        static Store s;
+        std::vector<HostBlock> v;
+        for (int i = 0; i < 50; ++i) {
+            v.push_back(s.get(64 * K));
+            for (uint32_t j = 0; j < 33; ++j) reinterpret_cast<uint32_t *>(v[i].p)[j] = 7 << 2 | j % 4;
+        }
+        for (auto &x : v) s.put_when(x, 33, 8 << 2, ~3u);
+        auto in_v = [&](HostBlock b) {
+            for (auto &x : v)
+                if (x.p == b.p) return true;
+            return false;
+        };
+        HostBlock other = s.get(64 * K);
+        CHECK(!in_v(other));
+        s.put(other);
+        const size_t before = g_bytes, allocs = g_allocs;
+        for (int i = 0; i < 50; i += 2)                    // of half of them all, of one all but the last
+            for (uint32_t j = 0; j < 33u - (i == 0); ++j) reinterpret_cast<uint32_t *>(v[i].p)[j] = 8 << 2 | 1;
+        std::vector<HostBlock> w;
+        for (int i = 0; i < 25; ++i) {
+            w.push_back(s.get(64 * K));
+            CHECK(w[i].p == other.p || (in_v(w[i]) && w[i].p != v[0].p));
+        }
+        CHECK(g_allocs == allocs);
+        w.push_back(s.get(64 * K));
+        CHECK(!in_v(w.back()) && g_allocs == allocs + 1);
+        for (auto &x : w) s.put(x);
+        for (int i = 0; i < 50; ++i)
+            if (i % 2 || i == 0)
+                for (uint32_t j = 0; j < 33; ++j) reinterpret_cast<uint32_t *>(v[i].p)[j] = 8 << 2;
+        HostBlock last = s.get(64 * K);
+        s.put_when(last, 0, 0, 0);                         // (nothing to wait for)
+        CHECK(g_bytes - before + 51 * 64 * K <= Store::kKeepBytes + 64 * K);
+    }
+    {
+        // the same from several threads, another one writing the words
+        static Store s;
+        std::mutex lock;
+        std::vector<unsigned char *> todo;
+        bool stop = false;
+        std::thread gpu([&] {
+            for (;;) {
+                std::vector<unsigned char *> now;
+                {
+                    std::lock_guard<std::mutex> hold(lock);
+                    if (stop && todo.empty()) return;
+                    now.swap(todo);
+                }
+                for (unsigned char *p : now)
+                    for (uint32_t j = 0; j < 5; ++j) __atomic_store_n(reinterpret_cast<uint32_t *>(p) + j, 9 << 2, __ATOMIC_RELAXED);
+            }
+        });
+        std::vector<std::thread> threads;
+        for (unsigned t = 0; t < 3; ++t)
+            threads.emplace_back([&] {
+                for (int i = 0; i < 3000; ++i) {
+                    HostBlock b = s.get(64 * K);
+                    CHECK(b.p && __atomic_load_n(reinterpret_cast<uint32_t *>(b.p), __ATOMIC_RELAXED) != 1);   // (1: in use)
+                    for (uint32_t j = 0; j < 5; ++j) __atomic_store_n(reinterpret_cast<uint32_t *>(b.p) + j, 1, __ATOMIC_RELAXED);
+                    {
+                        std::lock_guard<std::mutex> hold(lock);
+                        todo.push_back(b.p);
+                    }
+                    s.put_when(b, 5, 9 << 2, ~3u);
+                }
+            });
+        for (auto &th : threads) th.join();
+        {
+            std::lock_guard<std::mutex> hold(lock);
+            stop = true;
+        }
+        gpu.join();
+    }
+    {
         static Store s;
         g_none = true;
         HostBlock a = s.get(5);

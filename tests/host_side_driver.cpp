@@ -28,6 +28,7 @@ constexpr size_t kParamBytes = 176;                // of a step kernel's last ar
 
 struct Work {                                      // a kernel that has been launched
     std::string name;
+    void *stream = nullptr;
     uint32_t *seen = nullptr, *told = nullptr;     // host words it will write, of sentences 0 .. B - 1
     const uint32_t *words = nullptr;               // host words it will read
     int B = 0;
@@ -47,14 +48,24 @@ static int g_B, g_step;                            // of the step that is about 
 
 static int error(int e) { if (e != kOk) g_last_error = e; return e; }
 
-static void gpu_runs()
+static void run(const Work &w)
 {
-    for (Work &w : g_queue) {
-        for (int b = 0; w.seen && b < w.B; ++b) w.seen[b] = 1;
-        for (int b = 0; w.told && b < w.B; ++b) w.told[b] = w.value;
-        g_done.push_back(w);
-    }
+    for (int b = 0; w.seen && b < w.B; ++b) w.seen[b] = 1;
+    for (int b = 0; w.told && b < w.B; ++b) w.told[b] = w.value;
+    g_done.push_back(w);
+}
+static void gpu_runs()                             // all that has been launched
+{
+    for (const Work &w : g_queue) run(w);
     g_queue.clear();
+}
+static void gpu_runs(void *stream, int most = 1 << 30)
+{
+    std::vector<Work> left;
+    for (const Work &w : g_queue)
+        if (w.stream == stream && most-- > 0) run(w);
+        else left.push_back(w);
+    g_queue.swap(left);
 }
 
 extern "C" {
@@ -96,7 +107,7 @@ int hipHostFree(void *p)                           // (never handed out again, s
 int hipMemcpyAsync(void *, const void *, size_t, int, void *) { ++g_calls; return kOk; }
 int hipStreamIsCapturing(void *, int *status) { ++g_calls; *status = g_capturing; return kOk; }
 int hipThreadExchangeStreamCaptureMode(int *) { ++g_calls; return kOk; }
-int hipStreamSynchronize(void *) { ++g_calls; ++g_syncs; gpu_runs(); return kOk; }
+int hipStreamSynchronize(void *stream) { ++g_calls; ++g_syncs; gpu_runs(stream); return kOk; }
 
 static bool in_host_memory(const unsigned char *p)
 {
@@ -104,13 +115,14 @@ static bool in_host_memory(const unsigned char *p)
         if (p >= h.first && p < h.first + h.second) return true;
     return false;
 }
-int hipLaunchKernel(const void *kernel, Dim3 grid, Dim3, void **args, size_t, void *)
+int hipLaunchKernel(const void *kernel, Dim3 grid, Dim3, void **args, size_t, void *stream)
 {
     ++g_calls;
     if (g_fail_launch >= 0 && g_fail_launch-- == 0) return error(kErrorLaunchOutOfResources);
     ++g_launches;
     Work w;
     w.name = g_names[kernel];
+    w.stream = stream;
     auto params = [&](const void *from) {
         for (size_t at = 0; at < kParamBytes; at += 8) {
             unsigned char *p;
@@ -152,12 +164,12 @@ static unsigned char *workspace(int B, int k, int V, int N)
     return g_ws = static_cast<unsigned char *>(aligned_alloc(256, (g_ws_bytes + 255) / 256 * 256));
 }
 
-static int init(dba_ctx **ctx, int B, int k, int V, int N)
+static int init(dba_ctx **ctx, int B, int k, int V, int N, void *stream = nullptr)
 {
     std::vector<int32_t> none(B + 1, 0);
     g_B = B;
     workspace(B, k, V, N);
-    return LIB(dba_init)(ctx, B, k, V, N, 2, 0, nullptr, none.data(), none.data(), g_ws, g_ws_bytes, nullptr);
+    return LIB(dba_init)(ctx, B, k, V, N, 2, 0, nullptr, none.data(), none.data(), g_ws, g_ws_bytes, stream);
 }
 
 static int step(dba_ctx *ctx)
@@ -257,11 +269,54 @@ static void calls_of_a_step()
     }
 }
 
+// dba_destroy does not wait for steps and uses no stream for them; the block goes to another ctx only when the last step that
+// writes to it has.
+static void steps_under_way()
+{
+    auto stream = [](int i) { return reinterpret_cast<void *>(uintptr_t(i + 1)); };
+    constexpr int kMany = 60;
+    std::set<unsigned char *> blocks;
+    const auto begin = std::chrono::steady_clock::now();
+    for (int i = 0; i < kMany; ++i) {
+        dba_ctx *c = nullptr;
+        CHECK(init(&c, 5, 3, 60, 9, stream(i)) == DBA_OK);
+        CHECK(blocks.insert(block_of_last_init()).second);
+        ask(c);
+        for (int t = 0; t < 2; ++t) CHECK(step(c) == DBA_OK && g_queue.back().told && g_queue.back().stream == stream(i));
+        if (i % 2) gpu_runs(stream(i), 1);                 // the first of the two
+        const int syncs = g_syncs;
+        LIB(dba_destroy)(c);
+        CHECK(g_syncs == syncs);
+    }
+    CHECK(std::chrono::steady_clock::now() - begin < std::chrono::seconds(1));
+    CHECK(g_queue.size() == kMany + kMany / 2 && g_released.empty());
+    for (int i = 0; i < kMany; i += 3) gpu_runs(stream(i));
+    std::set<unsigned char *> again;
+    for (int i = 0; i < kMany / 3; ++i) {                  // (all held at a time)
+        dba_ctx *c = nullptr;
+        CHECK(init(&c, 5, 3, 60, 9, stream(kMany)) == DBA_OK);
+        CHECK(blocks.count(block_of_last_init()) && again.insert(block_of_last_init()).second);
+    }
+    for (const Work &w : g_queue) CHECK(!w.told || !again.count(reinterpret_cast<unsigned char *>(w.told)));
+    dba_ctx *c = nullptr;
+    CHECK(init(&c, 5, 3, 60, 9, stream(kMany)) == DBA_OK && !blocks.count(block_of_last_init()));
+    gpu_runs();
+    LIB(dba_destroy)(c);
+    // all are through: what the store does not keep has been freed once the next block comes back
+    CHECK(init(&c, 5, 3, 60, 9, stream(kMany)) == DBA_OK);
+    ask(c);
+    CHECK(step(c) == DBA_OK);
+    gpu_runs();
+    LIB(dba_destroy)(c);
+    CHECK(g_host.size() - g_released.size() <= 32 + again.size());
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> scenarios = {
         {"launch_errors", launch_errors},
         {"calls_of_a_step", calls_of_a_step},
+        {"steps_under_way", steps_under_way},
     };
     if (argc != 3 || !scenarios.count(argv[2])) return 2;
     g_lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);
