@@ -60,6 +60,8 @@ typedef struct dba_ctx dba_ctx;
  * Bytes of device workspace dba_init needs for a job of B sentences, beam k,
  * vocabulary V and at most N steps (Alg. 1 inputs N, k).  max_cons_tokens is
  * an upper bound on the constraint tokens of any sentence (0..64).
+ * Never less for a greater B, k or N, and the same for every V: a workspace made
+ * for the largest job serves every smaller one.
  * Returns 0 if an argument is out of range.
  */
 DBA_API size_t dba_workspace_bytes(int B, int k, int V, int N, int max_cons_tokens);

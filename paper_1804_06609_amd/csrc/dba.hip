@@ -570,15 +570,18 @@ constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 struct Layout {
     size_t beam[2], sentences, rowlists, conskeys;
-    size_t place_lists, place_keys;     // the same for steps of one launch, empty between steps (where the shape has such steps)
+    size_t place_lists, place_keys;     // the same for steps of one launch, empty between steps
     size_t hist_token, hist_backptr;
     size_t fin_tokens, fin_len, fin_score, fin_status, all_finished, best;
     size_t total;
 };
 
-bool one_launch_shape(size_t B, size_t k, size_t V);
+constexpr size_t kComputeUnits = 256;
+constexpr size_t kOneLaunchRows = 22 * kComputeUnits / 4;   // no step of more beam rows takes one launch
 
-Layout make_layout(size_t B, size_t k, size_t V, size_t N)
+// Grows with B, k and N and goes by nothing else, so that a workspace made for the largest job serves every smaller one: a shape
+// has its places for steps of one launch whether it takes such steps or not.
+Layout make_layout(size_t B, size_t k, size_t N)
 {
     Layout L;
     size_t off = 0;
@@ -591,7 +594,7 @@ Layout make_layout(size_t B, size_t k, size_t V, size_t N)
     L.sentences = take(B * sizeof(Sentence));
     L.rowlists = take(B * k * kWave * sizeof(u64));
     L.conskeys = take(B * k * kMaxCons * sizeof(u64));
-    const size_t places = one_launch_shape(B, k, V) ? B * k : 0;
+    const size_t places = std::min(B * k, kOneLaunchRows);
     L.place_lists = take(places * kWave * sizeof(u64));
     L.place_keys = take(places * kMaxCons * sizeof(u64));
     L.hist_token = take(N * B * k * sizeof(int32_t));
@@ -611,7 +614,6 @@ Layout make_layout(size_t B, size_t k, size_t V, size_t N)
 // 810 / 520 and 810 / 200 at 8 MB.
 bool staged_tokens(size_t B, size_t N) { return B * N * 4 <= 512 * 1024; }
 
-constexpr size_t kComputeUnits = 256;
 constexpr size_t kLdsPerUnit = 160 * 1024;
 constexpr size_t kLdsPerLaunch = 64 * 1024;   // what a launch may ask for as it is
 
@@ -634,7 +636,7 @@ bool one_launch_shape(size_t B, size_t k, size_t V)
 {
     const size_t rows = B * k;
     if (rows <= 2 * kComputeUnits) return k <= 32;
-    return rows * 4 <= 22 * kComputeUnits && (k <= 16 ? V >= 512 : k <= 28 && V >= 4096);
+    return rows <= kOneLaunchRows && (k <= 16 ? V >= 512 : k <= 28 && V >= 4096);
 }
 
 // How the stream phase of a step is launched: one workgroup per beam row, and
@@ -905,7 +907,7 @@ extern "C" {
 DBA_API size_t dba_workspace_bytes(int B, int k, int V, int N, int max_cons_tokens)
 {
     if (!shape_ok(B, k, V, N, max_cons_tokens)) return 0;
-    return make_layout((size_t)B, (size_t)k, (size_t)V, (size_t)N).total;
+    return make_layout((size_t)B, (size_t)k, (size_t)N).total;
 }
 
 // dba_init proper; may throw std::bad_alloc from its host tables (caught by dba_init)
@@ -938,7 +940,7 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     // The constraint words go to a block of host memory that the kernel of dba_init reads itself, or, where there
     // is none (large batches), through a copy to the workspace.  (Opening a session, the caller's allocations included, with
     // all tables made on the host, copied and waited for / like this: one sentence 51 / 38 us, 64 sentences 119 / 48.)
-    const Layout L = make_layout((size_t)B, (size_t)k, (size_t)V, (size_t)N);
+    const Layout L = make_layout((size_t)B, (size_t)k, (size_t)N);
     const size_t words_bytes = (size_t)B * kMaxCons * sizeof(uint32_t);
     struct Holder {
         HostBlock block;

@@ -26,8 +26,18 @@ def test_wide_beams_with_16_bit_rows_beyond_two_rows_a_compute_unit():
         assert dba.dba_debug_launches(B, k, V, fmt) == launches, (B, k, V, fmt)
 
 
-def test_only_shapes_with_steps_of_one_launch_have_places_of_their_own():
-    """1024 bytes a row in the workspace, for steps whose keys no step of two launches may write over."""
-    for B, k, without, beyond in ((88, 16, 511, 512), (50, 28, 4095, 4096)):
-        more = dba.dba_workspace_bytes(B, k, beyond, 1, 0) - dba.dba_workspace_bytes(B, k, without, 1, 0)
-        assert more == B * k * 1024, (B, k, more)
+def test_a_workspace_for_the_largest_job_serves_every_smaller_one():
+    """Steps of one launch have places of their own, 1024 bytes a row, in the workspace of every shape up to 1408 rows, and
+    larger ones have no less: the size grows with the batch, the beam and the steps and goes by nothing else."""
+    def size(B, k, N=100, V=32000):
+        return dba.dba_workspace_bytes(B, k, V, N, 0)
+    for larger, smaller in (((72, 20), (70, 20)), ((89, 16), (88, 16)), ((50, 29), (50, 28)), ((105, 20), (71, 20))):
+        assert size(*larger) > size(*smaller), (larger, smaller)
+    for k in list(range(1, 65)):
+        for B in (1, 8, 15, 16, 17, 22, 25, 44, 64, 88, 89, 511, 512, 513, 703, 704, 1407, 1408, 1409, 2000, 65534):
+            here = size(B, k)
+            assert size(B + 1, k) >= here and size(B, k, 101) >= here and (k == 64 or size(B, k + 1) >= here), (B, k)
+            assert len({size(B, k, V=V) for V in (64, 511, 512, 4095, 4096, 32000, 1 << 20)}) == 1, (B, k)
+    for B, k, rows in ((1, 1, 1), (88, 16, 1408), (89, 16, 1408), (1000, 64, 1408)):
+        without = 2 * 32 * B * k + 2112 * B + 1024 * B * k   # the two beams, the constraints, the lists and keys of two launches
+        assert 1024 * rows <= size(B, k, 1) - without <= 1024 * rows + 8 * B * k + (4 * 4 + 33) * B + 20 * 256, (B, k)
