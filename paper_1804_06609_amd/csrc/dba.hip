@@ -371,6 +371,13 @@ __global__ __launch_bounds__(kWave) void dba_init_kernel(int B, int k, const uin
     const int b = (int)blockIdx.x, lane = lane_id();
     const size_t at = (size_t)b * kMaxCons + lane;
     const uint32_t word = __hip_atomic_load(words + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    // (past the L2, like every store here)
+    auto put = [](auto *to, auto value) { __hip_atomic_store(to, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    if (p.rowlists)                                        // steps of one launch: all places empty, while the words are on their way
+        for (int h = 0; h < k; ++h) {
+            put(p.rowlists + ((size_t)b * k + h) * kWave + lane, (u64)0);
+            put(p.conskeys + ((size_t)b * k + h) * kWave + lane, (u64)0);
+        }
     const bool valid = (word & kNoToken) == 0, begins = valid && (word & kBeginsPhrase) != 0;
     const int tok = valid ? (int)(word & ~kBeginsPhrase) : 0;
     const u64 starts = __ballot(begins);
@@ -391,8 +398,6 @@ __global__ __launch_bounds__(kWave) void dba_init_kernel(int B, int k, const uin
             btok = btok == -1 || btok == f ? f : -2;
         }
     }
-    // (past the L2, like every store here)
-    auto put = [](auto *to, auto value) { __hip_atomic_store(to, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
     Sentence *s = const_cast<Sentence *>(p.sentences) + b;
     put(s->tok + lane, tok);
     put(s->phr_off + lane, lane < P ? off[lane] : lane == P ? C : 0);
@@ -407,11 +412,6 @@ __global__ __launch_bounds__(kWave) void dba_init_kernel(int B, int k, const uin
     }
     static_assert(sizeof(BestCompleted) == 4 * sizeof(u64), "four words");
     if (lane < 4) put(reinterpret_cast<u64 *>(p.best + b) + lane, (u64)0);
-    if (p.rowlists)                                        // steps of one launch: all places empty
-        for (int h = 0; h < k; ++h) {
-            put(p.rowlists + ((size_t)b * k + h) * kWave + lane, (u64)0);
-            put(p.conskeys + ((size_t)b * k + h) * kWave + lane, (u64)0);
-        }
     if (lane < k) {
         const size_t i = (size_t)b * k + lane;
         put(&p.beam_nxt[i].score, lane == 0 ? 0.0f : -INFINITY);
@@ -715,6 +715,16 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem, bool free)
     const bool long_rows = row_bytes >= (elem == 4 ? 7u : 6u) * 8 * 4096;
     plan.tiles = plan.waves == 8 && (rows <= kComputeUnits || (plan.one && rows <= 2 * kComputeUnits && long_rows)) ? 4 : 2;
     return plan;
+}
+
+// Whether any step of this shape hands its keys over in places that must be empty: the element type decides, step by step.
+bool hands_over(size_t B, size_t k, size_t V)
+{
+    for (const unsigned elem : {4u, 2u}) {
+        const StreamPlan plan = stream_plan(B, k, V, elem, true);
+        if (plan.one && !plan.sentence) return true;
+    }
+    return false;
 }
 
 // How often a sentence's workgroup looks for the rows' keys: a look takes about a microsecond, and the rows two to four times
@@ -1039,7 +1049,7 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
         set_tables(c, p);
         p.beam_nxt = at<Hyp>(c, L.beam[0]);
         c->one_launch = seen != nullptr && one_launch_shape((size_t)B, (size_t)k, (size_t)V);
-        if (c->one_launch) {
+        if (c->one_launch && hands_over((size_t)B, (size_t)k, (size_t)V)) {
             p.rowlists = at<u64>(c, L.place_lists);
             p.conskeys = at<u64>(c, L.place_keys);
         }

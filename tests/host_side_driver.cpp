@@ -311,12 +311,32 @@ static void steps_under_way()
     CHECK(g_host.size() - g_released.size() <= 32 + again.size());
 }
 
+// dba_init empties the places of steps of one launch where a step of some element type uses them, and there alone.
+static void places_made_empty()
+{
+    const struct { int B, k, V; bool used; } shapes[] = {
+        {16, 10, 32000, true}, {1, 5, 1000, false} /* a workgroup per sentence */, {1, 5, 1025, true} /* with 32 bits */, {1, 5, 2049, true},
+        {89, 8, 41000, true} /* with 16 bits */, {89, 8, 82000, false}, {64, 20, 32000, true} /* with 16 bits */, {64, 29, 32000, false},
+        {30, 17, 1000, true} /* with 32 bits */, {30, 17, 7500, false}, {30, 17, 8192, true}, {1409, 1, 1000, false}};
+    for (auto &s : shapes) {
+        dba_ctx *c = nullptr;
+        CHECK(init(&c, s.B, s.k, s.V, 9) == DBA_OK);
+        // the beam, the constraints, the flags and the records, then the lists and the keys
+        const size_t n = g_queue.back().pointers.size();
+        if (n != (s.used ? 6u : 4u)) printf("%d x %d x %d: %zu\n", s.B, s.k, s.V, n);
+        CHECK(n == (s.used ? 6u : 4u));
+        gpu_runs();
+        LIB(dba_destroy)(c);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, void (*)()> scenarios = {
         {"launch_errors", launch_errors},
         {"calls_of_a_step", calls_of_a_step},
         {"steps_under_way", steps_under_way},
+        {"places_made_empty", places_made_empty},
     };
     if (argc != 3 || !scenarios.count(argv[2])) return 2;
     g_lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);

@@ -22,7 +22,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["launch_errors", "calls_of_a_step", "steps_under_way"])
+@pytest.mark.parametrize("scenario", ["launch_errors", "calls_of_a_step", "steps_under_way", "places_made_empty"])
 def test_host_side(driver, scenario):
     run = subprocess.run([driver, binding.LIB_PATH, scenario], capture_output=True, text=True, timeout=120)
     assert run.returncode == 0 and run.stdout == scenario + " ok\n", run.stdout + run.stderr
