@@ -41,20 +41,25 @@ DBA_API int dba_debug_wave_select(int n_cases, const uint64_t *keys_host, const 
 /*
  * Diagnostic: how the stream phase of a step is laid out for a shape at the default options (host only, no GPU
  * needed), so that tests can tell which kernel a shape reaches.  plan_host [4]: wavefronts per beam row, 4 KB tiles each
- * wavefront keeps in flight, bytes of LDS a workgroup asks for (its own and what it leaves unused to
- * keep other workgroups off its compute unit), beam rows numbered eight sentences abreast.
+ * wavefront keeps in flight, bytes of LDS a workgroup needs and, in the first of two launches, leaves unused to
+ * keep other workgroups off its compute unit, beam rows numbered eight sentences abreast.  (Steps with one workgroup per
+ * sentence, dba_debug_per_sentence, are laid out otherwise.)
  */
 DBA_API int dba_debug_stream_plan(int B, int k, int V, int logp_format, int32_t *plan_host);
 
 /* Diagnostic: launches of a step of this shape at the default options, 1 or 2 (host only). */
 DBA_API int dba_debug_launches(int B, int k, int V, int logp_format);
 
+/* Diagnostic: 1 if a step of this shape takes one workgroup per sentence for both its parts at the default options, else 0 (host only). */
+DBA_API int dba_debug_per_sentence(int B, int k, int V, int logp_format);
+
 /*
  * Diagnostic: on != 0: in steps of this ctx that take one launch the sentences' workgroups look for the rows' keys once
  * and then give up, so that rows take the sentences on themselves, which otherwise happens on a busy GPU or with
  * rows that take unusually long; on = 1: numbered before the rows', they all do; on = 2: numbered behind them as usual,
  * so that some may find all rows ended.  The results are the same.  Returns 1 if steps of this ctx may take
- * one launch (dba_debug_launches), else 0.
+ * one launch (dba_debug_launches: with some shapes the element type decides), else 0.  Steps with one workgroup per
+ * sentence (dba_debug_per_sentence) wait for nothing, and nothing changes for them.
  */
 DBA_API int dba_debug_sentences_first(dba_ctx *ctx, int on);
 

@@ -45,6 +45,7 @@ _SIGNATURES = {
     "dba_debug_wave_select": (_I, [_I] + [_P] * 5 + [ctypes.c_size_t, _P]),
     "dba_debug_stream_plan": (_I, [_I] * 4 + [_P]),
     "dba_debug_launches": (_I, [_I] * 4),
+    "dba_debug_per_sentence": (_I, [_I] * 4),
     "dba_debug_sentences_first": (_I, [_P, _I]),
     "dba_debug_row_max": (_I, [_P, _I, _I, _P, _P]),
 }
@@ -193,6 +194,13 @@ def dba_debug_launches(B: int, k: int, V: int, logp_format: int = DBA_LOGP_F32) 
     rc = load().dba_debug_launches(B, k, V, logp_format)
     _check(min(rc, DBA_OK))
     return rc
+
+
+def dba_debug_per_sentence(B: int, k: int, V: int, logp_format: int = DBA_LOGP_F32) -> bool:
+    """Whether a step of this shape takes one workgroup per sentence."""
+    rc = load().dba_debug_per_sentence(B, k, V, logp_format)
+    _check(min(rc, DBA_OK))
+    return rc == 1
 
 
 def dba_debug_sentences_first(ctx, on: int) -> bool:

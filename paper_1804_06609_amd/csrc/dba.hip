@@ -701,7 +701,8 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem, bool free)
     // less up to 4000 rows, 0 to 1.4 % more at 8000 and above).  Workgroups are kept apart by LDS they do not use; at
     // least a tenth of a unit's LDS stays free for other work.
     const size_t share = (rows + kComputeUnits - 1) / kComputeUnits;
-    plan.spare_lds = plan.waves == 8 ? (share > 4 ? spread_lds<8, 3>(3) : 0)
+    plan.spare_lds = plan.one            ? 0               // (the sentences' workgroups are to find room beside the rows)
+                     : plan.waves == 8 ? (share > 4 ? spread_lds<8, 3>(3) : 0)
                      : share <= 4 || share == 8 || (share > 8 && row_bytes < 49152) ? 0
                                                 : spread_lds<4, 7>(share < 8 ? share : 6);
     // Tiles in flight per wave: four where every row has a compute unit to itself and its latencies show
@@ -1513,6 +1514,13 @@ DBA_API int dba_debug_launches(int B, int k, int V, int logp_format)
     if (!shape_ok(B, k, V, 1, 0) || logp_format < DBA_LOGP_F32 || logp_format > DBA_LOGP_BF16)
         return fail(nullptr, DBA_EINVAL, "dba_debug_launches: bad argument");
     return stream_plan((size_t)B, (size_t)k, (size_t)V, logp_format == DBA_LOGP_F32 ? 4u : 2u, true).one ? 1 : 2;
+}
+
+DBA_API int dba_debug_per_sentence(int B, int k, int V, int logp_format)
+{
+    if (!shape_ok(B, k, V, 1, 0) || logp_format < DBA_LOGP_F32 || logp_format > DBA_LOGP_BF16)
+        return fail(nullptr, DBA_EINVAL, "dba_debug_per_sentence: bad argument");
+    return stream_plan((size_t)B, (size_t)k, (size_t)V, logp_format == DBA_LOGP_F32 ? 4u : 2u, true).sentence ? 1 : 0;
 }
 
 DBA_API int dba_debug_stream_plan(int B, int k, int V, int logp_format, int32_t *plan_host)

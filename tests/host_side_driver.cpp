@@ -248,7 +248,9 @@ static void launch_errors()
 // thread is not looked at, and stays there.
 static void calls_of_a_step()
 {
-    const struct { int B, k, V, launches; } shapes[] = {{1, 5, 1000, 1}, {16, 10, 32000, 1}, {2, 40, 1000, 2}};
+    const struct { int B, k, V, launches; const char *first, *last; } shapes[] = {
+        {1, 5, 1000, 1, "dba_sentence_kernel", "dba_sentence_kernel"}, {1, 5, 1025, 1, "dba_step_kernel", "dba_step_kernel"},
+        {16, 10, 32000, 1, "dba_step_kernel", "dba_step_kernel"}, {2, 40, 1000, 2, "dba_stream_kernel", "dba_merge_kernel"}};
     for (auto &s : shapes) {
         dba_ctx *c = nullptr;
         g_last_error = kErrorInvalidValue;
@@ -257,6 +259,8 @@ static void calls_of_a_step()
             const int calls = g_calls, launches = g_launches;
             CHECK(step(c) == DBA_OK);
             CHECK(g_launches == launches + s.launches && g_calls == calls + 1 + s.launches);
+            CHECK(g_queue[g_queue.size() - s.launches].name.find(s.first) != std::string::npos);
+            CHECK(g_queue.back().name.find(s.last) != std::string::npos);
         }
         ask(c);
         CHECK(g_last_error == kErrorInvalidValue);

@@ -24,23 +24,27 @@ def _bytes(ses):
     (88, 16, 512, ("f32",), True), (89, 16, 512, ("f32",), False), (88, 16, 511, ("f32",), False), (1408, 1, 700, ("f16",), True),
     (176, 8, 1031, ("bf16", "f32"), True), (127, 11, 2049, ("f32", "f16"), True), (93, 15, 3001, ("f32",), True), (64, 11, 41001, ("f32", "bf16"), True),
     (65, 11, 41001, ("f32", "bf16"), True), (89, 8, 41001, ("bf16", "f32"), True), (46, 16, 41001, ("f16", "f32"), True),
-    (18, 28, 7168, ("f32", "f16"), True), (18, 28, 7169, ("f32",), True), (30, 17, 1000, ("f32",), True), (1, 17, 17, ("f32",), True), (5, 24, 1024, ("f32", "bf16"), True),
+    (18, 28, 7168, ("f32", "f16"), True), (18, 28, 7169, ("f32",), None), (30, 17, 1000, ("f32",), True), (1, 17, 17, ("f32",), True), (5, 24, 1024, ("f32", "bf16"), True),
     (50, 28, 4096, ("f16", "f32"), True), (31, 17, 9001, ("bf16", "f32"), True), (50, 28, 4095, ("f16",), False), (25, 24, 16387, ("f32", "f16", "bf16"), True),
     (3, 8, 1024, ("f32", "bf16"), True), (3, 8, 1023, ("f32", "f16"), True), (41, 4, 2047, ("f32", "bf16"), True), (5, 2, 4093, ("f32",), True), (2, 1, 8190, ("bf16", "f32"), True),
     (7, 5, 700, ("f16",), True), (768, 1, 600, ("f32",), True), (769, 1, 600, ("f32",), True), (6, 8, 60, ("f32", "bf16"), True), (2, 7, 9, ("f32",), True)])
 def test_one_launch_and_two(B, k, V, fmts, one):
     """Every step against the two launches, with the element types by turns (where they decide how many launches a step takes,
     the places that rows hand their keys over in are left empty by both), the step with its own scratch among them, and with the
-    sentences' workgroups giving up at once."""
+    sentences' workgroups giving up at once.  one: whether steps of these element types take one launch (None: of such a ctx some
+    might, these take two)."""
     import torch
+    import paper_1804_06609_amd as dba
     tdt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
+    code = {"f32": dba.DBA_LOGP_F32, "f16": dba.DBA_LOGP_F16, "bf16": dba.DBA_LOGP_BF16}
     wl = si.make_small(9700 + V + k, B, k, V, 6, max_phrases=4, max_len=3, dup_prob=0.3)
     wl.eos_switch = 4
     dev = [torch.from_numpy(wl.logp(t)).cuda().to(tdt[fmts[t // 2 % len(fmts)]]) for t in range(wl.T)]
     two, is_one = _session(wl, 8)
     assert not is_one
     others = [_session(wl, 0, first) for first in (0, 1, 2)]
-    assert all(o[1] == one for o in others)
+    assert all(o[1] == (one is not False) for o in others)
+    assert any(dba.dba_debug_launches(B, k, V, code[f]) == 1 for f in fmts) == (one is True)
     for t in range(wl.T):
         two.step(dev[t])
         want = _bytes(two)
@@ -70,6 +74,8 @@ def test_floors_of_rows_of_one_tile_to_six(k, fmt):
 def test_a_sentence_in_one_workgroup(B, k, V, fmt, shape):
     """Rows of up to four tiles, one wave each, against the oracle: rising rows and equal elements fill a wave's room for groups and for keys."""
     import harness
+    import paper_1804_06609_amd as dba
+    assert dba.dba_debug_per_sentence(B, k, V, {None: dba.DBA_LOGP_F32, "f16": dba.DBA_LOGP_F16, "bf16": dba.DBA_LOGP_BF16}[fmt])
     base = si.make_small(9850 + V, B, k, V, 8, max_phrases=4, max_len=3, dup_prob=0.3)
     if shape == "zipf":
         wl = base

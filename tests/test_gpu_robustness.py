@@ -294,6 +294,7 @@ def _one_launch_decode(wl, dev, stream, first, waves=0):
 
 @pytest.mark.parametrize("B,k,V,fmt,one", [
     (256, 1, 300, None, True), (512, 1, 300, None, True), (513, 1, 300, None, False), (34, 15, 9000, None, True), (16, 32, 2100, "bf16", True), (17, 31, 700, None, False), (85, 3, 1200, "f16", True), (32, 8, 1000, None, True), (28, 9, 4100, "bf16", True),
+    (256, 1, 4097, None, True), (512, 1, 4097, None, True), (85, 3, 6200, "f16", True), (32, 8, 1025, None, True), (1, 5, 1025, None, True),
     (23, 11, 8200, None, True), (21, 12, 2000, None, True), (16, 16, 16500, "f16", True), (15, 17, 700, None, True), (8, 32, 8300, None, True),
     (7, 33, 600, None, False), (3, 20, 33001, None, True), (1, 5, 1000, None, True), (2, 32, 40000, "bf16", True)])
 def test_steps_of_one_launch(B, k, V, fmt, one):
@@ -360,8 +361,8 @@ def test_steps_of_one_launch_side_by_side():
 
 
 @pytest.mark.parametrize("first", [1, 2])
-@pytest.mark.parametrize("B,k,V,fmt", [(8, 5, 200, None), (40, 12, 500, None), (16, 10, 32000, None), (20, 24, 3000, None),
-                                       (2, 32, 40000, "bf16"), (26, 10, 33000, "f16"), (3, 20, 300001, None), (512, 1, 700, None)])
+@pytest.mark.parametrize("B,k,V,fmt", [(8, 9, 200, None), (40, 12, 500, None), (16, 10, 32000, None), (20, 24, 3000, None),
+                                       (2, 32, 40000, "bf16"), (26, 10, 33000, "f16"), (3, 20, 300001, None), (769, 1, 700, None), (512, 1, 4097, None)])
 def test_sentences_that_give_up_waiting(B, k, V, fmt, first):
     """A sentence's workgroup that looks for the rows' keys once and gives up (a limit of 0 looks set by the host; in
     earnest it runs out where rows take unusually long): the row that ends last takes the sentence on, or the
@@ -376,7 +377,8 @@ def test_sentences_that_give_up_waiting(B, k, V, fmt, first):
     import paper_1804_06609_amd as dba
     two, _ = _one_launch_decode(wl, dev, stream, 0, waves=8)
     ses, one = _one_launch_decode(wl, dev, stream, first)
-    assert one
+    code = {None: dba.DBA_LOGP_F32, "f16": dba.DBA_LOGP_F16, "bf16": dba.DBA_LOGP_BF16}[fmt]
+    assert one and dba.dba_debug_launches(B, k, V, code) == 1 and not dba.dba_debug_per_sentence(B, k, V, code)
     for t in range(wl.T):
         dba.dba_debug_sentences_first(ses.ctx, first if t % 4 != 3 else 0)
         two.step(dev[t])

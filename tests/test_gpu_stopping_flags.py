@@ -84,28 +84,49 @@ def test_flags_with_steps_in_a_graph():
 
 
 def test_a_ctx_that_goes_with_steps_under_way_leaves_its_block_alone():
-    """Many decodes, each destroyed right behind steps whose flags were asked for before: the next one, which gets its block of host
-    memory, reads what its own steps wrote."""
+    """A decode that is destroyed with steps under way on its stream, whose flags were asked for before, and another one on
+    a stream of its own right behind it: between the other's step and its question the first one's steps write their words, which
+    are not the other's to read.  (Were the block of host memory handed on with the ctx, the flags would be the first one's.)"""
     import torch
     import paper_1804_06609_amd as dba
     T = 12
     lp, session = _decode(40, 10, 9000, T, 9960)
-    lp2, small = _decode(33, 3, 200, T, 9970)
+    lp2, small = _decode(67, 3, 200, T, 9970)              # (as many sentences and more: its words would lie where the first one's are)
+    ref = session()
+    for t in range(T):
+        ref.step(lp[t])
+    theirs = ref.finished()
+    ref.close()
     ref, want = small(), []
     for t in range(T):
         ref.step(lp2[t])
         want.append(ref.finished())
-    for _ in range(20):
-        ses, nxt = session(), None
-        ses.finished()
-        for t in range(T):
-            ses.step(lp[t])
-        dba.dba_destroy(ses.ctx)
-        ses.ctx = None
-        nxt = small()
-        for t in range(T):
-            nxt.step(lp2[t])
-            assert (nxt.finished() == want[t]).all(), t
-        nxt.close()
-        torch.cuda.synchronize()
     ref.close()
+    t0 = 2
+    assert (theirs != want[t0][:40]).any()
+    a = torch.randn(4096, 4096, device="cuda")
+    a @ a
+    torch.cuda.synchronize()
+    for _ in range(4):
+        first, second = torch.cuda.Stream(), torch.cuda.Stream()
+        with torch.cuda.stream(first):
+            ses = session(first)
+            ses.finished()
+            for _ in range(20):                            # some milliseconds of work ahead of its steps
+                a @ a
+            for t in range(T):
+                ses.step(lp[t])
+        dba.dba_destroy(ses.ctx)
+        ses.ctx = None                                     # (its buffers stay until its stream is through)
+        assert not first.query()                           # nothing has waited for it
+        with torch.cuda.stream(second):
+            nxt = small(second)
+            nxt.finished()
+            for t in range(T):
+                nxt.step(lp2[t])
+                if t == t0:
+                    second.synchronize()
+                    assert not first.query()
+                    first.synchronize()
+                assert (nxt.finished() == want[t]).all(), t
+            nxt.close()

@@ -26,6 +26,24 @@ def test_wide_beams_with_16_bit_rows_beyond_two_rows_a_compute_unit():
         assert dba.dba_debug_launches(B, k, V, fmt) == launches, (B, k, V, fmt)
 
 
+def test_a_workgroup_per_sentence_for_short_rows_and_narrow_beams():
+    """Eight tiles of 4 KB in all, four a row, 768 sentences."""
+    f32, f16, bf16 = dba.DBA_LOGP_F32, dba.DBA_LOGP_F16, dba.DBA_LOGP_BF16
+    for B, k, V, fmt, per_sentence in ((1, 5, 1000, f32, 1), (3, 8, 1024, f32, 1), (3, 8, 1025, f32, 0), (3, 8, 2048, bf16, 1), (3, 8, 2049, bf16, 0), (3, 9, 60, f32, 0),
+                                       (3, 4, 2048, f16, 1), (3, 4, 2048, f32, 1), (3, 4, 2049, f32, 0), (3, 5, 1025, f32, 0), (3, 3, 2730, f32, 0), (3, 3, 2048, f32, 1),
+                                       (2, 2, 4096, f32, 1), (2, 2, 4097, f32, 0), (2, 1, 4096, f32, 1), (2, 1, 4097, f32, 0), (2, 1, 8192, bf16, 1), (2, 1, 8193, bf16, 0),
+                                       (768, 1, 600, f32, 1), (769, 1, 600, f32, 0), (176, 8, 600, f32, 1), (177, 8, 600, f32, 0), (512, 1, 300, f32, 1), (513, 1, 300, f32, 0)):
+        assert dba.dba_debug_per_sentence(B, k, V, fmt) == bool(per_sentence), (B, k, V, fmt)
+        assert not per_sentence or dba.dba_debug_launches(B, k, V, fmt) == 1
+
+
+def test_no_lds_is_left_unused_beside_a_row_of_a_single_launch():
+    for B, k, V, fmt in ((96, 12, 32003, dba.DBA_LOGP_BF16), (64, 20, 32000, dba.DBA_LOGP_F16), (1408, 1, 32000, dba.DBA_LOGP_F32), (80, 16, 32000, dba.DBA_LOGP_F32)):
+        assert dba.dba_debug_launches(B, k, V, fmt) == 1
+        assert dba.dba_debug_stream_plan(B, k, V, fmt)[2] == dba.dba_debug_stream_plan(1, 10, 1000, fmt)[2], (B, k, V, fmt)
+    assert dba.dba_debug_stream_plan(64, 20, 32000, dba.DBA_LOGP_F32)[2] > dba.dba_debug_stream_plan(1, 10, 1000)[2]
+
+
 def test_a_workspace_for_the_largest_job_serves_every_smaller_one():
     """Steps of one launch have places of their own, 1024 bytes a row, in the workspace of every shape up to 1408 rows, and
     larger ones have no less: the size grows with the batch, the beam and the steps and goes by nothing else."""
