@@ -219,8 +219,10 @@ DBA_API int dba_get_state(dba_ctx *ctx, float *score_host, uint64_t *met_mask_ho
  *                               launch for both parts of a small step (B*k <= 512, and k <= 16, or k <= 32
  *                               with rows of at least 32 KB, or k <= 28 with fp32 rows of at most 28 KB; k <= 16 and B*k <= 1408,
  *                               or 704 with rows of 160 KB and more; k <= 28 there with 16-bit rows of 8 to 160 KB), else so many
- *                               (four up to k = 16, eight up to 32 or for more than 256 sentences, sixteen beyond).  Four-wave workgroups need less room
- *                               at once on a GPU that is busy with other work.
+ *                               (four up to k = 16, eight up to 32 or for more than 256 sentences, sixteen beyond).  4 and 8
+ *                               always take two launches.  They are of use where three or more large decodes with 16-bit log-probs share a GPU
+ *                               (1000 rows and more of 64 KB: 3 to 5 % less time); wherever else 0 takes one
+ *                               launch, decodes side by side take 4 to 30 % longer with them.
  */
 #define DBA_OPT_ADJUSTMENT 2
 #define DBA_OPT_NORMALIZE_FINISHED 3

@@ -630,8 +630,9 @@ constexpr size_t spread_lds(size_t n)
 // workgroups need room beside the rows); with two rows a unit up to k = 32, where the rows have eight waves.  Per step, two launches /
 // one: 768 rows of 32000 fp32, k = 12, 24.2 / 23.2 us, 1152 of 32003 bf16 20.9 / 19.5, 1280, k = 16, 32.8 / 32.2, 1275 of 16000 22.0 / 20.8, 1024
 // of 8000 14.5 / 13.9, 960 of 2000 11.7 / 10.8, 600 of 1000 11.0 / 10.5; but 1700 of 32000 41.6 / 43.3, 1600 of 2000 13.2 / 14.6, 5000 of 2000
-// 22.0 / 24.5, and with k = 20 to 32 and four waves 1280 of 32000 34.2 / 34.3, 2048 49.6 / 51.1.  (More than two rows a unit of a tile's eighth
-// or less, vocabularies of a few hundred, keep two launches.)
+// 22.0 / 24.5, and with k = 20 to 32 and four waves 1280 of 32000 34.2 / 34.3, 2048 49.6 / 51.1.  Vocabularies of a few
+// hundred keep two launches beyond two rows a unit, where one would be less again: 600 rows of 300 9.85 / 7.7, 1024, k = 8, 10.5 / 8.2, 1408, k = 16, 11.75 /
+// 10.8, as from 512 tokens on, 1408 of 520, k = 16, 11.8 / 10.85.)
 bool one_launch_shape(size_t B, size_t k, size_t V)
 {
     const size_t rows = B * k;
@@ -677,10 +678,15 @@ StreamPlan stream_plan(size_t B, size_t k, size_t V, unsigned elem, bool free)
     // 32000, k = 20, 19.95 / 18.8; 256 rows, k = 32, 16.5 / 15.45), but with four waves up to 0.35 more at k = 18, 0.5 at 24, 0.9 at 28 and 1.2 at
     // 32.  So short rows get eight too, though most of these have no tile, to k = 28 (fp32, two launches with four / one with eight: 200
     // rows of 2000, k = 20, 10.3 / 9.7 us, 126 of 4000, k = 18, 10.8 / 9.75, 504 11.7 / 10.8, 448 of 7000, k = 28, 13.0 / 12.2; 512 of 5000, k = 32, 12.8 /
-    // 13.5; 16-bit rows gain less, 240 of 6000, k = 20, 11.15 / 10.7, and are left as they are, like rows of 28 to 32 KB).
+    // 13.5; 16-bit rows gain less, 240 of 6000, k = 20, 11.15 / 10.7, and are left as they are; so are rows of 28 to 32 KB, where one
+    // launch with eight waves would be less as well: 144 of 7800, k = 24, 11.85 / 10.65, 500 of 7500, k = 20, 12.75 / 12.0, 504 of 8100, k = 28, 13.65 / 12.9).
     // Beyond two rows a unit 16-bit rows also with k = 17 to 28 and four waves: there are half the bytes in front of what one launch
     // saves (bf16, 544 rows of 32000, k = 17, 18.35 / 17.6, 1080, k = 24, 22.75 / 22.0, 1200 of 8000, k = 20, 15.9 / 15.2, 1400 of 16000, k =
-    // 28, 21.45 / 20.9; k = 32 equal; fp32 1080 of 12000, k = 18, 18.05 / 17.9, 1200 of 16000 21.6 / 21.3, but 1400 of 24000, k = 28, 31.9 / 32.65, 600 of 8000 13.9 / 14.05).
+    // 28, 21.45 / 20.9; k = 32 equal).  But three such decodes side by side are 3 to 4 % slower than with two launches where the rows are 64 KB (3 x 1280 of 32000, k =
+    // 20, 40.9 / 42.5, 3 x 1152 of 32003, k = 12, 37.1 / 38.5; two of them 33.1 / 30.9 and 29.8 / 28.2, three with rows of 32 KB 26.4 / 23.1): the sentences' workgroups hold room that
+    // rows of the others could have, whatever LDS is left unused, however often they look and whenever they give up.  fp32 stays at two, where the difference is
+    // small and changes sign: 1080 of 12000, k = 18, 18.1 / 17.8, 527 of 32000, k = 17, 23.15 / 22.5, 960 of 16000, k = 24, equal, 1280 of 32000, k = 20, 34.0 / 34.25, 1400 of
+    // 24000, k = 28, 31.35 / 31.65.
     plan.one = free && one_launch_shape(B, k, V) &&
                (rows <= 2 * kComputeUnits ? k <= 16 || plan.waves == 8
                                           : rows * plan.waves <= 22 * kComputeUnits && (k <= 16 || (elem == 2 && plan.waves == 4)));

@@ -38,8 +38,8 @@ constexpr int kFinEosBlocked = 4;     // beam-state flag: constraints unmet, end
 
 // One hypothesis of a beam in memory, two 16-byte words: who needs all of it has two loads or stores, and a kernel one pointer (an
 // array for each member, seven loads and stores and seven pointers, and seven pointers to the constraints' tables filled the scalar
-// registers of both phases: 15 to 51 of them spilled in the kernels of one launch, now 2 to 12, none in the second of two.  Per step,
-// before / now: one sentence of five rows of 1000 8.55 / 8.2 us, ten of 32000 10.6 / 10.4, 160 rows 12.4 / 12.1, 168 of 50001 13.0 / 12.7,
+// registers of both phases: 15 to 51 of them spilled in the kernels of one launch, now 2 to 16; none in
+// the second of two, but with four merge waves fixed by the caller beyond k = 16: 13, and 35 beyond 32.  Per step, before / now: one sentence of five rows of 1000 8.55 / 8.2 us, ten of 32000 10.6 / 10.4, 160 rows 12.4 / 12.1, 168 of 50001 13.0 / 12.7,
 // 595 of 24157 18.95 / 18.35, 1280 of 32000 32.2 / 32.0).
 struct __attribute__((aligned(16))) Hyp {
     float score;                      // -inf: empty slot
@@ -1285,39 +1285,40 @@ __device__ __forceinline__ void merge_phase(const StepParams &p, const u64 *rowl
 #pragma unroll
         for (int i = 0; i < kRowsPerWave; ++i) ck[i] = ck[i] == kNoKey ? 0 : ck[i];
     } else {
-    if constexpr (kPacked) {
+        // left by an earlier launch or by the other waves: there already
+        if constexpr (kPacked) {
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const uint32_t i = (uint32_t)(j * kWave + lane);
-            rl[j] = 0;
-            if (i < (uint32_t)(k * k)) {
-                const uint32_t h = (i * inv_k) >> 16, at = i - h * (uint32_t)k;
-                head_bits |= (at == 0 ? 1u : 0u) << j;
-                rl[j] = rowlists[at_row((int)h) + at];
+            for (int j = 0; j < J; ++j) {
+                const uint32_t i = (uint32_t)(j * kWave + lane);
+                rl[j] = 0;
+                if (i < (uint32_t)(k * k)) {
+                    const uint32_t h = (i * inv_k) >> 16, at = i - h * (uint32_t)k;
+                    head_bits |= (at == 0 ? 1u : 0u) << j;
+                    rl[j] = rowlists[at_row((int)h) + at];
+                }
+            }
+        } else if constexpr (kHalves) {
+            // register i: rows wave + 2 i MW and wave + (2 i + 1) MW
+#pragma unroll
+            for (int i = 0; i < kLists; ++i) {
+                const int h = wave + (2 * i + (lane >> 5)) * MW;
+                rl[i] = 0;
+                if (h < k && (lane & 31) < k) rl[i] = rowlists[at_row(h) + (lane & 31)];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < kLists; ++i) {
+                const int h = wave + i * MW;
+                rl[i] = 0;
+                if (h < k) rl[i] = rowlists[at_row(h) + lane];
             }
         }
-    } else if constexpr (kHalves) {
-        // register i: rows wave + 2 i MW and wave + (2 i + 1) MW
 #pragma unroll
-        for (int i = 0; i < kLists; ++i) {
-            const int h = wave + (2 * i + (lane >> 5)) * MW;
-            rl[i] = 0;
-            if (h < k && (lane & 31) < k) rl[i] = rowlists[at_row(h) + (lane & 31)];
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < kLists; ++i) {
+        for (int i = 0; i < kRowsPerWave; ++i) {
             const int h = wave + i * MW;
-            rl[i] = 0;
-            if (h < k) rl[i] = rowlists[at_row(h) + lane];
+            ck[i] = 0;
+            if (h < k) ck[i] = conskeys[at_row(h) + lane];
         }
-    }
-#pragma unroll
-    for (int i = 0; i < kRowsPerWave; ++i) {
-        const int h = wave + i * MW;
-        ck[i] = 0;
-        if (h < k) ck[i] = conskeys[at_row(h) + lane];
-    }
     }
     __builtin_amdgcn_sched_barrier(0);
     const int mb = p.met_bits;
