@@ -37,8 +37,8 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E peak
 # rocprofv3 FETCH_SIZE / WRITE_SIZE runs summarised in profiles/ (scaled against a plain copy), and
 # the digest of the kernel sources those counters were taken with: the line carries the figure only
 # while the sources are still those, null otherwise.
-TRAFFIC_BYTES_PER_LAUNCH = 167034076
-TRAFFIC_KERNEL_SHA16 = "0f2afa8411a15bea"
+TRAFFIC_BYTES_PER_LAUNCH = 167030143
+TRAFFIC_KERNEL_SHA16 = "1b881b2890bd6535"
 
 
 def kernel_sources_sha16() -> str:
