@@ -632,7 +632,7 @@ constexpr size_t spread_lds(size_t n)
 // of 8000 14.5 / 13.9, 960 of 2000 11.7 / 10.8, 600 of 1000 11.0 / 10.5; but 1700 of 32000 41.6 / 43.3, 1600 of 2000 13.2 / 14.6, 5000 of 2000
 // 22.0 / 24.5, and with k = 20 to 32 and four waves 1280 of 32000 34.2 / 34.3, 2048 49.6 / 51.1.  Vocabularies of a few
 // hundred keep two launches beyond two rows a unit, where one would be less again: 600 rows of 300 9.85 / 7.7, 1024, k = 8, 10.5 / 8.2, 1408, k = 16, 11.75 /
-// 10.8, as from 512 tokens on, 1408 of 520, k = 16, 11.8 / 10.85.)
+// 10.8, as from 512 tokens on, 1408 of 520, k = 16, 11.8 / 10.85.
 bool one_launch_shape(size_t B, size_t k, size_t V)
 {
     const size_t rows = B * k;
@@ -829,8 +829,8 @@ HostBlocks<PinnedMemory> &host_blocks()
     return *blocks;
 }
 
-// A launch that tells how it went: hipGetLastError, behind the <<< >>> form, may tell of an earlier call on this thread, of whomever,
-// and takes that error from its owner.  (Nor does this one pass its grid through the runtime first: a step's call takes 2.85 instead of 3.05
+// A launch that tells how it went, so that of one that failed it is known that no kernel of it is under way: hipGetLastError, behind the <<< >>> form,
+// may tell of an earlier call on this thread, of whomever, and takes that error from its owner.  (Nor does this one pass its grid through the runtime first: a step's call takes 2.85 instead of 3.05
 // us with one launch and 5.27 instead of 5.65 with two, which is the time of a step where short ones of several decodes alternate.)
 template <typename... P, typename... A>
 hipError_t launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t stream, const A &...a)
@@ -1065,7 +1065,6 @@ static int init_impl(dba_ctx **out, int B, int k, int V, int N, int eos_id, int 
     if (e == hipSuccess && !seen) e = hipStreamSynchronize(c->stream);   // the words are freed on return
     if (e != hipSuccess) {
         const int rc = fail(nullptr, DBA_EHIP, "dba_init: HIP error: %s", hipGetErrorString(e));
-        held.block.p = nullptr;                            // (never used again: whatever went wrong, nothing is known to wait for)
         delete c;
         return rc;
     }
@@ -1263,10 +1262,8 @@ static int step_impl(dba_ctx *c, const void *logp_dev, int logp_format, int32_t 
         }
 #undef MERGE
     }
-    if (e != hipSuccess) {
-        if (tells) c->block.p = nullptr;                   // (never used again: whatever went wrong, its words are not to be relied upon)
-        return fail(c, DBA_EHIP, "dba_step: launch failed: %s", hipGetErrorString(e));
-    }
+    // (nothing that writes to the block has been launched then: the words to wait for are still those of the step before)
+    if (e != hipSuccess) return fail(c, DBA_EHIP, "dba_step: launch failed: %s", hipGetErrorString(e));
     c->steps += 1;
     if (tells) {
         c->told = c->steps;

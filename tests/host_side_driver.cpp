@@ -242,6 +242,23 @@ static void launch_errors()
         if (rc == DBA_OK) LIB(dba_destroy)(a);
         LIB(dba_destroy)(b);
     }
+    // calls that fail again and again keep nothing
+    dba_ctx *c = nullptr;
+    CHECK(init(&c, 3, 4, 50, 9) == DBA_OK);
+    ask(c);
+    CHECK(step(c) == DBA_OK);
+    const size_t blocks = g_host.size();
+    for (int i = 0; i < 100; ++i) {
+        dba_ctx *none = nullptr;
+        g_fail_launch = 0;
+        CHECK(init(&none, 3, 4, 50, 9) == DBA_EHIP && !none);
+        g_fail_launch = 0;
+        CHECK(step(c) == DBA_EHIP);
+    }
+    CHECK(g_host.size() <= blocks + 1);
+    CHECK(step(c) == DBA_OK && g_queue.back().told);       // (and the ctx goes on as before)
+    gpu_runs();
+    LIB(dba_destroy)(c);
 }
 
 // A step asks whether its stream is being captured and launches its kernels: the error that another call has left on the
